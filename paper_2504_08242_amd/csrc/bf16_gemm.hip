@@ -471,15 +471,22 @@ hipError_t configure_one() {
 
 }  // namespace
 
-// Instantiations: (row blocks, column blocks, wave grid) per epilogue.  256-row tiles for prefill-sized
-// chunks; 128- and 64-row tiles with narrow N for short chunks, where the grid must be wide enough to keep
-// every CU streaming weights.
-#define JUP_GEMM_SHAPES(X)                                                          \
-    X(8, 1, 4, 1, EPI_QKV) X(8, 2, 4, 1, EPI_QKV) X(8, 3, 8, 1, EPI_QKV) X(8, 6, 4, 2, EPI_QKV)            \
-    X(4, 2, 4, 1, EPI_QKV) X(2, 2, 2, 2, EPI_QKV) X(4, 3, 4, 1, EPI_QKV) X(4, 6, 4, 2, EPI_QKV) \
-    X(8, 2, 4, 1, EPI_SWIGLU) X(8, 3, 4, 1, EPI_SWIGLU) X(8, 4, 4, 2, EPI_SWIGLU) X(8, 6, 4, 2, EPI_SWIGLU) X(8, 8, 4, 2, EPI_SWIGLU) \
-    X(4, 4, 4, 1, EPI_SWIGLU) X(2, 4, 2, 2, EPI_SWIGLU) X(1, 3, 1, 3, EPI_SWIGLU) X(1, 4, 1, 4, EPI_SWIGLU) X(4, 3, 4, 1, EPI_SWIGLU) X(2, 3, 2, 3, EPI_SWIGLU) X(4, 6, 4, 1, EPI_SWIGLU) X(2, 6, 2, 3, EPI_SWIGLU) \
-    X(8, 4, 4, 2, EPI_PARTIAL) X(8, 8, 4, 2, EPI_PARTIAL) X(4, 4, 4, 1, EPI_PARTIAL) X(4, 4, 4, 2, EPI_PARTIAL) X(2, 4, 2, 2, EPI_PARTIAL) X(2, 2, 2, 2, EPI_PARTIAL) X(4, 2, 4, 1, EPI_PARTIAL)
+// Instantiations: (row blocks, column blocks, wave grid) per epilogue.  First the tall tiles of chunks of more than 128
+// rows (kTallTiles below prices them), then the tiles of short chunks, narrow in N so that the grid is wide enough to
+// keep every CU streaming weights, and those of chunks that share the GPU.
+#define JUP_GEMM_TALL(X, EPI)                                                                              \
+    X(8, 8, 4, 2, EPI) X(8, 6, 4, 2, EPI) X(8, 4, 4, 2, EPI) X(6, 8, 2, 4, EPI) X(6, 4, 2, 2, EPI)         \
+    X(4, 8, 2, 4, EPI) X(4, 6, 4, 2, EPI) X(4, 4, 4, 2, EPI)
+#define JUP_GEMM_SHAPES(X)                                                                                 \
+    JUP_GEMM_TALL(X, EPI_QKV) X(6, 6, 2, 2, EPI_QKV) X(4, 3, 4, 1, EPI_QKV)                                \
+    JUP_GEMM_TALL(X, EPI_SWIGLU) X(6, 6, 2, 2, EPI_SWIGLU) X(4, 3, 4, 1, EPI_SWIGLU) X(8, 3, 4, 1, EPI_SWIGLU) \
+    JUP_GEMM_TALL(X, EPI_PARTIAL)                                                                          \
+    X(8, 1, 4, 1, EPI_QKV) X(8, 2, 4, 1, EPI_QKV) X(8, 3, 8, 1, EPI_QKV)                                   \
+    X(4, 2, 4, 1, EPI_QKV) X(2, 2, 2, 2, EPI_QKV)                                                          \
+    X(8, 2, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU) X(2, 4, 2, 2, EPI_SWIGLU)                          \
+    X(1, 3, 1, 3, EPI_SWIGLU) X(1, 4, 1, 4, EPI_SWIGLU) X(2, 3, 2, 3, EPI_SWIGLU) X(4, 6, 4, 1, EPI_SWIGLU) \
+    X(2, 6, 2, 3, EPI_SWIGLU)                                                                              \
+    X(4, 4, 4, 1, EPI_PARTIAL) X(2, 4, 2, 2, EPI_PARTIAL) X(2, 2, 2, 2, EPI_PARTIAL) X(4, 2, 4, 1, EPI_PARTIAL)
 
 hipError_t gemm_configure() {
     hipError_t e = hipSuccess;
@@ -489,6 +496,65 @@ hipError_t gemm_configure() {
 #undef X
     return e;
 }
+
+// ---- which instantiation serves a launch ------------------------------------------------------------------
+struct TileShape {
+    int bmb, nb, wm, wn;  // row blocks, column blocks, waves along M, waves along N
+};
+
+namespace {
+
+// Tiles of a chunk of more than 128 rows that has the chip to itself.  A launch is priced as rounds of workgroups (one
+// workgroup per CU: the ring fills LDS) times what a round of the tile takes, and the cheapest tile (and number of K
+// splits) wins.  The constants are fitted to a sweep of all tiles over 129 .. 2048 rows of the eight projections of the 7B
+// and the 13B shapes (us on one MI355X; fit within 5 % on average; the pick costs 0.8 % more than the best measured
+// tile on average and 6 % at worst).  What it replaced picked the width of a 256-row tile and nothing else; measured
+// before -> after on the 7B shapes: QKV of 2048 rows 208 -> 175 us, of 539 rows (three 256-row tiles for 17 row blocks)
+// 94 -> 59 us; gate/up of 539 rows 123 -> 104 us, of 320 rows 74 -> 59 us; down of 539 rows 69 -> 58 us with its share
+// of the reduction; on the 13B shapes gate/up of 512 rows 136 -> 113 us, QKV 102 -> 76 us.
+struct TileCost {
+    TileShape t;
+    int epilogues;            // 1 << EPI_*: what it is instantiated for
+    float stage, round, qkv;  // us per K stage of 32, per round of workgroups, more per round with the QKV epilogue
+};
+constexpr int kWideEpi = 1 << EPI_QKV | 1 << EPI_SWIGLU, kAnyEpi = kWideEpi | 1 << EPI_PARTIAL;
+constexpr TileCost kTallTiles[] = {
+    {{8, 8, 4, 2}, kAnyEpi, 0.608f, 9.9f, 4.0f}, {{8, 6, 4, 2}, kAnyEpi, 0.496f, 6.3f, 5.3f},
+    {{8, 4, 4, 2}, kAnyEpi, 0.386f, 5.5f, 2.6f}, {{6, 8, 2, 4}, kAnyEpi, 0.496f, 8.1f, 2.5f},
+    {{6, 4, 2, 2}, kAnyEpi, 0.282f, 7.5f, 2.0f}, {{4, 8, 2, 4}, kAnyEpi, 0.401f, 5.4f, 2.2f},
+    {{4, 6, 4, 2}, kAnyEpi, 0.322f, 4.7f, 2.8f}, {{4, 4, 4, 2}, kAnyEpi, 0.230f, 4.1f, 2.0f},
+    {{6, 6, 2, 2}, kWideEpi, 0.437f, 0.3f, 2.3f}, {{4, 3, 4, 1}, kWideEpi, 0.196f, 4.9f, 1.4f},
+    {{8, 3, 4, 1}, 1 << EPI_SWIGLU, 0.343f, 1.0f, 0.0f},
+};
+constexpr float kLaunchUs = 3.0f;
+constexpr float kPartRound = 0.84f;       // a round that fills few CUs still takes this much of a full one
+constexpr float kPartialUsPerByte = 1.0f / 5.2e6f;  // what the reduce + norm pass pays to read a partial sum back
+
+struct TallPick {
+    TileShape t;
+    int splits;
+};
+
+TallPick pick_tall(int epi, int M, int N, int K) {
+    TallPick best{};
+    float best_us = 0.f;
+    const int stages = K / G_BK;
+    for (const TileCost& c : kTallTiles) {
+        if (!(c.epilogues >> epi & 1)) continue;
+        const int tiles = div_up(M, 32 * c.t.bmb) * div_up(N, 32 * c.t.nb);
+        for (int splits = 1; splits <= (epi == EPI_PARTIAL ? 8 : 1); ++splits) {
+            if (stages % splits || (splits > 1 && tiles * splits > kCUs)) continue;
+            const int wgs = tiles * splits, rest = wgs % kCUs;
+            const float rounds = (float)(wgs / kCUs) + (rest ? kPartRound + (1.f - kPartRound) * rest / kCUs : 0.f);
+            float us = kLaunchUs + rounds * (c.stage * (stages / splits) + c.round + (epi == EPI_QKV ? c.qkv : 0.f));
+            if (epi == EPI_PARTIAL) us += 4.f * M * N * splits * kPartialUsPerByte;
+            if (best.splits == 0 || us < best_us) { best = {c.t, splits}; best_us = us; }
+        }
+    }
+    return best;
+}
+
+}  // namespace
 
 // The projections whose N (= d_model) alone cannot fill the chip are split along K; the fp32 partial sums are
 // added up, in split order, by the reduce + norm kernel that follows.
@@ -522,27 +588,8 @@ int gemm_partial_col_blocks(int M, int N, int K) {
 // Measured on the 7B shapes with four lanes: 4 x 512 tokens 274k -> 286k tokens/s, 8 x 256 tokens 204k -> 224k,
 // 16 x 128 and 8 x 64 tokens +3-4 % (no split at all: -4 % there); alone on the chip the same cap costs 8 % (one
 // launch then has to fill it).
-// The output projection of a prefill-sized chunk (K no longer than N, 129 to 512 rows) alone on the chip: 128 x 128
-// tiles with two splits (four for up to 256 rows) instead of 256 x 128 tiles with four.  The K loop is a little slower
-// (a third more LDS traffic per flop), but half the partial sums are written and read back: measured at 512 rows of the 7B shapes, O
-// projection 28.3 -> 29.4 us, the reduce + norm pass behind it 13.7 -> 10.2 us, the prompt +1.5 %.  (The same for the
-// down projection, whose K loop is 2.7 times as long, measured slower: 52.3 -> 59.4 us.)
-static bool square_prefill_projection(int M, int N, int K, bool shared) {
-    // (the down projection too for up to 256 rows: four splits of 86 stages instead of eight of 43; measured at 256
-    // rows 35.9 -> 36.5 us, the reduce + norm pass behind it reads half the partial sums, the prompt as 8 x 256 +1.5 %)
-    return !shared && M > 128 && M <= 512 && (K <= N || M <= 256);  // (longer chunks keep the tall tile)
-}
-
 int gemm_plan_splits(int M, int N, int K, bool shared) {
-    if (square_prefill_projection(M, N, K, shared)) {
-        const int tiles = div_up(M, 128) * div_up(N, 128);
-        int splits = 1;
-        // (up to 256 rows two splits would leave half of the CUs idle: four; measured at 256 rows, O projection
-        // 25.7 -> 21.1 us, the reduce + norm pass behind it 9.8 -> 10.8 us)
-        const int cap = M <= 256 ? 4 : 2;
-        while (tiles * splits * 2 <= kCUs && (K / G_BK) % (splits * 2) == 0 && splits < cap) splits *= 2;
-        return splits;
-    }
+    if (M > 128 && !shared) return pick_tall(EPI_PARTIAL, M, N, K).splits;
     // beside other chunks' kernels: the widest tile of the chunk's row count (see launch_gemm_partial)
     const int nb = shared ? (pick_row_blocks(M) >= 8 ? 8 : 4) : gemm_partial_col_blocks(M, N, K);
     const int s = splits_for(M, N, K, nb);
@@ -571,14 +618,9 @@ int pick_blocks(int M, int N, const int* cands, int n_cands) {
 }
 }  // namespace
 
-// ---- which instantiation serves a launch ------------------------------------------------------------------
-struct TileShape {
-    int bmb, nb, wm, wn;  // row blocks, column blocks, waves along M, waves along N
-};
-
 namespace {
 
-TileShape pick_qkv(int M, int N, bool shared_gpu) {
+TileShape pick_qkv(int M, int N, int K, bool shared_gpu) {
     const int bmb = pick_row_blocks(M);
     // 128-token chunks beside other chunks' kernels: 96-column tiles (half again as much work per workgroup; alone on
     // the chip 64 columns win, 24.0 vs 28.8 us at 64 rows).  Measured with four lanes: 13B shapes, 8 x 128 tokens
@@ -586,24 +628,20 @@ TileShape pick_qkv(int M, int N, bool shared_gpu) {
     if (shared_gpu && bmb == 4) return {4, 3, 4, 1};
     if (bmb == 2) return {2, 2, 2, 2};
     if (bmb == 4) return {4, 2, 4, 1};
-    // 129 to 256 rows alone on the chip: 128 x 96 tiles instead of 256 x 64 (at N = 12288 256 workgroups instead of 192,
-    // and 14 KB instead of 20 KB through the fill path per stage); measured at 256 rows: 48.9 -> 42.8 us
-    if (!shared_gpu && M > 128 && M <= 256) return {4, 3, 4, 1};
+    // (1024 rows stay on 256 x 96 tiles, the documented tiling of that chunk length)
+    if (!shared_gpu && M != 1024) return pick_tall(EPI_QKV, M, N, K).t;
     static const int cands[] = {1, 2, 3};
     const int nb = pick_blocks(M, N, cands, 3);
     // Beside another chunk's kernels (overlapped multi-chunk call) half as many tiles of twice the width do the
     // same work in a quarter less CU time, and the other chunk uses the CUs they leave free: 76 us instead of 59 us
     // for this launch alone, but +1.7 % for the 4 x 512 prompt.  Alone on the chip the narrow tile wins (-6 %).
     if (nb == 3 && shared_gpu && M > 256) return {8, 6, 4, 2};
-    // 385 to 512 rows alone on the chip: 128 x 192 tiles fill the same 256 CUs with 11 % fewer bytes through the fill
-    // path per stage (20 KB against 22.5 KB); measured at 512 rows: 59.5 -> 57.8 us
-    if (nb == 3 && M > 384 && M <= 512) return {4, 6, 4, 2};
     if (nb == 3) return {8, 3, 8, 1};  // 8 waves of 32 x 96: measured 1.3 % faster than 4 of 64 x 96
     if (nb == 2) return {8, 2, 4, 1};
     return {8, 1, 4, 1};
 }
 
-TileShape pick_swiglu(int M, int N, bool shared_gpu) {
+TileShape pick_swiglu(int M, int N, int K, bool shared_gpu) {
     const int bmb = pick_row_blocks(M);
     // A short chunk is bound by streaming the weights, and every CU that streams adds bandwidth: the narrower
     // tile (96 columns) when its tiles still fit one round of workgroups (measured at 64 rows, N = 22016:
@@ -620,27 +658,24 @@ TileShape pick_swiglu(int M, int N, bool shared_gpu) {
     if (bmb == 2 && M <= 32) return narrow ? TileShape{1, 3, 1, 3} : TileShape{1, 4, 1, 4};
     if (bmb == 2) return narrow ? TileShape{2, 3, 2, 3} : TileShape{2, 4, 2, 2};
     if (bmb == 4) return narrow ? TileShape{4, 3, 4, 1} : TileShape{4, 4, 4, 1};
+    if (!shared_gpu) return pick_tall(EPI_SWIGLU, M, N, K).t;
     static const int cands[] = {2, 3, 4, 6};
     const int nb = pick_blocks(M, N, cands, 4);
     // beside other chunks' kernels: the widest tile (see pick_qkv); 256 x 256 over 256 x 192: +1.9 %
-    if (nb == 6 && shared_gpu) return {8, 8, 4, 2};
-    if (nb == 6) return {8, 6, 4, 2};
+    if (nb == 6) return {8, 8, 4, 2};
     if (nb == 4) return {8, 4, 4, 2};
     if (nb == 3) return {8, 3, 4, 1};
     return {8, 2, 4, 1};
 }
 
 TileShape pick_partial(int M, int N, int K, bool shared_gpu) {
-    // (eight waves of 32 x 64 on the 128 x 128 tile: two per SIMD; 29.85 -> 28.8 us against four waves of 32 x 128)
-    if (square_prefill_projection(M, N, K, shared_gpu)) return {4, 4, 4, 2};
     const int bmb = pick_row_blocks(M);
+    if (bmb == 8) return shared_gpu ? TileShape{8, 8, 4, 2}  // beside other chunks' kernels the widest tile (see pick_qkv)
+                                    : pick_tall(EPI_PARTIAL, M, N, K).t;
     // (short chunks beside other chunks' kernels keep the 128-column tile: 64-token chunks +3 %, 128-token +5 %)
     const bool narrow = gemm_partial_col_blocks(M, N, K) == 2 && !shared_gpu;
     if (bmb == 2) return narrow ? TileShape{2, 2, 2, 2} : TileShape{2, 4, 2, 2};
-    if (bmb == 4) return narrow ? TileShape{4, 2, 4, 1} : TileShape{4, 4, 4, 1};
-    // beside other chunks' kernels: the widest tile, as for QKV and gate/up (256 x 256 over 256 x 128: +2.4 %)
-    if (shared_gpu) return {8, 8, 4, 2};
-    return {8, 4, 4, 2};
+    return narrow ? TileShape{4, 2, 4, 1} : TileShape{4, 4, 4, 1};
 }
 
 template <int EPI>
@@ -657,12 +692,12 @@ hipError_t dispatch(TileShape t, const GemmArgs& a, hipStream_t s) {
 
 hipError_t launch_gemm_qkv(GemmArgs a, hipStream_t s) {
     a.splits = 1;
-    return dispatch<EPI_QKV>(pick_qkv(a.M, a.N, a.shared_gpu), a, s);
+    return dispatch<EPI_QKV>(pick_qkv(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 
 hipError_t launch_gemm_swiglu(GemmArgs a, hipStream_t s) {
     a.splits = 1;
-    return dispatch<EPI_SWIGLU>(pick_swiglu(a.M, a.N, a.shared_gpu), a, s);
+    return dispatch<EPI_SWIGLU>(pick_swiglu(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 
 hipError_t launch_gemm_partial(GemmArgs a, hipStream_t s) {
@@ -675,8 +710,8 @@ void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_
     TileShape t{};
     int epi = EPI_PARTIAL;
     switch (kind) {
-        case GEMM_QKV: t = pick_qkv(M, 3 * d_model, shared_gpu); epi = EPI_QKV; break;
-        case GEMM_GATE_UP: t = pick_swiglu(M, 2 * d_ffn, shared_gpu); epi = EPI_SWIGLU; break;
+        case GEMM_QKV: t = pick_qkv(M, 3 * d_model, d_model, shared_gpu); epi = EPI_QKV; break;
+        case GEMM_GATE_UP: t = pick_swiglu(M, 2 * d_ffn, d_model, shared_gpu); epi = EPI_SWIGLU; break;
         case GEMM_O: t = pick_partial(M, d_model, d_model, shared_gpu); break;
         case GEMM_DOWN: t = pick_partial(M, d_model, d_ffn, shared_gpu); break;
     }
