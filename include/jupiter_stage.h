@@ -268,19 +268,19 @@ JUP_API jup_status_t jup_stage_prefill_chunk_static(jup_stage_t *stage, const vo
  * else of them).  Computes what n_chunks calls of jup_stage_prefill_chunk() in order compute, the first at
  * pos_offset: the same cache entries are written, the final length is the same, and without
  * jup_stage_enable_overlap() outputs and cache values are equal bit for bit.  With it they are equal up to the
- * summation order of fp32 partial sums (the projections back to d_model split K into fewer pieces while other
- * chunks share the GPU), i.e. to the last bits of a bf16 value; the call is deterministic either way.
+ * summation order of fp32 partial sums (the projections back to d_model split K according to the rows they
+ * get, and to whether other chunks share the GPU), i.e. to the last bits of a bf16 value; the call is deterministic
+ * either way.
  *   hidden_in     [sum of chunk_tokens, d_model]; the chunks follow each other
  *   chunk_tokens  HOST array [n_chunks], each 0 .. the stage's max_chunk_tokens
  *   hidden_out    [sum of chunk_tokens, d_model]; may be the same buffer as hidden_in
- * After jup_stage_enable_overlap() a JUP_BF16 stage lets consecutive chunks overlap on the GPU: they go round
- * n_lanes lanes (a stream plus a scratch buffer each; lane 0 is `stream` with the stage's own workspace), and a
- * chunk waits, per layer, only for the cache appends of the chunks before it before its own attention.  The
- * ramp-up and the tail of one chunk's kernels are then filled with another chunk's work, and the weights of a
- * layer that one chunk streamed from HBM are still in the last-level cache when the next chunk asks for them
- * (the paper fills the stages of a pipeline with sub-sequences in the same way, across devices).  Chunks of up
- * to 256 tokens use all enabled lanes; longer ones all of them when their number is a multiple of four, else two.
- * On return all
+ * After jup_stage_enable_overlap() a JUP_BF16 stage (or a JUP_BF16_W4 one with its bf16 copy, all chunks longer than 64
+ * tokens) computes consecutive chunks of up to 1024 tokens together, in groups of up to 2048 tokens as far as the scratch
+ * handed over there reaches: the weights of a layer are then read once per group.  Longer chunks overlap on the GPU
+ * instead: they go round n_lanes lanes (a stream plus a scratch buffer each; lane 0 is `stream` with the stage's own
+ * workspace), and a chunk waits, per layer, only for the cache appends of the chunks before it before its own attention
+ * (the paper fills the stages of a pipeline with sub-sequences in the same way, across devices); all enabled lanes when
+ * their number is a multiple of four, else two.  On return all
  * work is ordered before whatever is enqueued on `stream` next.  Without jup_stage_enable_overlap(), and in check
  * mode, the chunks simply run one after the other on `stream`.
  * Errors: as jup_stage_prefill_chunk(); every chunk is validated before anything is enqueued.

@@ -31,3 +31,32 @@ def test_bf16_tall_tiles(d_model, n_heads, d_ffn, rows, tiles):
     g, o = p.run_both(hidden, [7, rows])
     p.check(g[7:], o[7:], f"{rows} rows of d {d_model}")
     p.check(p.kv_gpu()[0], p.oracle.kv[0], "cache")
+
+
+@pytest.mark.parametrize("n_lanes,chunks,limit", [
+    (2, [70, 3, 0, 129, 64, 300], 300),     # one group: row counts that are no multiple of a row block
+    (2, [250] * 9, 250),                    # more rows than the lanes' buffer holds: several groups
+    (4, [768, 768, 600, 1], 768),           # more than 2048 rows: groups of about the same height
+    (3, [1025, 30, 1100, 5], 1100),         # a chunk above 1024 tokens: the lanes
+])
+def test_bf16_chunks_in_one_call(n_lanes, chunks, limit):
+    """The multi-chunk call with overlap enabled against the oracle, behind a cached prefix, on a cache that is a fork."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=1024, n_heads=8, d_ffn=2816, n_layers=2)
+    total = sum(chunks)
+    p = Pair(cfg, "bf16", seed=limit, max_positions=total + 40, max_chunk_tokens=limit)
+    p.stage.enable_overlap(n_lanes)
+    hidden = p.hidden(total + 40)
+    p.gpu_chunk(hidden[:40], 0)
+    p.oracle.prefill_chunk(hidden[:40], 0)
+    fork = p.kv.fork(40, total + 40)
+    x = torch.from_numpy(hidden[40:]).to("cuda:0", p.td)
+    y = p.stage.prefill_chunks(x, chunks, 40, fork)
+    assert len(fork) == total + 40
+    want = p.oracle.prefill_chunk(hidden[40:], 40)
+    p.check(y.float().cpu().numpy(), want, "hidden states")
+    kv = fork.view().float().cpu().numpy()
+    for l in range(cfg["n_layers"]):
+        p.check(kv[l], p.oracle.kv[l][:, :, 40:total + 40], f"cache layer {l}")
+    again = p.stage.prefill_chunks(x, chunks, 40, fork)
+    assert torch.equal(again, y)
