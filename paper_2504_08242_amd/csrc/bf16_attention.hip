@@ -89,6 +89,70 @@ __device__ inline float max_across_halves(float x) {
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// max over the two 16-lane rows of each half.
+__device__ inline float max_across_rows(float x) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// Merge of the key ranges of a query block across workgroups, run by the THREADS computing threads of each of them behind
+// their coherent stores of the range's un-normalised rows and statistics.  Every wave waits until its (chip-coherent) stores
+// have been performed, the workgroup counts itself in, and the workgroup that finds all others already counted does the
+// merge.  Nobody waits for anybody.  flag: an LDS word nobody else uses any more.
+template <int QR, int THREADS>
+__device__ __forceinline__ void merge_key_ranges(int tid, int* flag, const float* split_buf, int* split_count, int block, int ranges,
+                                                 int n_splits, int q0, int n, int row0, int head, int d_model, u16* o) {
+    wait_stores_performed();
+    __syncthreads();
+    if (tid == 0) {
+        const int before = arrive_coherent(split_count + block);
+        *flag = before == n_splits - 1;
+        if (before == n_splits - 1) split_count[block] = 0;  // ready for the next launch on this stream
+    }
+    __syncthreads();
+    if (!*flag) return;
+    const float* base = split_buf + (size_t)block * ranges * QR * kAttSplitRow;
+    for (int idx = tid; idx < QR * 16; idx += THREADS) {
+        const int qr = idx >> 4, ch = idx & 15;
+        const int qrow = q0 + qr;
+        if (qrow >= n) continue;
+        // (max, sum) of every key range: at most 8, loops unrolled under a condition so that the array stays in
+        // registers; all loads first, then the sums in range order, whoever came last
+        static_assert(att_max_splits(1) <= 8, "the merge holds at most 8 ranges");
+        float2 stat[8], val[8][4];  // every load is issued before the first is used: they come from memory, not L2
+#pragma unroll
+        for (int sp = 0; sp < 8; ++sp)
+            if (sp < n_splits) {
+                const float* row = base + ((size_t)sp * QR + qr) * kAttSplitRow;
+                stat[sp] = load_coherent2(row + 128);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) val[sp][e] = load_coherent2(row + ch * 8 + 2 * e);
+            }
+        float m_all = -INFINITY;
+#pragma unroll
+        for (int sp = 0; sp < 8; ++sp)
+            if (sp < n_splits) m_all = fmaxf(m_all, stat[sp].x);
+        float l_all = 0.f;
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int sp = 0; sp < 8; ++sp)
+            if (sp < n_splits && stat[sp].x != -INFINITY) {  // (-inf: a range this query sees nothing of)
+                const float w = exp2f(stat[sp].x - m_all);
+                l_all += stat[sp].y * w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[2 * e] += val[sp][e].x * w;
+                    acc[2 * e + 1] += val[sp][e].y * w;
+                }
+            }
+        const float inv = 1.0f / l_all;
+        u32x4 out;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv);
+        *(u32x4*)(o + tiled_offset(row0 + qrow, head * 16 + ch, d_model >> 5)) = out;
+    }
+}
+
 template <int NQ, int LPQ = 1, int KP = 4>
 __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(const u16* __restrict__ q, u16* __restrict__ o,
                                                                   int n, int d_model, int n_heads, int pos0_arg,
@@ -393,66 +457,342 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
     }
     if (n_splits == 1) return;
 
-    // ---- merge the key ranges of the query block across workgroups ---------------------------------------------------
-    // Every wave waits until its (chip-coherent) stores have been performed, the workgroup counts itself in, and the
-    // workgroup that finds all others already counted does the merge.  Nobody waits for anybody.
-    wait_stores_performed();
-    __syncthreads();
-    int* flag = (int*)(lds + kStatOffset);  // (the statistics in LDS are no longer needed)
-    if (tid_m == 0) {
-        const int before = arrive_coherent(split_count + blockIdx.x);
-        *flag = before == n_splits - 1;
-        if (before == n_splits - 1) split_count[blockIdx.x] = 0;  // ready for the next launch on this stream
+    merge_key_ranges<QR, 64 * KP * NQ>(tid_m, (int*)(lds + kStatOffset), split_buf, split_count, blockIdx.x, gridDim.y, n_splits, q0, n, row0, head,
+                                       d_model, o);
+}
+
+// ---- short chunks: one query block of 16 or 32 per workgroup --------------------------------------------------------
+// Decode-sized and short chunks have a handful of query blocks, so what a workgroup is short of is tiles in flight: a tile
+// is a trip to the caches or to HBM (1 - 1.5 us) away, and a pair of K and V tiles feeds its wave for half a microsecond.
+// Here every wave works alone: it owns the key tiles wave, wave + 8, ... of the workgroup's range and one LDS slot for a K
+// and one for a V tile, refills the K slot as soon as the scores are out of it and the V slot as soon as the products
+// are, and meets the others at one barrier in front of the loop (the queries, shared through LDS) and at those of the
+// merge.  128 KB per CU are then in flight from the first microsecond on, where the loader waves of the kernel above keep
+// one tile per key quarter ahead and a round lasts as long as a tile's trip.  Same tile layouts, products and softmax as
+// there.  Measured against that kernel (one query block, loader waves; 32 heads, us per launch): 1 token behind 576
+// positions 9.1 -> 7.4, behind 8192 31.7 -> 27.3 (4.9 TB/s of keys and values); 64 tokens behind 576 10.0 -> 7.9; 128 tokens
+// behind 2048 24.4 -> 18.7.  What is left at 576 positions is the path into LDS of the 32 CUs (19 pairs of tiles of 16 KB at
+// 49 B/clk: 2.7 us), the first trip to memory (1.3 us), entry and merge; two workgroups per head would halve the first and
+// pay as much for the exchange.  Chunks of up to 16 tokens (QW = 16) run on the 16x16x32 MFMA: half the products, exponentials and merged rows of
+// the 32-wide block, whose other half they would leave empty.  Its operand layout (lane = 16 g + c): A[m = c][k = 8 g + e],
+// B[k = 8 g + e][n = c], D[m = 4 g + i][n = c] in register i < 4; the PV contraction index 8 g + e stands for key
+// 4 g + e (e < 4) or 16 + 4 g + e - 4 of the tile, and the V fragment is read for exactly that order.
+constexpr int kShortWaves = 8;
+constexpr int kShortQ = kShortWaves * kSlotBytes;          // LDS offset of the query block, K tile layout
+constexpr int kShortStat = kShortQ + kTileBytes;           // statistics of the waves, [8][QW] maxima, then sums
+constexpr int kShortLds = kShortStat + 2 * kShortWaves * 32 * 4;
+static_assert(kShortWaves * 32 * 132 * 4 <= kShortStat, "merge regions overlap the statistics");
+
+template <int QW>
+__global__ __launch_bounds__(64 * kShortWaves) void short_attention_bf16(const u16* __restrict__ q, u16* __restrict__ o, int n,
+                                                                         int d_model, int n_heads, int pos0_arg, KvView kv_arg,
+                                                                         int layer, float scale_log2e,
+                                                                         const BranchTable* __restrict__ branches,
+                                                                         const TreeTable* __restrict__ tree,
+                                                                         float* __restrict__ split_buf,
+                                                                         int* __restrict__ split_count) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    constexpr int NW = kShortWaves;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & (QW - 1), hh = lane / QW;  // the lane's query column, and which of the 64 / QW lanes of it this is
+    // grid: heads x query blocks (of all branches) x key ranges; no division stands between the entry and the first load,
+    // and the query blocks of a head that read the same range run side by side on one XCD (one L2)
+    const int head = blockIdx.x, split = blockIdx.z, block = blockIdx.y * n_heads + head;
+    const int q_blocks = (n + QW - 1) / QW;
+    int branch = 0, qb = blockIdx.y;
+    if (branches && q_blocks == 1) {
+        branch = qb;
+        qb = 0;
+    } else if (branches) {
+        branch = qb / q_blocks;
+        qb -= branch * q_blocks;
     }
-    __syncthreads();
-    if (!*flag) return;
-    const float* base = split_buf + (size_t)blockIdx.x * gridDim.y * QR * kAttSplitRow;
-    for (int idx = tid_m; idx < QR * 16; idx += 64 * KP * NQ) {
-        const int qr = idx >> 4, ch = idx & 15;
-        const int qrow = q0 + qr;
-        if (qrow >= n) continue;
-        // (max, sum) of every key range: at most 8, loops unrolled under a condition so that the array stays in
-        // registers; all loads first, then the sums in range order, whoever came last
-        static_assert(att_max_splits(1) <= 8, "the merge holds at most 8 ranges");
-        float2 stat[8], val[8][4];  // every load is issued before the first is used: they come from memory, not L2
+    const int q0 = (q_blocks - 1 - qb) * QW;
+    const int row0 = branch * n;
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_byte_address(lds));
+    const int lrow = lane >> 4, lp = lane & 15;
+
+    // this wave's four rows of the query block into LDS (K tile layout); rows past the chunk repeat its last one
+    if (4 * wave < QW) {
+        const int r = 4 * wave + lrow;
+        const u16* qp = q + (size_t)(row0 + min(q0 + r, n - 1)) * d_model + head * 128;
+        load_to_lds_16(qp + (lp ^ (r & 15)) * 8, lds0 + kShortQ + wave * 1024);
+    }
+    const int pos0 = __builtin_amdgcn_readfirstlane(branches ? branches->pos0[branch] : pos0_arg);
+    KvView kv = branches ? branches->kv[branch] : kv_arg;
+    kv.own = (void*)uniform_ptr((const char*)kv.own);
+    kv.parent = (const void*)uniform_ptr((const char*)kv.parent);
+    kv.n_shared = __builtin_amdgcn_readfirstlane(kv.n_shared);
+    kv.own_cap = __builtin_amdgcn_readfirstlane(kv.own_cap);
+    kv.parent_cap = __builtin_amdgcn_readfirstlane(kv.parent_cap);
+    const int n_keys = pos0 + min(q0 + QW, n);  // keys the last query of the block sees
+    const int n_tiles = (n_keys + kKT - 1) / kKT;
+    const int last_key = n_keys - 1;
+    const int first_masked_tile = tree ? pos0 / kKT : (pos0 + q0 + 1) / kKT;  // (see chunk_attention_bf16)
+
+    // key splits over workgroups: this one owns the tiles [t_lo, t_hi) of the query block
+    const int n_splits = min(att_key_splits(n, n_tiles), (int)gridDim.z);
+    if (split >= n_splits) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (nothing may land in LDS once the workgroup is gone)
+        return;
+    }
+    int t_lo = 0, t_hi = n_tiles;
+    if (n_splits > 1) {
+        t_lo = (unsigned)(split * n_tiles) / (unsigned)n_splits;  // at most 8 x 2^26
+        t_hi = (unsigned)((split + 1) * n_tiles) / (unsigned)n_splits;
+    }
+
+    // ---- tile fill: load j covers rows 4j..4j+3 (1 KB of LDS); lane i lands at row 4j + (i >> 4), position i & 15, and
+    // fetches the chunk that belongs there
+    const size_t plane_k = ((size_t)layer * 2 + 0) * n_heads + head;
+    const size_t plane_v = ((size_t)layer * 2 + 1) * n_heads + head;
+    auto fill = [&](int tile, bool v_part) __attribute__((always_inline)) {
+        const unsigned dst = lds0 + wave * kSlotBytes + (v_part ? kTileBytes : 0);
+        const size_t plane = v_part ? plane_v : plane_k;
+        const u16* own = (const u16*)kv.own + plane * (size_t)kv.own_cap * 128;
+        const u16* par = (const u16*)kv.parent + plane * (size_t)kv.parent_cap * 128;
+        const int key0 = tile * kKT;
+        if (key0 + kKT - 1 <= last_key && (key0 >= kv.n_shared || key0 + kKT <= kv.n_shared)) {
+            const bool shared = key0 < kv.n_shared;
+            const char* base = uniform_ptr((const char*)((shared ? par : own) + (size_t)(shared ? key0 : key0 - kv.n_shared) * 128));
+            const unsigned vch = (((lp >> 2) ^ lrow) << 2) | (lp & 3);
 #pragma unroll
-        for (int sp = 0; sp < 8; ++sp)
-            if (sp < n_splits) {
-                const float* row = base + ((size_t)sp * QR + qr) * kAttSplitRow;
-                stat[sp] = load_coherent2(row + 128);
+            for (int j = 0; j < 8; ++j)
+                load_to_lds_16(base + j * 1024, lrow * 256 + (v_part ? vch : (lp ^ (4 * (j & 3) + lrow))) * 16, dst + j * 1024);
+        } else {  // the last tile, or one across the border of the shared prefix: keys past the last repeat it
 #pragma unroll
-                for (int e = 0; e < 4; ++e) val[sp][e] = load_coherent2(row + ch * 8 + 2 * e);
+            for (int j = 0; j < 8; ++j) {
+                const int r = 4 * j + lrow;
+                const int key = min(key0 + r, last_key);
+                const bool shared = key < kv.n_shared;
+                const unsigned row_off = (unsigned)(shared ? key : key - kv.n_shared) * 128u;  // elements, < 2^31
+                const unsigned ch = v_part ? ((((lp >> 2) ^ (r & 3)) << 2) | (lp & 3)) : (lp ^ (r & 15));
+                load_to_lds_16((shared ? par : own) + row_off + ch * 8, dst + j * 1024);
             }
+        }
+    };
+    int tile = t_lo + wave;
+    if (tile < t_hi) {
+        fill(tile, false);
+        fill(tile, true);
+        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");  // the query rows have landed, the tiles are on their way
+    } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    __builtin_amdgcn_s_barrier();
+
+    constexpr int KS = QW == 16 ? 4 : 8;   // MFMA steps over the head's 128 features
+    constexpr int NS = QW == 16 ? 8 : 16;  // scores of a tile per lane
+    constexpr int DB = QW == 16 ? 8 : 4;   // output blocks of QW features
+    typedef float acc_t __attribute__((ext_vector_type(QW == 16 ? 4 : 16)));
+    // 16-byte chunk `hh` of K (or Q) row c; the chunk of MFMA step ks is 64 / QW * ks further: an XOR in this layout
+    constexpr unsigned kStep = QW == 16 ? 64 : 32;
+    const unsigned k_lane = c * 256 + ((hh ^ (c & 15)) * 16);
+    bf16x8 qf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(lds + kShortQ + (k_lane ^ (kStep * ks)));
+    acc_t oacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < (QW == 16 ? 4 : 16); ++r) oacc[db][r] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    const int G = lane >> 4, s = lane & 15;
+    const int vt_row = QW == 16 ? 4 * G + (s >> 2) : 4 * (G >> 1) + (s >> 2);
+    const unsigned v_base = lds0 + wave * kSlotBytes + kTileBytes;
+    unsigned v_lane[4];  // by 64-byte feature group (32 features)
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+        v_lane[db] = v_base + vt_row * 256 + ((db ^ (vt_row & 3)) << 6) + ((QW == 16 ? 0 : 2 * (G & 1)) + ((s & 3) >> 1)) * 16 +
+                     8 * (s & 1);
+    // key of the lane's score number r, relative to the tile
+    auto key_of = [&](int r) { return QW == 16 ? 16 * (r >> 2) + 4 * hh + (r & 3) : acc_row(r, hh); };
+    const int q_abs = pos0 + q0 + c;  // cache entry of this lane's query
+    const unsigned long long q_sees = tree ? tree->sees[min(q0 + c, n - 1)] : 0ull;
+    const unsigned char* k_base = lds + wave * kSlotBytes;
+
+    for (; tile < t_hi; tile += NW) {
+        const bool more = tile + NW < t_hi;
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // the K tile has landed; V may be in flight
+
+        // ---- S^T = K Q^T ----
+        bf16x8 kf[8];
+        float sv[NS];
+        if constexpr (QW == 16) {
+#pragma unroll
+            for (int f = 0; f < 8; ++f) kf[f] = *(const bf16x8*)(k_base + (f >> 2) * 4096 + (k_lane ^ (kStep * (f & 3))));
+            f32x4 sacc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int f = 0; f < 8; ++f)
+                sacc[f & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[4 * (f & 1) + (f >> 1)], qf[f >> 1], sacc[f & 1], 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < NS; ++r) sv[r] = sacc[r >> 2][r & 3];
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const bf16x8*)(k_base + (k_lane ^ (kStep * ks)));
+            f32x16 sacc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) sacc = mfma32(kf[ks], qf[ks], sacc);
+#pragma unroll
+            for (int r = 0; r < NS; ++r) sv[r] = sacc[r];
+        }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the K slot has been read
+            fill(tile + NW, false);
+        }
+
+        // ---- online softmax (a lane owns one query column) ----
+        if (tile >= first_masked_tile) {
+            asm volatile("");  // keeps this a branch (see chunk_attention_bf16)
+            const int key0 = tile * kKT;
+            if (tree) {
+#pragma unroll
+                for (int r = 0; r < NS; ++r) {
+                    const int rel = key0 + key_of(r) - pos0;
+                    if (rel >= 0 && (rel >= kMaxTreeTokens || !((q_sees >> (rel & 63)) & 1))) sv[r] = -INFINITY;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < NS; ++r)
+                    if (key0 + key_of(r) > q_abs) sv[r] = -INFINITY;
+            }
+        }
+        float mt = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < NS; ++r) mt = fmaxf(mt, sv[r]);
+        if constexpr (QW == 16) mt = max_across_rows(mt);
+        mt = max_across_halves(mt) * scale_log2e;
+        const bool grow = mt > m_run + 8.0f;
+        const float m_new = grow ? mt : m_run;
+        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = grow ? __builtin_amdgcn_exp2f(m_run - m_safe) : 1.0f;
+        const bool rescale = grow && m_run != -INFINITY;
+        float ps = 0.f;
+        bf16x8 pf[NS / 8];
+#pragma unroll
+        for (int r = 0; r < NS; ++r) {
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], scale_log2e, -m_safe));
+            ps += p;
+            pf[r >> 3][r & 7] = (__bf16)p;
+        }
+        l_run = l_run * alpha + ps;
+        m_run = m_new;
+        if (__any(rescale)) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < (QW == 16 ? 4 : 16); ++r) oacc[db][r] *= alpha;
+        }
+
+        // ---- O^T += V^T P^T ----
+        if (more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // V has landed, the next K may be in flight
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        u32x4 vf[8];
+        [&]<int... F>(std::integer_sequence<int, F...>) {
+            (([&] {
+                 // QW = 32: feature block F / 2, key half F % 2; QW = 16: feature block F, all 32 keys
+                 constexpr int at = QW == 16 ? (F % 2) * 32 : (F % 2) * 16 * 256;
+                 constexpr int next = QW == 16 ? 16 * 256 : 8 * 256;
+                 const u32x2 lo = ds_read_tr16<at>(v_lane[F / 2]);
+                 const u32x2 hi = ds_read_tr16<at + next>(v_lane[F / 2]);
+                 vf[F] = (u32x4){lo[0], lo[1], hi[0], hi[1]};
+             }()),
+             ...);
+        }(std::make_integer_sequence<int, 8>{});
+        [&]<int... F>(std::integer_sequence<int, F...>) {
+            (([&] {
+                 wait_tr_reads<14 - 2 * F>(vf[F]);
+                 if constexpr (QW == 16)
+                     oacc[F] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[F]), pf[0], oacc[F], 0, 0, 0);
+                 else
+                     oacc[F / 2] = mfma32(__builtin_bit_cast(bf16x8, vf[F]), pf[F % 2], oacc[F / 2]);
+             }()),
+             ...);
+        }(std::make_integer_sequence<int, 8>{});
+        if (more) fill(tile + NW, true);  // (every read of the V slot has been waited for)
+    }
+
+    // ---- merge the waves ----
+    constexpr int kORow = 132;
+    constexpr int kRegion = QW * kORow;
+    float* obuf = (float*)lds;
+    float* stat_m = (float*)(lds + kShortStat);
+    float* stat_l = stat_m + NW * QW;
+    {
+        float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+        if (QW == 16) l_tot += __shfl_xor(l_tot, 16, 64);
+        if (hh == 0) {
+            stat_m[wave * QW + c] = m_run;
+            stat_l[wave * QW + c] = l_tot;
+        }
+    }
+    __syncthreads();  // statistics visible; every wave is done with its slots
+    const bool live = q0 + c < n;
+    if (live) {
+        float sm[NW], sl[NW];  // all reads first, no branch between them
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            sm[w] = stat_m[w * QW + c];
+            sl[w] = stat_l[w * QW + c];
+        }
         float m_all = -INFINITY;
 #pragma unroll
-        for (int sp = 0; sp < 8; ++sp)
-            if (sp < n_splits) m_all = fmaxf(m_all, stat[sp].x);
+        for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, sm[w]);
+        const float m_ref = m_all == -INFINITY ? 0.f : m_all;  // (a range this query sees nothing of: every weight is 0)
         float l_all = 0.f;
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int sp = 0; sp < 8; ++sp)
-            if (sp < n_splits && stat[sp].x != -INFINITY) {  // (-inf: a range this query sees nothing of)
-                const float w = exp2f(stat[sp].x - m_all);
-                l_all += stat[sp].y * w;
+        for (int w = 0; w < NW; ++w) l_all += sl[w] * __builtin_amdgcn_exp2f(sm[w] - m_ref);
+        // one workgroup for all keys: normalised here; key splits: left un-normalised for the merge across workgroups
+        const float wscale = __builtin_amdgcn_exp2f(m_run - m_ref) * (n_splits > 1 ? 1.0f : 1.0f / l_all);
+        float* mine = obuf + wave * kRegion + c * kORow;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[2 * e] += val[sp][e].x * w;
-                    acc[2 * e + 1] += val[sp][e].y * w;
-                }
-            }
-        const float inv = 1.0f / l_all;
-        u32x4 out;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv);
-        *(u32x4*)(o + tiled_offset(row0 + qrow, head * 16 + ch, d_model >> 5)) = out;
+        for (int f = 0; f < (QW == 16 ? 8 : 16); ++f) {  // four consecutive features per write
+            const int db = QW == 16 ? f : f >> 2, r = QW == 16 ? 0 : 4 * (f & 3);
+            *(float4*)(mine + (QW == 16 ? 16 * f : 8 * f) + 4 * hh) =
+                make_float4(oacc[db][r] * wscale, oacc[db][r + 1] * wscale, oacc[db][r + 2] * wscale, oacc[db][r + 3] * wscale);
+        }
+        if (n_splits > 1 && wave == 0 && hh == 0)  // statistics of this key range, one pair per query row
+            store_coherent2(split_buf + ((size_t)(block * gridDim.z + split) * QW + c) * kAttSplitRow + 128, m_all, l_all);
     }
+    __syncthreads();
+    for (int idx = tid; idx < min(QW, n - q0) * 16; idx += 64 * NW) {
+        const int qr = idx >> 4, ch = idx & 15;
+        const float* src = obuf + qr * kORow + ch * 8;
+        float4 a = *(const float4*)src, b = *(const float4*)(src + 4);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            const float4 a2 = *(const float4*)(src + w * kRegion), b2 = *(const float4*)(src + w * kRegion + 4);
+            a.x += a2.x; a.y += a2.y; a.z += a2.z; a.w += a2.w;
+            b.x += b2.x; b.y += b2.y; b.z += b2.z; b.w += b2.w;
+        }
+        if (n_splits > 1) {
+            float* dst = split_buf + ((size_t)(block * gridDim.z + split) * QW + qr) * kAttSplitRow + ch * 8;
+            store_coherent2(dst, a.x, a.y);
+            store_coherent2(dst + 2, a.z, a.w);
+            store_coherent2(dst + 4, b.x, b.y);
+            store_coherent2(dst + 6, b.z, b.w);
+            continue;
+        }
+        u32x4 out;
+        out[0] = pack_bf16x2(a.x, a.y); out[1] = pack_bf16x2(a.z, a.w);
+        out[2] = pack_bf16x2(b.x, b.y); out[3] = pack_bf16x2(b.z, b.w);
+        *(u32x4*)(o + tiled_offset(row0 + q0 + qr, head * 16 + ch, d_model >> 5)) = out;
+    }
+    if (n_splits == 1) return;
+    merge_key_ranges<QW, 64 * NW>(tid, (int*)(lds + kShortStat), split_buf, split_count, block, gridDim.z, n_splits, q0, n, row0, head,
+                                  d_model, o);
 }
 
 }  // namespace
 
 hipError_t attention_configure() {
-    hipError_t e = hipFuncSetAttribute((const void*)chunk_attention_bf16<1, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kAttLds);
+    hipError_t e = hipFuncSetAttribute((const void*)short_attention_bf16<16>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       kShortLds);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute((const void*)short_attention_bf16<32>, hipFuncAttributeMaxDynamicSharedMemorySize, kShortLds);
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)chunk_attention_bf16<4, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             kAttLds);
@@ -461,9 +801,6 @@ hipError_t attention_configure() {
                                kAttLds);
 }
 
-// Block sizes: 4 NQ computing waves + 4 loader waves per part loaded separately.  Chunks of up to 64 tokens run
-// one query block per workgroup with separate K and V loaders (decode-sized attention is a chain of short
-// rounds, each as long as its tile fill); longer chunks two query blocks sharing every tile.
 namespace {
 // a split launch must fit the scratch the workspace reserves for it (it does by construction: see att_split_rows)
 bool split_fits(const AttScratch& sc, int wgs, int splits, int query_rows) {
@@ -486,15 +823,17 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     }
     // chunks of up to 256 tokens behind a long cached sequence: several workgroups per query block (key splits)
     const int splits = att_key_splits(n, (pos0 + n + kKT - 1) / kKT);
-    // 32 queries per workgroup up to 64 tokens, and up to 128 when the launch has the chip to itself (twice the
-    // workgroups of the 64-query variant, which a launch this small needs more than shared tile fills: measured on
-    // 128-token chunks, 7B shapes 18.4 -> 17.0 us, 13B shapes 14.6 -> 13.0 us; inside an overlapped call the same
-    // choice costs 2-3.5 %, at 256 tokens it gains nothing)
-    if (n <= (shared_gpu ? 64 : 128)) {
+    // One query block per workgroup up to 64 tokens, up to 128 when the launch has the chip to itself, and beyond that as
+    // long as all its workgroups run at once (256 CUs, one workgroup each); with more of them the 64-query variant's shared
+    // tile fills win.  Measured, 64-query variant -> one block: 32 heads, 256 tokens behind 256 positions (256 workgroups)
+    // 10.4 -> 7.7 us, behind 2048 (512 workgroups) 31.0 -> 34.3 us; 320 tokens behind 256 (320 workgroups) 11.3 -> 12.4 us;
+    // 8 heads, 512 tokens behind 1024 (128 workgroups) 17.2 -> 12.3 us.
+    const bool short_blocks = n <= 64 || (!shared_gpu && (n <= 128 || (n + 31) / 32 * n_heads * splits <= 256));
+    if (short_blocks) {
         const int wgs = (n + 31) / 32 * n_heads;
         if (!split_fits(sc, wgs, splits, 32)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((chunk_attention_bf16<1, 2>), dim3(wgs, splits), dim3(768), kAttLds, s, q, o, n, d_model,
-                           n_heads, pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
+        hipLaunchKernelGGL(n <= 16 ? short_attention_bf16<16> : short_attention_bf16<32>,
+                           dim3(n_heads, (n + 31) / 32, splits), dim3(64 * kShortWaves), kShortLds, s, q, o, n, d_model, n_heads, pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
     } else {
         const int wgs = (n + 63) / 64 * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
@@ -513,8 +852,8 @@ hipError_t launch_branch_attention(const u16* q, u16* o, int n, int n_branches, 
     if (n <= 64) {
         const int wgs = n_branches * ((n + 31) / 32) * n_heads;
         if (!split_fits(sc, wgs, splits, 32)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((chunk_attention_bf16<1, 2>), dim3(wgs, splits), dim3(768), kAttLds, s, q, o, n, d_model,
-                           n_heads, 0, none, layer, scale_log2e, branches, no_tree, sc.split_buf, sc.split_count);
+        hipLaunchKernelGGL(n <= 16 ? short_attention_bf16<16> : short_attention_bf16<32>,
+                           dim3(n_heads, n_branches * ((n + 31) / 32), splits), dim3(64 * kShortWaves), kShortLds, s, q, o, n, d_model, n_heads, 0, none, layer, scale_log2e, branches, no_tree, sc.split_buf, sc.split_count);
     } else {
         const int wgs = n_branches * ((n + 63) / 64) * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;

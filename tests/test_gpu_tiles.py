@@ -60,3 +60,30 @@ def test_bf16_chunks_in_one_call(n_lanes, chunks, limit):
         p.check(kv[l], p.oracle.kv[l][:, :, 40:total + 40], f"cache layer {l}")
     again = p.stage.prefill_chunks(x, chunks, 40, fork)
     assert torch.equal(again, y)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "w4"])
+@pytest.mark.parametrize("n,pos,shared", [
+    (1, 0, 0), (1, 31, 17), (15, 33, 32), (16, 240, 100), (17, 255, 255), (31, 256, 1), (33, 500, 490), (64, 700, 333),
+    (5, 1100, 1024), (16, 2300, 0), (17, 2300, 2299),   # several key ranges per query block
+    (65, 40, 0), (129, 700, 64), (256, 1, 0), (300, 5, 5),
+])
+def test_short_attention(dtype, n, pos, shared):
+    """Query blocks of 16 and 32 rows, partial blocks, key counts around a tile and around a second key range, forks whose
+    border falls inside a tile, and the tree mask against the oracle."""
+    cfg = dict(si.LLAMA7B_STAGE, d_model=256, n_heads=2, d_ffn=128, n_layers=1)
+    p = Pair(cfg, dtype, seed=n + pos, max_positions=pos + n, max_chunk_tokens=max(n, 512))
+    hidden = p.hidden(pos + n)
+    p.run_both(hidden[:shared], [min(512, shared - i) for i in range(0, shared, 512)] or [0])
+    kv = p.kv.fork(shared, pos + n) if shared else p.kv
+    for lo in range(shared, pos, 512):
+        h = hidden[lo:min(pos, lo + 512)]
+        p.gpu_chunk(h, lo, kv)
+        p.oracle.prefill_chunk(h, lo)
+    h = hidden[pos:]
+    first = p.gpu_chunk(h, pos, kv)
+    p.check(first, p.oracle.prefill_chunk(h, pos), "chunk")
+    assert np.array_equal(p.gpu_chunk(h, pos, kv), first)
+    if n <= 64:
+        parents = si.make_token_tree(n, 3)
+        p.check(p.gpu_tree(h, pos, parents, kv), p.oracle.prefill_tree(h, parents, pos), "tree")
