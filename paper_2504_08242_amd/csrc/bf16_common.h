@@ -200,7 +200,7 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
 hipError_t launch_branch_attention(const u16* q, u16* o, int n, int n_branches, int d_model, int n_heads,
                              const BranchTable* branches, int max_keys, int layer, hipStream_t s, AttScratch scratch);
 
-// ---- packing, rotary table, reduce + norm (bf16_misc.hip) -------------------------------------------
+// ---- packing, first kernel of a call, reduce + norm (bf16_misc.hip) -------------------------------------------
 void launch_pack_qkv(u16* dst, const u16* wq, const u16* wk, const u16* wv, int d, hipStream_t s);
 void launch_pack_gate_up(u16* dst, const u16* wg, const u16* wu, int d, int f, hipStream_t s);
 void launch_pack_plain(u16* dst, const u16* w, int n_rows, int k, hipStream_t s);
@@ -210,16 +210,25 @@ void launch_expand_qkv(u16* dst, const void* cq, const void* ck, const void* cv,
 void launch_expand_gate_up(u16* dst, const void* cg, const void* cu, const float* sg, const float* su, int d, int f,
                            hipStream_t s);
 void launch_expand_plain(u16* dst, const void* c, const float* sc, int n_rows, int k, hipStream_t s);
-// (the rotary-table kernel is the first of every call; it also clears the call's arrival counters: zero[0 .. n_zero))
-void launch_rope_table(float2* tab, int n, int pos0, float theta, int* zero, int n_zero, hipStream_t s);
-void launch_rope_table_tree(float2* tab, int n, int pos0, const TreeTable* tree, float theta, int* zero, int n_zero,
-                            hipStream_t s);
-void launch_rope_table_branches(float2* tab, int n_rows, const BranchTable* branches, float theta, int* zero, int n_zero,
-                                hipStream_t s);
-void launch_write_branch_table(const BranchTable& host_table, BranchTable* dst, hipStream_t s);
-// x32 <- (hidden_in ? hidden_in : x32) + sum_s partial[s];  xn <- rmsnorm(x32) * g (if g), tiled layout;
-// out <- bf16(x32) (if out), row-major
-void launch_reduce_norm(float* x32, const u16* hidden_in, const float* partial, int splits, size_t split_stride,
-                        const u16* g, u16* xn, u16* out, int n, int d, float eps, hipStream_t s);
+// The first kernel of a call: norm of the first layer (x32 <- hidden_in, xn <- rmsnorm * g), the rotary table of the rows,
+// zero[0 .. n_zero) <- 0 (the call's arrival counters), and the call's table, if it has one, to dst.
+struct BeginArgs {
+    float* x32;
+    const u16* hidden_in;
+    const u16* g;
+    u16* xn;
+    int n, d;
+    float eps;
+    float2* rope;  // [n][64]
+    float theta;
+    int* zero;
+    int n_zero;
+};
+void launch_begin_chunk(const BeginArgs& a, int pos0, hipStream_t s);
+void launch_begin_tree(const BeginArgs& a, int pos0, const TreeTable& t, TreeTable* dst, hipStream_t s);
+void launch_begin_branches(const BeginArgs& a, const BranchTable& t, BranchTable* dst, hipStream_t s);
+// x32 <- x32 + sum_s partial[s];  xn <- rmsnorm(x32) * g (if g), tiled layout;  out <- bf16(x32) (if out), row-major
+void launch_reduce_norm(float* x32, const float* partial, int splits, size_t split_stride, const u16* g, u16* xn, u16* out,
+                        int n, int d, float eps, hipStream_t s);
 
 }  // namespace jup

@@ -1,7 +1,8 @@
 // Orchestration of the bf16 (matrix-core) path: one stage forward over one sub-sequence with its
 // cached prefix (Jupiter paper, Sec. IV-A.2); decoder layer of Sec. II-A in its Llama-2 form.
 //
-// Per layer, seven launches on one stream (the caller's, or a lane's stream of the overlapped multi-chunk call):
+// One launch that prepares the call (norm of the first layer, rotary table; bf16_misc.hip), then per layer seven (six in the
+// first) on one stream (the caller's, or a lane's stream of the overlapped multi-chunk call):
 //   reduce+norm  ->  QKV GEMM (+ rotary + KV append)  ->  chunk attention  ->  O GEMM (K-split partials)
 //   ->  reduce+norm  ->  gate/up GEMM (+ SwiGLU)  ->  down GEMM (K-split partials)
 // The projections back to d_model are too narrow to fill 256 CUs with tall tiles, so they split K and
@@ -89,22 +90,24 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     if (c.n_layers == 0) return hipMemcpyAsync(hidden_out, hidden_in, (size_t)n * d * 2, hipMemcpyDeviceToDevice, s);
     const BranchTable* bt_dev = nullptr;
     const TreeTable* tree_dev = nullptr;
-    // the first kernel of the call builds the rotary table and clears the arrival counters of the call's split launches
     const AttScratch att{(float*)(ws + st.wl.att_split), (int*)(ws + st.wl.att_count), st.wl.att_split_rows,
                          st.wl.att_count_n};
-    const int n_zero = (int)att.counters;
     int max_keys = 0;  // batched branches: the longest key range
-    if (bt) {
-        bt_dev = (const BranchTable*)(ws + st.wl.branches);
-        launch_write_branch_table(*bt, (BranchTable*)(ws + st.wl.branches), s);
-        launch_rope_table_branches(rope, n, bt_dev, c.rope_theta, att.split_count, n_zero, s);
-        for (int b = 0; b < bt->n_branches; ++b) max_keys = bt->pos0[b] + bt->n_tok > max_keys ? bt->pos0[b] + bt->n_tok : max_keys;
-    } else if (tree) {
-        tree_dev = (const TreeTable*)(ws + st.wl.tree);
-        launch_write_tree_table(*tree, (TreeTable*)(ws + st.wl.tree), s);
-        launch_rope_table_tree(rope, n, pos, tree_dev, c.rope_theta, att.split_count, n_zero, s);
-    } else {
-        launch_rope_table(rope, n, pos, c.rope_theta, att.split_count, n_zero, s);
+    {
+        TraceScope ts(st, JUP_K_RMSNORM, s);
+        const BeginArgs a{x32, (const u16*)hidden_in, (const u16*)((const char*)st.packed + st.pl.g_attn), xn, n, d, c.rms_eps,
+                          rope, c.rope_theta, att.split_count, (int)att.counters};
+        if (bt) {
+            bt_dev = (const BranchTable*)(ws + st.wl.branches);
+            launch_begin_branches(a, *bt, (BranchTable*)(ws + st.wl.branches), s);
+            for (int b = 0; b < bt->n_branches; ++b)
+                max_keys = bt->pos0[b] + bt->n_tok > max_keys ? bt->pos0[b] + bt->n_tok : max_keys;
+        } else if (tree) {
+            tree_dev = (const TreeTable*)(ws + st.wl.tree);
+            launch_begin_tree(a, pos, *tree, (TreeTable*)(ws + st.wl.tree), s);
+        } else {
+            launch_begin_chunk(a, pos, s);
+        }
     }
 
     const bool shared = link != nullptr;  // other chunks' kernels run beside this chunk's
@@ -121,13 +124,9 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         const char* wb = (const char*)st.packed + (size_t)l * st.pl.layer_bytes;
         const u16* g1 = (const u16*)(wb + st.pl.g_attn);
         const u16* g2 = (const u16*)(wb + st.pl.g_mlp);
-        {
+        if (l > 0) {
             TraceScope ts(st, JUP_K_RMSNORM, s);
-            if (l == 0)
-                launch_reduce_norm(x32, (const u16*)hidden_in, nullptr, 0, 0, g1, xn, nullptr, n, d, c.rms_eps, s);
-            else
-                launch_reduce_norm(x32, nullptr, partial, splits_down, split_stride, g1, xn, nullptr, n, d, c.rms_eps,
-                                   s);
+            launch_reduce_norm(x32, partial, splits_down, split_stride, g1, xn, nullptr, n, d, c.rms_eps, s);
         }
         {
             TraceScope ts(st, JUP_K_GEMM_QKV, s);
@@ -158,7 +157,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         }
         {
             TraceScope ts(st, JUP_K_RMSNORM, s);
-            launch_reduce_norm(x32, nullptr, partial, splits_o, split_stride, g2, xn, nullptr, n, d, c.rms_eps, s);
+            launch_reduce_norm(x32, partial, splits_o, split_stride, g2, xn, nullptr, n, d, c.rms_eps, s);
         }
         {
             TraceScope ts(st, JUP_K_GEMM_GATE_UP, s);
@@ -177,7 +176,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     }
     if (e != hipSuccess) return e;
     // last layer's down-projection partials + residual -> hidden_out
-    launch_reduce_norm(x32, nullptr, partial, splits_down, split_stride, nullptr, nullptr, (u16*)hidden_out, n, d,
+    launch_reduce_norm(x32, partial, splits_down, split_stride, nullptr, nullptr, (u16*)hidden_out, n, d,
                        c.rms_eps, s);
     return hipGetLastError();
 }

@@ -74,51 +74,6 @@ __global__ void pack_tiled(u16* __restrict__ dst, const void* __restrict__ s0, c
     }
 }
 
-// The first kernel of a call also clears the arrival counters its later kernels count in (a fill by a kernel, not a
-// memset: the call may be captured in a graph).
-__device__ inline void clear_counters(int* zero, int n_zero) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x) zero[i] = 0;
-}
-
-// tab[t][i] = (cos, sin)((pos0 + t) * theta^(-2i/128)); angles in fp64 so that large positions stay exact.
-__global__ void rope_table(float2* __restrict__ tab, int n, int pos0, float theta, int* __restrict__ zero, int n_zero) {
-    clear_counters(zero, n_zero);
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= n * 64) return;
-    const int i = gid & 63, t = gid >> 6;
-    const double ang = (double)(pos0 + t) * pow((double)theta, -(double)i / 64.0);
-    tab[gid] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
-// Token-tree call: token t sits tree->depth[t] positions behind the cached sequence.
-__global__ void rope_table_tree(float2* __restrict__ tab, int n, int pos0, const TreeTable* __restrict__ tree,
-                                float theta, int* __restrict__ zero, int n_zero) {
-    clear_counters(zero, n_zero);
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= n * 64) return;
-    const int i = gid & 63, t = gid >> 6;
-    const double ang = (double)(pos0 + tree->depth[t]) * pow((double)theta, -(double)i / 64.0);
-    tab[gid] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
-// Batched-branch call: row r is token r % n_tok of branch r / n_tok.
-__global__ void rope_table_branches(float2* __restrict__ tab, int n_rows, const BranchTable* __restrict__ bt,
-                                    float theta, int* __restrict__ zero, int n_zero) {
-    clear_counters(zero, n_zero);
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= n_rows * 64) return;
-    const int i = gid & 63, r = gid >> 6;
-    const int b = r / bt->n_tok, t = r - b * bt->n_tok;
-    const double ang = (double)(bt->pos0[b] + t) * pow((double)theta, -(double)i / 64.0);
-    tab[gid] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
-// The table of a batched-branch call travels as a kernel argument and is parked in the workspace, where the
-// kernels of the call find it (no host-to-device copy on the hot path).
-__global__ void write_branch_table(const BranchTable t, BranchTable* __restrict__ dst) {
-    if (threadIdx.x == 0) *dst = t;
-}
-
 // One block per row, IT float4 per thread (the row stays in registers between the two passes).  A row has
 // few bytes and there are few rows, so the block is wide (d/8 threads when that is a whole number of waves):
 // every load of a thread is independent and enough of them must be in flight per CU to cover HBM latency.
@@ -127,12 +82,11 @@ __global__ void write_branch_table(const BranchTable t, BranchTable* __restrict_
 //   xn  <- bf16(v * rsqrt(mean v^2 + eps) * g)   (when g != NULL)
 //   out <- bf16(v)                        (when out != NULL)
 template <int IT>
-__global__ __launch_bounds__(1024) void reduce_norm(float* __restrict__ x32, const u16* __restrict__ hidden_in,
-                                                    const float* __restrict__ partial, int splits, size_t split_stride,
-                                                    const u16* __restrict__ g, u16* __restrict__ xn,
-                                                    u16* __restrict__ out, int d, float eps) {
+__device__ __forceinline__ void norm_row(size_t row, float* __restrict__ x32, const u16* __restrict__ hidden_in,
+                                         const float* __restrict__ partial, int splits, size_t split_stride,
+                                         const u16* __restrict__ g, u16* __restrict__ xn, u16* __restrict__ out, int d,
+                                         float eps) {
     __shared__ float part[16];
-    const size_t row = blockIdx.x;
     const int nvec = d >> 2;  // float4 per row
     const int nthr = blockDim.x;
     float4 v[IT];
@@ -189,6 +143,74 @@ __global__ __launch_bounds__(1024) void reduce_norm(float* __restrict__ x32, con
     }
 }
 
+template <int IT>
+__global__ __launch_bounds__(1024) void reduce_norm(float* __restrict__ x32, const float* __restrict__ partial, int splits,
+                                                    size_t split_stride, const u16* __restrict__ g, u16* __restrict__ xn,
+                                                    u16* __restrict__ out, int d, float eps) {
+    norm_row<IT>(blockIdx.x, x32, nullptr, partial, splits, split_stride, g, xn, out, d, eps);
+}
+
+// ---- the first kernel of a call --------------------------------------------------------------------------------------
+// Positions of the call's rows; the table of a token tree or of batched branches travels as a kernel argument and is parked
+// in the workspace, where the kernels behind this one find it (no host-to-device copy on the hot path).
+struct ChunkRows {
+    int pos0;
+    __device__ int position(int row) const { return pos0 + row; }
+    __device__ void park() const {}
+};
+struct TreeRows {
+    TreeTable t;
+    TreeTable* dst;
+    int pos0;
+    __device__ int position(int row) const { return pos0 + t.depth[row]; }  // depth[row] positions behind the cached sequence
+    __device__ void park() const { *dst = t; }
+};
+struct BranchRows {
+    BranchTable t;
+    BranchTable* dst;
+    __device__ int position(int row) const {  // row = token row % n_tok of branch row / n_tok
+        const int b = row / t.n_tok;
+        return t.pos0[b] + row - b * t.n_tok;
+    }
+    __device__ void park() const { *dst = t; }
+};
+
+// Everything a call needs before its first projection, in one launch: blocks 0 .. n - 1 norm a row of hidden_in each; the
+// blocks behind them write the rotary table, tab[row][i] = (cos, sin)(position * theta^(-2i/128)) with the angles in fp64 so
+// that large positions stay exact, clear the arrival counters the call's later kernels count in (a fill by a kernel, not a
+// memset: the call may be captured in a graph), and park the table.  They run beside the norm; as launches of their own in
+// front of it they took 2.5 - 4.5 us of every call, and the table another 2 - 4 us.
+template <int IT, class Rows>
+__global__ __launch_bounds__(1024) void begin_call(float* __restrict__ x32, const u16* __restrict__ hidden_in,
+                                                   const u16* __restrict__ g, u16* __restrict__ xn, int n, int d, float eps,
+                                                   float2* __restrict__ tab, float theta, int* __restrict__ zero, int n_zero,
+                                                   const Rows rows) {
+    if ((int)blockIdx.x < n) {
+        norm_row<IT>(blockIdx.x, x32, hidden_in, nullptr, 0, 0, g, xn, nullptr, d, eps);
+        return;
+    }
+    const int gid = (blockIdx.x - n) * blockDim.x + threadIdx.x, all = (gridDim.x - n) * blockDim.x;
+    if (gid == 0) rows.park();
+    for (int i = gid; i < n_zero; i += all) zero[i] = 0;
+    if (gid >= n * 64) return;
+    const int i = gid & 63, row = gid >> 6;
+    const double ang = (double)rows.position(row) * pow((double)theta, -(double)i / 64.0);
+    tab[gid] = make_float2((float)cos(ang), (float)sin(ang));
+}
+
+template <class Rows>
+void launch_begin(const BeginArgs& a, const Rows& rows, hipStream_t s) {
+    const bool wide = a.d % 512 == 0 && a.d / 8 <= 1024;
+    const int threads = wide ? a.d / 8 : 256;
+    const dim3 grid(a.n + (a.n * 64 + threads - 1) / threads);
+    if (wide)
+        hipLaunchKernelGGL((begin_call<2, Rows>), grid, dim3(threads), 0, s, a.x32, a.hidden_in, a.g, a.xn, a.n, a.d, a.eps,
+                           a.rope, a.theta, a.zero, a.n_zero, rows);
+    else
+        hipLaunchKernelGGL((begin_call<8, Rows>), grid, dim3(threads), 0, s, a.x32, a.hidden_in, a.g, a.xn, a.n, a.d, a.eps,
+                           a.rope, a.theta, a.zero, a.n_zero, rows);
+}
+
 }  // namespace
 
 void launch_pack_qkv(u16* dst, const u16* wq, const u16* wk, const u16* wv, int d, hipStream_t s) {
@@ -220,29 +242,20 @@ void launch_expand_plain(u16* dst, const void* c, const float* sc, int n_rows, i
     hipLaunchKernelGGL(pack_tiled<true>, dim3(n_rows), dim3(256), 0, s, dst, c, (const void*)nullptr,
                        (const void*)nullptr, sc, (const float*)nullptr, (const float*)nullptr, k, 0, (int)PACK_PLAIN);
 }
-void launch_rope_table(float2* tab, int n, int pos0, float theta, int* zero, int n_zero, hipStream_t s) {
-    hipLaunchKernelGGL(rope_table, dim3((n * 64 + 255) / 256), dim3(256), 0, s, tab, n, pos0, theta, zero, n_zero);
+void launch_begin_chunk(const BeginArgs& a, int pos0, hipStream_t s) { launch_begin(a, ChunkRows{pos0}, s); }
+void launch_begin_tree(const BeginArgs& a, int pos0, const TreeTable& t, TreeTable* dst, hipStream_t s) {
+    launch_begin(a, TreeRows{t, dst, pos0}, s);
 }
-void launch_rope_table_tree(float2* tab, int n, int pos0, const TreeTable* tree, float theta, int* zero, int n_zero,
-                            hipStream_t s) {
-    hipLaunchKernelGGL(rope_table_tree, dim3((n * 64 + 255) / 256), dim3(256), 0, s, tab, n, pos0, tree, theta, zero,
-                       n_zero);
+void launch_begin_branches(const BeginArgs& a, const BranchTable& t, BranchTable* dst, hipStream_t s) {
+    launch_begin(a, BranchRows{t, dst}, s);
 }
-void launch_rope_table_branches(float2* tab, int n_rows, const BranchTable* branches, float theta, int* zero, int n_zero,
-                                hipStream_t s) {
-    hipLaunchKernelGGL(rope_table_branches, dim3((n_rows * 64 + 255) / 256), dim3(256), 0, s, tab, n_rows, branches,
-                       theta, zero, n_zero);
-}
-void launch_write_branch_table(const BranchTable& host_table, BranchTable* dst, hipStream_t s) {
-    hipLaunchKernelGGL(write_branch_table, dim3(1), dim3(64), 0, s, host_table, dst);
-}
-void launch_reduce_norm(float* x32, const u16* hidden_in, const float* partial, int splits, size_t split_stride,
+void launch_reduce_norm(float* x32, const float* partial, int splits, size_t split_stride,
                         const u16* g, u16* xn, u16* out, int n, int d, float eps, hipStream_t s) {
     if (d % 512 == 0 && d / 8 <= 1024)
-        hipLaunchKernelGGL(reduce_norm<2>, dim3(n), dim3(d / 8), 0, s, x32, hidden_in, partial, splits, split_stride, g,
+        hipLaunchKernelGGL(reduce_norm<2>, dim3(n), dim3(d / 8), 0, s, x32, partial, splits, split_stride, g,
                            xn, out, d, eps);
     else
-        hipLaunchKernelGGL(reduce_norm<8>, dim3(n), dim3(256), 0, s, x32, hidden_in, partial, splits, split_stride, g,
+        hipLaunchKernelGGL(reduce_norm<8>, dim3(n), dim3(256), 0, s, x32, partial, splits, split_stride, g,
                            xn, out, d, eps);
 }
 

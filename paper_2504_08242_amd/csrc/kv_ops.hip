@@ -24,8 +24,15 @@ __global__ __launch_bounds__(256) void kv_keep(Piece* own, int own_cap, int n_pl
     if (gid >= (long long)n_planes * pieces) return;
     const int plane = (int)(gid / pieces), piece = (int)(gid % pieces);
     Piece* col = own + ((size_t)plane * own_cap + base) * pieces + piece;
-    for (int j = 0; j < list.n; ++j)
-        if (list.slots[j] != j) col[(size_t)j * pieces] = col[(size_t)list.slots[j] * pieces];
+    for (int j0 = 0; j0 < list.n; j0 += 8) {  // eight sources in flight; none of them, or of a later eight, is a destination
+        Piece p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (j0 + e < list.n) p[e] = col[(size_t)list.slots[j0 + e] * pieces];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (j0 + e < list.n && list.slots[j0 + e] != j0 + e) col[(size_t)(j0 + e) * pieces] = p[e];
+    }
 }
 
 }  // namespace
