@@ -122,6 +122,79 @@ struct GemmArgs {
     float* partial;  // [splits][M][N] fp32
     // EPI_SWIGLU
     u16* act;  // [M, N/2] in the tiled layout (it is the down projection's A operand)
+    // EPI_QKV, EPI_SWIGLU, up to kMaxSplitRows rows: rows of A that are x * gain, not normalised; the results of row m are
+    // multiplied by 1 / rms(m): row_factor[m], or (up to kMaxProjectRows rows) what the [M][K / 16] partial sums of squares
+    // ssq give.  Both null: the rows of A are normalised.
+    const float* row_factor;
+    const float* ssq;
+    float rms_eps;
+};
+
+// ---- projections back to d_model of up to 64 rows (row_gemm.hip) --------------------------------------
+constexpr int kMaxProjectRows = 16;  // up to here one launch that finishes the residual and the next projection's rows,
+constexpr int kMaxSplitRows = 64;    // batches of such chunks up to here: fp32 partial sums that give the same bits
+int row_splits(int N);               // K splits of a bf16 projection of either kind: 2, 4 or 8
+struct RowArgs {
+    const u16* A;          // [M, K] tiled
+    const void* W;         // [N, K] tiled bf16, or packed 4-bit codes
+    const float* w_scale;  // 4-bit stages only
+    int M, N, K;
+    int splits;            // of K: row_splits(N), 4-bit stages w4_plan_splits(N, K)
+    // launch_project_rows
+    float* x32;            // [M, N] residual stream: read, and written unless out is set
+    const u16* gain;       // gain of the norm that follows
+    u16* xn;               // [M, N] tiled: bf16(x * gain)
+    float* ssq;            // [M][N / 16] sums of squares of x
+    u16* out;              // non-null: the stage's output, row-major; xn, ssq and x32 are then not written
+    // launch_project_split
+    float* partial;        // [splits][M][N]
+};
+hipError_t rows_configure();  // raises the dynamic-LDS limit (once per process)
+hipError_t launch_project_rows(bool w4, const RowArgs& a, hipStream_t s);
+hipError_t launch_project_split(const RowArgs& a, hipStream_t s);
+
+// 1 / rms of a row comes out of two kernels (reduce_norm, and the projections behind row_gemm.hip) with the same bits: sums of
+// squares of 16 consecutive features, four neighbouring lanes holding four each ...
+__device__ __forceinline__ float sum_squares_16(float4 x) {
+    float s = __builtin_fmaf(x.w, x.w, __builtin_fmaf(x.z, x.z, __builtin_fmaf(x.y, x.y, x.x * x.x)));
+    s += __shfl_xor(s, 1, 64);
+    return s + __shfl_xor(s, 2, 64);
+}
+// ... and a wave per row over its d / 16 partial sums (at most 512), lane t adding those number t, t + 64, ... in order.
+__device__ __forceinline__ float row_scale(float lane_sum, int d, float eps) {
+    return 1.0f / sqrtf(wave_sum(lane_sum) / (float)d + eps);
+}
+// The factors of up to kMaxProjectRows rows from their partial sums in memory, dealt to WAVES waves.  Split in two: the
+// loads are issued before a kernel's main loop, and added up behind it.
+template <int WAVES>
+struct RowScale {
+    static constexpr int ROWS = (kMaxProjectRows + WAVES - 1) / WAVES;
+    float v[ROWS][8];
+    __device__ __forceinline__ void begin(const float* ssq, int rows, int wave, int lane, int d) {
+        const int n = d / 16;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (64 * k < n) {
+                const int j = min(lane + 64 * k, n - 1);
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) v[i][k] = ssq[(size_t)min(wave + WAVES * i, rows - 1) * n + j];
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(float* dst, int rows, int wave, int lane, int d, float eps) {
+        const int n = d / 16;
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            const int row = wave + WAVES * i;
+            if (row >= rows) break;
+            float s = lane < n ? v[i][0] : 0.f;
+#pragma unroll
+            for (int k = 1; k < 8; ++k)
+                if (64 * k < n) s += lane + 64 * k < n ? v[i][k] : 0.f;
+            const float f = row_scale(s, d, eps);
+            if (lane == 0) dst[row] = f;
+        }
+    }
 };
 
 enum GemmKind { GEMM_QKV, GEMM_O, GEMM_GATE_UP, GEMM_DOWN };
@@ -135,6 +208,19 @@ hipError_t launch_gemm_partial(GemmArgs a, hipStream_t s);
 // name of the instantiation a projection of M rows runs as (benchmarks: which tiling a counter reading belongs to)
 void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_gpu, char* buf, size_t size);
 hipError_t gemm_configure();  // raises the dynamic-LDS limit of every instantiation (once per process)
+
+// Eight 4-bit codes of one dword (packed as w4_gemm.hip describes) as bf16 values 128 + code.
+__device__ inline bf16x8 w4_expand(unsigned w) {
+    u32x4 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = ((w >> (4 * j)) & 0x000F000Fu) | 0x43004300u;
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// A group of 128 input features: t = sum of a (128 + code), rs = sum of a.  (One expression for every kernel.)
+__device__ __forceinline__ float w4_group(float acc, float scale, float t, float rs) {
+    return __builtin_fmaf(scale, __builtin_fmaf(-136.0f, rs, t), acc);
+}
 
 // ---- projections of a 4-bit stage (w4_gemm.hip) ----------------------------------------------------
 // epi: EPI_QKV, EPI_SWIGLU or EPI_PARTIAL; the tiling fields of `a` are filled here.  EPI_PARTIAL writes
@@ -227,8 +313,9 @@ struct BeginArgs {
 void launch_begin_chunk(const BeginArgs& a, int pos0, hipStream_t s);
 void launch_begin_tree(const BeginArgs& a, int pos0, const TreeTable& t, TreeTable* dst, hipStream_t s);
 void launch_begin_branches(const BeginArgs& a, const BranchTable& t, BranchTable* dst, hipStream_t s);
-// x32 <- x32 + sum_s partial[s];  xn <- rmsnorm(x32) * g (if g), tiled layout;  out <- bf16(x32) (if out), row-major
-void launch_reduce_norm(float* x32, const float* partial, int splits, size_t split_stride, const u16* g, u16* xn, u16* out,
-                        int n, int d, float eps, hipStream_t s);
+// x32 <- x32 + sum_s partial[s];  if g: xn <- rmsnorm(x32) * g (tiled layout), or with factor xn <- x32 * g and factor <-
+// 1 / rms of the rows;  out <- bf16(x32) (if out), row-major
+void launch_reduce_norm(float* x32, const float* partial, int splits, size_t split_stride, const u16* g, u16* xn,
+                        float* factor, u16* out, int n, int d, float eps, hipStream_t s);
 
 }  // namespace jup

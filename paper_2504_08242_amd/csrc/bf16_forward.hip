@@ -1,8 +1,11 @@
 // Orchestration of the bf16 (matrix-core) path: one stage forward over one sub-sequence with its
 // cached prefix (Jupiter paper, Sec. IV-A.2); decoder layer of Sec. II-A in its Llama-2 form.
 //
-// One launch that prepares the call (norm of the first layer, rotary table; bf16_misc.hip), then per layer seven (six in the
-// first) on one stream (the caller's, or a lane's stream of the overlapped multi-chunk call):
+// One launch that prepares the call (norm of the first layer, rotary table; bf16_misc.hip), then per layer, up to 16 rows,
+// five launches on one stream (the caller's):
+//   QKV GEMM (+ rotary + KV append)  ->  chunk attention  ->  O projection (+ residual)  ->  gate/up GEMM (+ SwiGLU)
+//   ->  down projection (+ residual)
+// and seven (the first norm is the preparing launch's) for more rows (the caller's stream, or a lane's of the multi-chunk call):
 //   reduce+norm  ->  QKV GEMM (+ rotary + KV append)  ->  chunk attention  ->  O GEMM (K-split partials)
 //   ->  reduce+norm  ->  gate/up GEMM (+ SwiGLU)  ->  down GEMM (K-split partials)
 // The projections back to d_model are too narrow to fill 256 CUs with tall tiles, so they split K and
@@ -16,6 +19,7 @@ hipError_t bf16_pack_weights(const jup_stage& st, const jup_layer_weights_t* lay
     const jup_stage_config_t& c = st.cfg;
     const size_t d = c.d_model;
     hipError_t e = gemm_configure();
+    if (e == hipSuccess) e = rows_configure();
     if (e == hipSuccess) e = attention_configure();
     if (e != hipSuccess) return e;
     for (int l = 0; l < c.n_layers; ++l) {
@@ -85,6 +89,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     u16* act = (u16*)(ws + st.wl.act);
     float* partial = (float*)(ws + st.wl.partial);
     float2* rope = (float2*)(ws + st.wl.rope);
+    float* factor = (float*)(ws + st.wl.factor);
     const size_t split_stride = (size_t)n * d;
 
     if (c.n_layers == 0) return hipMemcpyAsync(hidden_out, hidden_in, (size_t)n * d * 2, hipMemcpyDeviceToDevice, s);
@@ -117,16 +122,40 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     const bool w4 = c.dtype == JUP_BF16_W4 && !expanded;
     const size_t wqkv = expanded ? st.pl.xqkv : st.pl.wqkv, wo = expanded ? st.pl.xo : st.pl.wo;
     const size_t wgu = expanded ? st.pl.xgu : st.pl.wgu, wdown = expanded ? st.pl.xdown : st.pl.wdown;
-    const int splits_o = w4 ? w4_plan_splits(d, d) : gemm_plan_splits(n, d, d, shared);
-    const int splits_down = w4 ? w4_plan_splits(d, f) : gemm_plan_splits(n, d, f, shared);
+    // Back to d_model.  Calls of up to 16 rows: the O / down projections finish the residual and the rows of the next
+    // projection themselves (row_gemm.hip); their sums of squares take the place of the partial sums in the workspace.  All
+    // other calls leave partial sums to the reduce + norm pass; batches of branches of up to 16 tokens in a form that gives
+    // every branch the bits it has alone (up to 64 rows).
+    const bool rows = n <= kMaxProjectRows && !shared;
+    const bool small_branches = !rows && bt && bt->n_tok <= kMaxProjectRows && n <= kMaxSplitRows;
+    const bool as_rows = rows || small_branches;
+    const int splits_o = w4 ? w4_plan_splits(d, d) : as_rows ? row_splits(d) : gemm_plan_splits(n, d, d, shared);
+    const int splits_down = w4 ? w4_plan_splits(d, f) : as_rows ? row_splits(d) : gemm_plan_splits(n, d, f, shared);
+    float* late_factor = small_branches ? factor : nullptr;
+    float* ssq = partial;
+    // back to d_model: in [n, k] times w; gain: of the norm that follows (null behind the last layer)
+    auto project = [&](const u16* in, const void* w, const void* w_scale, int k, const u16* gain) {
+        if (rows || (small_branches && !w4)) {
+            RowArgs a{};
+            a.A = in; a.W = w; a.w_scale = (const float*)w_scale; a.M = n; a.N = d; a.K = k;
+            a.splits = k == d ? splits_o : splits_down;
+            a.x32 = x32; a.gain = gain; a.xn = xn; a.ssq = ssq; a.out = gain ? nullptr : (u16*)hidden_out;
+            a.partial = partial;
+            return rows ? launch_project_rows(w4, a, s) : launch_project_split(a, s);
+        }
+        GemmArgs a{};
+        a.A = in; a.W = (const u16*)w; a.w_scale = (const float*)w_scale; a.M = n; a.N = d; a.K = k;
+        a.partial = partial; a.shared_gpu = shared;
+        return w4 ? launch_gemm_w4(EPI_PARTIAL, a, s) : launch_gemm_partial(a, s);
+    };
     hipError_t e = hipSuccess;
     for (int l = 0; l < c.n_layers && e == hipSuccess; ++l) {
         const char* wb = (const char*)st.packed + (size_t)l * st.pl.layer_bytes;
         const u16* g1 = (const u16*)(wb + st.pl.g_attn);
         const u16* g2 = (const u16*)(wb + st.pl.g_mlp);
-        if (l > 0) {
+        if (l > 0 && !rows) {
             TraceScope ts(st, JUP_K_RMSNORM, s);
-            launch_reduce_norm(x32, partial, splits_down, split_stride, g1, xn, nullptr, n, d, c.rms_eps, s);
+            launch_reduce_norm(x32, partial, splits_down, split_stride, g1, xn, late_factor, nullptr, n, d, c.rms_eps, s);
         }
         {
             TraceScope ts(st, JUP_K_GEMM_QKV, s);
@@ -135,6 +164,8 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
             a.q_out = q; a.rope = rope; a.kv = kv; a.layer = l; a.n_heads = H; a.d_model = d; a.pos0 = pos;
             a.branches = bt_dev;
             a.shared_gpu = shared;
+            a.ssq = rows && l > 0 ? ssq : nullptr; a.rms_eps = c.rms_eps;
+            a.row_factor = l > 0 ? late_factor : nullptr;
             a.w_scale = (const float*)(wb + st.pl.sqkv);
             e = w4 ? launch_gemm_w4(EPI_QKV, a, s) : launch_gemm_qkv(a, s);
         }
@@ -150,33 +181,30 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         }
         {
             TraceScope ts(st, JUP_K_GEMM_O, s);
-            GemmArgs a{};
-            a.A = o; a.W = (const u16*)(wb + wo); a.M = n; a.N = d; a.K = d; a.partial = partial; a.shared_gpu = shared;
-            a.w_scale = (const float*)(wb + st.pl.so);
-            if (e == hipSuccess) e = w4 ? launch_gemm_w4(EPI_PARTIAL, a, s) : launch_gemm_partial(a, s);
+            if (e == hipSuccess) e = project(o, wb + wo, wb + st.pl.so, d, g2);
         }
-        {
+        if (!rows) {
             TraceScope ts(st, JUP_K_RMSNORM, s);
-            launch_reduce_norm(x32, partial, splits_o, split_stride, g2, xn, nullptr, n, d, c.rms_eps, s);
+            launch_reduce_norm(x32, partial, splits_o, split_stride, g2, xn, late_factor, nullptr, n, d, c.rms_eps, s);
         }
         {
             TraceScope ts(st, JUP_K_GEMM_GATE_UP, s);
             GemmArgs a{};
             a.A = xn; a.W = (const u16*)(wb + wgu); a.M = n; a.N = 2 * f; a.K = d; a.act = act; a.shared_gpu = shared;
+            a.ssq = rows ? ssq : nullptr; a.rms_eps = c.rms_eps;
+            a.row_factor = late_factor;
             a.w_scale = (const float*)(wb + st.pl.sgu);
             if (e == hipSuccess) e = w4 ? launch_gemm_w4(EPI_SWIGLU, a, s) : launch_gemm_swiglu(a, s);
         }
         {
             TraceScope ts(st, JUP_K_GEMM_DOWN, s);
-            GemmArgs a{};
-            a.A = act; a.W = (const u16*)(wb + wdown); a.M = n; a.N = d; a.K = f; a.partial = partial; a.shared_gpu = shared;
-            a.w_scale = (const float*)(wb + st.pl.sdown);
-            if (e == hipSuccess) e = w4 ? launch_gemm_w4(EPI_PARTIAL, a, s) : launch_gemm_partial(a, s);
+            const u16* next_g = l + 1 < c.n_layers ? (const u16*)(wb + st.pl.layer_bytes + st.pl.g_attn) : nullptr;
+            if (e == hipSuccess) e = project(act, wb + wdown, wb + st.pl.sdown, f, next_g);
         }
     }
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || rows) return e;
     // last layer's down-projection partials + residual -> hidden_out
-    launch_reduce_norm(x32, partial, splits_down, split_stride, nullptr, nullptr, (u16*)hidden_out, n, d,
+    launch_reduce_norm(x32, partial, splits_down, split_stride, nullptr, nullptr, nullptr, (u16*)hidden_out, n, d,
                        c.rms_eps, s);
     return hipGetLastError();
 }

@@ -66,7 +66,10 @@ struct Shape {
     static_assert(NB % WN == 0 && BMB % WM == 0, "tile does not split evenly over the waves");
     // as many ring slots as LDS holds (at most 8: the in-flight count must fit the 6-bit vmcnt)
     static constexpr int STAGES = kLdsBudget / STAGE_BYTES > 8 ? 8 : kLdsBudget / STAGE_BYTES;
-    static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
+    // tiles that chunks of up to 16 rows take: the factors of rows with partial sums of squares, behind the ring
+    static constexpr bool ROW_SCALE = BMB <= 2;
+    static constexpr int RING_BYTES = STAGES * STAGE_BYTES;
+    static constexpr int LDS_BYTES = RING_BYTES + (ROW_SCALE ? kMaxProjectRows * 4 : 0);
     static_assert(STAGES >= 4 && (STAGES - 2) * LPW < 64, "ring depth");
 };
 
@@ -199,6 +202,21 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     };
 
     constexpr bool FETCH = true;
+    // Up to 16 rows that come with partial sums of squares: those are loaded ahead of the ring's first stages and added up
+    // behind the K loop.
+    constexpr bool ROW_SCALE = S::ROW_SCALE && EPI != EPI_PARTIAL;
+    float* scale_of_row = (float*)(smem + S::RING_BYTES);
+    RowScale<S::WAVES> sq;
+    const bool scaled = ROW_SCALE && a.ssq;
+    if (scaled) sq.begin(a.ssq, a.M, wave, lane, a.K);
+    // 1 / rms of this lane's token in every row block of the wave, where the rows of A are not normalised (small tiles only:
+    // on the tall ones it cost the 512-row launches 1 %)
+    float factor[MBW];
+#pragma unroll
+    for (int mb = 0; mb < MBW; ++mb) factor[mb] = 1.0f;
+    if (ROW_SCALE && a.row_factor)
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb) factor[mb] = a.row_factor[min(m0 + (wm * MBW + mb) * 32 + (lane & 31), a.M - 1)];
 
     // ---- LDS -> register fragment addresses -------------------------------------------------------------
     // Fragment row = 32*block + c (c = lane & 31), chunk = 2*ks + hh.  Block bases are multiples of 32,
@@ -347,6 +365,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     const int row_base = m0 + wm * WROWS + 4 * hh;
     const int nw0 = n0 + wn * NBW * 32;  // first column of this wave
     auto row_of = [&](int mb, int i) { return row_base + mb * 32 + 8 * (i >> 2) + (i & 3); };
+    if constexpr (ROW_SCALE) {
+            if (scaled) {
+                sq.finish(scale_of_row, a.M, wave, lane, a.K, a.rms_eps);
+                __syncthreads();
+#pragma unroll
+                for (int mb = 0; mb < MBW; ++mb) factor[mb] = scale_of_row[min(wm * WROWS + mb * 32 + c, kMaxProjectRows - 1)];
+            }
+    }
 
     if (EPI == EPI_PARTIAL) {
         float* pbase = a.partial + (size_t)split * a.M * a.N + nw0 + c;
@@ -378,11 +404,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
             for (int mb = 0; mb < MBW; ++mb) {
                 const int m = m0 + wm * WROWS + mb * 32 + c;
                 if (m >= a.M) continue;
+                const float f = ROW_SCALE ? factor[mb] : 1.0f;
                 u32x4 out;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float g0 = acc[mb][nb][2 * e], g1 = acc[mb][nb][2 * e + 1];
-                    const float u0 = acc[mb][nb][8 + 2 * e], u1 = acc[mb][nb][8 + 2 * e + 1];
+                    const float g0 = acc[mb][nb][2 * e] * f, g1 = acc[mb][nb][2 * e + 1] * f;
+                    const float u0 = acc[mb][nb][8 + 2 * e] * f, u1 = acc[mb][nb][8 + 2 * e + 1] * f;
                     out[e] = pack_bf16x2(g0 * __builtin_amdgcn_rcpf(1.0f + __expf(-g0)) * u0,
                                          g1 * __builtin_amdgcn_rcpf(1.0f + __expf(-g1)) * u1);
                 }
@@ -416,20 +443,21 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
                     const int b = m / a.branches->n_tok, t = m - b * a.branches->n_tok;
                     dst = kv_slot_bf16(a.branches->kv[b], a.layer, which - 1, head, a.n_heads, a.branches->pos0[b] + t);
                 }
+                const float f = ROW_SCALE ? factor[mb] : 1.0f;
                 u32x4 lo, hi;
                 if (which == 2) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        lo[e] = pack_bf16x2(acc[mb][nb][2 * e], acc[mb][nb][2 * e + 1]);
-                        hi[e] = pack_bf16x2(acc[mb][nb][8 + 2 * e], acc[mb][nb][8 + 2 * e + 1]);
+                        lo[e] = pack_bf16x2(acc[mb][nb][2 * e] * f, acc[mb][nb][2 * e + 1] * f);
+                        hi[e] = pack_bf16x2(acc[mb][nb][8 + 2 * e] * f, acc[mb][nb][8 + 2 * e + 1] * f);
                     }
                 } else {
                     const float4* rp = (const float4*)(a.rope + (size_t)m * 64 + f_lo);  // 8 (cos, sin) pairs
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float4 cs = rp[e];  // (cos, sin) of indices f_lo + 2 e, f_lo + 2 e + 1
-                        const float l0 = acc[mb][nb][2 * e], l1 = acc[mb][nb][2 * e + 1];
-                        const float h0 = acc[mb][nb][8 + 2 * e], h1 = acc[mb][nb][8 + 2 * e + 1];
+                        const float l0 = acc[mb][nb][2 * e] * f, l1 = acc[mb][nb][2 * e + 1] * f;
+                        const float h0 = acc[mb][nb][8 + 2 * e] * f, h1 = acc[mb][nb][8 + 2 * e + 1] * f;
                         // lo' = lo cos - hi sin ; hi' = hi cos + lo sin
                         lo[e] = pack_bf16x2(l0 * cs.x - h0 * cs.y, l1 * cs.z - h1 * cs.w);
                         hi[e] = pack_bf16x2(h0 * cs.x + l0 * cs.y, h1 * cs.z + l1 * cs.w);
@@ -715,7 +743,8 @@ void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_
         case GEMM_O: t = pick_partial(M, d_model, d_model, shared_gpu); break;
         case GEMM_DOWN: t = pick_partial(M, d_model, d_ffn, shared_gpu); break;
     }
-    snprintf(buf, size, "gemm_bf16<%d,%d,%d,%d,%d>", t.bmb, t.nb, t.wm, t.wn, epi);
+    if (epi == EPI_PARTIAL && M <= kMaxProjectRows && !shared_gpu) snprintf(buf, size, "project_rows<bf16>");
+    else snprintf(buf, size, "gemm_bf16<%d,%d,%d,%d,%d>", t.bmb, t.nb, t.wm, t.wn, epi);
 }
 
 }  // namespace jup

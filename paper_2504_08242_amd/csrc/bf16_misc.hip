@@ -80,13 +80,15 @@ __global__ void pack_tiled(u16* __restrict__ dst, const void* __restrict__ s0, c
 //   v    = (hidden_in ? bf16 row of hidden_in : x32 row) + sum over splits of the partial rows
 //   x32 <- v                              (when anything was added or the row came from hidden_in)
 //   xn  <- bf16(v * rsqrt(mean v^2 + eps) * g)   (when g != NULL)
+//   LATE: xn <- bf16(v * g), factor <- 1 / sqrt(mean v^2 + eps); the projection that reads the rows multiplies its results
+//          by the factor, as it has to behind row_gemm.hip, whose bits these are
 //   out <- bf16(v)                        (when out != NULL)
-template <int IT>
+template <int IT, bool LATE = false>
 __device__ __forceinline__ void norm_row(size_t row, float* __restrict__ x32, const u16* __restrict__ hidden_in,
                                          const float* __restrict__ partial, int splits, size_t split_stride,
                                          const u16* __restrict__ g, u16* __restrict__ xn, u16* __restrict__ out, int d,
-                                         float eps) {
-    __shared__ float part[16];
+                                         float eps, float* __restrict__ factor = nullptr) {
+    __shared__ float part[LATE ? 512 : 16];  // LATE: sums of squares of 16 features
     const int nvec = d >> 2;  // float4 per row
     const int nthr = blockDim.x;
     float4 v[IT];
@@ -118,36 +120,53 @@ __device__ __forceinline__ void norm_row(size_t row, float* __restrict__ x32, co
                 *(u32x2*)(out + row * d + idx * 4) = o;
             }
             v[it] = x;
-            ss += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+            if constexpr (LATE) {  // (four neighbouring lanes are in or out together)
+                ss = sum_squares_16(x);
+                if ((idx & 3) == 0) part[idx >> 2] = ss;
+            } else {
+                ss += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+            }
         }
     }
     if (!g) return;
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    float tot = 0.f;
-    for (int w = 0; w < (nthr >> 6); ++w) tot += part[w];  // same order in every thread
-    const float inv = 1.0f / sqrtf(tot / (float)d + eps);
+    auto write_rows = [&](float inv) {
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const int idx = threadIdx.x + it * nthr;
-        if (idx < nvec) {
-            const u32x2 gg = *(const u32x2*)(g + idx * 4);
-            u32x2 o;
-            o[0] = pack_bf16x2(v[it].x * inv * __uint_as_float(gg[0] << 16),
-                               v[it].y * inv * __uint_as_float(gg[0] & 0xffff0000u));
-            o[1] = pack_bf16x2(v[it].z * inv * __uint_as_float(gg[1] << 16),
-                               v[it].w * inv * __uint_as_float(gg[1] & 0xffff0000u));
-            *(u32x2*)(xn + tiled_offset((int)row, idx >> 1, d >> 5) + (idx & 1) * 4) = o;
+        for (int it = 0; it < IT; ++it) {
+            const int idx = threadIdx.x + it * nthr;
+            if (idx < nvec) {
+                const u32x2 gg = *(const u32x2*)(g + idx * 4);
+                u32x2 o;
+                o[0] = pack_bf16x2(v[it].x * inv * __uint_as_float(gg[0] << 16),
+                                   v[it].y * inv * __uint_as_float(gg[0] & 0xffff0000u));
+                o[1] = pack_bf16x2(v[it].z * inv * __uint_as_float(gg[1] << 16),
+                                   v[it].w * inv * __uint_as_float(gg[1] & 0xffff0000u));
+                *(u32x2*)(xn + tiled_offset((int)row, idx >> 1, d >> 5) + (idx & 1) * 4) = o;
+            }
         }
+    };
+    if constexpr (LATE) {
+        write_rows(1.0f);
+        __syncthreads();
+        if (threadIdx.x >= 64) return;
+        float lane_sum = 0.f;
+        for (int j = threadIdx.x; j < d / 16; j += 64) lane_sum += part[j];
+        const float inv = row_scale(lane_sum, d, eps);
+        if (threadIdx.x == 0) factor[row] = inv;
+    } else {
+        ss = wave_sum(ss);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+        __syncthreads();
+        float tot = 0.f;
+        for (int w = 0; w < (nthr >> 6); ++w) tot += part[w];  // same order in every thread
+        write_rows(1.0f / sqrtf(tot / (float)d + eps));
     }
 }
 
-template <int IT>
+template <int IT, bool LATE>
 __global__ __launch_bounds__(1024) void reduce_norm(float* __restrict__ x32, const float* __restrict__ partial, int splits,
                                                     size_t split_stride, const u16* __restrict__ g, u16* __restrict__ xn,
-                                                    u16* __restrict__ out, int d, float eps) {
-    norm_row<IT>(blockIdx.x, x32, nullptr, partial, splits, split_stride, g, xn, out, d, eps);
+                                                    float* __restrict__ factor, u16* __restrict__ out, int d, float eps) {
+    norm_row<IT, LATE>(blockIdx.x, x32, nullptr, partial, splits, split_stride, g, xn, out, d, eps, factor);
 }
 
 // ---- the first kernel of a call --------------------------------------------------------------------------------------
@@ -249,14 +268,13 @@ void launch_begin_tree(const BeginArgs& a, int pos0, const TreeTable& t, TreeTab
 void launch_begin_branches(const BeginArgs& a, const BranchTable& t, BranchTable* dst, hipStream_t s) {
     launch_begin(a, BranchRows{t, dst}, s);
 }
-void launch_reduce_norm(float* x32, const float* partial, int splits, size_t split_stride,
-                        const u16* g, u16* xn, u16* out, int n, int d, float eps, hipStream_t s) {
-    if (d % 512 == 0 && d / 8 <= 1024)
-        hipLaunchKernelGGL(reduce_norm<2>, dim3(n), dim3(d / 8), 0, s, x32, partial, splits, split_stride, g,
-                           xn, out, d, eps);
-    else
-        hipLaunchKernelGGL(reduce_norm<8>, dim3(n), dim3(256), 0, s, x32, partial, splits, split_stride, g,
-                           xn, out, d, eps);
+void launch_reduce_norm(float* x32, const float* partial, int splits, size_t split_stride, const u16* g, u16* xn,
+                        float* factor, u16* out, int n, int d, float eps, hipStream_t s) {
+    const bool wide = d % 512 == 0 && d / 8 <= 1024;
+    auto* kernel = wide ? (factor ? reduce_norm<2, true> : reduce_norm<2, false>)
+                        : (factor ? reduce_norm<8, true> : reduce_norm<8, false>);
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(wide ? d / 8 : 256), 0, s, x32, partial, splits, split_stride, g, xn, factor, out,
+                       d, eps);
 }
 
 }  // namespace jup

@@ -1,0 +1,368 @@
+// Projections back to d_model (output and down projection) for chunks of up to 64 rows.
+//
+// A decode-sized layer is a chain of short launches, and two of the seven did nothing but add up the K splits of these
+// projections and normalise a handful of rows: 4 - 5 us each for a few hundred KB.  Up to 16 rows project_rows finishes
+// them in one launch, x += A W^T and with it everything the next projection needs of the norm that follows: a workgroup owns
+// 16 output features and ALL of K (its eight waves split K and meet in LDS), so the sums are complete inside it: it adds
+// the residual, writes the new residual stream and the rows bf16(x * g), and leaves the sum of squares of its 16 features.
+// The norm's 1 / rms is a factor of the whole row and commutes with the projection: the next projection multiplies its
+// results by it (RowScale in bf16_common.h adds up the d / 16 partial sums of squares of every row).
+//
+//   * 16 features per workgroup make d / 16 workgroups (256 for d = 4096: every CU), each streaming a contiguous 1 KB of
+//     weights per wave and K step straight into registers, non-temporally (every weight is read once), a batch ahead.
+//     The rows of A come from L2, 16 bytes per lane; rows past the chunk repeat its last one.
+//   * At 16 rows a workgroup reads as many bytes of A as of bf16 weights, at 64 rows it would be four times as many and the
+//     path from L2 bounds it (measured: O / down 14.9 / 34 us against 9.1 / 20.5 us + 4.8 us for each reduce + norm pass).
+//     17 to 64 rows keep K splits over workgroups, partial sums and the reduce + norm pass: with bf16 weights project_split
+//     below, 64 x 64 tiles through LDS; with 4-bit codes the kernel of w4_gemm.hip.
+//   * Either way the MFMA, the ranges of K a sum is made of and the order they are added in are the same, whatever the row
+//     count: a branch computes the same bits alone and batched with others.  bf16: MFMA 16x16x32, eight ranges, those of a
+//     split added up first.  4-bit: the eight waves of every split.
+//
+// Measured on the 7B shapes at 5 rows (us, two K-split launches and two reduce + norm passes -> two launches): bf16
+// 7.2 + 17.4 + 2 x 4.8 -> 7.7 + 17.4; 4-bit 3.7 + 9.2 + 2 x 4.3 -> 5.9 + 12.8.  A whole call: 5 rows of six bf16 layers
+// 723 -> 681 us, one row of eight 4-bit layers 460 -> 424 us.  A batch of branches pays for the equal bits: 8 x 5 rows of two
+// bf16 layers 203 -> 207 us.
+#include "bf16_common.h"
+
+namespace jup {
+namespace {
+
+constexpr int kRowCols = 16;         // output features per workgroup of project_rows
+constexpr int kRanges = 8;           // bf16: K ranges; 4-bit: K ranges per split
+constexpr int kMaxRowSplits = 8;
+
+// MFMA 16x16x32 (lane = 16 q + r): A: lane supplies A[m = r][k = 8 q + e], e < 8; B: B[k = 8 q + e][n = r];
+// D: lane holds D[m = 4 q + i][n = r] in register i < 4.
+__device__ inline f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// bf16 weights, 16 features from feature f0 on, 16 rows, K range `range`: D = W A^T, a lane ends up with 4 features (4 q ..)
+// of one row (r).
+__device__ __forceinline__ f32x4 range_bf16(const RowArgs& a, int f0, int range, int lane) {
+    constexpr int U = 8;  // K steps per batch; one batch is multiplied while the next is on its way
+    const int r = lane & 15, q = lane >> 4;
+    const int KT = a.K / 32;
+    int s = range * KT / kRanges;
+    const int s1 = (range + 1) * KT / kRanges;
+    // a K step of 32 rows is a 2 KB block of the tiled layout, 16 rows are half of it (1 KB of consecutive bytes)
+    const char* w_block = (const char*)a.W + (size_t)(f0 >> 5) * KT * 2048;
+    const unsigned w_lane = 2 * (unsigned)tiled_offset((f0 & 16) + r, q, KT);
+    const unsigned a_lane = 2 * (unsigned)tiled_offset(min(r, a.M - 1), q, KT);
+    struct Batch {
+        u32x4 w[U];
+        bf16x8 a[U];
+    };
+    auto load = [&](Batch& b, int at, int u) __attribute__((always_inline)) {
+        b.w[u] = __builtin_nontemporal_load((const u32x4*)(uniform_ptr(w_block + (size_t)(at + u) * 2048) + w_lane));
+        b.a[u] = *(const bf16x8*)(uniform_ptr((const char*)a.A + (size_t)(at + u) * 2048) + a_lane);
+    };
+    auto load_all = [&](Batch& b, int at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) load(b, at, u);
+    };
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](const Batch& b, int u) __attribute__((always_inline)) {
+        acc = mfma16(__builtin_bit_cast(bf16x8, b.w[u]), b.a[u], acc);
+    };
+    Batch even, odd;
+    const int rem = (s1 - s) % U;  // the first, partial batch
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u < rem) load(even, s, u);
+    s += rem;
+    if (s < s1) load_all(odd, s);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u < rem) multiply(even, u);
+    while (s < s1) {
+        if (s + U < s1) load_all(even, s + U);
+#pragma unroll
+        for (int u = 0; u < U; ++u) multiply(odd, u);
+        s += U;
+        if (s >= s1) break;
+        if (s + U < s1) load_all(odd, s + U);
+#pragma unroll
+        for (int u = 0; u < U; ++u) multiply(even, u);
+        s += U;
+    }
+    return acc;
+}
+
+// 4-bit codes (layout and arithmetic of w4_gemm.hip): a lane ends up with 4 rows (4 q ..) of one feature (r), whose scale it
+// applies group by group.  The 8 x splits ranges are dealt to the eight waves, `splits` consecutive ones each; a range's sum
+// goes to red[range] when its last group is done.
+__device__ __forceinline__ void ranges_w4(const RowArgs& a, float (*red)[16 * kRowCols], int f0, int wave, int lane) {
+    const int r = lane & 15, q = lane >> 4;
+    const int G = a.K / 128;
+    auto first_group = [&](int R) {  // of range R: wave R % 8 of split R / 8
+        const int split = R >> 3, ws0 = split * G / a.splits, ws1 = (split + 1) * G / a.splits;
+        return ws0 + (R & 7) * (ws1 - ws0) / kRanges;
+    };
+    const int tile = f0 >> 6, cg = (f0 >> 4) & 3;  // 64-column tile of the packed codes, 16-column block in it
+    const char* w_block = (const char*)a.W + ((size_t)tile * G * 4 + cg) * 1024;
+    const char* s_block = (const char*)(a.w_scale + (size_t)tile * G * 64 + cg);
+    const unsigned w_lane = lane * 16, s_lane = r * 16;
+    const unsigned a_lane = 2 * (unsigned)tiled_offset(min(r, a.M - 1), q, a.K / 32);
+    const u32x4 ones_bits = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
+    struct Group {
+        u32x4 w;
+        float sc;
+        bf16x8 a[4];
+    };
+    auto load = [&](Group& d, int g) __attribute__((always_inline)) {
+        d.w = __builtin_nontemporal_load((const u32x4*)(uniform_ptr(w_block + (size_t)g * 4096) + w_lane));
+        d.sc = *(const float*)(uniform_ptr(s_block + (size_t)g * 256) + s_lane);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            d.a[ks] = *(const bf16x8*)(uniform_ptr((const char*)a.A + (size_t)(4 * g + ks) * 2048) + a_lane);
+    };
+    int g = first_group(wave * a.splits);
+    const int g1 = first_group((wave + 1) * a.splits);
+    Group cur, next, far;  // three groups in flight per wave
+    if (g < g1) load(cur, g);
+    if (g + 1 < g1) load(next, g + 1);
+    for (int R = wave * a.splits; R < (wave + 1) * a.splits; ++R) {
+        const int end = first_group(R + 1);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (; g < end; ++g) {
+            if (g + 2 < g1) load(far, g + 2);
+            f32x4 t = {0.f, 0.f, 0.f, 0.f}, rs = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                rs = mfma16(cur.a[ks], ones, rs);
+                t = mfma16(cur.a[ks], w4_expand(cur.w[ks]), t);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = w4_group(acc[i], cur.sc, t[i], rs[i]);
+            cur = next;
+            next = far;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[R][(4 * q + i) * kRowCols + r] = acc[i];
+    }
+}
+
+// x += eight range sums, PER of them to a split; HALVES: the two halves of a split are added up first
+template <int PER, bool HALVES>
+__device__ __forceinline__ void add_ranges(float4& x, const float (*red)[16 * kRowCols], int tid) {
+    constexpr int HALF = HALVES && PER > 1 ? PER / 2 : PER;
+    float4 p[kRanges];
+#pragma unroll
+    for (int w = 0; w < kRanges; ++w) p[w] = *(const float4*)&red[w][tid * 4];
+    auto add = [](float4& to, const float4& v) { to.x += v.x; to.y += v.y; to.z += v.z; to.w += v.w; };
+#pragma unroll
+    for (int s = 0; s < kRanges; s += PER) {
+#pragma unroll
+        for (int h = s; h < s + PER; h += HALF) {
+#pragma unroll
+            for (int w = h + 1; w < h + HALF; ++w) add(p[h], p[w]);
+            if (h > s) add(p[s], p[h]);
+        }
+        add(x, p[s]);
+    }
+}
+
+template <bool W4>
+__global__ __launch_bounds__(64 * kRanges) void project_rows(const RowArgs a) {
+    extern __shared__ __attribute__((aligned(16))) float red_lds[];  // per range, [row][feature]
+    float (*red)[16 * kRowCols] = (float (*)[16 * kRowCols])red_lds;
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // four features of one row per thread of the first wave: the residual is on its way while the products run
+    const int row = tid >> 2, col = blockIdx.x * kRowCols + 4 * (tid & 3);
+    const bool mine = tid < 64 && row < a.M;
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (mine) x = *(const float4*)(a.x32 + (size_t)row * a.N + col);
+    if constexpr (W4) {
+        ranges_w4(a, red, blockIdx.x * kRowCols, wave, lane);
+    } else {
+        const f32x4 acc = range_bf16(a, blockIdx.x * kRowCols, wave, lane);
+        *(f32x4*)&red[wave][r * kRowCols + 4 * q] = acc;
+    }
+    __syncthreads();
+    if (!mine) return;
+    // sums of the splits, each added to the residual in turn
+    if constexpr (W4) {
+        for (int s = 0; s < a.splits; ++s) add_ranges<kRanges, false>(x, red + s * kRanges, tid);
+    } else if (a.splits == 8) {
+        add_ranges<1, true>(x, red, tid);
+    } else if (a.splits == 4) {
+        add_ranges<2, true>(x, red, tid);
+    } else {
+        add_ranges<4, true>(x, red, tid);
+    }
+    if (a.out) {  // the call's last projection: the stage's output
+        u32x2 o;
+        o[0] = pack_bf16x2(x.x, x.y);
+        o[1] = pack_bf16x2(x.z, x.w);
+        *(u32x2*)(a.out + (size_t)row * a.N + col) = o;
+        return;
+    }
+    *(float4*)(a.x32 + (size_t)row * a.N + col) = x;
+    const u32x2 g = *(const u32x2*)(a.gain + col);
+    u32x2 o;
+    o[0] = pack_bf16x2(x.x * __uint_as_float(g[0] << 16), x.y * __uint_as_float(g[0] & 0xffff0000u));
+    o[1] = pack_bf16x2(x.z * __uint_as_float(g[1] << 16), x.w * __uint_as_float(g[1] & 0xffff0000u));
+    *(u32x2*)(a.xn + tiled_offset(row, col >> 3, a.N >> 5) + (col & 7)) = o;
+    const float ss = sum_squares_16(x);  // (the four threads of a row are in or out together)
+    if ((tid & 3) == 0) a.ssq[(size_t)row * (a.N / kRowCols) + blockIdx.x] = ss;
+}
+
+// Partial sums of up to 64 rows, bf16 weights: a workgroup owns 64 rows x 64 features and the 8 / splits consecutive K ranges
+// of its split; GROUPS = 2 groups of four waves take one half of them each (a wave 32 rows x 32 features) and add up at the
+// end.  A group brings rows and weights through a ring of its own in LDS, in pairs of K steps (16 KB: the 32-row blocks of
+// the tiled layout are LDS images), four pairs deep, with one barrier per pair.  The launch is bound by streaming the weights
+// as long as a pair's chain of wait, fragment reads and products stays short: with one group, whose chain nothing covers, the
+// O / down launches took 9.9 / 23 us at 64 rows of the 7B shapes.
+constexpr int kPairBytes = 16384, kPairs = 4;
+
+// 1 KB per wave into LDS; NT: the weights, which are read once
+template <bool NT>
+__device__ __forceinline__ void load_unit(const char* uniform_base, unsigned lane_offset, unsigned lds) {
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+                     : : "v"(lane_offset), "s"(uniform_base), "s"(lds) : "memory", "m0");
+    else load_to_lds_16(uniform_base, lane_offset, lds);
+}
+
+template <int GROUPS>
+__global__ __launch_bounds__(256 * GROUPS) void project_split(const RowArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char ring[];
+    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = wave8 >> 2, wave = wave8 & 3, wm = wave & 1, wn = wave >> 1;
+    const int KT = a.K / 32, split = blockIdx.y, per = kRanges / a.splits / GROUPS;  // ranges per group
+    auto range_start = [&](int range) { return range * KT / kRanges; };
+    auto count_of = [&](int g) { return range_start((split * GROUPS + g + 1) * per) - range_start((split * GROUPS + g) * per); };
+    int range = (split * GROUPS + group) * per;
+    const int first = range_start(range), count = count_of(group);  // K steps of this group
+    const int pairs = (count + 1) / 2;
+    const int rounds = GROUPS == 1 ? pairs : (max(count_of(0), count_of(1)) + 1) / 2;  // (the groups share the barriers)
+    // A K step in LDS: two 2 KB blocks of rows, two of weights.  Wave w copies its KB number w of either: half w & 1 of row
+    // block w >> 1 and the same of the weights' blocks.  Row blocks past the chunk repeat its last one.
+    const char* a_src = (const char*)a.A + ((size_t)min(wave >> 1, (a.M - 1) >> 5) * KT + first) * 2048 + (wave & 1) * 1024;
+    const char* w_src = (const char*)a.W + ((size_t)(blockIdx.x * 2 + (wave >> 1)) * KT + first) * 2048 + (wave & 1) * 1024;
+    unsigned char* mine = ring + group * kPairs * kPairBytes;
+    const unsigned ring0 = __builtin_amdgcn_readfirstlane(lds_byte_address(mine));
+    auto issue = [&](int pair) __attribute__((always_inline)) {  // four loads per wave
+        const unsigned dst = ring0 + (pair & (kPairs - 1)) * kPairBytes + wave * 1024;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const size_t at = (size_t)min(2 * pair + h, count - 1) * 2048;
+            load_unit<false>(uniform_ptr(a_src + at), lane * 16, dst + h * 8192);
+            load_unit<true>(uniform_ptr(w_src + at), lane * 16, dst + h * 8192 + 4096);
+        }
+    };
+    for (int p = 0; p < kPairs - 1 && p < pairs; ++p) issue(p);
+
+    // fragment of 16 rows: chunk q of row r of the 16-row half
+    unsigned off[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) off[h] = 2 * (unsigned)tiled_offset(16 * h + r, q, 1);
+    f32x4 acc[2][2], sum[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto close_range = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                sum[i][j] += acc[i][j];
+                acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+    };
+    int boundary = range_start(range + 1) - first;
+    for (int p = 0; p < rounds; ++p) {
+        // pair p has landed when at most the loads of the pairs behind it are in flight (the last of them: p + 2)
+        if (p + 2 < pairs) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else if (p + 1 < pairs) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();  // (every wave has read pair p - 1, whose slot is refilled now)
+        if (p >= pairs) continue;
+        if (p + kPairs - 1 < pairs) issue(p + kPairs - 1);
+        const unsigned char* slot = mine + (p & (kPairs - 1)) * kPairBytes;
+        bf16x8 x[2][2], w[2][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                x[h][i] = *(const bf16x8*)(slot + h * 8192 + wm * 2048 + off[i]);
+                w[h][i] = *(const bf16x8*)(slot + h * 8192 + 4096 + wn * 2048 + off[i]);
+            }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (2 * p + h < count) {
+                while (2 * p + h == boundary) {  // (ranges may be empty)
+                    close_range();
+                    ++range;
+                    boundary = range_start(range + 1) - first;
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(w[h][i], x[h][j], acc[i][j]);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave has read the pair
+    }
+    close_range();
+    if constexpr (GROUPS == 2) {  // the second group's sums through LDS
+        __syncthreads();
+        f32x4* other = (f32x4*)ring;
+        const int t = threadIdx.x & 255;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (group == 1) other[i * 256 + t] = sum[i >> 1][i & 1];
+        __syncthreads();
+        if (group == 1) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i >> 1][i & 1] += other[i * 256 + t];
+    }
+    float* dst = a.partial + (size_t)split * a.M * a.N + blockIdx.x * 64 + wn * 32 + 4 * q;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int row = wm * 32 + 16 * j + r;
+        if (row >= a.M) continue;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) *(f32x4*)(dst + (size_t)row * a.N + 16 * i) = sum[i][j];
+    }
+}
+
+bool bad(bool w4, const RowArgs& a, int rows) {
+    return a.M < 1 || a.M > rows || a.N % 64 || a.N > 8192 || a.K % (w4 ? 128 : 32) || a.splits < 1 ||
+           a.splits > kMaxRowSplits || (!w4 && a.splits != row_splits(a.N));
+}
+
+}  // namespace
+
+// As many splits (a divisor of the eight ranges) as keep the grid of 64-feature tiles within one round of workgroups (two up to
+// the widest stage, 8192).
+int row_splits(int N) {
+    int splits = 2;
+    while (splits < kRanges && N / 64 * splits * 2 <= 256) splits *= 2;
+    return splits;
+}
+
+hipError_t rows_configure() {
+    return hipFuncSetAttribute((const void*)project_split<2>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kPairs * kPairBytes);
+}
+
+hipError_t launch_project_rows(bool w4, const RowArgs& a, hipStream_t s) {
+    if (bad(w4, a, kMaxProjectRows)) return hipErrorInvalidValue;
+    const int lds = (w4 ? a.splits : 1) * kRanges * 16 * kRowCols * 4;  // at most 64 KB
+    hipLaunchKernelGGL(w4 ? project_rows<true> : project_rows<false>, dim3(a.N / kRowCols), dim3(64 * kRanges), lds, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_project_split(const RowArgs& a, hipStream_t s) {
+    if (bad(false, a, kMaxSplitRows)) return hipErrorInvalidValue;
+    if (a.splits < kRanges)
+        hipLaunchKernelGGL(project_split<2>, dim3(a.N / 64, a.splits), dim3(512), 2 * kPairs * kPairBytes, s, a);
+    else hipLaunchKernelGGL(project_split<1>, dim3(a.N / 64, a.splits), dim3(256), kPairs * kPairBytes, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace jup

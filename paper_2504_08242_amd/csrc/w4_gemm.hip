@@ -83,13 +83,6 @@ __global__ __launch_bounds__(256) void pack_w4(unsigned char* __restrict__ dst, 
     }
 }
 
-__device__ inline bf16x8 w4_expand(unsigned w) {
-    u32x4 v;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = ((w >> (4 * j)) & 0x000F000Fu) | 0x43004300u;
-    return __builtin_bit_cast(bf16x8, v);
-}
-
 // What a wave fetches for one K group: the codes of its four column blocks and their scales, and four A fragments
 // per row group.
 struct W4Codes {
@@ -102,8 +95,10 @@ struct W4Rows {
 };
 
 template <int EPI, int RG, int WAVES, bool STREAM_ONCE>
-__global__ __launch_bounds__(64 * WAVES) void gemm_w4(const GemmArgs a) {
+// (up to 16 rows: 128 registers per lane, so that two workgroups share a CU and the widest grids take one round)
+__global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const GemmArgs a) {
     __shared__ float red[WAVES][16][W4_TILE_N];
+    __shared__ float scale_of_row[16];  // 1 / rms of up to 16 rows that come with partial sums of squares
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 15, q = lane >> 4;
     const int tile = blockIdx.x % a.n_tiles, split = blockIdx.x / a.n_tiles, rg0 = blockIdx.y * RG;
@@ -179,7 +174,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_w4(const GemmArgs a) {
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d.a[j][ks], b[ks], t, 0, 0, 0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[j][cg][i] += sc[cg] * (t[i] - 136.0f * rs[j][i]);
+                for (int i = 0; i < 4; ++i) acc[j][cg][i] = w4_group(acc[j][cg][i], sc[cg], t[i], rs[j][i]);
             }
         }
     };
@@ -193,10 +188,14 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_w4(const GemmArgs a) {
     constexpr bool ROWS_AHEAD = RG <= 2;
     W4Codes cur, nxt;
     W4Rows<RG> rows, rows_nxt;
+    const bool scaled = RG == 1 && EPI != EPI_PARTIAL && a.ssq;  // (the barriers in front of the epilogue publish the factors)
+    RowScale<WAVES> sq;
+    if (scaled) sq.begin(a.ssq, a.M, wave, lane, a.K);
     if (g0 < g1) {
         fetch_codes(cur, g0);
         if (ROWS_AHEAD) fetch_rows(rows, g0);
     }
+    if (scaled) sq.finish(scale_of_row, a.M, wave, lane, a.K, a.rms_eps);  // (behind the loop its registers would spill)
     for (int g = g0; g < g1; ++g) {
         if (g + 1 < g1) {
             fetch_codes(nxt, g + 1);
@@ -227,6 +226,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_w4(const GemmArgs a) {
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) v += red[w][m][n];
             const int row = 16 * (rg0 + j) + m;
+            if (scaled) v *= scale_of_row[m];
+            else if (EPI != EPI_PARTIAL && a.row_factor) v *= a.row_factor[min(row, a.M - 1)];
             if (EPI == EPI_PARTIAL) {
                 if (row < a.M) a.partial[((size_t)split * a.M + row) * a.N + col] = v;
             } else if (EPI == EPI_SWIGLU) {

@@ -87,3 +87,32 @@ def test_short_attention(dtype, n, pos, shared):
     if n <= 64:
         parents = si.make_token_tree(n, 3)
         p.check(p.gpu_tree(h, pos, parents, kv), p.oracle.prefill_tree(h, parents, pos), "tree")
+
+
+@pytest.mark.parametrize("d_model,n_heads,d_ffn", [
+    (256, 2, 128),       # fewer K steps than ranges: some are empty
+    (2304, 18, 1408),    # ranges of unequal length, four splits
+    (5120, 40, 3456),    # two splits
+])
+@pytest.mark.parametrize("dtype", ["bf16", "w4"])
+def test_row_projections(dtype, d_model, n_heads, d_ffn):
+    """Output and down projections of calls of up to 16 rows and of batches of such branches (17 to 64 rows), two layers deep
+    (the norm between them is a factor of the rows): against the oracle, and a branch has the same bits alone, batched within
+    16 rows and batched beyond."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=n_heads, d_ffn=d_ffn, n_layers=2)
+    p = Pair(cfg, dtype, seed=d_model, max_positions=48, max_chunk_tokens=64)
+    for n in (1, 15, 16, 17):
+        g, o = p.run_both(p.hidden(20 + n, tag=n), [20, n])
+        p.check(g, o, f"{n} rows")
+        p.check(p.kv_gpu()[:, :, :, :20 + n], p.oracle.kv[:, :, :, :20 + n], f"cache, {n} rows")
+    for branches, n in ((3, 5), (16, 1), (9, 2), (2, 9), (11, 3), (4, 16)):
+        h = p.hidden(branches * n, tag=100 + n).reshape(branches, n, d_model)
+        alone = [p.gpu_chunk(h[b], 20) for b in range(branches)]
+        kvs = [p.kv.fork(20, 40) for _ in range(branches)]
+        y = p.stage.prefill_branches(torch.from_numpy(h.reshape(-1, d_model)).to("cuda:0", p.td), n, [20] * branches, kvs)
+        y = y.float().cpu().numpy().reshape(branches, n, d_model)
+        for b in range(branches):
+            assert np.array_equal(y[b], alone[b]), (branches, n, b)
+        for kv in kvs:
+            kv.destroy()
