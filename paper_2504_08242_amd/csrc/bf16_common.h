@@ -29,6 +29,20 @@ __device__ inline const char* uniform_ptr(const char* p) {
     return (const char*)(((unsigned long long)hi << 32) | lo);
 }
 
+// Loads at a wave-uniform address plus a 32-bit lane offset: one instruction with the address in scalar registers (through a
+// plain pointer the compiler, which cannot see that the address is global memory, takes flat loads and 64-bit adds per lane).
+template <class T>
+__device__ __forceinline__ T load_at(const char* uniform_base, unsigned lane_offset) {
+    typedef const __attribute__((address_space(1))) char* global_bytes;
+    return *(const __attribute__((address_space(1))) T*)((global_bytes)uniform_ptr(uniform_base) + lane_offset);
+}
+template <class T>  // read once: non-temporal
+__device__ __forceinline__ T load_once_at(const char* uniform_base, unsigned lane_offset) {
+    typedef const __attribute__((address_space(1))) char* global_bytes;
+    return __builtin_nontemporal_load(
+        (const __attribute__((address_space(1))) T*)((global_bytes)uniform_ptr(uniform_base) + lane_offset));
+}
+
 // 16 bytes per lane from global memory straight into LDS: lane i's piece lands at lds_base + 16 i, where
 // lds_base (a wave-uniform LDS byte address) travels in M0.  Issued as text so that the caller controls every
 // wait itself: the hardware counts these loads in vmcnt only, and the caller orders them against LDS reads of
@@ -210,10 +224,17 @@ void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_
 hipError_t gemm_configure();  // raises the dynamic-LDS limit of every instantiation (once per process)
 
 // Eight 4-bit codes of one dword (packed as w4_gemm.hip describes) as bf16 values 128 + code.
-__device__ inline bf16x8 w4_expand(unsigned w) {
+struct W4Bits {  // constants the compiler does not know, in a vector and a scalar register: and + or are then one instruction
+    unsigned mask, bias;
+    __device__ __forceinline__ W4Bits() {
+        asm volatile("v_mov_b32 %0, 0x000f000f" : "=v"(mask));
+        asm volatile("s_mov_b32 %0, 0x43004300" : "=s"(bias));
+    }
+};
+__device__ __forceinline__ bf16x8 w4_expand(unsigned w, const W4Bits& k) {
     u32x4 v;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = ((w >> (4 * j)) & 0x000F000Fu) | 0x43004300u;
+    for (int j = 0; j < 4; ++j) v[j] = ((w >> (4 * j)) & k.mask) | k.bias;
     return __builtin_bit_cast(bf16x8, v);
 }
 

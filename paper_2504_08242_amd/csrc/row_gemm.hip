@@ -20,8 +20,8 @@
 //     split added up first.  4-bit: the eight waves of every split.
 //
 // Measured on the 7B shapes at 5 rows (us, two K-split launches and two reduce + norm passes -> two launches): bf16
-// 7.2 + 17.4 + 2 x 4.8 -> 7.7 + 17.4; 4-bit 3.7 + 9.2 + 2 x 4.3 -> 5.9 + 12.8.  A whole call: 5 rows of six bf16 layers
-// 723 -> 681 us, one row of eight 4-bit layers 460 -> 424 us.  A batch of branches pays for the equal bits: 8 x 5 rows of two
+// 7.2 + 17.4 + 2 x 4.8 -> 7.7 + 17.4; 4-bit 3.7 + 9.2 + 2 x 4.3 -> 5.9 + 12.8.  A whole call: 5 rows of eight bf16 layers
+// 723 -> 681 us, one row of eight 4-bit layers 460 -> 416 us.  A batch of branches pays for the equal bits: 8 x 5 rows of two
 // bf16 layers 203 -> 207 us.
 #include "bf16_common.h"
 
@@ -53,8 +53,8 @@ __device__ __forceinline__ f32x4 range_bf16(const RowArgs& a, int f0, int range,
         bf16x8 a[U];
     };
     auto load = [&](Batch& b, int at, int u) __attribute__((always_inline)) {
-        b.w[u] = __builtin_nontemporal_load((const u32x4*)(uniform_ptr(w_block + (size_t)(at + u) * 2048) + w_lane));
-        b.a[u] = *(const bf16x8*)(uniform_ptr((const char*)a.A + (size_t)(at + u) * 2048) + a_lane);
+        b.w[u] = load_once_at<u32x4>(w_block + (size_t)(at + u) * 2048, w_lane);
+        b.a[u] = load_at<bf16x8>((const char*)a.A + (size_t)(at + u) * 2048, a_lane);
     };
     auto load_all = [&](Batch& b, int at) __attribute__((always_inline)) {
 #pragma unroll
@@ -105,17 +105,18 @@ __device__ __forceinline__ void ranges_w4(const RowArgs& a, float (*red)[16 * kR
     const unsigned a_lane = 2 * (unsigned)tiled_offset(min(r, a.M - 1), q, a.K / 32);
     const u32x4 ones_bits = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
     const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
+    const W4Bits bits;
     struct Group {
         u32x4 w;
         float sc;
         bf16x8 a[4];
     };
     auto load = [&](Group& d, int g) __attribute__((always_inline)) {
-        d.w = __builtin_nontemporal_load((const u32x4*)(uniform_ptr(w_block + (size_t)g * 4096) + w_lane));
-        d.sc = *(const float*)(uniform_ptr(s_block + (size_t)g * 256) + s_lane);
+        d.w = load_once_at<u32x4>(w_block + (size_t)g * 4096, w_lane);
+        d.sc = load_at<float>(s_block + (size_t)g * 256, s_lane);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
-            d.a[ks] = *(const bf16x8*)(uniform_ptr((const char*)a.A + (size_t)(4 * g + ks) * 2048) + a_lane);
+            d.a[ks] = load_at<bf16x8>((const char*)a.A + (size_t)(4 * g + ks) * 2048, a_lane);
     };
     int g = first_group(wave * a.splits);
     const int g1 = first_group((wave + 1) * a.splits);
@@ -131,7 +132,7 @@ __device__ __forceinline__ void ranges_w4(const RowArgs& a, float (*red)[16 * kR
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 rs = mfma16(cur.a[ks], ones, rs);
-                t = mfma16(cur.a[ks], w4_expand(cur.w[ks]), t);
+                t = mfma16(cur.a[ks], w4_expand(cur.w[ks], bits), t);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[i] = w4_group(acc[i], cur.sc, t[i], rs[i]);

@@ -15,13 +15,13 @@
 //     ks holding the eight codes of column r for k = 128 g + 32 ks + 8 q + e.  Inside a dword, nibble p < 4 is
 //     element 2 p and nibble p + 4 is element 2 p + 1: ((w >> 4 j) & 0x000F000F) | 0x43004300 is then the bf16 pair
 //     (128 + code[2 j], 128 + code[2 j + 1]) -- two instructions per two weights, exact (a bf16 mantissa holds
-//     128..255 in steps of one).
+//     128..255 in steps of one).  and + or are one instruction only if at most one of the constants is a literal (W4Bits).
 //   * The offset of 136 = 128 + 8 leaves through the row sums of A: sum_k A[m][k] (128 + c) - 136 sum_k A[m][k].
 //     The row sums of a group come from one more MFMA per K step against a register of ones, and a group's
 //     result enters the fp32 accumulator as scale * (t - 136 * rowsum): 4 FMAs per lane, group and column block.
 //     Products of a bf16 value and an integer below 256 are exact in fp32, the sums round as any fp32 sum does.
 //   * A (16 rows of the tiled activation layout per row group) is read from L2 with 16-byte loads, up to 1 KB per
-//     wave and K step; lanes whose row lies past the chunk fetch nothing.
+//     wave and K step; lanes whose row lies past the chunk repeat its last row.
 #include "bf16_common.h"
 
 namespace jup {
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void pack_w4(unsigned char* __restrict__ dst, 
 // per row group.
 struct W4Codes {
     u32x4 w[4];
-    float4 sc;
+    f32x4 sc;
 };
 template <int RG>
 struct W4Rows {
@@ -99,7 +99,7 @@ template <int EPI, int RG, int WAVES, bool STREAM_ONCE>
 __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const GemmArgs a) {
     __shared__ float red[WAVES][16][W4_TILE_N];
     __shared__ float scale_of_row[16];  // 1 / rms of up to 16 rows that come with partial sums of squares
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
     const int tile = blockIdx.x % a.n_tiles, split = blockIdx.x / a.n_tiles, rg0 = blockIdx.y * RG;
     const int G = a.K / W4_GROUP;
@@ -109,41 +109,36 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
     const int g0 = ws0 + wave * cnt / WAVES, g1 = ws0 + (wave + 1) * cnt / WAVES;
 
     const int k_stages = a.K / 32;
-    // Lanes whose row lies past the chunk fetch nothing (a 5-token chunk reads 5 of the 16 rows of its fragment) and
-    // multiply zeros; their results are dropped.
-    int a_row[RG];
-    bool a_live[RG];
+    // Rows past the chunk repeat its last one (no extra cache lines); their results are dropped.  With 64 rows the vector
+    // instructions beside the MFMAs are what bounds a wave: one instruction instead of two per expanded dword, no execution
+    // masks and zero fills around the loads of rows took the passes of a 512-row call on the 7B shapes from 184 to 157 us
+    // (gate/up), 110 to 96 (QKV) and 77 to 70 (O / down, mean), one row of eight layers from 424 to 416 us.  (Tried and slower:
+    // rows and codes of a group through LDS, shared by all waves in step, 178 - 205 us for gate/up.)
+    unsigned a_lane[RG];
 #pragma unroll
-    for (int j = 0; j < RG; ++j) {
-        a_row[j] = 16 * (rg0 + j) + r;
-        a_live[j] = a_row[j] < a.M;
-    }
-    const unsigned char* wbase = (const unsigned char*)a.W + (size_t)tile * G * 4096 + lane * 16;
-    const float* sbase = a.w_scale + ((size_t)tile * G * 16 + r) * 4;
+    for (int j = 0; j < RG; ++j) a_lane[j] = 2 * (unsigned)tiled_offset(min(16 * (rg0 + j) + r, a.M - 1), q, k_stages);
+    const char* wbase = (const char*)a.W + (size_t)tile * G * 4096;
+    const char* sbase = (const char*)(a.w_scale + (size_t)tile * G * 64);
+    const W4Bits bits;
     // STREAM_ONCE (one pass over the codes, up to 64 rows): every code is read exactly once, with the non-temporal hint,
     // so that the stream does not push the KV cache and the activations out of the caches (measured at 5 rows per call:
     // the attention launch behind the projections 15.0 -> 12.2 us, a step of 8 branches 3.96 -> 3.62 ms).  Longer chunks
     // take several passes, which find the codes in L2, and inside an overlapped call the other chunks' launches find them
     // in the caches (as for the bf16 kernels: not measured separately for the codes).
-    auto fetch_codes = [&](W4Codes& d, int g) {
+    auto fetch_codes = [&](W4Codes& d, int g) __attribute__((always_inline)) {
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg) {
-            const u32x4* src = (const u32x4*)(wbase + ((size_t)g * 4 + cg) * 1024);
-            if constexpr (STREAM_ONCE) d.w[cg] = __builtin_nontemporal_load(src);
-            else d.w[cg] = *src;
+            const char* src = wbase + (size_t)g * 4096 + cg * 1024;
+            d.w[cg] = STREAM_ONCE ? load_once_at<u32x4>(src, lane * 16) : load_at<u32x4>(src, lane * 16);
         }
-        d.sc = *(const float4*)(sbase + (size_t)g * 64);
+        d.sc = load_at<f32x4>(sbase + (size_t)g * 256, r * 16);
     };
-    const u32x4 zero_bits = {0u, 0u, 0u, 0u};
-    const bf16x8 zero_frag = __builtin_bit_cast(bf16x8, zero_bits);
-    auto fetch_rows = [&](W4Rows<RG>& d, int g) {
+    auto fetch_rows = [&](W4Rows<RG>& d, int g) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < RG; ++j)
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                d.a[j][ks] = zero_frag;
-                if (a_live[j]) d.a[j][ks] = *(const bf16x8*)(a.A + tiled_offset(a_row[j], (4 * g + ks) * 4 + q, k_stages));
-            }
+            for (int ks = 0; ks < 4; ++ks)
+                d.a[j][ks] = load_at<bf16x8>((const char*)a.A + (size_t)g * 8192 + ks * 2048, a_lane[j]);
     };
 
     f32x4 acc[RG][4];
@@ -162,12 +157,12 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) rs[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d.a[j][ks], ones, rs[j], 0, 0, 0);
         }
-        const float sc[4] = {c.sc.x, c.sc.y, c.sc.z, c.sc.w};
+        const f32x4 sc = c.sc;
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg) {
             bf16x8 b[4];  // one expansion of the codes serves every row group
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) b[ks] = w4_expand(c.w[cg][ks]);
+            for (int ks = 0; ks < 4; ++ks) b[ks] = w4_expand(c.w[cg][ks], bits);
 #pragma unroll
             for (int j = 0; j < RG; ++j) {
                 f32x4 t = {0.f, 0.f, 0.f, 0.f};
@@ -201,7 +196,10 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
             fetch_codes(nxt, g + 1);
             if (ROWS_AHEAD) fetch_rows(rows_nxt, g + 1);
         }
-        if (!ROWS_AHEAD) fetch_rows(rows, g);
+        if (!ROWS_AHEAD) {
+            fetch_rows(rows, g);
+            __builtin_amdgcn_sched_barrier(0);  // all on their way before the first wait (gate/up of 512 rows: 157 us, else 168)
+        }
         compute(cur, rows);
         cur = nxt;
         if (ROWS_AHEAD) rows = rows_nxt;
