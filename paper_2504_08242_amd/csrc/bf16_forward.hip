@@ -89,7 +89,8 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     u16* act = (u16*)(ws + st.wl.act);
     float* partial = (float*)(ws + st.wl.partial);
     float2* rope = (float2*)(ws + st.wl.rope);
-    float* factor = (float*)(ws + st.wl.factor);
+    // 1 / rms of the rows (small branches): lives from a reduce + norm pass to the projection behind it, when nothing is in o
+    float* factor = (float*)(ws + st.wl.o);
     const size_t split_stride = (size_t)n * d;
 
     if (c.n_layers == 0) return hipMemcpyAsync(hidden_out, hidden_in, (size_t)n * d * 2, hipMemcpyDeviceToDevice, s);

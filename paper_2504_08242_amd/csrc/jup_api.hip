@@ -122,7 +122,6 @@ WorkspaceLayout workspace_layout(const jup_stage_config_t& c, int32_t T, bool br
     w.act = off;  off += align_up(t * f * e);
     w.rope = off; off += align_up(t * (size_t)(c.head_dim / 2) * 8);
     w.partial = off; off += f32 ? 0 : align_up(8 * t * d * 4);
-    w.factor = off; off += f32 ? 0 : align_up(t * 4);
     w.branches = off; off += f32 ? 0 : align_up(sizeof(BranchTable));
     w.tree = off; off += align_up(sizeof(TreeTable));
     w.att_split_rows = f32 ? 0 : att_split_rows(T, c.n_heads, branches);

@@ -42,7 +42,6 @@ struct WorkspaceLayout {
     size_t act;   // [T, f] silu(gate) * up
     size_t rope;  // [T, head_dim/2] float2 (cos, sin) of the chunk's positions
     size_t partial;  // bf16 only: [8][T, d] fp32 K-split partial sums of the O / down projections
-    size_t factor;   // bf16 only: [T] fp32 1 / rms of the rows
     size_t branches; // bf16 only: BranchTable of a batched-branch call
     size_t tree;     // TreeTable of a token-tree call
     // bf16 only: scratch of attention launches that split the keys of a query block over workgroups
