@@ -442,15 +442,16 @@ def main():
                     "tflops": round(step_flops / pc_s / 1e12, 1),
                     "frac_of_bf16_mfma_peak": round(step_flops / pc_s / 1e12 / PEAK_BF16_TFLOPS, 4)}
 
-    # The same prompt in one call, consecutive chunks overlapping on several streams.
+    # The same prompt in one call with overlap enabled: chunks computed in groups, long ones on several streams.
     overlapped = None
     if step_overlapped is not None:
         # no clock probe here: the process has four hardware queues, the call's four streams take them all, and a probe
         # on a fifth stream would hold one lane's queue for as long as it runs
         o_elapsed, _ = timed(step_overlapped)
         o_ms = o_elapsed / args.steps * 1e3
-        overlapped = {"what": f"one jup_stage_prefill_chunks call for the whole prompt, consecutive chunks overlapping on "
-                              f"{lanes_used} streams (all chunks at hand: a pipeline's first stage)",
+        overlapped = {"what": f"one jup_stage_prefill_chunks call for the whole prompt, overlap enabled on {lanes_used} "
+                              f"lanes, consecutive chunks of up to 1024 tokens computed together (all chunks at hand: a "
+                              f"pipeline's first stage)",
                       "tokens_per_s": round(tokens_per_step * args.steps / o_elapsed, 1), "ms_per_step": round(o_ms, 4),
                       "tflops": round(step_flops / (o_ms * 1e-3) / 1e12, 1),
                       "frac_of_bf16_mfma_peak": round(step_flops / (o_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, 4)}
