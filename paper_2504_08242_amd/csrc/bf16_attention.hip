@@ -209,10 +209,14 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
 
     // key splits over workgroups: this one owns the tiles [t_lo, t_hi) of the query block
     // (never more than the launch provides: a launch that does not split has gridDim.y = 1)
-    const int n_splits = min(att_key_splits(n, n_tiles), (int)gridDim.y);
+    // Ranges are dealt by 64 queries whatever NQ: 32-query workgroups (a chunk of 65 to 128 tokens alone) then sum the same
+    // ranges as 64-query ones (the same chunk in a batch of branches).
+    const int range_tiles = NQ == 1 ? (pos0 + min((q0 | 63) + 1, n) + kKT - 1) / kKT : n_tiles;
+    const int n_splits = min(att_key_splits(n, range_tiles), (int)gridDim.y);
     const int ks = blockIdx.y;
     if (ks >= n_splits) return;  // (a branch or query block with fewer keys than the longest of the launch)
-    const int t_lo = (int)((long)ks * n_tiles / n_splits), t_hi = (int)((long)(ks + 1) * n_tiles / n_splits);
+    const int t_lo = (int)((long)ks * range_tiles / n_splits);
+    const int t_hi = min((int)((long)(ks + 1) * range_tiles / n_splits), n_tiles);
     const int n_own = t_hi - t_lo;
     const int cnt = n_own > g ? (n_own - g + KP - 1) / KP : 0;  // tiles of this key partition
     const int max_cnt = (n_own + KP - 1) / KP;                  // of partition 0: every wave runs that many rounds
@@ -796,6 +800,8 @@ hipError_t attention_configure() {
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)short_attention_bf16<32>, hipFuncAttributeMaxDynamicSharedMemorySize, kShortLds);
     if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute((const void*)chunk_attention_bf16<1, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttLds);
+    if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)chunk_attention_bf16<4, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             kAttLds);
     if (e != hipSuccess) return e;
@@ -825,17 +831,22 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     }
     // chunks of up to 256 tokens behind a long cached sequence: several workgroups per query block (key splits)
     const int splits = att_key_splits(n, (pos0 + n + kKT - 1) / kKT);
-    // One query block per workgroup up to 64 tokens, up to 128 when the launch has the chip to itself, and beyond that as
-    // long as all its workgroups run at once (256 CUs, one workgroup each); with more of them the 64-query variant's shared
-    // tile fills win.  Measured, 64-query variant -> one block: 32 heads, 256 tokens behind 256 positions (256 workgroups)
-    // 10.4 -> 7.7 us, behind 2048 (512 workgroups) 31.0 -> 34.3 us; 320 tokens behind 256 (320 workgroups) 11.3 -> 12.4 us;
-    // 8 heads, 512 tokens behind 1024 (128 workgroups) 17.2 -> 12.3 us.
-    const bool short_blocks = n <= 64 || (!shared_gpu && (n <= 128 || (n + 31) / 32 * n_heads * splits <= 256));
-    if (short_blocks) {
+    // Up to 64 tokens the barrier-free waves; above, the key quarters: a chunk of more than 64 tokens rounds its probabilities
+    // as the longer groups of the multi-chunk call and the batches of branches do (how the keys are dealt to waves decides
+    // which reference a probability is rounded against).  One query block per workgroup up to 128 tokens when the launch has
+    // the chip to itself (twice the workgroups of the 64-query variant, which a launch this small needs more than shared
+    // tile fills: measured on 128-token chunks, 7B shapes 18.4 -> 17.0 us, 13B shapes 14.6 -> 13.0 us; inside an overlapped
+    // call the same choice costs 2-3.5 %, at 256 tokens it gains nothing): the same bits, see the key ranges there.
+    if (n <= 64) {
         const int wgs = (n + 31) / 32 * n_heads;
         if (!split_fits(sc, wgs, splits, 32)) return hipErrorInvalidValue;
         hipLaunchKernelGGL(n <= 16 ? short_attention_bf16<16> : short_attention_bf16<32>,
                            dim3(n_heads, (n + 31) / 32, splits), dim3(64 * kShortWaves), kShortLds, s, q, o, n, d_model, n_heads, pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
+    } else if (n <= 128 && !shared_gpu) {
+        const int wgs = (n + 31) / 32 * n_heads;
+        if (!split_fits(sc, wgs, splits, 32)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((chunk_attention_bf16<1, 2>), dim3(wgs, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+                           pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
     } else {
         const int wgs = (n + 63) / 64 * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;

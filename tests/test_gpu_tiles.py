@@ -116,3 +116,21 @@ def test_row_projections(dtype, d_model, n_heads, d_ffn):
             assert np.array_equal(y[b], alone[b]), (branches, n, b)
         for kv in kvs:
             kv.destroy()
+
+
+@pytest.mark.parametrize("n,branches", [(65, 3), (100, 2), (128, 4), (129, 2), (200, 3), (256, 2), (300, 2)])
+@pytest.mark.parametrize("pos", [20, 1975, 2100])   # 1975: a second key range for 64 queries that the first 32 alone do not reach
+def test_attention_of_long_branches_alone_and_batched(n, branches, pos):
+    """Branches of more than 64 tokens: alone (32-query workgroups up to 128 tokens) and batched (64-query workgroups) the
+    attention has the same bits, on a stage whose projections do not depend on the rows of the launch (4-bit codes)."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=256, n_heads=2, d_ffn=128, n_layers=1)
+    p = Pair(cfg, "w4", seed=n, max_positions=pos + n, max_chunk_tokens=max(branches * n, 512))
+    prefix = p.hidden(pos)
+    for lo in range(0, pos, 512):
+        p.gpu_chunk(prefix[lo:lo + 512], lo)
+    h = p.hidden(branches * n, tag=1).reshape(branches, n, 256)
+    alone = [p.gpu_chunk(h[b], pos) for b in range(branches)]
+    kvs = [p.kv.fork(pos, pos + n) for _ in range(branches)]
+    y = p.stage.prefill_branches(torch.from_numpy(h.reshape(-1, 256)).to("cuda:0", p.td), n, [pos] * branches, kvs)
+    assert np.array_equal(y.float().cpu().numpy().reshape(branches, n, 256), np.stack(alone))
