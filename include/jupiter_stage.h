@@ -269,8 +269,9 @@ JUP_API jup_status_t jup_stage_prefill_chunk_static(jup_stage_t *stage, const vo
  * pos_offset: the same cache entries are written, the final length is the same, and without
  * jup_stage_enable_overlap() outputs and cache values are equal bit for bit.  With it they are equal up to the
  * summation order of fp32 partial sums (the projections back to d_model split K according to the rows they
- * get, and to whether other chunks share the GPU), i.e. to the last bits of a bf16 value; the call is deterministic
- * either way.
+ * get, and to whether other chunks share the GPU) and to the key a row's attention probabilities were scaled by when
+ * they were rounded to bf16 (kernels for chunks of different lengths deal the keys differently), i.e. to the last
+ * bits of a bf16 value; the call is deterministic either way.
  *   hidden_in     [sum of chunk_tokens, d_model]; the chunks follow each other
  *   chunk_tokens  HOST array [n_chunks], each 0 .. the stage's max_chunk_tokens
  *   hidden_out    [sum of chunk_tokens, d_model]; may be the same buffer as hidden_in

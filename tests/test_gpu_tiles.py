@@ -134,3 +134,28 @@ def test_attention_of_long_branches_alone_and_batched(n, branches, pos):
     kvs = [p.kv.fork(pos, pos + n) for _ in range(branches)]
     y = p.stage.prefill_branches(torch.from_numpy(h.reshape(-1, 256)).to("cuda:0", p.td), n, [pos] * branches, kvs)
     assert np.array_equal(y.float().cpu().numpy().reshape(branches, n, 256), np.stack(alone))
+
+
+@pytest.mark.parametrize("one_call", [False, True])
+@pytest.mark.parametrize("n", [1, 5, 16, 17, 33, 64, 65, 128, 129, 300, 1100])
+def test_attention_of_peaked_rows_returns_the_value(n, one_call):
+    """Every query sees only itself: queries and keys are 4 times the normalised rows, so its own score lies some 170 above
+    all others.  The value row must come back exactly, whatever that score is: the largest probability takes no rounding.
+    Values and output projection are the identity, the rest of the layer adds nothing, and the residual is too small to
+    show."""
+    d = 256
+    cfg = dict(si.LLAMA7B_STAGE, d_model=d, n_heads=2, d_ffn=128, n_layers=1, rms_eps=0.0)
+    layers = si.make_layers(cfg, seed=n, bf16=True)
+    eye = np.eye(d, dtype=np.float32)
+    layers[0].update(wq=4 * eye, wk=4 * eye, wv=eye, wo=eye, w_down=np.zeros((d, 128), np.float32), g_attn=np.ones(d, np.float32))
+    p = Pair(cfg, "bf16", seed=n, max_positions=4 * n, max_chunk_tokens=n, layers_np=layers)
+    h = p.hidden(4 * n) * np.float32(2.0 ** -50)
+    if one_call:   # several chunks as one group, or (above 1024 tokens) beside each other
+        import torch
+        p.stage.enable_overlap(2)
+        y = p.stage.prefill_chunks(torch.from_numpy(h).to("cuda:0", p.td), [n] * 4, 0, p.kv).float().cpu().numpy()
+    else:
+        y = np.concatenate([p.gpu_chunk(h[i:i + n], i) for i in range(0, 4 * n, n)])
+    v = p.kv_gpu()[0, 1].transpose(1, 0, 2).reshape(4 * n, d)
+    assert np.abs(v).max() > 1.0
+    assert np.array_equal(y, v)
