@@ -318,9 +318,12 @@ JUP_API jup_status_t jup_stage_enable_overlap(jup_stage_t *stage, int32_t n_lane
  *   pos_offsets  HOST array [n_branches]: pos_offset of every branch's chunk (rules of jup_kv_check_append)
  *   kvs          HOST array [n_branches] of caches, all different, none the parent of another in the list
  *   hidden_out   [n_branches * n_tokens, d_model]; may be the same buffer as hidden_in
- * The result equals n_branches calls of jup_stage_prefill_chunk(), one per branch, bit for bit in the
- * JUP_BF16 path's caches and outputs (rows do not interact outside attention, and every row meets the same
- * arithmetic in the same order either way).  On success every cache b has length pos_offsets[b] + n_tokens.
+ * The result equals n_branches calls of jup_stage_prefill_chunk(), one per branch (rows do not interact outside
+ * attention).  Bit for bit, every row meeting the same arithmetic in the same order either way: on a JUP_BF16 stage
+ * up to 64 rows (n_branches * n_tokens), up to 128 for n_tokens <= 16 and d_model <= 4096; on a JUP_BF16_W4 stage
+ * without its bf16 copy whatever the rows.  More rows of bf16 weights divide the K of the projections back to d_model differently: equal up
+ * to the summation order of fp32 partial sums.  (A stage with the bf16 copy reads it for more than 64 rows in all.)
+ * On success every cache b has length pos_offsets[b] + n_tokens.
  * Errors: as jup_stage_prefill_chunk(); all branches are validated before anything is enqueued, and on error
  * no cache changes.
  */

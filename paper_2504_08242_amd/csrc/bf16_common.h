@@ -144,9 +144,10 @@ struct GemmArgs {
     float rms_eps;
 };
 
-// ---- projections back to d_model of up to 64 rows (row_gemm.hip) --------------------------------------
-constexpr int kMaxProjectRows = 16;  // up to here one launch that finishes the residual and the next projection's rows,
-constexpr int kMaxSplitRows = 64;    // batches of such chunks up to here: fp32 partial sums that give the same bits
+// ---- projections back to d_model of chunks of up to 16 rows and of batches of them (row_gemm.hip) --------------------
+constexpr int kMaxProjectRows = 16;  // up to here one launch that finishes the residual and the next projection's rows;
+constexpr int kMaxSplitRows = 128;   // batches of such chunks up to here: fp32 partial sums that give the same bits (bf16 weights:
+int max_split_rows(int N);           // up to here)
 int row_splits(int N);               // K splits of a bf16 projection of either kind: 2, 4 or 8
 struct RowArgs {
     const u16* A;          // [M, K] tiled
@@ -213,7 +214,7 @@ struct RowScale {
 
 enum GemmKind { GEMM_QKV, GEMM_O, GEMM_GATE_UP, GEMM_DOWN };
 
-// Fills the tiling fields of `a` for the given problem and launches.  Returns the number of K splits
+// Fill the tiling fields of `a` for the given problem and launch; gemm_plan_splits: the number of K splits
 // used (the caller sums that many partial buffers for EPI_PARTIAL).
 int gemm_plan_splits(int M, int N, int K, bool shared);  // shared: see GemmArgs::shared_gpu
 hipError_t launch_gemm_qkv(GemmArgs a, hipStream_t s);

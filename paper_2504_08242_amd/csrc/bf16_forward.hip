@@ -89,7 +89,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     u16* act = (u16*)(ws + st.wl.act);
     float* partial = (float*)(ws + st.wl.partial);
     float2* rope = (float2*)(ws + st.wl.rope);
-    // 1 / rms of the rows (small branches): lives from a reduce + norm pass to the projection behind it, when nothing is in o
+    // 1 / rms of the rows (branches of up to 16 tokens): lives from a reduce + norm pass to the projection behind it, when nothing is in o
     float* factor = (float*)(ws + st.wl.o);
     const size_t split_stride = (size_t)n * d;
 
@@ -126,9 +126,10 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     // Back to d_model.  Calls of up to 16 rows: the O / down projections finish the residual and the rows of the next
     // projection themselves (row_gemm.hip); their sums of squares take the place of the partial sums in the workspace.  All
     // other calls leave partial sums to the reduce + norm pass; batches of branches of up to 16 tokens in a form that gives
-    // every branch the bits it has alone (up to 64 rows).
+    // every branch the bits it has alone: bf16 weights up to max_split_rows, codes whatever the rows.  (The bf16 copy of a
+    // 4-bit stage is not what a branch of up to 64 rows runs on alone.)
     const bool rows = n <= kMaxProjectRows && !shared;
-    const bool small_branches = !rows && bt && bt->n_tok <= kMaxProjectRows && n <= kMaxSplitRows;
+    const bool small_branches = !rows && bt && bt->n_tok <= kMaxProjectRows && (w4 || (!expanded && n <= max_split_rows(d)));
     const bool as_rows = rows || small_branches;
     const int splits_o = w4 ? w4_plan_splits(d, d) : as_rows ? row_splits(d) : gemm_plan_splits(n, d, d, shared);
     const int splits_down = w4 ? w4_plan_splits(d, f) : as_rows ? row_splits(d) : gemm_plan_splits(n, d, f, shared);

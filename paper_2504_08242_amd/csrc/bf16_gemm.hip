@@ -129,7 +129,9 @@ struct Frags {
     bf16x8 b[NB];
 };
 
-template <int BMB, int NB, int WM, int WN, int EPI>
+// FACTOR: the results of a row may have to be multiplied by its 1 / rms.  A template parameter because on the tall tiles of
+// long chunks, which never need it, the test alone cost the 512-row launches 1 %.
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR = BMB <= 2 && EPI != EPI_PARTIAL>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     using S = Shape<BMB, NB, WM, WN>;
     constexpr int G_BM = S::BM;
@@ -209,12 +211,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     RowScale<S::WAVES> sq;
     const bool scaled = ROW_SCALE && a.ssq;
     if (scaled) sq.begin(a.ssq, a.M, wave, lane, a.K);
-    // 1 / rms of this lane's token in every row block of the wave, where the rows of A are not normalised (small tiles only:
-    // on the tall ones it cost the 512-row launches 1 %)
+    // 1 / rms of this lane's token in every row block of the wave, where the rows of A are not normalised
     float factor[MBW];
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb) factor[mb] = 1.0f;
-    if (ROW_SCALE && a.row_factor)
+    if (FACTOR && a.row_factor)
 #pragma unroll
         for (int mb = 0; mb < MBW; ++mb) factor[mb] = a.row_factor[min(m0 + (wm * MBW + mb) * 32 + (lane & 31), a.M - 1)];
 
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
             for (int mb = 0; mb < MBW; ++mb) {
                 const int m = m0 + wm * WROWS + mb * 32 + c;
                 if (m >= a.M) continue;
-                const float f = ROW_SCALE ? factor[mb] : 1.0f;
+                const float f = FACTOR ? factor[mb] : 1.0f;
                 u32x4 out;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
                     const int b = m / a.branches->n_tok, t = m - b * a.branches->n_tok;
                     dst = kv_slot_bf16(a.branches->kv[b], a.layer, which - 1, head, a.n_heads, a.branches->pos0[b] + t);
                 }
-                const float f = ROW_SCALE ? factor[mb] : 1.0f;
+                const float f = FACTOR ? factor[mb] : 1.0f;
                 u32x4 lo, hi;
                 if (which == 2) {
 #pragma unroll
@@ -479,7 +480,7 @@ int div_up(int x, int y) { return (x + y - 1) / y; }
 // Row blocks of the tile for a chunk of M tokens.
 int pick_row_blocks(int M) { return M > 128 ? 8 : M > 64 ? 4 : 2; }
 
-template <int BMB, int NB, int WM, int WN, int EPI>
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
 hipError_t launch(GemmArgs a, hipStream_t s) {
     a.n_stride = 32 * NB;
     a.n_tiles = div_up(a.N, a.n_stride);
@@ -487,13 +488,13 @@ hipError_t launch(GemmArgs a, hipStream_t s) {
     a.kt_per_split = a.K / G_BK / a.splits;
     const int grid = a.m_tiles * a.n_tiles * a.splits;
     using S = Shape<BMB, NB, WM, WN>;
-    hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI>), dim3(grid), dim3(S::THREADS), S::LDS_BYTES, s, a);
+    hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR>), dim3(grid), dim3(S::THREADS), S::LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
-template <int BMB, int NB, int WM, int WN, int EPI>
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
 hipError_t configure_one() {
-    return hipFuncSetAttribute((const void*)gemm_bf16<BMB, NB, WM, WN, EPI>,
+    return hipFuncSetAttribute((const void*)gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR>,
                                hipFuncAttributeMaxDynamicSharedMemorySize, Shape<BMB, NB, WM, WN>::LDS_BYTES);
 }
 
@@ -515,12 +516,19 @@ hipError_t configure_one() {
     X(1, 3, 1, 3, EPI_SWIGLU) X(1, 4, 1, 4, EPI_SWIGLU) X(2, 3, 2, 3, EPI_SWIGLU) X(4, 6, 4, 1, EPI_SWIGLU) \
     X(2, 6, 2, 3, EPI_SWIGLU)                                                                              \
     X(4, 4, 4, 1, EPI_PARTIAL) X(2, 4, 2, 2, EPI_PARTIAL) X(2, 2, 2, 2, EPI_PARTIAL) X(4, 2, 4, 1, EPI_PARTIAL)
+// Batches of more than 64 rows of branches of up to 16 tokens: rows with a factor (see FACTOR; the tiles of up to 64 rows
+// all take one)
+#define JUP_GEMM_FACTOR_SHAPES(X) \
+    X(4, 2, 4, 1, EPI_QKV) X(4, 3, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU)
 
 hipError_t gemm_configure() {
     hipError_t e = hipSuccess;
     auto acc = [&](hipError_t r) { if (e == hipSuccess) e = r; };
-#define X(BMB, NB, WM, WN, EPI) acc(configure_one<BMB, NB, WM, WN, EPI>());
+#define X(BMB, NB, WM, WN, EPI) acc(configure_one<BMB, NB, WM, WN, EPI, BMB <= 2 && EPI != EPI_PARTIAL>());
     JUP_GEMM_SHAPES(X)
+#undef X
+#define X(BMB, NB, WM, WN, EPI) acc(configure_one<BMB, NB, WM, WN, EPI, true>());
+    JUP_GEMM_FACTOR_SHAPES(X)
 #undef X
     return e;
 }
@@ -710,21 +718,36 @@ template <int EPI>
 hipError_t dispatch(TileShape t, const GemmArgs& a, hipStream_t s) {
 #define X(BMB, NB, WM, WN, E)                                                         \
     if constexpr (E == EPI)                                                           \
-        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN) return launch<BMB, NB, WM, WN, EPI>(a, s);
+        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN) return launch<BMB, NB, WM, WN, EPI, BMB <= 2 && EPI != EPI_PARTIAL>(a, s);
     JUP_GEMM_SHAPES(X)
 #undef X
     return hipErrorInvalidConfiguration;  // a shape the pick functions name but the list above does not hold
+}
+
+// 65 to 128 rows with a factor: the tile that rows without one take.
+template <int EPI>
+hipError_t dispatch_factor(const GemmArgs& a, hipStream_t s) {
+    if (a.M > kMaxSplitRows) return hipErrorInvalidValue;
+    const TileShape t = EPI == EPI_QKV ? pick_qkv(a.M, a.N, a.K, false) : pick_swiglu(a.M, a.N, a.K, false);
+#define X(BMB, NB, WM, WN, E)                                                         \
+    if constexpr (E == EPI)                                                           \
+        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN) return launch<BMB, NB, WM, WN, EPI, true>(a, s);
+    JUP_GEMM_FACTOR_SHAPES(X)
+#undef X
+    return hipErrorInvalidConfiguration;
 }
 
 }  // namespace
 
 hipError_t launch_gemm_qkv(GemmArgs a, hipStream_t s) {
     a.splits = 1;
+    if (a.row_factor && a.M > 64) return dispatch_factor<EPI_QKV>(a, s);
     return dispatch<EPI_QKV>(pick_qkv(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 
 hipError_t launch_gemm_swiglu(GemmArgs a, hipStream_t s) {
     a.splits = 1;
+    if (a.row_factor && a.M > 64) return dispatch_factor<EPI_SWIGLU>(a, s);
     return dispatch<EPI_SWIGLU>(pick_swiglu(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 

@@ -1,4 +1,4 @@
-// Projections back to d_model (output and down projection) for chunks of up to 64 rows.
+// Projections back to d_model (output and down projection) for chunks of up to 16 rows and for batches of such chunks.
 //
 // A decode-sized layer is a chain of short launches, and two of the seven did nothing but add up the K splits of these
 // projections and normalise a handful of rows: 4 - 5 us each for a few hundred KB.  Up to 16 rows project_rows finishes
@@ -13,8 +13,9 @@
 //     The rows of A come from L2, 16 bytes per lane; rows past the chunk repeat its last one.
 //   * At 16 rows a workgroup reads as many bytes of A as of bf16 weights, at 64 rows it would be four times as many and the
 //     path from L2 bounds it (measured: O / down 14.9 / 34 us against 9.1 / 20.5 us + 4.8 us for each reduce + norm pass).
-//     17 to 64 rows keep K splits over workgroups, partial sums and the reduce + norm pass: with bf16 weights project_split
-//     below, 64 x 64 tiles through LDS; with 4-bit codes the kernel of w4_gemm.hip.
+//     More rows (branches of up to 16 tokens in one call) keep K splits over workgroups, partial sums and the reduce + norm
+//     pass: with bf16 weights, up to 128 rows, project_split below, tiles of 64 or 128 rows x 64 features through LDS; with
+//     4-bit codes the kernel of w4_gemm.hip.
 //   * Either way the MFMA, the ranges of K a sum is made of and the order they are added in are the same, whatever the row
 //     count: a branch computes the same bits alone and batched with others.  bf16: MFMA 16x16x32, eight ranges, those of a
 //     split added up first.  4-bit: the eight waves of every split.
@@ -210,13 +211,22 @@ __global__ __launch_bounds__(64 * kRanges) void project_rows(const RowArgs a) {
     if ((tid & 3) == 0) a.ssq[(size_t)row * (a.N / kRowCols) + blockIdx.x] = ss;
 }
 
-// Partial sums of up to 64 rows, bf16 weights: a workgroup owns 64 rows x 64 features and the 8 / splits consecutive K ranges
-// of its split; GROUPS = 2 groups of four waves take one half of them each (a wave 32 rows x 32 features) and add up at the
-// end.  A group brings rows and weights through a ring of its own in LDS, in pairs of K steps (16 KB: the 32-row blocks of
-// the tiled layout are LDS images), four pairs deep, with one barrier per pair.  The launch is bound by streaming the weights
-// as long as a pair's chain of wait, fragment reads and products stays short: with one group, whose chain nothing covers, the
-// O / down launches took 9.9 / 23 us at 64 rows of the 7B shapes.
-constexpr int kPairBytes = 16384, kPairs = 4;
+// Partial sums of batches, bf16 weights: a workgroup owns 32 RB rows x 64 features and the 8 / splits consecutive K ranges
+// of its split; GROUPS = 2 groups of four waves take one half of them each (a wave 16 RB rows x 32 features) and add up at the
+// end.  A group brings rows and weights through rings of its own in LDS, in pairs of K steps (the 32-row blocks of the tiled
+// layout are LDS images), with one barrier per pair: 16 KB per pair and four pairs deep for up to 64 rows (RB = 2), 24 KB and
+// three deep for more (RB = 4).  The launch is bound by streaming the weights as long as a pair's chain of wait, fragment reads
+// and products stays short: with one group, whose chain nothing covers, the O / down launches took 9.9 / 23 us at 64 rows of
+// the 7B shapes.  (RB = 4 with rows and weights in rings of their own, copied by different waves: rows one pair ahead and
+// weights five 16 x 5 rows of two layers 264 -> 288 us, two and three ahead no difference.)
+template <int RB>
+struct SplitRing {
+    static constexpr int STEP_BYTES = (RB + 2) * 2048;  // a K step: RB blocks of rows, two of weights
+    static constexpr int PAIR_BYTES = 2 * STEP_BYTES;
+    static constexpr int PAIRS = RB == 2 ? 4 : 3;
+    static constexpr int LOADS = 2 * (RB / 2 + 1);      // per wave and pair
+    static constexpr int BYTES = PAIRS * PAIR_BYTES;    // per group
+};
 
 // 1 KB per wave into LDS; NT: the weights, which are read once
 template <bool NT>
@@ -227,8 +237,9 @@ __device__ __forceinline__ void load_unit(const char* uniform_base, unsigned lan
     else load_to_lds_16(uniform_base, lane_offset, lds);
 }
 
-template <int GROUPS>
+template <int GROUPS, int RB>
 __global__ __launch_bounds__(256 * GROUPS) void project_split(const RowArgs a) {
+    using R = SplitRing<RB>;
     extern __shared__ __attribute__((aligned(1024))) unsigned char ring[];
     const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
     const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -240,59 +251,65 @@ __global__ __launch_bounds__(256 * GROUPS) void project_split(const RowArgs a) {
     const int first = range_start(range), count = count_of(group);  // K steps of this group
     const int pairs = (count + 1) / 2;
     const int rounds = GROUPS == 1 ? pairs : (max(count_of(0), count_of(1)) + 1) / 2;  // (the groups share the barriers)
-    // A K step in LDS: two 2 KB blocks of rows, two of weights.  Wave w copies its KB number w of either: half w & 1 of row
-    // block w >> 1 and the same of the weights' blocks.  Row blocks past the chunk repeat its last one.
-    const char* a_src = (const char*)a.A + ((size_t)min(wave >> 1, (a.M - 1) >> 5) * KT + first) * 2048 + (wave & 1) * 1024;
+    // A K step in LDS: RB 2 KB blocks of rows, two of weights.  Wave w copies half w & 1 of row blocks w >> 1, (w >> 1) + 2, ..
+    // and the same half of weight block w >> 1.  Row blocks past the chunk repeat its last one.
+    const char* a_src[RB / 2];
+#pragma unroll
+    for (int i = 0; i < RB / 2; ++i)
+        a_src[i] = (const char*)a.A + ((size_t)min((wave >> 1) + 2 * i, (a.M - 1) >> 5) * KT + first) * 2048 + (wave & 1) * 1024;
     const char* w_src = (const char*)a.W + ((size_t)(blockIdx.x * 2 + (wave >> 1)) * KT + first) * 2048 + (wave & 1) * 1024;
-    unsigned char* mine = ring + group * kPairs * kPairBytes;
+    unsigned char* mine = ring + group * R::BYTES;
     const unsigned ring0 = __builtin_amdgcn_readfirstlane(lds_byte_address(mine));
-    auto issue = [&](int pair) __attribute__((always_inline)) {  // four loads per wave
-        const unsigned dst = ring0 + (pair & (kPairs - 1)) * kPairBytes + wave * 1024;
+    auto issue = [&](int pair) __attribute__((always_inline)) {  // R::LOADS loads per wave
+        const unsigned dst = ring0 + (unsigned)pair % R::PAIRS * R::PAIR_BYTES + wave * 1024;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const size_t at = (size_t)min(2 * pair + h, count - 1) * 2048;
-            load_unit<false>(uniform_ptr(a_src + at), lane * 16, dst + h * 8192);
-            load_unit<true>(uniform_ptr(w_src + at), lane * 16, dst + h * 8192 + 4096);
+#pragma unroll
+            for (int i = 0; i < RB / 2; ++i)
+                load_unit<false>(uniform_ptr(a_src[i] + at), lane * 16, dst + h * R::STEP_BYTES + i * 4096);
+            load_unit<true>(uniform_ptr(w_src + at), lane * 16, dst + h * R::STEP_BYTES + RB * 2048);
         }
     };
-    for (int p = 0; p < kPairs - 1 && p < pairs; ++p) issue(p);
+    for (int p = 0; p < R::PAIRS - 1 && p < pairs; ++p) issue(p);
 
     // fragment of 16 rows: chunk q of row r of the 16-row half
     unsigned off[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) off[h] = 2 * (unsigned)tiled_offset(16 * h + r, q, 1);
-    f32x4 acc[2][2], sum[2][2];
+    f32x4 acc[2][RB], sum[2][RB];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < RB; ++j) acc[i][j] = sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto close_range = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < RB; ++j) {
                 sum[i][j] += acc[i][j];
                 acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
     };
     int boundary = range_start(range + 1) - first;
     for (int p = 0; p < rounds; ++p) {
-        // pair p has landed when at most the loads of the pairs behind it are in flight (the last of them: p + 2)
-        if (p + 2 < pairs) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else if (p + 1 < pairs) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        // pair p has landed when at most the loads of the pairs behind it are in flight (PAIRS - 2 of them, fewer at the end)
+        if (R::PAIRS > 3 && p + 2 < pairs) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * R::LOADS) : "memory");
+        else if (p + 1 < pairs) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(R::LOADS) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();  // (every wave has read pair p - 1, whose slot is refilled now)
         if (p >= pairs) continue;
-        if (p + kPairs - 1 < pairs) issue(p + kPairs - 1);
-        const unsigned char* slot = mine + (p & (kPairs - 1)) * kPairBytes;
-        bf16x8 x[2][2], w[2][2];
+        if (p + R::PAIRS - 1 < pairs) issue(p + R::PAIRS - 1);
+        const unsigned char* slot = mine + (unsigned)p % R::PAIRS * R::PAIR_BYTES;
+        bf16x8 x[2][RB], w[2][2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                x[h][i] = *(const bf16x8*)(slot + h * 8192 + wm * 2048 + off[i]);
-                w[h][i] = *(const bf16x8*)(slot + h * 8192 + 4096 + wn * 2048 + off[i]);
-            }
+            for (int j = 0; j < RB; ++j)
+                x[h][j] = *(const bf16x8*)(slot + h * R::STEP_BYTES + ((wm * RB + j) >> 1) * 2048 + off[j & 1]);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) w[h][i] = *(const bf16x8*)(slot + h * R::STEP_BYTES + (RB + wn) * 2048 + off[i]);
+        }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             if (2 * p + h < count) {
@@ -304,7 +321,7 @@ __global__ __launch_bounds__(256 * GROUPS) void project_split(const RowArgs a) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(w[h][i], x[h][j], acc[i][j]);
+                    for (int j = 0; j < RB; ++j) acc[i][j] = mfma16(w[h][i], x[h][j], acc[i][j]);
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave has read the pair
@@ -315,17 +332,17 @@ __global__ __launch_bounds__(256 * GROUPS) void project_split(const RowArgs a) {
         f32x4* other = (f32x4*)ring;
         const int t = threadIdx.x & 255;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (group == 1) other[i * 256 + t] = sum[i >> 1][i & 1];
+        for (int i = 0; i < 2 * RB; ++i)
+            if (group == 1) other[i * 256 + t] = sum[i / RB][i % RB];
         __syncthreads();
         if (group == 1) return;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sum[i >> 1][i & 1] += other[i * 256 + t];
+        for (int i = 0; i < 2 * RB; ++i) sum[i / RB][i % RB] += other[i * 256 + t];
     }
     float* dst = a.partial + (size_t)split * a.M * a.N + blockIdx.x * 64 + wn * 32 + 4 * q;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int row = wm * 32 + 16 * j + r;
+    for (int j = 0; j < RB; ++j) {
+        const int row = wm * 16 * RB + 16 * j + r;
         if (row >= a.M) continue;
 #pragma unroll
         for (int i = 0; i < 2; ++i) *(f32x4*)(dst + (size_t)row * a.N + 16 * i) = sum[i][j];
@@ -347,8 +364,29 @@ int row_splits(int N) {
     return splits;
 }
 
+// 128 rows as long as a workgroup walks a quarter of K or less.  Measured against the partial-sum tiles that any other chunk
+// takes (without the equal bits), batches of 72 to 128 rows, two layers: d = 1024 .. 4096 2 - 9 % faster (with the rest of the
+// call), d = 5120 .. 8192, where two splits fill the chip, 3 - 5 % slower.
+int max_split_rows(int N) { return row_splits(N) >= 4 ? kMaxSplitRows : 64; }
+
+namespace {
+template <int GROUPS, int RB>
+hipError_t configure_split() {
+    return hipFuncSetAttribute((const void*)project_split<GROUPS, RB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               GROUPS * SplitRing<RB>::BYTES);
+}
+
+template <int GROUPS, int RB>
+void run_split(const RowArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL((project_split<GROUPS, RB>), dim3(a.N / 64, a.splits), dim3(256 * GROUPS), GROUPS * SplitRing<RB>::BYTES, s, a);
+}
+}  // namespace
+
 hipError_t rows_configure() {
-    return hipFuncSetAttribute((const void*)project_split<2>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kPairs * kPairBytes);
+    hipError_t e = configure_split<1, 2>();
+    if (e == hipSuccess) e = configure_split<1, 4>();
+    if (e == hipSuccess) e = configure_split<2, 2>();
+    return e == hipSuccess ? configure_split<2, 4>() : e;
 }
 
 hipError_t launch_project_rows(bool w4, const RowArgs& a, hipStream_t s) {
@@ -360,9 +398,9 @@ hipError_t launch_project_rows(bool w4, const RowArgs& a, hipStream_t s) {
 
 hipError_t launch_project_split(const RowArgs& a, hipStream_t s) {
     if (bad(false, a, kMaxSplitRows)) return hipErrorInvalidValue;
-    if (a.splits < kRanges)
-        hipLaunchKernelGGL(project_split<2>, dim3(a.N / 64, a.splits), dim3(512), 2 * kPairs * kPairBytes, s, a);
-    else hipLaunchKernelGGL(project_split<1>, dim3(a.N / 64, a.splits), dim3(256), kPairs * kPairBytes, s, a);
+    const bool two = a.splits < kRanges;  // one range per split leaves nothing to deal to a second group
+    if (a.M <= 64) two ? run_split<2, 2>(a, s) : run_split<1, 2>(a, s);
+    else two ? run_split<2, 4>(a, s) : run_split<1, 4>(a, s);
     return hipGetLastError();
 }
 

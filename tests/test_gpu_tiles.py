@@ -159,3 +159,29 @@ def test_attention_of_peaked_rows_returns_the_value(n, one_call):
     v = p.kv_gpu()[0, 1].transpose(1, 0, 2).reshape(4 * n, d)
     assert np.abs(v).max() > 1.0
     assert np.array_equal(y, v)
+
+
+@pytest.mark.parametrize("d_model,n_heads,d_ffn", [(256, 2, 128), (2304, 18, 1408), (4096, 32, 11008), (5120, 40, 3456)])
+@pytest.mark.parametrize("dtype", ["bf16", "w4"])
+def test_batched_branches_of_more_than_64_rows_have_the_bits_they_have_alone(dtype, d_model, n_heads, d_ffn):
+    """Batches of 65 to 128 rows (bf16 stages wider than 4096: up to 64) of branches of up to 16 tokens (row projections alone,
+    partial sums of the same ranges batched, the norm's factor on either side); 4-bit codes at any row count and branch length."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=n_heads, d_ffn=d_ffn, n_layers=2)
+    p = Pair(cfg, dtype, seed=d_model, max_positions=160, max_chunk_tokens=320)
+    p.gpu_chunk(p.hidden(20), 0)
+    cases = [(13, 5), (16, 5), (5, 16), (6, 16), (7, 14), (8, 16), (16, 8)]
+    if dtype == "bf16" and d_model > 4096:
+        cases = [(12, 5), (8, 8), (4, 16)]
+    codes = [(9, 16), (16, 16), (4, 17), (3, 33), (4, 64), (5, 64), (2, 65), (2, 130)]
+    for branches, n in cases + (codes if dtype == "w4" else []):
+        h = p.hidden(branches * n, tag=100 + n).reshape(branches, n, d_model)
+        alone = [p.gpu_chunk(h[b], 20) for b in range(branches)]
+        bits = p.kv.view()[:, :, :, 20:20 + n].clone()   # of the last branch
+        kvs = [p.kv.fork(20, 20 + n) for _ in range(branches)]
+        y = p.stage.prefill_branches(torch.from_numpy(h.reshape(-1, d_model)).to("cuda:0", p.td), n, [20] * branches, kvs)
+        y = y.float().cpu().numpy().reshape(branches, n, d_model)
+        assert np.array_equal(y, np.stack(alone)), (branches, n)
+        assert torch.equal(kvs[-1].view(), bits), (branches, n)
+        for kv in kvs:
+            kv.destroy()
