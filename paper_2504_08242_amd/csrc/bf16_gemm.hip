@@ -613,7 +613,6 @@ int splits_for(int M, int N, int K, int nb) {
 // with 43 stages per workgroup, keeps the wide tile: 28.3 vs 29.5 us).
 int gemm_partial_col_blocks(int M, int N, int K) {
     const int bmb = pick_row_blocks(M);
-    if (bmb >= 8) return 4;
     const int stages_wide = K / G_BK / splits_for(M, N, K, 4);
     return stages_wide < (bmb == 2 ? 64 : 32) ? 2 : 4;
 }
@@ -664,14 +663,13 @@ TileShape pick_qkv(int M, int N, int K, bool shared_gpu) {
     if (shared_gpu && bmb == 4) return {4, 3, 4, 1};
     if (bmb == 2) return {2, 2, 2, 2};
     if (bmb == 4) return {4, 2, 4, 1};
-    // (1024 rows stay on 256 x 96 tiles, the documented tiling of that chunk length)
-    if (!shared_gpu && M != 1024) return pick_tall(EPI_QKV, M, N, K).t;
+    if (!shared_gpu) return pick_tall(EPI_QKV, M, N, K).t;
     static const int cands[] = {1, 2, 3};
     const int nb = pick_blocks(M, N, cands, 3);
     // Beside another chunk's kernels (overlapped multi-chunk call) half as many tiles of twice the width do the
     // same work in a quarter less CU time, and the other chunk uses the CUs they leave free: 76 us instead of 59 us
-    // for this launch alone, but +1.7 % for the 4 x 512 prompt.  Alone on the chip the narrow tile wins (-6 %).
-    if (nb == 3 && shared_gpu && M > 256) return {8, 6, 4, 2};
+    // for this launch alone, but +1.7 % for the 4 x 512 prompt.
+    if (nb == 3 && M > 256) return {8, 6, 4, 2};
     if (nb == 3) return {8, 3, 8, 1};  // 8 waves of 32 x 96: measured 1.3 % faster than 4 of 64 x 96
     if (nb == 2) return {8, 2, 4, 1};
     return {8, 1, 4, 1};

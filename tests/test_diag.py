@@ -103,8 +103,11 @@ def test_kernel_name_reports_the_documented_tile_policy():
         ("gemm_qkv", 128, False): "gemm_bf16<4,2,4,1,0>", ("gemm_gate_up", 128, False): "gemm_bf16<4,3,4,1,2>",
         ("gemm_qkv", 64, False): "gemm_bf16<2,2,2,2,0>", ("gemm_gate_up", 64, False): "gemm_bf16<2,3,2,3,2>",
         ("gemm_gate_up", 5, False): "gemm_bf16<1,3,1,3,2>", ("gemm_qkv", 5, False): "gemm_bf16<2,2,2,2,0>",
-        ("gemm_gate_up", 1024, False): "gemm_bf16<8,6,4,2,2>", ("gemm_qkv", 1024, False): "gemm_bf16<8,3,8,1,0>",
+        ("gemm_gate_up", 1024, False): "gemm_bf16<8,6,4,2,2>", ("gemm_qkv", 1024, False): "gemm_bf16<8,6,4,2,0>",
     }
     got = {k: stage.kernel_name(K[k[0]], k[1], k[2]) for k in want}
     assert got == want, {k: (got[k], want[k]) for k in want if got[k] != want[k]}
+    for kernel in ("gemm_qkv", "gemm_o", "gemm_gate_up", "gemm_down"):   # no row count is a case of its own
+        for rows in range(256, 2049, 256):
+            assert stage.kernel_name(K[kernel], rows) == stage.kernel_name(K[kernel], rows - 1), (kernel, rows)
     stage.destroy()
