@@ -276,13 +276,14 @@ JUP_API jup_status_t jup_stage_prefill_chunk_static(jup_stage_t *stage, const vo
  *   chunk_tokens  HOST array [n_chunks], each 0 .. the stage's max_chunk_tokens
  *   hidden_out    [sum of chunk_tokens, d_model]; may be the same buffer as hidden_in
  * After jup_stage_enable_overlap() a JUP_BF16 stage (or a JUP_BF16_W4 one with its bf16 copy, all chunks longer than 64
- * tokens) computes consecutive chunks of up to 1024 tokens together, in groups of up to 2048 tokens as far as the scratch
- * handed over there reaches: the weights of a layer are then read once per group.  Longer chunks overlap on the GPU
- * instead: they go round n_lanes lanes (a stream plus a scratch buffer each; lane 0 is `stream` with the stage's own
- * workspace), and a chunk waits, per layer, only for the cache appends of the chunks before it before its own attention
- * (the paper fills the stages of a pipeline with sub-sequences in the same way, across devices); all enabled lanes when
- * their number is a multiple of four, else two.  On return all
- * work is ordered before whatever is enqueued on `stream` next.  Without jup_stage_enable_overlap(), and in check
+ * tokens) computes consecutive chunks of up to 1024 tokens (896 with two lanes) together, in groups of up to 2048 tokens
+ * as far as the scratch handed over there reaches: the weights of a layer are then read once per group.  If a chunk is
+ * longer, or the groups would hold fewer than two chunks on average, the chunks overlap on the GPU instead: they go
+ * round n_lanes lanes (a stream plus a scratch buffer each; lane 0 is `stream` with the stage's own workspace), and a
+ * chunk waits, per layer, only for the cache appends of the chunks before it before its own attention (the paper fills the
+ * stages of a pipeline with sub-sequences in the same way, across devices); all enabled lanes when the number of chunks is
+ * a multiple of four, else two.  On return all work is ordered before whatever is enqueued on `stream` next.  Without
+ * jup_stage_enable_overlap(), and in check
  * mode, the chunks simply run one after the other on `stream`.
  * Errors: as jup_stage_prefill_chunk(); every chunk is validated before anything is enqueued.
  */

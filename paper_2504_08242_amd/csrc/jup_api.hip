@@ -132,6 +132,50 @@ WorkspaceLayout workspace_layout(const jup_stage_config_t& c, int32_t T, bool br
     return w;
 }
 
+// Chunks of up to 1024 (two lanes: 896) tokens are computed TOGETHER: consecutive ones form groups of up to 2048 rows that go through
+// the layers as one chunk.  The causal mask makes the two the same sums (a query sees the cached prefix and the rows
+// before it, whether an earlier call or its own put them there), the weights of a layer are read once per group, and
+// the projections get tiles of full height.  Measured on 2 layers of the 7B shapes, four lanes -> groups: 8 x 64
+// tokens 1300 -> 483 us, 8 x 256 2541 -> 1655, 4 x 512 1775 -> 1600, 4 x 768 2999 -> 2572, 2 x 1024 1728 -> 1603,
+// 4 x 1024 3370 -> 3372; 13B shapes, 4 x 512 2990 -> 2445.  Longer chunks fill the chip by themselves and keep the
+// lanes (2 x 2048: 3229 on lanes, 3374 one after the other).  So do chunks whose scratch does not fit together, where a group
+// would be one chunk run alone (two lanes, max_chunk_tokens = 1024: 2 x 1024 1740 us in groups of one, 1589 on lanes, 4 x 1024
+// 3647 and 3296; 13B shapes 2 x 1024 2573 and 2472).  With two chunks to a group, two lanes -> groups: 2 x 896 1537 -> 1494 us,
+// 4 x 896 3174 -> 3126, 2 x 960 1567 -> 1566, 4 x 960 3252 -> 3276, 4 x 900 3080 -> 3134, 700, 1024, 700, 1024 2909 -> 3012:
+// groups up to 896 tokens; four lanes -> groups: 4 x 900 3152 -> 3134, 4 x 960 3364 -> 3278, the four above 3062 -> 3010.
+ChunkGroups plan_chunk_groups(const jup_stage_config_t& c, const int32_t* chunk_tokens, int32_t n_chunks, int32_t n_lanes,
+                              size_t room) {
+    ChunkGroups g{};
+    int64_t total = 0;
+    int32_t longest = 0, busy = 0, groups = 0;
+    for (int i = 0; i < n_chunks; ++i) {
+        total += chunk_tokens[i];
+        busy += chunk_tokens[i] > 0;
+        longest = chunk_tokens[i] > longest ? chunk_tokens[i] : longest;
+    }
+    if (longest > (n_lanes > 2 ? 1024 : 896) || busy < 2) return g;
+    // the most rows whose scratch fits (it grows with the rows)
+    int32_t lo = longest, hi = (int32_t)(total < 2048 ? total : 2048);  // (one chunk fits by construction)
+    while (lo < hi) {
+        const int32_t mid = lo + (hi - lo + 1) / 2;
+        if (workspace_layout(c, mid, false).total <= room) lo = mid;
+        else hi = mid - 1;
+    }
+    const int64_t n = (total + lo - 1) / lo;
+    g.most = lo;
+    g.even = (int32_t)((total + n - 1) / n);
+    for (int i = 0, rows = 0; i <= n_chunks; ++i) {
+        const int32_t next = i < n_chunks ? chunk_tokens[i] : 0;
+        if (g.closes(rows, next) || (i == n_chunks && rows > 0)) {
+            ++groups;
+            rows = 0;
+        }
+        rows += next;
+    }
+    if (2 * groups > busy + 1) g.most = 0;
+    return g;
+}
+
 }  // namespace jup
 
 extern "C" {
@@ -700,21 +744,10 @@ jup_status_t jup_stage_prefill_chunks(jup_stage_t* stage, const void* hidden_in,
         return JUP_OK;
     }
 
-    // Chunks of up to 1024 tokens are computed TOGETHER: consecutive ones form groups of up to 2048 rows that go through
-    // the layers as one chunk.  The causal mask makes the two the same sums (a query sees the cached prefix and the rows
-    // before it, whether an earlier call or its own put them there), the weights of a layer are read once per group, and
-    // the projections get tiles of full height.  Measured on 2 layers of the 7B shapes, four lanes -> groups: 8 x 64
-    // tokens 1300 -> 483 us, 8 x 256 2541 -> 1655, 4 x 512 1775 -> 1600, 4 x 768 2999 -> 2572, 2 x 1024 1728 -> 1603,
-    // 4 x 1024 3370 -> 3372; 13B shapes, 4 x 512 2990 -> 2445.  Longer chunks fill the chip by themselves and keep the
-    // lanes below (2 x 2048: 3229 on lanes, 3374 one after the other).  The group's scratch is the lanes' buffer.
-    int longest = 0;
-    for (int c = 0; c < n_chunks; ++c) longest = chunk_tokens[c] > longest ? chunk_tokens[c] : longest;
-    if (longest <= 1024) {
-        const size_t room = (size_t)(o->n_lanes - 1) * jup_stage_workspace_bytes(&stage->cfg, stage->max_chunk_tokens);
-        int most = (int)(total < 2048 ? total : 2048);
-        while (most > longest && jup::workspace_layout(stage->cfg, most, false).total > room) --most;
-        if (most < longest) most = longest;  // (one chunk fits by construction)
-        const long groups = (total + most - 1) / most, even = (total + groups - 1) / groups;
+    // Together in groups (the group's scratch is the lanes' buffer), or round the lanes.
+    const size_t room = (size_t)(o->n_lanes - 1) * jup_stage_workspace_bytes(&stage->cfg, stage->max_chunk_tokens);
+    const jup::ChunkGroups g = jup::plan_chunk_groups(stage->cfg, chunk_tokens, n_chunks, o->n_lanes, room);
+    if (g.most > 0) {
         jup_stage view = *stage;
         view.overlap = nullptr;
         view.workspace = o->workspace[1];
@@ -724,7 +757,7 @@ jup_status_t jup_stage_prefill_chunks(jup_stage_t* stage, const void* hidden_in,
         const int32_t len_before = kv->len;
         for (int c = 0; c <= n_chunks; ++c) {
             const int n = c < n_chunks ? chunk_tokens[c] : 0;
-            if (rows > 0 && (c == n_chunks || rows + n > most || rows >= even)) {
+            if (g.closes(rows, n) || (c == n_chunks && rows > 0)) {
                 view.wl = jup::workspace_layout(stage->cfg, rows, false);
                 view.max_chunk_tokens = rows;
                 rc = prefill_one(me, &view, in, rows, pos, nullptr, false, kv, out, stream);

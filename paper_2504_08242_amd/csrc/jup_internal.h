@@ -53,6 +53,16 @@ struct WorkspaceLayout {
 // branches: the workspace also serves jup_stage_prefill_branches (more query blocks per launch: more scratch)
 WorkspaceLayout workspace_layout(const jup_stage_config_t& c, int32_t T, bool branches = true);
 
+// Multi-chunk call with overlap enabled: consecutive chunks are computed together in groups of up to `most` rows, a group
+// being closed as soon as it has `even` of them.  most = 0: not worth it, the chunks go round the n_lanes lanes.  room: bytes
+// of scratch a group may use (that of the lanes but the first).
+struct ChunkGroups {
+    int32_t most, even;
+    bool closes(int32_t rows, int32_t next) const { return rows > 0 && (rows + next > most || rows >= even); }
+};
+ChunkGroups plan_chunk_groups(const jup_stage_config_t& c, const int32_t* chunk_tokens, int32_t n_chunks, int32_t n_lanes,
+                              size_t room);
+
 // Where the attention and append kernels find a cache: positions < n_shared live in the parent's
 // buffer (stride parent_cap), the rest in the own buffer at slot (position - n_shared).
 struct KvView {

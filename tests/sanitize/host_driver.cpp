@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "jupiter_plan.h"
+#include "jup_internal.h"
 #include "jupiter_stage.h"
 
 #define EXPECT(cond)                                                                  \
@@ -149,7 +150,45 @@ static void planner() {
     EXPECT(jup_seq_plan_create(xs, 3, ys, 2, q, 8, 65, 64, &plan) == JUP_EINVAL);
 }
 
+// How a multi-chunk call with overlap enabled deals its chunks: groups where they hold about two chunks each, else lanes.
+static void chunk_groups() {
+    jup_stage_config_t c7 = cfg_7b(JUP_BF16), c13 = c7, wide = c7, small = c7;
+    c13.d_model = 5120; c13.n_heads = 40; c13.d_ffn = 13824;
+    wide.d_model = 8192; wide.n_heads = 64; wide.d_ffn = 28672;
+    small.d_model = 2048; small.n_heads = 16; small.d_ffn = 5632;
+    for (const jup_stage_config_t& c : {c7, c13, wide, small}) {
+        auto room = [&](int lanes, int limit) { return (size_t)(lanes - 1) * jup_stage_workspace_bytes(&c, limit); };
+        auto plan = [&](std::vector<int32_t> chunks, int lanes, int limit) {
+            const jup::ChunkGroups g = jup::plan_chunk_groups(c, chunks.data(), (int32_t)chunks.size(), lanes, room(lanes, limit));
+            if (g.most > 0) {  // the scratch of a group fits, that of one more row does not (or no group could use it)
+                int64_t total = 0;
+                for (int n : chunks) total += n;
+                EXPECT(jup::workspace_layout(c, g.most, false).total <= room(lanes, limit));
+                EXPECT(g.most == 2048 || g.most == total || jup::workspace_layout(c, g.most + 1, false).total > room(lanes, limit));
+                EXPECT(g.even >= 1 && g.even <= g.most);
+            }
+            return g;
+        };
+        // two lanes: the other lane's scratch does not hold two such chunks, or lanes are faster
+        EXPECT(plan({1024, 1024}, 2, 1024).most == 0 && plan({1024, 1024, 1024, 1024}, 2, 1024).most == 0);
+        EXPECT(plan({700, 1024, 0, 700, 1024}, 2, 1024).most == 0 && plan({1024, 1024}, 2, 2048).most == 0);
+        EXPECT(plan({896, 896}, 2, 1024).most == 1792 && plan({897, 897}, 2, 1024).most == 0);
+        EXPECT(plan({40, 40}, 2, 64).most == 80 && plan({800, 800, 64}, 2, 800).most > 0);
+        // more lanes
+        EXPECT(plan({1024, 1024}, 4, 1024).most == 2048 && plan({1024, 1024}, 3, 1024).most == 2048);
+        EXPECT(plan({700, 1024, 0, 700, 1024}, 3, 1024).most == 2048);
+        EXPECT(plan({1024, 1024, 64}, 3, 1024).most == 2048);
+        EXPECT(plan({512, 512, 512, 512}, 4, 512).most >= 1024);
+        EXPECT(plan({1025, 30, 1100, 5}, 4, 1100).most == 0);             // longer than 1024: lanes
+        EXPECT(plan({64, 0, 0}, 4, 64).most == 0 && plan({0, 0}, 4, 64).most == 0);
+        const jup::ChunkGroups g = plan({300, 300, 300, 300, 300, 300, 300, 300}, 4, 1024);
+        EXPECT(g.most == 2048 && g.even == 1200);                         // two groups of four, not six and two
+        EXPECT(!g.closes(0, 300) && !g.closes(900, 300) && g.closes(1200, 300) && g.closes(1900, 300));
+    }
+}
+
 int main() {
+    chunk_groups();
     stage_and_cache_validation();
     planner();
     std::printf("host_driver ok\n");

@@ -185,3 +185,41 @@ def test_batched_branches_of_more_than_64_rows_have_the_bits_they_have_alone(dty
         assert torch.equal(kvs[-1].view(), bits), (branches, n)
         for kv in kvs:
             kv.destroy()
+
+
+@pytest.mark.parametrize("d_model,n_heads,d_ffn,dtype,n_lanes,chunks,tiles", [
+    # two chunks a second lane's scratch cannot hold together: side by side
+    (1024, 8, 2816, "bf16", 2, [1024, 1024, 1000], {}),
+    # short chunks between long ones: the tiles of short chunks that share the GPU
+    (1024, 8, 2816, "bf16", 4, [1100, 64, 100, 300, 1050, 33, 128, 5],
+     {("gemm_gate_up", 64): "2,6,2,3", ("gemm_gate_up", 100): "4,6,4,1", ("gemm_qkv", 100): "4,3,4,1", ("gemm_o", 33): "2,4,2,2",
+      ("gemm_down", 128): "4,4,4,1", ("gemm_qkv", 1100): "8,6,4,2", ("gemm_o", 300): "8,8,4,2"}),
+    (256, 2, 1024, "bf16", 3, [2065, 129, 1030], {("gemm_qkv", 129): "8,1,4,1", ("gemm_gate_up", 2065): "8,3,4,1"}),
+    (512, 4, 2048, "bf16", 2, [1297, 300, 2065], {("gemm_gate_up", 1297): "8,4,4,2", ("gemm_gate_up", 2065): "8,8,4,2"}),
+    (768, 6, 128, "bf16", 2, [1030, 769], {("gemm_qkv", 769): "8,2,4,1", ("gemm_gate_up", 769): "8,2,4,1"}),
+    (5632, 44, 128, "bf16", 2, [1025, 129], {("gemm_qkv", 129): "8,3,8,1"}),
+    (1024, 8, 2816, "w4", 2, [1024, 1024], {}),                   # the bf16 copy of a 4-bit stage
+    (1024, 8, 2816, "w4", 4, [1100, 65, 300, 1026], {}),
+])
+def test_chunks_beside_each_other(d_model, n_heads, d_ffn, dtype, n_lanes, chunks, tiles):
+    """Chunks of one call on several streams: against the oracle, behind a cached prefix; three times the same bits (a chunk
+    that did not wait for the cache entries of the one before would show as a run-to-run difference)."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=n_heads, d_ffn=d_ffn, n_layers=2 if d_model <= 1024 else 1)
+    total = sum(chunks)
+    p = Pair(cfg, dtype, seed=total, max_positions=total + 70, max_chunk_tokens=max(chunks), w4_expanded=dtype == "w4")
+    p.stage.enable_overlap(n_lanes)
+    for (kernel, rows), tile in tiles.items():
+        name = p.stage.kernel_name(jb.KERNEL_IDS[kernel], rows, True)
+        assert name.startswith(f"gemm_bf16<{tile},"), (kernel, rows, name)
+    hidden = p.hidden(total + 70)
+    p.gpu_chunk(hidden[:70], 0)
+    want = p.oracle.prefill_chunk(hidden, 0)
+    x = torch.from_numpy(hidden[70:]).to("cuda:0", p.td)
+    y = p.stage.prefill_chunks(x, chunks, 70, p.kv).clone()
+    kv = p.kv.view().clone()
+    p.check(y.float().cpu().numpy(), want[70:], "hidden states")
+    p.check(kv.float().cpu().numpy(), p.oracle.kv, "cache")
+    for _ in range(3):
+        assert torch.equal(p.stage.prefill_chunks(x, chunks, 70, p.kv), y)
+        assert torch.equal(p.kv.view(), kv)

@@ -84,7 +84,7 @@ def test_library_host_logic_under_asan_and_ubsan():
         run([hipcc, *base, *san_flags, "-c", os.path.join(jbuild.CSRC, src), "-o", obj])
         objs.append(obj)
     drv = os.path.join(OUT, "host_driver.o")
-    run([hipcc, "-O1", "-g", "-std=c++20", "-I", os.path.join(ROOT, "include"), "-fsanitize=address,undefined",
+    run([hipcc, "-O1", "-g", "-std=c++20", "-I", os.path.join(ROOT, "include"), "-I", jbuild.CSRC, "-fsanitize=address,undefined",
          "-fno-sanitize-recover=all", "-fno-gpu-sanitize", "-c", os.path.join(HERE, "host_driver.cpp"), "-o", drv])
     rest = [o for o in plain if os.path.basename(o) not in ("jup_api.o", "jup_plan.o")]
     exe = os.path.join(OUT, "host_driver")
