@@ -10,23 +10,43 @@ from paper_2504_08242_amd import synth_inputs as si
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d_model,n_heads,d_ffn,rows,tiles", [
+TALL_TILES = [
+    (256, 2, 128, 129, {"gemm_gate_up": "8,3,4,1"}),
+    (1024, 8, 128, 129, {"gemm_gate_up": "4,3,4,1"}),
     (1024, 8, 2816, 129, {"gemm_qkv": "4,3,4,1", "gemm_o": "4,4,4,2"}),
+    (1024, 8, 2688, 257, {"gemm_gate_up": "4,4,4,2"}),
+    (1024, 8, 4096, 961, {"gemm_gate_up": "8,4,4,2"}),
     (1024, 8, 2816, 1025, {"gemm_qkv": "4,4,4,2", "gemm_gate_up": "6,6,2,2", "gemm_down": "4,6,4,2"}),
+    (1024, 8, 4096, 1297, {"gemm_gate_up": "6,8,2,4"}),
+    (1024, 8, 2688, 2065, {"gemm_down": "8,4,4,2"}),
     (1536, 12, 4224, 607, {"gemm_gate_up": "4,6,4,2"}),
     (1536, 12, 4224, 897, {"gemm_qkv": "6,6,2,2"}),
+    (1792, 14, 6272, 513, {"gemm_down": "4,8,2,4"}),
+    (1792, 14, 128, 961, {"gemm_qkv": "4,6,4,2"}),
+    (1792, 14, 128, 2321, {"gemm_qkv": "8,8,4,2"}),
     (2048, 16, 5632, 641, {"gemm_qkv": "6,4,2,2", "gemm_down": "6,4,2,2"}),
     (2048, 16, 5632, 1025, {"gemm_gate_up": "8,8,4,2", "gemm_down": "8,6,4,2"}),
+    (2048, 16, 128, 1937, {"gemm_qkv": "8,6,4,2"}),
+    (2304, 18, 6272, 257, {"gemm_gate_up": "6,4,2,2"}),
     (4096, 32, 11008, 639, {"gemm_qkv": "4,8,2,4", "gemm_gate_up": "4,8,2,4", "gemm_down": "6,8,2,4"}),
     (4096, 32, 11008, 893, {"gemm_qkv": "6,8,2,4", "gemm_gate_up": "8,6,4,2", "gemm_down": "8,8,4,2"}),
-])
+    (4352, 34, 128, 385, {"gemm_qkv": "8,4,4,2"}),
+]
+EPILOGUE = {"gemm_qkv": 0, "gemm_o": 1, "gemm_down": 1, "gemm_gate_up": 2}
+COVERED = {f"gemm_bf16<{tile},{EPILOGUE[kernel]}>" for *_, tiles in TALL_TILES for kernel, tile in tiles.items()}
+
+
+@pytest.mark.parametrize("d_model,n_heads,d_ffn,rows,tiles", TALL_TILES)
 def test_bf16_tall_tiles(d_model, n_heads, d_ffn, rows, tiles):
-    """Every tile of the projections of chunks above 128 rows, with a ragged last row block and a short prefix."""
+    """Every tile of the projections of chunks above 128 rows, with a ragged last row block and a short prefix; whatever else
+    other chunk lengths of these stages run is among them."""
     cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=n_heads, d_ffn=d_ffn, n_layers=1)
     p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 7, max_chunk_tokens=rows)
     for kernel, tile in tiles.items():
         name = p.stage.kernel_name(jb.KERNEL_IDS[kernel], rows)
         assert name.startswith(f"gemm_bf16<{tile},"), (kernel, name)
+    picked = {p.stage.kernel_name(jb.KERNEL_IDS[kernel], n) for n in range(129, 4097, 16) for kernel in EPILOGUE}
+    assert picked <= COVERED, picked - COVERED
     hidden = p.hidden(rows + 7)
     g, o = p.run_both(hidden, [7, rows])
     p.check(g[7:], o[7:], f"{rows} rows of d {d_model}")
