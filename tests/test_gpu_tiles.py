@@ -213,10 +213,10 @@ def test_batched_branches_of_more_than_64_rows_have_the_bits_they_have_alone(dty
     # short chunks between long ones: the tiles of short chunks that share the GPU
     (1024, 8, 2816, "bf16", 4, [1100, 64, 100, 300, 1050, 33, 128, 5],
      {("gemm_gate_up", 64): "2,6,2,3", ("gemm_gate_up", 100): "4,6,4,1", ("gemm_qkv", 100): "4,3,4,1", ("gemm_o", 33): "2,4,2,2",
-      ("gemm_down", 128): "4,4,4,1", ("gemm_qkv", 1100): "8,6,4,2", ("gemm_o", 300): "8,8,4,2"}),
+      ("gemm_down", 128): "4,4,4,1", ("gemm_qkv", 1100): "8,2,4,1", ("gemm_o", 300): "8,8,4,2"}),
     (256, 2, 1024, "bf16", 3, [2065, 129, 1030], {("gemm_qkv", 129): "8,1,4,1", ("gemm_gate_up", 2065): "8,3,4,1"}),
     (512, 4, 2048, "bf16", 2, [1297, 300, 2065], {("gemm_gate_up", 1297): "8,4,4,2", ("gemm_gate_up", 2065): "8,8,4,2"}),
-    (768, 6, 128, "bf16", 2, [1030, 769], {("gemm_qkv", 769): "8,2,4,1", ("gemm_gate_up", 769): "8,2,4,1"}),
+    (768, 6, 128, "bf16", 2, [1809, 769], {("gemm_qkv", 1809): "8,6,4,2", ("gemm_gate_up", 769): "8,2,4,1"}),
     (5632, 44, 128, "bf16", 2, [1025, 129], {("gemm_qkv", 129): "8,3,8,1"}),
     (1024, 8, 2816, "w4", 2, [1024, 1024], {}),                   # the bf16 copy of a 4-bit stage
     (1024, 8, 2816, "w4", 4, [1100, 65, 300, 1026], {}),
