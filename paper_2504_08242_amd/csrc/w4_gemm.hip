@@ -171,6 +171,11 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[j][cg][i] = w4_group(acc[j][cg][i], sc[cg], t[i], rs[j][i]);
             }
+            // 64 rows: one column block's expansion at a time.  Free to overlap them the compiler takes 250 registers, two waves
+            // of which are a whole SIMD: not even a one-wave kernel of another stream fits beside a workgroup then, it keeps
+            // a CU to itself, and a grid of 256 workgroups (O, down) takes a second round.  228 as here: 64-row call of
+            // eight layers beside such a kernel 879 -> 786 us, alone 776 -> 772.
+            if (RG == 4) __builtin_amdgcn_sched_barrier(0);
         }
     };
 
@@ -268,7 +273,7 @@ template <int EPI, int RG>
 hipError_t launch_rg(GemmArgs a, hipStream_t s) {
     // Eight waves per workgroup split its K range, whatever the row count: the order in which the K shares are summed
     // is then the same for a branch submitted alone and batched with others, and the two give the same bits.  Measured
-    // on the 7B shapes at 64 rows per pass (246 registers per lane, so eight waves per CU either way): two workgroups of
+    // on the 7B shapes at 64 rows per pass (228 registers per lane, so eight waves per CU either way): two workgroups of
     // four waves per CU run gate/up 4-5 % faster (its 344 workgroups then fit one round instead of two) and QKV 40 %
     // slower than one of eight; at 5 rows 4, 8 and 16 waves measured within 5 % of each other.
     constexpr int WAVES = W4_WAVES;
