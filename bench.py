@@ -12,8 +12,9 @@ situation of every pipeline stage but the first, which receives a sub-sequence w
 those steps.  Beside it the JSON line carries
   per_call    every call bracketed by an event pair: median milliseconds per chunk index (q(chunk, c * chunk)) and
               tokens/s = sum of tokens / sum of call times;
-  overlapped  the same prompt fed with ONE jup_stage_prefill_chunks call whose consecutive chunks overlap on up to four
-              streams (possible where all chunks are at hand, i.e. at a pipeline's first stage); --no-overlap skips it;
+  overlapped  the same prompt fed with ONE jup_stage_prefill_chunks call with overlap enabled: consecutive chunks are
+              computed in groups, long ones beside each other on up to four streams (possible where all chunks are at hand,
+              i.e. at a pipeline's first stage); --no-overlap skips it;
   clock_mhz   the shader clock the chip held during the timed steps (a one-wave probe kernel on a second stream);
   roofline    the dominant kernel (the gate/up GEMM with the SwiGLU epilogue), timed in place with HIP events;
   cpu_baseline  the CPU oracle timed on this machine's host cores on a bounded sample of the same workload.
@@ -110,8 +111,8 @@ def main():
     ap.add_argument("--w4-codes-only", action="store_true",
                     help="with --w4: no bf16 copy, chunks of more than 64 rows take one pass over the codes per 64 rows")
     ap.add_argument("--no-overlap", action="store_true",
-                    help="skip the `overlapped` leg (one jup_stage_prefill_chunks call whose consecutive chunks overlap "
-                         "on several streams); profiling runs use this, so that every kernel's duration is its own")
+                    help="skip the `overlapped` leg (one jup_stage_prefill_chunks call with overlap enabled); profiling runs "
+                         "use this, so that every kernel's duration is its own")
     ap.add_argument("--vendor-gemm", action="store_true",
                     help="also time torch.matmul (the vendor GEMM library, no fused epilogue) on the four projection "
                          "shapes of the workload's chunk and report it as `vendor_gemm`: context for the per-kernel times")
@@ -123,8 +124,9 @@ def main():
                          "wave in flight), the HBM stream probe (disjoint regions read once) and the LDS read probe, and report "
                          "them as `fill_calibration`")
     ap.add_argument("--lanes", type=int, default=4,
-                    help="lanes enabled for the overlapped call (2..4; for chunks above 256 tokens the library uses all "
-                         "of them only when the number of chunks is a multiple of four, else two)")
+                    help="lanes enabled for the overlapped call (2..4; chunks of up to 1024 tokens, 896 with two lanes, are "
+                         "computed in groups in the lanes' scratch; longer ones use all lanes when their number is a multiple "
+                         "of four, else two)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-sample-tokens", type=int, default=1024,
                     help="the oracle is timed on the first this-many tokens of the prompt, fed in the same chunks")

@@ -131,7 +131,10 @@ struct GemmArgs {
     KvView kv;
     int layer, n_heads, d_model, pos0;
     const BranchTable* branches;  // non-null: row m belongs to branch m / n_tok (kv and pos0 above are unused)
-    bool shared_gpu;     // another chunk's kernels run beside this launch (overlapped multi-chunk call)
+    // another chunk's kernels run beside this launch (multi-chunk call on lanes).  Short chunks get there between longer ones
+    // only: the figures beside their tiles are from lists of equal chunks of 64 to 512 tokens on four lanes, which are
+    // computed in groups otherwise (plan_chunk_groups).
+    bool shared_gpu;
     // EPI_PARTIAL
     float* partial;  // [splits][M][N] fp32
     // EPI_SWIGLU

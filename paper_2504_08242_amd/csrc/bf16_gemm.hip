@@ -620,7 +620,7 @@ int gemm_partial_col_blocks(int M, int N, int K) {
 // shared: another chunk's kernels run beside this launch (overlapped multi-chunk call).  Filling the chip with one
 // launch then matters less than the work per output: at most two splits (half or a quarter of the partial sums to
 // write and read back, longer K loops per workgroup); the CUs a launch leaves free go to the other chunks.
-// Measured on the 7B shapes with four lanes: 4 x 512 tokens 274k -> 286k tokens/s, 8 x 256 tokens 204k -> 224k,
+// Measured on the 7B shapes, equal chunks on four lanes (see GemmArgs::shared_gpu): 4 x 512 tokens 274k -> 286k tokens/s, 8 x 256 tokens 204k -> 224k,
 // 16 x 128 and 8 x 64 tokens +3-4 % (no split at all: -4 % there); alone on the chip the same cap costs 8 % (one
 // launch then has to fill it).
 int gemm_plan_splits(int M, int N, int K, bool shared) {
@@ -658,7 +658,7 @@ namespace {
 TileShape pick_qkv(int M, int N, int K, bool shared_gpu) {
     const int bmb = pick_row_blocks(M);
     // 128-token chunks beside other chunks' kernels: 96-column tiles (half again as much work per workgroup; alone on
-    // the chip 64 columns win, 24.0 vs 28.8 us at 64 rows).  Measured with four lanes: 13B shapes, 8 x 128 tokens
+    // the chip 64 columns win, 24.0 vs 28.8 us at 64 rows).  Measured on four lanes: 13B shapes, 8 x 128 tokens
     // +2 %; 7B shapes, 16 x 128 tokens +0-1 %; 192 columns +4 % and -1 %; 64-token chunks no difference either way.
     if (shared_gpu && bmb == 4) return {4, 3, 4, 1};
     if (bmb == 2) return {2, 2, 2, 2};

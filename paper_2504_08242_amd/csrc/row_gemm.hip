@@ -23,7 +23,11 @@
 // Measured on the 7B shapes at 5 rows (us, two K-split launches and two reduce + norm passes -> two launches): bf16
 // 7.2 + 17.4 + 2 x 4.8 -> 7.7 + 17.4; 4-bit 3.7 + 9.2 + 2 x 4.3 -> 5.9 + 12.8.  A whole call: 5 rows of eight bf16 layers
 // 723 -> 681 us, one row of eight 4-bit layers 460 -> 416 us.  A batch of branches pays for the equal bits: 8 x 5 rows of two
-// bf16 layers 203 -> 207 us.
+// bf16 layers 203 -> 207 us.  Narrow stages, whose d / 16 workgroups leave CUs idle (64 of them for d = 1024, each walking all
+// of K), gain more: their launches are short, and there are fewer.  Six layers, 1 / 16 rows, two launches and two passes -> two
+// launches (with the first kernel of a call and the attention of short chunks as they are now): bf16 d = 1024 257 -> 198 /
+// 263 -> 219 us, 2048 319 -> 273 / 346 -> 332, 4096 539 -> 496 / 585 -> 567; 4-bit d = 1024 202 -> 171 / 217 -> 186, 2048
+// 224 -> 206 / 246 -> 223, 4096 332 -> 299 / 366 -> 332.
 #include "bf16_common.h"
 
 namespace jup {
