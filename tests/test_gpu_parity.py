@@ -567,7 +567,8 @@ def assert_same_cache_entries(got_bits, want_bits, sentinel_bits):
 
 def run_chunks_case(p, chunks, pos0_chunks=(), exact=True):
     """jup_stage_prefill_chunks against one call per chunk: outputs, cache and length.  Bit for bit when the chunks
-    run one after the other; up to fp32 summation order (fewer K splits) when they overlap."""
+    run one after the other; up to rounding (fp32 summation order, the scale of attention probabilities) when they are
+    computed in groups."""
     import torch
     total = sum(pos0_chunks) + sum(chunks)
     h = p.hidden(total)
@@ -611,12 +612,12 @@ def run_chunks_case(p, chunks, pos0_chunks=(), exact=True):
 
 @pytest.mark.parametrize("n_lanes", [2, 3, 4])
 def test_bf16_overlapped_chunks_equal_one_call_per_chunk(n_lanes):
-    """Consecutive chunks on several streams: a chunk may only read what the chunks before it have already cached.
-    A missing dependency would show as a mismatch far above rounding, or as a run-to-run difference."""
+    """Overlap enabled, chunks of up to 192 tokens: computed in groups that go through the layers as one chunk.  (Chunks
+    beside each other on several streams: test_gpu_tiles.py, test_chunks_beside_each_other.)"""
     p = Pair(LLAMA7B_2L, "bf16", seed=41, max_positions=700, max_chunk_tokens=192)
     run_chunks_case(p, [64, 64, 64])                       # not enabled yet: one after the other
     p.stage.enable_overlap(n_lanes)
-    for rep in range(3):                                    # repeated: a missing dependency shows as a flaky mismatch
+    for rep in range(3):
         run_chunks_case(p, [128, 37, 0, 5, 192, 64, 1, 100], pos0_chunks=[50], exact=False)
     got, h = run_chunks_case(p, [160, 160, 160, 160], exact=False)
     o = [p.oracle.prefill_chunk(h[i * 160:(i + 1) * 160], i * 160) for i in range(4)]
@@ -749,7 +750,7 @@ def test_c2_7b_stage_512_tokens_in_8_chunks_of_64():
 
 
 def assert_one_call_equals(p, hidden, chunks, want):
-    """The benchmark's launch configuration: the prompt in one call, chunks overlapping on four lanes.  Against the
+    """The benchmark's launch configuration: the prompt in one call, overlap enabled with four lanes.  Against the
     oracle at the parity bar, and against one call per chunk up to fp32 summation order."""
     import torch
     kv_want = p.kv_gpu()
@@ -785,7 +786,7 @@ def test_c3_7b_stage_2048_tokens_chunk_sizes_128_to_2048():
             p.check(kv[l], p.oracle.kv[l], f"cache layer {l}, chunk size {size}")
         if size == 512:
             g512 = g
-    # the launch configuration of the benchmark: the whole prompt in one call, chunks overlapping on the GPU
+    # the launch configuration of the benchmark: the whole prompt in one call, overlap enabled
     import torch
     p.stage.enable_overlap(4)
     x = torch.from_numpy(hidden).to(device="cuda:0", dtype=p.td)

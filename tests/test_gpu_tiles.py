@@ -89,8 +89,9 @@ def test_bf16_chunks_in_one_call(n_lanes, chunks, limit):
     (65, 40, 0), (129, 700, 64), (256, 1, 0), (300, 5, 5),
 ])
 def test_short_attention(dtype, n, pos, shared):
-    """Query blocks of 16 and 32 rows, partial blocks, key counts around a tile and around a second key range, forks whose
-    border falls inside a tile, and the tree mask against the oracle."""
+    """Query blocks of 16 and 32 rows (chunks of up to 64 tokens; some longer ones on key quarters beside them), partial blocks,
+    key counts around a tile and around a second key range, forks whose border falls inside a tile, and the tree mask against
+    the oracle."""
     cfg = dict(si.LLAMA7B_STAGE, d_model=256, n_heads=2, d_ffn=128, n_layers=1)
     p = Pair(cfg, dtype, seed=n + pos, max_positions=pos + n, max_chunk_tokens=max(n, 512))
     hidden = p.hidden(pos + n)
