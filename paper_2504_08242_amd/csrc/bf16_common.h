@@ -17,7 +17,11 @@ __device__ inline u16 f2bf(float f) {
     return __builtin_bit_cast(u16, b);
 }
 __device__ inline float bf2f(u16 b) { return __uint_as_float((unsigned)b << 16); }
-__device__ inline unsigned pack_bf16x2(float lo, float hi) { return (unsigned)f2bf(lo) | ((unsigned)f2bf(hi) << 16); }
+__device__ inline unsigned pack_bf16x2(float lo, float hi) {  // (as a vector: one instruction, where two f2bf take four)
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
 
 // Tells the compiler that p is the same in every lane (it is: built from kernel arguments, the workgroup id
 // and the wave number).  Kept opaque so that "uniform base + 32-bit lane offset" survives to instruction
@@ -122,6 +126,7 @@ struct GemmArgs {
                    // 4-bit stages: the packed codes (w4_gemm.hip)
     const float* w_scale;  // 4-bit stages only: packed scales
     int M, N, K;
+    int n_tok;             // 4-bit stages only: rows of one chunk or branch (M, or M / number of branches)
     int m_tiles, n_tiles, splits;  // grid = m_tiles * n_tiles * splits workgroups
     int n_stride;                  // columns between consecutive N tiles (tile width actually owned)
     int kt_per_split;              // K tiles of 32 per split
@@ -251,8 +256,14 @@ __device__ __forceinline__ float w4_group(float acc, float scale, float t, float
 
 // ---- projections of a 4-bit stage (w4_gemm.hip) ----------------------------------------------------
 // epi: EPI_QKV, EPI_SWIGLU or EPI_PARTIAL; the tiling fields of `a` are filled here.  EPI_PARTIAL writes
-// w4_plan_splits(N, K) partial buffers.
+// w4_partial_splits(n_tok, N, K) partial buffers, w4_plan_splits(N, K) of them up to 32 tokens.
+int w4_partial_splits(int n_tok, int N, int K);
 int w4_plan_splits(int N, int K);
+// the kernel of longer chunks and branches (w4_wide.hip), and which projections take it
+bool w4_is_wide(int epi, int n_tok, int N, int K);
+int w4_wide_splits(int n_tok, int N, int K);
+hipError_t launch_gemm_w4_wide(int epi, const GemmArgs& a, hipStream_t s);
+hipError_t w4_wide_configure();  // raises the dynamic-LDS limit (once per process)
 hipError_t launch_gemm_w4(int epi, GemmArgs a, hipStream_t s);
 // dst / dst_scale: packed codes (N * K / 2 bytes) and packed scales (N * K / 128 floats) of one matrix
 void launch_pack_w4_qkv(unsigned char* dst, float* dst_scale, const void* cq, const void* ck, const void* cv,

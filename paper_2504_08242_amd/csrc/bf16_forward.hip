@@ -42,6 +42,7 @@ hipError_t w4_pack_weights(const jup_stage& st, const jup_layer_weights_t* layer
     const jup_stage_config_t& c = st.cfg;
     const size_t d = c.d_model;
     hipError_t e = attention_configure();
+    if (e == hipSuccess) e = w4_wide_configure();
     if (e == hipSuccess && c.w4_expanded) e = gemm_configure();
     if (e != hipSuccess) return e;
     for (int l = 0; l < c.n_layers; ++l) {
@@ -131,8 +132,9 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     const bool rows = n <= kMaxProjectRows && !shared;
     const bool small_branches = !rows && bt && bt->n_tok <= kMaxProjectRows && (w4 || (!expanded && n <= max_split_rows(d)));
     const bool as_rows = rows || small_branches;
-    const int splits_o = w4 ? w4_plan_splits(d, d) : as_rows ? row_splits(d) : gemm_plan_splits(n, d, d, shared);
-    const int splits_down = w4 ? w4_plan_splits(d, f) : as_rows ? row_splits(d) : gemm_plan_splits(n, d, f, shared);
+    const int n_tok = bt ? bt->n_tok : n;
+    const int splits_o = w4 ? w4_partial_splits(n_tok, d, d) : as_rows ? row_splits(d) : gemm_plan_splits(n, d, d, shared);
+    const int splits_down = w4 ? w4_partial_splits(n_tok, d, f) : as_rows ? row_splits(d) : gemm_plan_splits(n, d, f, shared);
     float* late_factor = small_branches ? factor : nullptr;
     float* ssq = partial;
     // back to d_model: in [n, k] times w; gain: of the norm that follows (null behind the last layer)
@@ -147,7 +149,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         }
         GemmArgs a{};
         a.A = in; a.W = (const u16*)w; a.w_scale = (const float*)w_scale; a.M = n; a.N = d; a.K = k;
-        a.partial = partial; a.shared_gpu = shared;
+        a.n_tok = n_tok; a.partial = partial; a.shared_gpu = shared;
         return w4 ? launch_gemm_w4(EPI_PARTIAL, a, s) : launch_gemm_partial(a, s);
     };
     hipError_t e = hipSuccess;
@@ -162,7 +164,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         {
             TraceScope ts(st, JUP_K_GEMM_QKV, s);
             GemmArgs a{};
-            a.A = xn; a.W = (const u16*)(wb + wqkv); a.M = n; a.N = 3 * d; a.K = d;
+            a.A = xn; a.W = (const u16*)(wb + wqkv); a.M = n; a.N = 3 * d; a.K = d; a.n_tok = n_tok;
             a.q_out = q; a.rope = rope; a.kv = kv; a.layer = l; a.n_heads = H; a.d_model = d; a.pos0 = pos;
             a.branches = bt_dev;
             a.shared_gpu = shared;
@@ -192,7 +194,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         {
             TraceScope ts(st, JUP_K_GEMM_GATE_UP, s);
             GemmArgs a{};
-            a.A = xn; a.W = (const u16*)(wb + wgu); a.M = n; a.N = 2 * f; a.K = d; a.act = act; a.shared_gpu = shared;
+            a.A = xn; a.W = (const u16*)(wb + wgu); a.M = n; a.N = 2 * f; a.K = d; a.n_tok = n_tok; a.act = act; a.shared_gpu = shared;
             a.ssq = rows ? ssq : nullptr; a.rms_eps = c.rms_eps;
             a.row_factor = late_factor;
             a.w_scale = (const float*)(wb + st.pl.sgu);

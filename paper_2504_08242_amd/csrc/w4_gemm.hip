@@ -122,7 +122,7 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
     const W4Bits bits;
     // STREAM_ONCE (one pass over the codes, up to 64 rows): every code is read exactly once, with the non-temporal hint,
     // so that the stream does not push the KV cache and the activations out of the caches (measured at 5 rows per call:
-    // the attention launch behind the projections 15.0 -> 12.2 us, a step of 8 branches 3.96 -> 3.62 ms).  Longer chunks
+    // the attention launch behind the projections 15.0 -> 12.2 us, a step of 8 branches 3.96 -> 3.62 ms).  More rows
     // take several passes, which find the codes in L2, and inside an overlapped call the other chunks' launches find them
     // in the caches (as for the bf16 kernels: not measured separately for the codes).
     auto fetch_codes = [&](W4Codes& d, int g) __attribute__((always_inline)) {
@@ -284,7 +284,7 @@ hipError_t launch_rg(GemmArgs a, hipStream_t s) {
     else hipLaunchKernelGGL((gemm_w4<EPI, RG, WAVES, false>), grid, dim3(64 * WAVES), 0, s, a);
     return hipGetLastError();
 }
-// Rows per pass over the codes: 16, 32 or 64 (a longer chunk takes several passes of 64).
+// Rows per pass over the codes: 16, 32 or 64 (more rows, in batches of branches of up to 32 tokens, take several passes of 64).
 template <int EPI>
 hipError_t launch_one(GemmArgs a, hipStream_t s) {
     if (a.M <= 16) return launch_rg<EPI, 1>(a, s);
@@ -304,8 +304,13 @@ int w4_plan_splits(int N, int K) {
     return splits;
 }
 
+int w4_partial_splits(int n_tok, int N, int K) {
+    return w4_is_wide(EPI_PARTIAL, n_tok, N, K) ? w4_wide_splits(n_tok, N, K) : w4_plan_splits(N, K);
+}
+
 hipError_t launch_gemm_w4(int epi, GemmArgs a, hipStream_t s) {
-    if (a.M <= 0 || a.N % W4_TILE_N || a.K % W4_GROUP) return hipErrorInvalidValue;
+    if (a.M <= 0 || a.n_tok <= 0 || a.N % W4_TILE_N || a.K % W4_GROUP) return hipErrorInvalidValue;
+    if (w4_is_wide(epi, a.n_tok, a.N, a.K)) return launch_gemm_w4_wide(epi, a, s);
     if (epi == EPI_PARTIAL) {
         a.splits = w4_plan_splits(a.N, a.K);
         return launch_one<EPI_PARTIAL>(a, s);

@@ -208,6 +208,30 @@ def test_batched_branches_of_more_than_64_rows_have_the_bits_they_have_alone(dty
             kv.destroy()
 
 
+@pytest.mark.parametrize("d_model,n_heads,d_ffn,rows", [
+    (256, 2, 128, [33, 65, 129]),               # fewer K groups than K shares
+    (768, 6, 896, [64, 200, 513]),              # groups no multiple of the shares, column tiles past the matrix
+    (1024, 8, 2816, [33, 65, 257, 384, 1024]),  # every shape, up to six K splits
+    (2304, 18, 1408, [129, 513, 1024]),
+    (5120, 40, 3456, [40, 200, 1024]),
+])
+def test_w4_projections_of_long_chunks(d_model, n_heads, d_ffn, rows):
+    """4-bit codes, more than 32 tokens: rows on and beside the edges of the tiles of 64 and 128 rows, every (row block, column,
+    K share) shape for some projection, against the oracle, behind a cached prefix; the same bits twice."""
+    cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=n_heads, d_ffn=d_ffn, n_layers=1)
+    p = Pair(cfg, "w4", seed=d_model + 1, max_positions=max(rows) + 5, max_chunk_tokens=max(rows))
+    for n in rows:
+        p.kv.reset()
+        p.oracle.reset()
+        h = p.hidden(n + 5)
+        p.gpu_chunk(h[:5], 0)
+        y = p.gpu_chunk(h[5:], 5)
+        want = p.oracle.prefill_chunk(h, 0)
+        p.check(y, want[5:], f"{n} rows")
+        p.check(p.kv_gpu()[:, :, :, :n + 5], p.oracle.kv[:, :, :, :n + 5], f"cache, {n} rows")
+        assert np.array_equal(p.gpu_chunk(h[5:], 5), y), n
+
+
 @pytest.mark.parametrize("d_model,n_heads,d_ffn,dtype,n_lanes,chunks,tiles", [
     # two chunks a second lane's scratch cannot hold together: side by side
     (1024, 8, 2816, "bf16", 2, [1024, 1024, 1000], {}),
