@@ -232,20 +232,20 @@ hipError_t launch_gemm_partial(GemmArgs a, hipStream_t s);
 void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_gpu, char* buf, size_t size);
 hipError_t gemm_configure();  // raises the dynamic-LDS limit of every instantiation (once per process)
 
-// Constants of the expansion that the compiler does not know, in a vector and a scalar register: and + or are then one
+// Constants of the expansion that the compiler does not know, in a vector and a scalar register: and + xor are then one
 // instruction.
 struct W4Bits {
     unsigned mask, bias;
     __device__ __forceinline__ W4Bits() {
         asm volatile("v_mov_b32 %0, 0x000f000f" : "=v"(mask));
-        asm volatile("s_mov_b32 %0, 0x43004300" : "=s"(bias));
+        asm volatile("s_mov_b32 %0, 0x43084308" : "=s"(bias));
     }
 };
 // Eight 4-bit codes of one dword (packed as w4_gemm.hip describes) as bf16 values 128 + code.
 __device__ __forceinline__ bf16x8 w4_expand(unsigned w, const W4Bits& k) {
     u32x4 v;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = ((w >> (4 * j)) & k.mask) | k.bias;
+    for (int j = 0; j < 4; ++j) v[j] = ((w >> (4 * j)) & k.mask) ^ k.bias;
     return __builtin_bit_cast(bf16x8, v);
 }
 

@@ -13,9 +13,10 @@
 //     four results share one column and take one scale.
 //   * Codes are stored per (64-column tile, 128-K group, 16-column block) as 1 KB: lane (r, q) owns 16 bytes, dword
 //     ks holding the eight codes of column r for k = 128 g + 32 ks + 8 q + e.  Inside a dword, nibble p < 4 is
-//     element 2 p and nibble p + 4 is element 2 p + 1: ((w >> 4 j) & 0x000F000F) | 0x43004300 is then the bf16 pair
-//     (128 + code[2 j], 128 + code[2 j + 1]) -- two instructions per two weights, exact (a bf16 mantissa holds
-//     128..255 in steps of one).  and + or are one instruction only if at most one of the constants is a literal (W4Bits).
+//     element 2 p and nibble p + 4 is element 2 p + 1, each as code ^ 8 (code - 8 in two's complement):
+//     ((w >> 4 j) & 0x000F000F) ^ 0x43084308 is then the bf16 pair (128 + code[2 j], 128 + code[2 j + 1]) -- two
+//     instructions per two weights, exact (a bf16 mantissa holds 128..255 in steps of one).  and + xor are one instruction
+//     only if at most one of the constants is a literal (W4Bits).
 //   * The offset of 136 = 128 + 8 leaves through the row sums of A: sum_k A[m][k] (128 + c) - 136 sum_k A[m][k].
 //     The row sums of a group come from one more MFMA per K step against a register of ones, and a group's
 //     result enters the fp32 accumulator as scale * (t - 136 * rowsum): 4 FMAs per lane, group and column block.
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(256) void pack_w4(unsigned char* __restrict__ dst, 
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
             const int e = p < 4 ? 2 * p : 2 * (p - 4) + 1;
-            v |= ((w >> (4 * e)) & 0xFu) << (4 * p);
+            v |= (((w >> (4 * e)) & 0xFu) ^ 8u) << (4 * p);
         }
         out[ks] = v;
     }

@@ -8,7 +8,7 @@
 //     one or half a group per share, one barrier per stage.
 //   * v_mfma_f32_32x32x16_bf16 (operand layout: bf16_gemm.hip).  A group of 128 features is eight steps into a temporary
 //     that then enters the sum times the column's scale: 16 vector instructions per 256 MFMA clocks and block.
-//   * A code becomes the bf16 value (code - 8) / 16, exactly (cvt_off: a signed nibble / 16; 14 instructions for eight codes),
+//   * A code becomes the bf16 value (code - 8) / 16, exactly (cvt_off: a signed nibble / 16; 13 instructions for eight codes),
 //     the sums are multiplied by 16 at the end.  No row sums of A are needed, as for the 128 + code form (seven instructions
 //     and one more MFMA per step and 16 rows), which beside a 32-column wave would double the MFMAs.
 //   * What bounds it is the waves' own instruction streams: a wave issues a vector instruction every 8 clocks, and a turn
@@ -56,18 +56,18 @@ __device__ inline void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x0F70);
 }
 
-// Eight 4-bit codes of one dword as the bf16 values (code - 8) / 16, exactly.
-__device__ __forceinline__ bf16x8 expand_exact(unsigned w) {
-    unsigned x = w ^ 0x88888888u, y = x >> 4;  // two's complement nibbles, one per byte
-    asm("" : "+v"(x), "+v"(y));                // (else the bytes of y become bit fields of x, an instruction each)
-    auto at = [](unsigned v, int byte) { return __builtin_amdgcn_cvt_off_f32_i4((int)((v >> (8 * byte)) & 0xffu)); };
-    u32x4 v;
-    v[0] = pack_bf16x2(at(x, 0), at(x, 2));
-    v[1] = pack_bf16x2(at(y, 0), at(y, 2));
-    v[2] = pack_bf16x2(at(x, 1), at(x, 3));
-    v[3] = pack_bf16x2(at(y, 1), at(y, 3));
-    return __builtin_bit_cast(bf16x8, v);
-}
+// Eight 4-bit codes of one dword as the bf16 values (code - 8) / 16, exactly, in two halves (elements 0, 1, 4, 5, then 2, 3, 6, 7).
+struct Nibbles {
+    unsigned x, y;  // one per byte: low, high
+    __device__ __forceinline__ explicit Nibbles(unsigned w) : x(w), y(w >> 4) {
+        asm("" : "+v"(x), "+v"(y));  // (else the bytes of y become bit fields of x, an instruction each)
+    }
+    static __device__ __forceinline__ float at(unsigned v, int byte) {
+        return __builtin_amdgcn_cvt_off_f32_i4((int)((v >> (8 * byte)) & 0xffu));
+    }
+    __device__ __forceinline__ void first(u32x4& v) const { v[0] = pack_bf16x2(at(x, 0), at(x, 2)); v[2] = pack_bf16x2(at(x, 1), at(x, 3)); }
+    __device__ __forceinline__ void second(u32x4& v) const { v[1] = pack_bf16x2(at(y, 0), at(y, 2)); v[3] = pack_bf16x2(at(y, 1), at(y, 3)); }
+};
 
 template <int EPI, int MB, int WN, int WK, bool ONCE>
 __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
@@ -90,11 +90,11 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
     const int gs0 = split * G / a.splits, gs1 = (split + 1) * G / a.splits;
     const int iters = (gs1 - gs0 + WK - 1) / WK;
 
-    const char* const rows0 = (const char*)a.A + (size_t)(m0 / 32) * KT * 2048;  // first row block of the tile
+    const char* const rows0 = uniform_ptr((const char*)a.A + (size_t)(m0 / 32) * KT * 2048);  // first row block of the tile
     // Rows: a stage is UNITS pieces of 1 KB, dealt to the waves.  A K share past the end of the range (last turn, count no
     // multiple of WK) repeats its last group, loads behind the last stage one cache line: the count of loads in flight is then
     // the same in every turn.
-    const unsigned lane16 = lane * 16;
+    const unsigned lane16 = lane * 16, ring0 = __builtin_amdgcn_readfirstlane(lds_byte_address(smem));
     unsigned row_at[S::LOADS];
     unsigned part_of[S::LOADS], part_of_last[S::LOADS];
 #pragma unroll
@@ -111,14 +111,14 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
         const int turn = min(it, iters - 1);
         const unsigned all = it < iters ? ~0u : 0u;
         const unsigned at = (unsigned)(gs0 + turn * WK) * 8192 + part * S::PART_BYTES;
-        unsigned char* slot = smem + (it * S::PARTS + part) % S::STAGES * S::STAGE_BYTES;
+        const unsigned slot = ring0 + (unsigned)(it * S::PARTS + part) % S::STAGES * S::STAGE_BYTES;
 #pragma unroll
         for (int q = 0; q < S::LOADS; ++q) {
             const int j = min(q * S::WAVES + wave, S::UNITS - 1);
             const unsigned off = (row_at[q] & all) + (at + (turn == iters - 1 ? part_of_last[q] : part_of[q]));
-            const auto* src = (const __attribute__((address_space(1))) void*)((const __attribute__((address_space(1))) char*)rows0 + off);
-            auto* dst = (__attribute__((address_space(3))) void*)(slot + j * 1024);
-            __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
+            // (as text: beside the builtin, which the compiler takes for a flat access, it waits for every load in flight
+            // in front of each use of a code or fragment)
+            load_to_lds_16(rows0, off, slot + j * 1024);
         }
     };
 
@@ -158,16 +158,18 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
 #pragma unroll
     for (int st = 0; st < ST - 1; ++st) issue_rows(st / PARTS, st % PARTS);
 
-    // A chunk: two row blocks times four MFMA steps (64 features).  CHUNKS of them make a group; with two stages per group the
-    // chunks of the first half of the features come first.
+    // A chunk: two row blocks times four MFMA steps (64 features).  CHUNKS of them make a group, the first half of its features
+    // for all row blocks, then the second.  Everything else is dealt out behind the eight MFMAs of a chunk: the fragments of
+    // the next chunk, the codes of four steps expanded (four row blocks: in chunks 1 and 2), with four row blocks the sums of
+    // a pair of them (pair 0 in chunk 3, pair 1 in chunk 0 of the next turn, when its MFMAs are done).
     constexpr int CHUNKS = MB, PAIRS = MB / 2;
-    constexpr int T = PARTS == 2 ? MB : 2;
-    f32x16 t[T];
-    bf16x8 f[8], b[MB == 2 ? 4 : 8];
-    auto read_frag = [&](int st, auto chunk, auto k) __attribute__((always_inline)) {
+    f32x16 t[MB];
+    bf16x8 f[8];
+    u32x4 b[MB == 2 ? 4 : 8];
+    auto read_frag = [&](int it, auto chunk, auto k) __attribute__((always_inline)) {
         constexpr int CH = decltype(chunk)::value, KK = decltype(k)::value;
-        constexpr int pair = PARTS == 2 ? CH % PAIRS : CH / 2, half = PARTS == 2 ? CH / PAIRS : CH % 2;
-        constexpr int s = KK >> 1, j = KK & 1;
+        constexpr int pair = CH % PAIRS, half = CH / PAIRS, s = KK >> 1, j = KK & 1;
+        const int st = it * PARTS + (PARTS == 2 ? half : 0);
         const unsigned char* slot = smem + st % ST * S::STAGE_BYTES + wk * S::PART_BYTES;
         f[KK] = *(const bf16x8*)(slot + (2 * pair + j) * WK * S::PART_BYTES + ((PARTS == 1 ? 4 * half : 0) + s >> 1) * 2048 + lane_off[s & 1]);
     };
@@ -181,19 +183,27 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
     __builtin_amdgcn_s_barrier();
     for8([&](auto k) __attribute__((always_inline)) { read_frag(0, std::integral_constant<int, 0>{}, k); });
 #pragma unroll
-    for (int s = 0; s < 4; ++s) b[s] = expand_exact(buf[0].w[s & 1][s >> 1]);
+    for (int s = 0; s < 4; ++s) {
+        const Nibbles n(buf[0].w[s & 1][s >> 1]);
+        n.first(b[s]);
+        n.second(b[s]);
+    }
+    float sc = 0.f;
+    if constexpr (MB == 4)
+#pragma unroll
+        for (int j = 2; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) t[j][i] = 0.f;
 
     auto iteration = [&](auto which, int it) __attribute__((always_inline)) {
         constexpr int B = decltype(which)::value;
         Codes& cur = buf[B];
         Codes& next = buf[(B + 1) % BUFS];
-        const bool live = gs0 + it * WK + wk < gs1;
+        Nibbles n(0);
         [&]<int... CHI>(std::integer_sequence<int, CHI...>) __attribute__((always_inline)) {
             ([&](auto chunk) __attribute__((always_inline)) {
                 constexpr int CH = decltype(chunk)::value;
-                constexpr int pair = PARTS == 2 ? CH % PAIRS : CH / 2, half = PARTS == 2 ? CH / PAIRS : CH % 2;
-                constexpr int part = PARTS == 2 ? half : 0;
-                const int st = it * PARTS + part;
+                constexpr int pair = CH % PAIRS, half = CH / PAIRS, part = PARTS == 2 ? half : 0;
                 if constexpr (CH == 0 || (PARTS == 2 && CH == PAIRS)) {  // a stage begins
                     // stage st + 1 has landed (its first fragments are read in this one): behind it in the queue are the
                     // rows of ST - 3 stages and the codes of the last ST - 2 turns of the stages that ask for some
@@ -205,45 +215,62 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 constexpr bool LAST = CH == CHUNKS - 1;
-                constexpr int t0 = T == MB ? 2 * pair : 0;
+                constexpr bool OF_THIS = CH == (MB == 2 ? 0 : 1), OF_NEXT = CH == (MB == 2 ? 1 : 2);
                 for8([&](auto k) __attribute__((always_inline)) {
                     constexpr int K = decltype(k)::value, s = K >> 1, j = K & 1;
                     if constexpr (half == 0 && s == 0) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) t[t0 + j][i] = 0.f;
+                        for (int i = 0; i < 16; ++i) t[2 * pair + j][i] = 0.f;
                     }
-                    t[t0 + j] = mfma32(f[K], b[MB == 2 ? s : 4 * half + s], t[t0 + j]);
+                    t[2 * pair + j] = mfma32(f[K], __builtin_bit_cast(bf16x8, b[MB == 2 ? s : 4 * half + s]), t[2 * pair + j]);
                     __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (LAST) read_frag(st + 1, std::integral_constant<int, 0>{}, k);
-                    else if constexpr (PARTS == 2 && CH + 1 == PAIRS) read_frag(st + 1, std::integral_constant<int, CH + 1>{}, k);
-                    else read_frag(st, std::integral_constant<int, CH + 1>{}, k);
-                    // codes of four steps are expanded behind the MFMAs of the first and the last chunk of a group
-                    if constexpr (CH == 0 && j == 1) b[MB == 2 ? s : 4 + s] = expand_exact(cur.w[s & 1][(4 + s) >> 1]);
-                    if constexpr (LAST && j == 1) {
-                        b[s] = expand_exact(next.w[s & 1][s >> 1]);
-                        asm volatile("" : "+v"(b[s]));  // (here, not behind the branch below)
+                    if constexpr (LAST) read_frag(it + 1, std::integral_constant<int, 0>{}, k);
+                    else read_frag(it, std::integral_constant<int, CH + 1>{}, k);
+                    // two row blocks: the four steps' registers are free once their MFMAs are issued
+                    if constexpr ((OF_THIS || OF_NEXT) && (MB == 4 || j == 1)) {
+                        constexpr int at = OF_NEXT ? s : 4 + s;
+                        u32x4& to = b[MB == 2 ? s : at];
+                        if (MB == 2 || j == 0) {
+                            n = Nibbles((OF_NEXT ? next : cur).w[at & 1][at >> 1]);
+                            n.first(to);
+                        }
+                        if (j == 1) {
+                            n.second(to);
+                            asm volatile("" : "+v"(to));  // (here, not in front of its use: the codes' registers are wanted)
+                        }
+                    }
+                    if constexpr (MB == 4 && (CH == 0 || CH == 3)) {
+                        constexpr int from = CH == 0 ? 2 : 0;
+#pragma unroll
+                        for (int i = 4 * K; i < 4 * K + 4; ++i)
+                            acc[from + i / 16][i % 16] = __builtin_fmaf(sc, t[from + i / 16][i % 16], acc[from + i / 16][i % 16]);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 });
-                if constexpr (half == 1) {
-                    if (live) {
+                // (a K share past the end of the range adds zero times the sum of a group that another share adds)
+                if constexpr (CH == CHUNKS - 2) sc = gs0 + it * WK + wk < gs1 ? cur.sc : 0.f;
+                if constexpr (MB == 2 && LAST) {
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
+                    for (int j = 0; j < 2; ++j)
 #pragma unroll
-                            for (int i = 0; i < 16; ++i)
-                                acc[2 * pair + j][i] = __builtin_fmaf(cur.sc, t[t0 + j][i], acc[2 * pair + j][i]);
-                    }
+                        for (int i = 0; i < 16; ++i) acc[j][i] = __builtin_fmaf(sc, t[j][i], acc[j][i]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }(std::integral_constant<int, CHI>{}), ...);
         }(std::make_integer_sequence<int, CHUNKS>{});
     };
     int it = 0;
     auto turn = [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
-        ((it < iters ? (iteration(std::integral_constant<int, I>{}, it), ++it) : 0), ...);
+        return ((iteration(std::integral_constant<int, I>{}, it), ++it < iters) && ...);
     };
-    while (it < iters) turn(std::make_integer_sequence<int, BUFS>{});
+    while (turn(std::make_integer_sequence<int, BUFS>{})) {}
 
     wait_vmcnt<0>();  // (the last loads still write to the ring)
+    if constexpr (MB == 4)
+#pragma unroll
+        for (int j = 2; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[j][i] = __builtin_fmaf(sc, t[j][i], acc[j][i]);
 
     // ---- sums of the K shares in order, then the epilogue, a row block at a time ----
     if constexpr (EPI == EPI_PARTIAL && WK == 1) {
