@@ -29,7 +29,7 @@
 // Key splits.  A decode-sized chunk behind a long cached sequence (Sec. V: a few tokens per step against the whole
 // prompt and everything generated so far) has one query block per head, far fewer workgroups than the chip has
 // CUs, and each would walk the whole cache alone.  Such a launch splits the key tiles of a query block into up to 8
-// contiguous ranges, one workgroup each (blockIdx.y).  Every workgroup leaves its un-normalised result and softmax
+// contiguous ranges, one workgroup each (blockIdx.z).  Every workgroup leaves its un-normalised result and softmax
 // statistics in a scratch buffer and counts itself in; the one that finds all others counted merges the ranges IN
 // RANGE ORDER with the log-sum-exp weights and writes the output, so the result does not depend on which workgroup
 // came last (bitwise reproducible), no workgroup ever waits for another, and there is no second launch.
@@ -182,11 +182,15 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
     const int g = wave % KP, qb = loader ? 0 : wave / KP;
     const int lpart = LPQ == 2 ? (wave - KP * NQ) / KP : -1;  // loader: 0 = K only, 1 = V only, -1 = both
     const int c = lane & 31, hh = lane >> 5;
-    const int head = blockIdx.x % n_heads;
+    // grid: heads x query blocks (of all branches) x key ranges (no division in front of the first load of a single chunk)
+    const int head = blockIdx.x, block = blockIdx.y * n_heads + head;
     const int q_blocks = (n + NQ * 32 - 1) / (NQ * 32);
-    const int bq = blockIdx.x / n_heads;
-    const int branch = bq / q_blocks;  // 0 without a branch table
-    const int q0 = (q_blocks - 1 - bq % q_blocks) * (NQ * 32);
+    int branch = 0, bq = blockIdx.y;
+    if (branches) {
+        branch = bq / q_blocks;
+        bq -= branch * q_blocks;
+    }
+    const int q0 = (q_blocks - 1 - bq) * (NQ * 32);
     const int row0 = branch * n;
     // (the same for every lane; read out of the vector registers a table load leaves them in, which the tile loop
     // cannot spare)
@@ -211,15 +215,18 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
     const size_t plane_v = ((size_t)layer * 2 + 1) * n_heads + head;
 
     // key splits over workgroups: this one owns the tiles [t_lo, t_hi) of the query block
-    // (never more than the launch provides: a launch that does not split has gridDim.y = 1)
+    // (never more than the launch provides: a launch that does not split has gridDim.z = 1)
     // Ranges are dealt by 64 queries whatever NQ: 32-query workgroups (a chunk of 65 to 128 tokens alone) then sum the same
     // ranges as 64-query ones (the same chunk in a batch of branches).
     const int range_tiles = NQ == 1 ? (pos0 + min((q0 | 63) + 1, n) + kKT - 1) / kKT : n_tiles;
-    const int n_splits = min(att_key_splits(n, range_tiles), (int)gridDim.y);
-    const int ks = blockIdx.y;
+    const int n_splits = min(att_key_splits(n, range_tiles), (int)gridDim.z);
+    const int ks = blockIdx.z;
     if (ks >= n_splits) return;  // (a branch or query block with fewer keys than the longest of the launch)
-    const int t_lo = (int)((long)ks * range_tiles / n_splits);
-    const int t_hi = min((int)((long)(ks + 1) * range_tiles / n_splits), n_tiles);
+    int t_lo = 0, t_hi = n_tiles;
+    if (n_splits > 1) {
+        t_lo = (unsigned)(ks * range_tiles) / (unsigned)n_splits;  // at most 4 x 2^26
+        t_hi = min((int)((unsigned)((ks + 1) * range_tiles) / (unsigned)n_splits), n_tiles);
+    }
     const int n_own = t_hi - t_lo;
     const int cnt = n_own > g ? (n_own - g + KP - 1) / KP : 0;  // tiles of this key partition
     const int max_cnt = (n_own + KP - 1) / KP;                  // of partition 0: every wave runs that many rounds
@@ -434,7 +441,7 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
                     make_float4(oacc[db][4 * gg] * wscale, oacc[db][4 * gg + 1] * wscale,
                                 oacc[db][4 * gg + 2] * wscale, oacc[db][4 * gg + 3] * wscale);
         if (n_splits > 1 && g == 0 && hh_m == 0) {  // statistics of this key range, one pair per query row
-            store_coherent2(split_buf + ((size_t)(blockIdx.x * gridDim.y + ks) * QR + qb * 32 + c_m) * kAttSplitRow + 128,
+            store_coherent2(split_buf + ((size_t)(block * gridDim.z + ks) * QR + qb * 32 + c_m) * kAttSplitRow + 128,
                             m_all, l_all);
         }
     }
@@ -452,7 +459,7 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
             b.x += b2.x; b.y += b2.y; b.z += b2.z; b.w += b2.w;
         }
         if (n_splits > 1) {
-            float* dst = split_buf + ((size_t)(blockIdx.x * gridDim.y + ks) * QR + qr) * kAttSplitRow + ch * 8;
+            float* dst = split_buf + ((size_t)(block * gridDim.z + ks) * QR + qr) * kAttSplitRow + ch * 8;
             store_coherent2(dst, a.x, a.y);
             store_coherent2(dst + 2, a.z, a.w);
             store_coherent2(dst + 4, b.x, b.y);
@@ -466,7 +473,7 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
     }
     if (n_splits == 1) return;
 
-    merge_key_ranges<QR, 64 * KP * NQ>(tid_m, (int*)(lds + kStatOffset), split_buf, split_count, blockIdx.x, gridDim.y, n_splits, q0, n, row0, head,
+    merge_key_ranges<QR, 64 * KP * NQ>(tid_m, (int*)(lds + kStatOffset), split_buf, split_count, block, gridDim.z, n_splits, q0, n, row0, head,
                                        d_model, o);
 }
 
@@ -828,7 +835,7 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     // the CUs idle: 33.7 vs 20.1 us at 512 queries over 1536 cached keys); beside other chunks it takes a sixth less
     // CU time: 4 x 512 tokens +2.4 %, no difference at 256-token chunks.
     if (shared_gpu && n > 256) {
-        hipLaunchKernelGGL((chunk_attention_bf16<4, 2, 2>), dim3((n + 127) / 128 * n_heads), dim3(768), kAttLds, s, q, o,
+        hipLaunchKernelGGL((chunk_attention_bf16<4, 2, 2>), dim3(n_heads, (n + 127) / 128), dim3(768), kAttLds, s, q, o,
                            n, d_model, n_heads, pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
         return hipGetLastError();
     }
@@ -848,12 +855,12 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     } else if (n <= 128 && !shared_gpu) {
         const int wgs = (n + 31) / 32 * n_heads;
         if (!split_fits(sc, wgs, splits, 32)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((chunk_attention_bf16<1, 2>), dim3(wgs, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        hipLaunchKernelGGL((chunk_attention_bf16<1, 2>), dim3(n_heads, (n + 31) / 32, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
     } else {
         const int wgs = (n + 63) / 64 * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(chunk_attention_bf16<2>, dim3(wgs, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        hipLaunchKernelGGL(chunk_attention_bf16<2>, dim3(n_heads, (n + 63) / 64, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
     }
     return hipGetLastError();
@@ -873,7 +880,7 @@ hipError_t launch_branch_attention(const u16* q, u16* o, int n, int n_branches, 
     } else {
         const int wgs = n_branches * ((n + 63) / 64) * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(chunk_attention_bf16<2>, dim3(wgs, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        hipLaunchKernelGGL(chunk_attention_bf16<2>, dim3(n_heads, n_branches * ((n + 63) / 64), splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            0, none, layer, scale_log2e, branches, no_tree, sc.split_buf, sc.split_count);
     }
     return hipGetLastError();

@@ -90,10 +90,20 @@ __device__ inline int arrive_coherent(int* counter) {
 // Waits until this wave's stores have been performed (a coherent store is performed when it is visible chip-wide).
 __device__ inline void wait_stores_performed() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup"); }
 
+// Sum over the wave, in every lane: pairs 32, 16, 8, 4, 2 and 1 lanes apart, in registers.
+template <int DPP>
+__device__ __forceinline__ float dpp_move(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), DPP, 0xf, 0xf, true));
+}
 __device__ inline float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    const u32x2 h = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+    v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    v += dpp_move<0x128>(v);  // row_ror:8
+    v += dpp_move<0x124>(v);  // row_ror:4 (lanes 8 apart are equal)
+    v += dpp_move<0x4E>(v);   // quad_perm 2, 3, 0, 1
+    return v + dpp_move<0xB1>(v);  // quad_perm 1, 0, 3, 2
 }
 
 // Cache plane (layer, K|V, head) -> row pointers.  Positions below n_shared live in the parent's buffer.
@@ -117,6 +127,17 @@ __device__ __host__ inline size_t tiled_offset(int row, int k_chunk, int k_stage
     return block * 1024 + (r >> 2) * 128 + ((((r & 3) << 2) + ch) ^ ((r >> 2) & 3)) * 8;
 }
 
+// x / d by a multiplication (a division by a run-time value is 20 dependent instructions, and in front of the first load of a
+// short kernel every instruction counts).  Exact for x * d < 2^32.
+struct Quotient {
+    unsigned d, mul;
+    __host__ void set(int by) {
+        d = by;
+        mul = 0xFFFFFFFFu / d + 1;
+    }
+    __device__ __forceinline__ int of(int x) const { return d == 1 ? x : (int)__umulhi((unsigned)x, mul); }
+};
+
 // ---- GEMM (bf16_gemm.hip) -----------------------------------------------------------------------
 enum { EPI_QKV = 0, EPI_PARTIAL = 1, EPI_SWIGLU = 2 };
 
@@ -128,6 +149,7 @@ struct GemmArgs {
     int M, N, K;
     int n_tok;             // 4-bit stages only: rows of one chunk or branch (M, or M / number of branches)
     int m_tiles, n_tiles, splits;  // grid = m_tiles * n_tiles * splits workgroups
+    Quotient by_m, by_n, by_splits;  // the three as divisors
     int n_stride;                  // columns between consecutive N tiles (tile width actually owned)
     int kt_per_split;              // K tiles of 32 per split
     // EPI_QKV
@@ -162,7 +184,7 @@ struct RowArgs {
     const void* W;         // [N, K] tiled bf16, or packed 4-bit codes
     const float* w_scale;  // 4-bit stages only
     int M, N, K;
-    int splits;            // of K: row_splits(N), 4-bit stages w4_plan_splits(N, K)
+    int splits;            // of K: row_splits(N), 4-bit stages w4_plan_splits(16, N, K)
     // launch_project_rows
     float* x32;            // [M, N] residual stream: read, and written unless out is set
     const u16* gain;       // gain of the norm that follows
@@ -180,8 +202,8 @@ hipError_t launch_project_split(const RowArgs& a, hipStream_t s);
 // squares of 16 consecutive features, four neighbouring lanes holding four each ...
 __device__ __forceinline__ float sum_squares_16(float4 x) {
     float s = __builtin_fmaf(x.w, x.w, __builtin_fmaf(x.z, x.z, __builtin_fmaf(x.y, x.y, x.x * x.x)));
-    s += __shfl_xor(s, 1, 64);
-    return s + __shfl_xor(s, 2, 64);
+    s += dpp_move<0xB1>(s);         // one lane further
+    return s + dpp_move<0x4E>(s);  // two
 }
 // ... and a wave per row over its d / 16 partial sums (at most 512), lane t adding those number t, t + 64, ... in order.
 __device__ __forceinline__ float row_scale(float lane_sum, int d, float eps) {
@@ -193,11 +215,14 @@ template <int WAVES>
 struct RowScale {
     static constexpr int ROWS = (kMaxProjectRows + WAVES - 1) / WAVES;
     float v[ROWS][8];
+    // ALL: also the loads a narrow stage has no use for, so that the compiler knows how many are in flight in front of the
+    // caller's next ones (else finish() waits for those, too)
+    template <bool ALL = false>
     __device__ __forceinline__ void begin(const float* ssq, int rows, int wave, int lane, int d) {
         const int n = d / 16;
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            if (64 * k < n) {
+            if (ALL || 64 * k < n) {
                 const int j = min(lane + 64 * k, n - 1);
 #pragma unroll
                 for (int i = 0; i < ROWS; ++i) v[i][k] = ssq[(size_t)min(wave + WAVES * i, rows - 1) * n + j];
@@ -256,9 +281,10 @@ __device__ __forceinline__ float w4_group(float acc, float scale, float t, float
 
 // ---- projections of a 4-bit stage (w4_gemm.hip) ----------------------------------------------------
 // epi: EPI_QKV, EPI_SWIGLU or EPI_PARTIAL; the tiling fields of `a` are filled here.  EPI_PARTIAL writes
-// w4_partial_splits(n_tok, N, K) partial buffers, w4_plan_splits(N, K) of them up to 32 tokens.
+// w4_partial_splits(n_tok, N, K) partial buffers, w4_plan_splits(n_tok, N, K) of them up to 32 tokens.
 int w4_partial_splits(int n_tok, int N, int K);
-int w4_plan_splits(int N, int K);
+int w4_plan_splits(int n_tok, int N, int K);
+int w4_rows(int M, int N, int K, int splits);  // rows per workgroup of the kernel of decode-sized chunks: 16, 32 or 64
 // the kernel of longer chunks and branches (w4_wide.hip), and which projections take it
 bool w4_is_wide(int epi, int n_tok, int N, int K);
 int w4_wide_splits(int n_tok, int N, int K);

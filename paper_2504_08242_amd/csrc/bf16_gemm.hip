@@ -151,10 +151,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
         const int q = gridDim.x >> 3, r = gridDim.x & 7;
         const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
         const int tile = xcd * q + min(xcd, r) + local;
-        mt = tile % a.m_tiles;
-        grp = tile / a.m_tiles;
+        grp = a.by_m.of(tile);
+        mt = tile - grp * a.m_tiles;
     }
-    const int nt = grp % a.n_tiles, split = grp / a.n_tiles;
+    const int split = a.by_n.of(grp), nt = grp - split * a.n_tiles;
     const int m0 = mt * G_BM, n0 = nt * a.n_stride;
     const int KT = a.kt_per_split;
 
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
         for (int nb = 0; nb < NBW; ++nb) {
             const int col = nw0 + nb * 32;  // packed column of the block: one (q|k|v, head, j) for all lanes
             if (col >= n_end) continue;
-            const int which = col / a.d_model;
+            const int which = (col >= a.d_model) + (col >= 2 * a.d_model);
             const int in_model = col - which * a.d_model;
             const int head = in_model >> 7, j = (in_model & 127) >> 5;
             const int f_lo = which == 2 ? 32 * j + 16 * hh : 16 * j + 8 * hh;  // first feature of registers 0..7
@@ -487,6 +487,9 @@ hipError_t launch(GemmArgs a, hipStream_t s) {
     a.m_tiles = div_up(a.M, 32 * BMB);
     a.kt_per_split = a.K / G_BK / a.splits;
     const int grid = a.m_tiles * a.n_tiles * a.splits;
+    a.by_m.set(a.m_tiles);
+    a.by_n.set(a.n_tiles);
+    if ((long)grid * (a.m_tiles > a.n_tiles ? a.m_tiles : a.n_tiles) >= 1l << 32) return hipErrorInvalidValue;
     using S = Shape<BMB, NB, WM, WN>;
     hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR>), dim3(grid), dim3(S::THREADS), S::LDS_BYTES, s, a);
     return hipGetLastError();

@@ -99,8 +99,9 @@ __device__ __forceinline__ f32x4 range_bf16(const RowArgs& a, int f0, int range,
 __device__ __forceinline__ void ranges_w4(const RowArgs& a, float (*red)[16 * kRowCols], int f0, int wave, int lane) {
     const int r = lane & 15, q = lane >> 4;
     const int G = a.K / 128;
+    const int shift = __builtin_ctz(a.splits);  // (a power of two)
     auto first_group = [&](int R) {  // of range R: wave R % 8 of split R / 8
-        const int split = R >> 3, ws0 = split * G / a.splits, ws1 = (split + 1) * G / a.splits;
+        const int split = R >> 3, ws0 = split * G >> shift, ws1 = (split + 1) * G >> shift;
         return ws0 + (R & 7) * (ws1 - ws0) / kRanges;
     };
     const int tile = f0 >> 6, cg = (f0 >> 4) & 3;  // 64-column tile of the packed codes, 16-column block in it
@@ -117,36 +118,72 @@ __device__ __forceinline__ void ranges_w4(const RowArgs& a, float (*red)[16 * kR
         bf16x8 a[4];
     };
     auto load = [&](Group& d, int g) __attribute__((always_inline)) {
-        d.w = load_once_at<u32x4>(w_block + (size_t)g * 4096, w_lane);
-        d.sc = load_at<float>(s_block + (size_t)g * 256, s_lane);
+        d.w = load_once_at<u32x4>(w_block, w_lane + (unsigned)g * 4096);
+        d.sc = load_at<float>(s_block, s_lane + (unsigned)g * 256);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
-            d.a[ks] = load_at<bf16x8>((const char*)a.A + (size_t)(4 * g + ks) * 2048, a_lane);
+            d.a[ks] = load_at<bf16x8>((const char*)a.A, a_lane + (unsigned)(4 * g + ks) * 2048);
     };
+    // SETS groups in flight per wave, each set of registers filled again as soon as its products are issued.
     int g = first_group(wave * a.splits);
     const int g1 = first_group((wave + 1) * a.splits);
-    Group cur, next, far;  // three groups in flight per wave
-    if (g < g1) load(cur, g);
-    if (g + 1 < g1) load(next, g + 1);
-    for (int R = wave * a.splits; R < (wave + 1) * a.splits; ++R) {
-        const int end = first_group(R + 1);
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (; g < end; ++g) {
-            if (g + 2 < g1) load(far, g + 2);
-            f32x4 t = {0.f, 0.f, 0.f, 0.f}, rs = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                rs = mfma16(cur.a[ks], ones, rs);
-                t = mfma16(cur.a[ks], w4_expand(cur.w[ks], bits), t);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = w4_group(acc[i], cur.sc, t[i], rs[i]);
-            cur = next;
-            next = far;
-        }
+    int R = wave * a.splits, end = first_group(R + 1);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto close = [&]() __attribute__((always_inline)) {  // the sum of range R is complete
 #pragma unroll
         for (int i = 0; i < 4; ++i) red[R][(4 * q + i) * kRowCols + r] = acc[i];
+        acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        end = first_group(++R + 1);
+    };
+    auto multiply = [&](const Group& d, int at) __attribute__((always_inline)) {
+        while (at == end) close();  // (ranges may be empty)
+        f32x4 t = {0.f, 0.f, 0.f, 0.f}, rs = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            rs = mfma16(d.a[ks], ones, rs);
+            t = mfma16(d.a[ks], w4_expand(d.w[ks], bits), t);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = w4_group(acc[i], d.sc, t[i], rs[i]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int SETS = 4;
+    Group set[SETS];
+    if (g1 - g < SETS) {
+        // (a path of its own: the compiler counts the loads in flight path by path, and where they may or may not be there it
+        // waits for all)
+#pragma unroll
+        for (int i = 0; i < SETS - 1; ++i)
+            if (g + i < g1) load(set[i], g + i);
+#pragma unroll
+        for (int i = 0; i < SETS - 1; ++i)
+            if (g + i < g1) multiply(set[i], g + i);
+    } else {
+#pragma unroll
+        for (int i = 0; i < SETS; ++i) {
+            load(set[i], g + i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        for (; g + 2 * SETS - 1 < g1; g += SETS) {
+#pragma unroll
+            for (int i = 0; i < SETS; ++i) {
+                multiply(set[i], g + i);
+                load(set[i], g + SETS + i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const int left = g1 - g;  // SETS to 2 SETS - 1
+#pragma unroll
+        for (int i = 0; i < SETS; ++i) {
+            multiply(set[i], g + i);
+            if (i + SETS < left) load(set[i], g + SETS + i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < SETS - 1; ++i)
+            if (i + SETS < left) multiply(set[i], g + SETS + i);
     }
+    while (R < (wave + 1) * a.splits) close();
 }
 
 // x += eight range sums, PER of them to a split; HALVES: the two halves of a split are added up first
@@ -175,11 +212,15 @@ __global__ __launch_bounds__(64 * kRanges) void project_rows(const RowArgs a) {
     float (*red)[16 * kRowCols] = (float (*)[16 * kRowCols])red_lds;
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // four features of one row per thread of the first wave: the residual is on its way while the products run
+    // four features of one row per thread of the first wave: residual and gain are on their way while the products run
     const int row = tid >> 2, col = blockIdx.x * kRowCols + 4 * (tid & 3);
     const bool mine = tid < 64 && row < a.M;
     float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (mine) x = *(const float4*)(a.x32 + (size_t)row * a.N + col);
+    u32x2 g = {0, 0};
+    if (mine) {
+        x = *(const float4*)(a.x32 + (size_t)row * a.N + col);
+        if (a.gain) g = *(const u32x2*)(a.gain + col);
+    }
     if constexpr (W4) {
         ranges_w4(a, red, blockIdx.x * kRowCols, wave, lane);
     } else {
@@ -206,7 +247,6 @@ __global__ __launch_bounds__(64 * kRanges) void project_rows(const RowArgs a) {
         return;
     }
     *(float4*)(a.x32 + (size_t)row * a.N + col) = x;
-    const u32x2 g = *(const u32x2*)(a.gain + col);
     u32x2 o;
     o[0] = pack_bf16x2(x.x * __uint_as_float(g[0] << 16), x.y * __uint_as_float(g[0] & 0xffff0000u));
     o[1] = pack_bf16x2(x.z * __uint_as_float(g[1] << 16), x.w * __uint_as_float(g[1] & 0xffff0000u));
@@ -248,7 +288,7 @@ __global__ __launch_bounds__(256 * GROUPS) void project_split(const RowArgs a) {
     const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
     const int wave8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = wave8 >> 2, wave = wave8 & 3, wm = wave & 1, wn = wave >> 1;
-    const int KT = a.K / 32, split = blockIdx.y, per = kRanges / a.splits / GROUPS;  // ranges per group
+    const int KT = a.K / 32, split = blockIdx.y, per = kRanges / GROUPS >> __builtin_ctz(a.splits);  // ranges per group
     auto range_start = [&](int range) { return range * KT / kRanges; };
     auto count_of = [&](int g) { return range_start((split * GROUPS + g + 1) * per) - range_start((split * GROUPS + g) * per); };
     int range = (split * GROUPS + group) * per;
@@ -355,7 +395,7 @@ __global__ __launch_bounds__(256 * GROUPS) void project_split(const RowArgs a) {
 
 bool bad(bool w4, const RowArgs& a, int rows) {
     return a.M < 1 || a.M > rows || a.N % 64 || a.N > 8192 || a.K % (w4 ? 128 : 32) || a.splits < 1 ||
-           a.splits > kMaxRowSplits || (!w4 && a.splits != row_splits(a.N));
+           a.splits > kMaxRowSplits || (a.splits & (a.splits - 1)) || (!w4 && a.splits != row_splits(a.N));
 }
 
 }  // namespace

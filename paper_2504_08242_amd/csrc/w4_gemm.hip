@@ -102,10 +102,12 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
     __shared__ float scale_of_row[16];  // 1 / rms of up to 16 rows that come with partial sums of squares
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
-    const int tile = blockIdx.x % a.n_tiles, split = blockIdx.x / a.n_tiles, rg0 = blockIdx.y * RG;
+    const int tile = blockIdx.x, split = blockIdx.y, rg0 = blockIdx.z * RG;
     const int G = a.K / W4_GROUP;
     // K groups of this workgroup, then of this wave (floor division: the shares differ by at most one group)
-    const int ws0 = (int)((long)split * G / a.splits), ws1 = (int)((long)(split + 1) * G / a.splits);
+    // (splits is a power of two: 64-bit and other divisions here were 300 scalar instructions in front of the first load)
+    const int shift = EPI == EPI_PARTIAL ? __builtin_ctz(a.splits) : 0;
+    const int ws0 = split * G >> shift, ws1 = (split + 1) * G >> shift;
     const int cnt = ws1 - ws0;
     const int g0 = ws0 + wave * cnt / WAVES, g1 = ws0 + (wave + 1) * cnt / WAVES;
 
@@ -118,8 +120,9 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
     unsigned a_lane[RG];
 #pragma unroll
     for (int j = 0; j < RG; ++j) a_lane[j] = 2 * (unsigned)tiled_offset(min(16 * (rg0 + j) + r, a.M - 1), q, k_stages);
-    const char* wbase = (const char*)a.W + (size_t)tile * G * 4096;
-    const char* sbase = (const char*)(a.w_scale + (size_t)tile * G * 64);
+    // (constant bases and 32-bit offsets: left to move the bases along, the compiler holds 64-bit addresses per lane)
+    const char* wbase = uniform_ptr((const char*)a.W + (size_t)tile * G * 4096);
+    const char* sbase = uniform_ptr((const char*)(a.w_scale + (size_t)tile * G * 64));
     const W4Bits bits;
     // STREAM_ONCE (one pass over the codes, up to 64 rows): every code is read exactly once, with the non-temporal hint,
     // so that the stream does not push the KV cache and the activations out of the caches (measured at 5 rows per call:
@@ -129,17 +132,17 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
     auto fetch_codes = [&](W4Codes& d, int g) __attribute__((always_inline)) {
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg) {
-            const char* src = wbase + (size_t)g * 4096 + cg * 1024;
-            d.w[cg] = STREAM_ONCE ? load_once_at<u32x4>(src, lane * 16) : load_at<u32x4>(src, lane * 16);
+            const unsigned at = (unsigned)g * 4096 + lane * 16 + cg * 1024;
+            d.w[cg] = STREAM_ONCE ? load_once_at<u32x4>(wbase, at) : load_at<u32x4>(wbase, at);
         }
-        d.sc = load_at<f32x4>(sbase + (size_t)g * 256, r * 16);
+        d.sc = load_at<f32x4>(sbase, (unsigned)g * 256 + r * 16);
     };
     auto fetch_rows = [&](W4Rows<RG>& d, int g) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < RG; ++j)
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks)
-                d.a[j][ks] = load_at<bf16x8>((const char*)a.A + (size_t)g * 8192 + ks * 2048, a_lane[j]);
+                d.a[j][ks] = load_at<bf16x8>((const char*)a.A, a_lane[j] + (unsigned)g * 8192 + ks * 2048);
     };
 
     f32x4 acc[RG][4];
@@ -161,54 +164,93 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
         const f32x4 sc = c.sc;
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg) {
-            bf16x8 b[4];  // one expansion of the codes serves every row group
+            f32x4 t[RG];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) b[ks] = w4_expand(c.w[cg][ks], bits);
+            for (int j = 0; j < RG; ++j) t[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < RG; ++j) {
-                f32x4 t = {0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < 4; ++ks) {  // one expansion of the codes serves every row group
+                const bf16x8 b = w4_expand(c.w[cg][ks], bits);
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d.a[j][ks], b[ks], t, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[j][cg][i] = w4_group(acc[j][cg][i], sc[cg], t[i], rs[j][i]);
+                for (int j = 0; j < RG; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d.a[j][ks], b, t[j], 0, 0, 0);
+                if (RG == 1 && (ks & 1)) __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+            for (int j = 0; j < RG; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[j][cg][i] = w4_group(acc[j][cg][i], sc[cg], t[j][i], rs[j][i]);
             // 64 rows: one column block's expansion at a time.  Free to overlap them the compiler takes 250 registers, two waves
             // of which are a whole SIMD: not even a one-wave kernel of another stream fits beside a workgroup then, it keeps
             // a CU to itself, and a grid of 256 workgroups (O, down) takes a second round.  228 as here: 64-row call of
-            // eight layers beside such a kernel 879 -> 786 us, alone 776 -> 772.
+            // eight layers beside such a kernel 879 -> 786 us, alone 776 -> 772.  (16 rows: half a block at a time, for the
+            // same reason: four waves of 128 registers.)
             if (RG == 4) __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // Two groups of codes (from HBM) in flight per wave: the next one is fetched before the current one is used.
-    // (Four in flight, a wave's whole share of K on the 7B shapes, measured no faster where the grid still fits one
-    // round of workgroups -- QKV 13.3 vs 13.0 us, down 11.6 vs 11.8 us at 5 rows -- and slower for gate/up, 20.5 vs
-    // 18.3 us: 216 registers per lane leave one workgroup per CU and its 344 workgroups then take two rounds.)  The
-    // rows of A (from L2) travel with them while the registers allow it (up to 32 rows); with 64 rows they are
-    // fetched when their group's turn comes, behind the prefetch of the next codes.
-    constexpr bool ROWS_AHEAD = RG <= 2;
-    W4Codes cur, nxt;
-    W4Rows<RG> rows, rows_nxt;
     const bool scaled = RG == 1 && EPI != EPI_PARTIAL && a.ssq;  // (the barriers in front of the epilogue publish the factors)
     RowScale<WAVES> sq;
-    if (scaled) sq.begin(a.ssq, a.M, wave, lane, a.K);
-    if (g0 < g1) {
-        fetch_codes(cur, g0);
-        if (ROWS_AHEAD) fetch_rows(rows, g0);
-    }
-    if (scaled) sq.finish(scale_of_row, a.M, wave, lane, a.K, a.rms_eps);  // (behind the loop its registers would spill)
-    for (int g = g0; g < g1; ++g) {
-        if (g + 1 < g1) {
-            fetch_codes(nxt, g + 1);
-            if (ROWS_AHEAD) fetch_rows(rows_nxt, g + 1);
+    if (scaled) sq.template begin<true>(a.ssq, a.M, wave, lane, a.K);
+    if constexpr (RG <= 2) {
+        // Two groups in flight per wave, codes (from HBM) and rows (from L2), in two sets of registers that take turns: a
+        // set is filled again as soon as its products are issued.  (As one set that is copied to the other the loads of a
+        // group only started when the group before had landed, one trip to HBM per group: gate/up of one row of the 7B
+        // shapes 14.2 -> 11.9 us, QKV 9.3 -> 8.1.)
+        struct Group {
+            W4Codes c;
+            W4Rows<RG> r;
+        };
+        Group even, odd;
+        auto fetch = [&](Group& d, int g) __attribute__((always_inline)) {
+            fetch_codes(d.c, g);
+            fetch_rows(d.r, g);
+        };
+        // (a path of its own for a wave's only group: the compiler counts the loads in flight path by path, and where they may or
+        // may not be there it waits for all)
+        auto factors = [&]() __attribute__((always_inline)) {
+            if (scaled) sq.finish(scale_of_row, a.M, wave, lane, a.K, a.rms_eps);  // (behind the loop its registers would spill)
+        };
+        if (g0 + 1 >= g1) {
+            if (g0 < g1) fetch(even, g0);
+            factors();
+            if (g0 < g1) compute(even.c, even.r);
+        } else {
+            int g = g0;
+            fetch(even, g);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_codes(odd.c, g + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            factors();  // (in front of the rows: their registers are not there yet)
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_rows(odd.r, g + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            for (; g + 3 < g1; g += 2) {  // (fences: left alone the scheduler puts both products in front of both fetches)
+                compute(even.c, even.r);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(even, g + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(odd.c, odd.r);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(odd, g + 3);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            compute(even.c, even.r);  // two or three are left
+            if (g + 2 < g1) fetch(even, g + 2);
+            compute(odd.c, odd.r);
+            if (g + 2 < g1) compute(even.c, even.r);
         }
-        if (!ROWS_AHEAD) {
+    } else {
+        // 64 rows: the next codes are on their way while the current ones are used; the rows are fetched when their group's
+        // turn comes.
+        W4Codes cur, nxt;
+        W4Rows<RG> rows;
+        if (g0 < g1) fetch_codes(cur, g0);
+        for (int g = g0; g < g1; ++g) {
+            if (g + 1 < g1) fetch_codes(nxt, g + 1);
             fetch_rows(rows, g);
             __builtin_amdgcn_sched_barrier(0);  // all on their way before the first wait (gate/up of 512 rows: 157 us, else 168)
+            compute(cur, rows);
+            cur = nxt;
         }
-        compute(cur, rows);
-        cur = nxt;
-        if (ROWS_AHEAD) rows = rows_nxt;
     }
 
     // ---- per row group: sum over the waves (fixed order), then the epilogue, one output row per wave and pass ----
@@ -218,6 +260,12 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
 #pragma unroll
     for (int j = 0; j < RG; ++j) {
         if (j > 0) __syncthreads();  // the sums of the row group before have been read
+        float2 cs[16 / WAVES];       // rotary table of this wave's rows, on its way while the sums meet
+        const int rr = col & 15, feature = rr < 8 ? ((col & 127) >> 4) * 8 + rr : 64 + ((col & 127) >> 4) * 8 + (rr - 8);
+        if constexpr (EPI == EPI_QKV)
+#pragma unroll
+            for (int pass = 0; pass < 16 / WAVES; ++pass)
+                cs[pass] = a.rope[(size_t)min(16 * (rg0 + j) + wave + WAVES * pass, a.M - 1) * 64 + (feature & 63)];
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg)
 #pragma unroll
@@ -235,23 +283,19 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
             if (EPI == EPI_PARTIAL) {
                 if (row < a.M) a.partial[((size_t)split * a.M + row) * a.N + col] = v;
             } else if (EPI == EPI_SWIGLU) {
-                const float up = __shfl_xor(v, 1, 64);  // the odd neighbour holds the up projection of the same output
+                const float up = dpp_move<0xB1>(v);  // the odd neighbour holds the up projection of the same output
                 if (!(n & 1) && row < a.M) {
                     const int oc = col >> 1;  // output feature
                     a.act[tiled_offset(row, oc >> 3, (a.N >> 1) >> 5) + (oc & 7)] =
                         f2bf(v * __builtin_amdgcn_rcpf(1.0f + __expf(-v)) * up);
                 }
             } else {  // EPI_QKV
-                const float other = __shfl_xor(v, 8, 64);  // rotary partner (lanes 0..7 <-> 8..15 of a 16-column block)
-                const int which = col / a.d_model;
+                const float other = dpp_move<0x128>(v);  // rotary partner (lanes 0..7 <-> 8..15 of a 16-column block)
+                const int which = (col >= a.d_model) + (col >= 2 * a.d_model);
                 const int in = col - which * a.d_model;
-                const int head = in >> 7, u = (in & 127) >> 4, rr = in & 15;
-                const int feature = rr < 8 ? 8 * u + rr : 64 + 8 * u + (rr - 8);
+                const int head = in >> 7;
                 float out = v;
-                if (which != 2 && row < a.M) {
-                    const float2 cs = a.rope[(size_t)row * 64 + (feature & 63)];
-                    out = rr < 8 ? v * cs.x - other * cs.y : v * cs.x + other * cs.y;
-                }
+                if (which != 2) out = rr < 8 ? v * cs[pass].x - other * cs[pass].y : v * cs[pass].x + other * cs[pass].y;
                 if (row < a.M) {
                     u16* dst;
                     if (which == 0) {
@@ -280,40 +324,54 @@ hipError_t launch_rg(GemmArgs a, hipStream_t s) {
     constexpr int WAVES = W4_WAVES;
     a.n_tiles = a.N / W4_TILE_N;
     a.m_tiles = (a.M + 16 * RG - 1) / (16 * RG);
-    const dim3 grid(a.n_tiles * a.splits, a.m_tiles);
+    const dim3 grid(a.n_tiles, a.splits, a.m_tiles);
     if (a.m_tiles == 1 && !a.shared_gpu) hipLaunchKernelGGL((gemm_w4<EPI, RG, WAVES, true>), grid, dim3(64 * WAVES), 0, s, a);
     else hipLaunchKernelGGL((gemm_w4<EPI, RG, WAVES, false>), grid, dim3(64 * WAVES), 0, s, a);
     return hipGetLastError();
 }
-// Rows per pass over the codes: 16, 32 or 64 (more rows, in batches of branches of up to 32 tokens, take several passes of 64).
 template <int EPI>
 hipError_t launch_one(GemmArgs a, hipStream_t s) {
-    if (a.M <= 16) return launch_rg<EPI, 1>(a, s);
-    if (a.M <= 32) return launch_rg<EPI, 2>(a, s);
-    return launch_rg<EPI, 4>(a, s);
+    const int rows = w4_rows(a.M, a.N, a.K, a.splits);
+    return rows == 16 ? launch_rg<EPI, 1>(a, s) : rows == 32 ? launch_rg<EPI, 2>(a, s) : launch_rg<EPI, 4>(a, s);
 }
 
 }  // namespace
 
+// Rows per workgroup, by rounds of workgroups: one per CU with 64 or 32 rows, two with 16.  16 where that is one workgroup per
+// CU, or where a wave has a single K group and two workgroups fit; then 32 (whose codes are expanded once for twice the
+// rows); then 16 on two workgroups per CU; then 64.  Measured on one MI355X (us): QKV of d_model 1024, 64 rows, 64 -> 16 per
+// workgroup 9.4 -> 4.7; of d_model 2048, 64 -> 32 12.7 -> 7.4; O of d_model 5120, 48 rows, 64 -> 16 12.1 -> 9.5; O of the 7B
+// shapes, 32 rows (one group per wave), 32 -> 16 5.6 -> 4.9, but QKV of those (four groups) 12.2 -> 13.3.  Whatever the rows, a
+// result's sums are the same.
+int w4_rows(int M, int N, int K, int splits) {
+    const int wgs = N / W4_TILE_N * splits, groups = (K / W4_GROUP + splits * W4_WAVES - 1) / (splits * W4_WAVES);
+    const int at_16 = wgs * ((M + 15) / 16), at_32 = wgs * ((M + 31) / 32);
+    if (M <= 16 || at_16 <= 256 || (groups == 1 && at_16 <= 512)) return 16;
+    if (M <= 32 || at_32 <= 256) return 32;
+    return at_16 <= 512 ? 16 : 64;
+}
+
 // Splits of K for the projections back to d_model (their N / 64 column tiles alone do not occupy the chip): as many
 // as keep the grid within about one workgroup per CU, at most 8 (the reduce + norm pass sums up to 8 partial
-// buffers), and no more than there are K groups.
-int w4_plan_splits(int N, int K) {
+// buffers), and no more than leave every wave a K group: with fewer groups than waves a split only adds partial sums
+// (and ranges to add up: one row of six layers of d_model 1024 157 -> 148 us).  More than
+// 16 tokens, whose rows weigh on the path from L2, spread over the CUs all the same.
+int w4_plan_splits(int n_tok, int N, int K) {
     const int tiles = N / W4_TILE_N, G = K / W4_GROUP;
     int splits = 1;
-    while (splits < 8 && tiles * splits * 2 <= 256 && splits * 2 <= G) splits *= 2;
+    while (splits < 8 && tiles * splits * 2 <= 256 && splits * 2 * (n_tok <= kMaxProjectRows ? W4_WAVES : 1) <= G) splits *= 2;
     return splits;
 }
 
 int w4_partial_splits(int n_tok, int N, int K) {
-    return w4_is_wide(EPI_PARTIAL, n_tok, N, K) ? w4_wide_splits(n_tok, N, K) : w4_plan_splits(N, K);
+    return w4_is_wide(EPI_PARTIAL, n_tok, N, K) ? w4_wide_splits(n_tok, N, K) : w4_plan_splits(n_tok, N, K);
 }
 
 hipError_t launch_gemm_w4(int epi, GemmArgs a, hipStream_t s) {
     if (a.M <= 0 || a.n_tok <= 0 || a.N % W4_TILE_N || a.K % W4_GROUP) return hipErrorInvalidValue;
     if (w4_is_wide(epi, a.n_tok, a.N, a.K)) return launch_gemm_w4_wide(epi, a, s);
     if (epi == EPI_PARTIAL) {
-        a.splits = w4_plan_splits(a.N, a.K);
+        a.splits = w4_plan_splits(a.n_tok, a.N, a.K);
         return launch_one<EPI_PARTIAL>(a, s);
     }
     a.splits = 1;

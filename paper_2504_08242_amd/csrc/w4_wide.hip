@@ -81,13 +81,13 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
         const int q = gridDim.x >> 3, r = gridDim.x & 7;
         const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
         const int tile = xcd * q + min(xcd, r) + local;
-        mt = tile % a.m_tiles;
-        grp = tile / a.m_tiles;
+        grp = a.by_m.of(tile);
+        mt = tile - grp * a.m_tiles;
     }
-    const int nt = grp % a.n_tiles, split = grp / a.n_tiles;
+    const int split = EPI == EPI_PARTIAL ? a.by_n.of(grp) : 0, nt = grp - split * a.n_tiles;
     const int m0 = mt * 32 * MB, n0 = nt * S::COLS;
     const int G = a.K / 128, KT = a.K / 32;
-    const int gs0 = split * G / a.splits, gs1 = (split + 1) * G / a.splits;
+    const int gs0 = EPI == EPI_PARTIAL ? a.by_splits.of(split * G) : 0, gs1 = EPI == EPI_PARTIAL ? a.by_splits.of((split + 1) * G) : G;
     const int iters = (gs1 - gs0 + WK - 1) / WK;
 
     const char* const rows0 = uniform_ptr((const char*)a.A + (size_t)(m0 / 32) * KT * 2048);  // first row block of the tile
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
         constexpr int pair = CH % PAIRS, half = CH / PAIRS, s = KK >> 1, j = KK & 1;
         const int st = it * PARTS + (PARTS == 2 ? half : 0);
         const unsigned char* slot = smem + st % ST * S::STAGE_BYTES + wk * S::PART_BYTES;
-        f[KK] = *(const bf16x8*)(slot + (2 * pair + j) * WK * S::PART_BYTES + ((PARTS == 1 ? 4 * half : 0) + s >> 1) * 2048 + lane_off[s & 1]);
+        f[KK] = *(const bf16x8*)(slot + (2 * pair + j) * WK * S::PART_BYTES + (((PARTS == 1 ? 4 * half : 0) + s) >> 1) * 2048 + lane_off[s & 1]);
     };
     auto for8 = [](auto fn) __attribute__((always_inline)) {
         [&]<int... K>(std::integer_sequence<int, K...>) __attribute__((always_inline)) {
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
                     *(u32x4*)(a.act + tiled_offset(m, pc >> 4, (a.N >> 1) >> 5)) = out;
                 } else {
                     // rotary indices 8 u .. 8 u + 7 of a head and their partners 64 further on
-                    const int which = pc / a.d_model, in = pc - which * a.d_model;
+                    const int which = (pc >= a.d_model) + (pc >= 2 * a.d_model), in = pc - which * a.d_model;
                     const int head = in >> 7, f = (in & 127) >> 1;
                     u32x4 lo, hi;
                     if (which == 2) {
@@ -371,7 +371,11 @@ hipError_t launch(GemmArgs a, hipStream_t s) {
     using S = WideShape<MB, WN, WK>;
     a.n_tiles = (a.N + S::COLS - 1) / S::COLS;
     a.m_tiles = (a.M + 32 * MB - 1) / (32 * MB);
+    a.by_m.set(a.m_tiles);
+    a.by_n.set(a.n_tiles);
+    a.by_splits.set(a.splits);
     const dim3 grid(a.n_tiles * a.m_tiles * a.splits);
+    if ((long)grid.x * (a.m_tiles > a.n_tiles ? a.m_tiles : a.n_tiles) >= 1l << 32) return hipErrorInvalidValue;
     if (a.m_tiles == 1 && !a.shared_gpu)
         hipLaunchKernelGGL((gemm_w4_wide<EPI, MB, WN, WK, true>), grid, dim3(S::THREADS), S::LDS_BYTES, s, a);
     else
@@ -384,16 +388,16 @@ hipError_t launch(GemmArgs a, hipStream_t s) {
 
 // A launch is priced as rounds of workgroups (one per CU) times what a round takes: turns of the loop and a fixed part.  The
 // constants are fitted to 900 timings of these shapes (33 .. 1024 rows, the projections of stages of d_model 1024, 2048,
-// 4096, 5120 and 8192, all numbers of splits): 4 % off on average; the pick costs 0.4 % more than the best shape measured
+// 4096, 5120 and 8192, all numbers of splits): 5 % off on average; the pick costs 0.4 % more than the best shape measured
 // on average and 10 % at worst.
 struct WideCost {
     int mb, wn, wk;
     float turn, round, qkv;  // us; qkv: more per round with the QKV epilogue
 };
-constexpr WideCost kWide[] = {{2, 1, 4, 1.36f, 1.6f, 1.3f}, {2, 2, 4, 1.63f, 2.3f, 1.2f}, {2, 3, 4, 2.05f, 3.1f, 1.1f},
-                              {4, 4, 2, 2.04f, 4.4f, 1.1f}, {4, 6, 1, 1.65f, 5.0f, 1.9f}, {4, 8, 1, 1.75f, 5.9f, 1.0f}};
+constexpr WideCost kWide[] = {{2, 1, 4, 1.37f, 1.4f, 1.2f}, {2, 2, 4, 1.54f, 2.3f, 1.4f}, {2, 3, 4, 1.96f, 3.1f, 1.3f},
+                              {4, 4, 2, 1.92f, 4.3f, 1.8f}, {4, 6, 1, 1.56f, 5.9f, 2.6f}, {4, 8, 1, 1.66f, 6.1f, 2.3f}};
 constexpr int kCUs = 256;
-constexpr float kLaunchUs = 3.0f, kPartRound = 0.8f;
+constexpr float kLaunchUs = 3.0f, kPartRound = 0.7f;
 constexpr float kPartialUsPerByte = 1.0f / 5.2e6f;  // what the reduce + norm pass pays to read a partial sum back
 
 int div_up(int x, int y) { return (x + y - 1) / y; }
@@ -452,23 +456,25 @@ hipError_t configure_one() {
                                S::LDS_BYTES);
 }
 
-// What a launch of w4_gemm.hip takes on 33 .. 64 rows (rounds of 64-column tiles, eight waves that split a K range).
+// What a launch of w4_gemm.hip takes on 64 rows (rounds of 64-column tiles of w4_rows rows, eight waves that split a K range;
+// fitted to the same stages within 10 %).
 float cost_of_rows(int epi, int N, int K) {
-    const int splits = epi == EPI_PARTIAL ? w4_plan_splits(N, K) : 1;
-    const float turns = (float)div_up(div_up(K / 128, splits), 8);
-    return kLaunchUs + rounds_of(N / 64 * splits) * (epi == EPI_PARTIAL ? 3.1f * turns + 2.4f : 2.9f * turns + 5.5f) +
-           (epi == EPI_PARTIAL ? 4.f * 64 * N * splits * kPartialUsPerByte : 0.f);
+    const int splits = epi == EPI_PARTIAL ? w4_plan_splits(64, N, K) : 1;
+    const int rows = w4_rows(64, N, K, splits);
+    const float groups = (float)div_up(div_up(K / 128, splits), 8);
+    const float round = rows == 64 ? 3.3f * groups + (epi == EPI_PARTIAL ? 1.5f : 2.6f) : (rows == 32 ? 1.9f : 1.0f) * groups + 0.2f;
+    return kLaunchUs + rounds_of(N / 64 * splits * (64 / rows) / (rows == 16 ? 2 : 1)) * round + (epi == EPI_PARTIAL ? 4.f * 64 * N * splits * kPartialUsPerByte : 0.f);
 }
 
 }  // namespace
 
 // More than 64 tokens: always (1.0 - 2.5 times as fast over the stages above).  33 .. 64 tokens: where it is the faster one alone,
-// e.g. gate/up of the 7B shapes 34 -> 23 us, QKV of d_model 8192 59 -> 40 us, down of the 13B shapes 26 -> 21 us; not down of
-// d_model 2048, 7.7 -> 8.8 us.  Up to 32 tokens the kernel of w4_gemm.hip takes half the time (QKV of the 7B shapes 14 us,
-// here 18).
+// e.g. gate/up of the 7B shapes 32 -> 22 us, QKV of d_model 8192 58 -> 39 us, down of the 13B shapes 25 -> 19 us; not QKV of
+// d_model 1024, 4.0 -> 7.1 us (0.95: it is 33 rows, too, that have to gain, which w4_gemm.hip does a tenth faster than 64).
+// Up to 32 tokens the kernel of w4_gemm.hip takes half the time (QKV of the 7B shapes 14 us, here 18).
 bool w4_is_wide(int epi, int n_tok, int N, int K) {
     if (n_tok <= 32) return false;
-    return n_tok > 64 || pick(epi, 64, N, K).us <= 1.03f * cost_of_rows(epi, N, K);
+    return n_tok > 64 || pick(epi, 64, N, K).us <= 0.95f * cost_of_rows(epi, N, K);
 }
 int w4_wide_splits(int n_tok, int N, int K) { return pick(EPI_PARTIAL, n_tok, N, K).splits; }
 
