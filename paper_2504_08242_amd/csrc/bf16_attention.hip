@@ -182,10 +182,16 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
     const int g = wave % KP, qb = loader ? 0 : wave / KP;
     const int lpart = LPQ == 2 ? (wave - KP * NQ) / KP : -1;  // loader: 0 = K only, 1 = V only, -1 = both
     const int c = lane & 31, hh = lane >> 5;
-    // grid: heads x query blocks (of all branches) x key ranges (no division in front of the first load of a single chunk)
-    const int head = blockIdx.x, block = blockIdx.y * n_heads + head;
+    // grid: heads x query blocks (of all branches) x key ranges (no division in front of the first load of a single chunk);
+    // see chunk_grid for x beyond the heads
     const int q_blocks = (n + NQ * 32 - 1) / (NQ * 32);
-    int branch = 0, bq = blockIdx.y;
+    int head = blockIdx.x, branch = 0, bq = blockIdx.y;
+    while (head >= n_heads) {
+        head -= n_heads;
+        bq += gridDim.y;
+        if (bq >= q_blocks) return;
+    }
+    const int block = bq * n_heads + head;
     if (branches) {
         branch = bq / q_blocks;
         bq -= branch * q_blocks;
@@ -845,6 +851,12 @@ namespace {
 bool split_fits(const AttScratch& sc, int wgs, int splits, int query_rows) {
     return splits == 1 || ((size_t)wgs * splits * query_rows <= sc.rows && (size_t)wgs <= sc.counters);
 }
+// heads x query blocks x key ranges.  A grid's y ends at 65535: the query blocks of a longer chunk (over 4 million tokens, far
+// beyond the chunks that split their keys) go on at x = n_heads, 2 n_heads, ...
+dim3 chunk_grid(int n_heads, int q_blocks, int splits) {
+    const int folds = (q_blocks + 65534) / 65535;
+    return dim3(n_heads * folds, (q_blocks + folds - 1) / folds, splits);
+}
 }  // namespace
 
 hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int n_heads, int pos0, const KvView& kv,
@@ -856,7 +868,7 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     // the CUs idle: 33.7 vs 20.1 us at 512 queries over 1536 cached keys); beside other chunks it takes a sixth less
     // CU time: 4 x 512 tokens +2.4 %, no difference at 256-token chunks.
     if (shared_gpu && n > 256) {
-        hipLaunchKernelGGL((chunk_attention_bf16<4, 2, 2>), dim3(n_heads, (n + 127) / 128), dim3(768), kAttLds, s, q, o,
+        hipLaunchKernelGGL((chunk_attention_bf16<4, 2, 2>), chunk_grid(n_heads, (n + 127) / 128, 1), dim3(768), kAttLds, s, q, o,
                            n, d_model, n_heads, pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
         return hipGetLastError();
     }
@@ -881,7 +893,7 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     } else {
         const int wgs = (n + 63) / 64 * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(chunk_attention_bf16<2>, dim3(n_heads, (n + 63) / 64, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        hipLaunchKernelGGL(chunk_attention_bf16<2>, chunk_grid(n_heads, (n + 63) / 64, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
     }
     return hipGetLastError();

@@ -128,14 +128,19 @@ __device__ __host__ inline size_t tiled_offset(int row, int k_chunk, int k_stage
 }
 
 // x / d by a multiplication (a division by a run-time value is 20 dependent instructions, and in front of the first load of a
-// short kernel every instruction counts).  Exact for x * d < 2^32.
+// short kernel every instruction counts).  mul exceeds 2^32 / d by less than 1, so x * mul / 2^32 exceeds x / d by less than
+// x / 2^32 < 1: its whole part is the quotient or one more.
 struct Quotient {
     unsigned d, mul;
     __host__ void set(int by) {
         d = by;
         mul = 0xFFFFFFFFu / d + 1;
     }
-    __device__ __forceinline__ int of(int x) const { return d == 1 ? x : (int)__umulhi((unsigned)x, mul); }
+    __device__ __host__ __forceinline__ int of(int x) const {  // x >= 0
+        if (d == 1) return x;
+        const unsigned q = (unsigned)(((unsigned long long)(unsigned)x * mul) >> 32);
+        return (int)(q - (q * d > (unsigned)x));
+    }
 };
 
 // ---- GEMM (bf16_gemm.hip) -----------------------------------------------------------------------

@@ -489,7 +489,6 @@ hipError_t launch(GemmArgs a, hipStream_t s) {
     const int grid = a.m_tiles * a.n_tiles * a.splits;
     a.by_m.set(a.m_tiles);
     a.by_n.set(a.n_tiles);
-    if ((long)grid * (a.m_tiles > a.n_tiles ? a.m_tiles : a.n_tiles) >= 1l << 32) return hipErrorInvalidValue;
     using S = Shape<BMB, NB, WM, WN>;
     hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR>), dim3(grid), dim3(S::THREADS), S::LDS_BYTES, s, a);
     return hipGetLastError();

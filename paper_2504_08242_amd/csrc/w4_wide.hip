@@ -375,7 +375,6 @@ hipError_t launch(GemmArgs a, hipStream_t s) {
     a.by_n.set(a.n_tiles);
     a.by_splits.set(a.splits);
     const dim3 grid(a.n_tiles * a.m_tiles * a.splits);
-    if ((long)grid.x * (a.m_tiles > a.n_tiles ? a.m_tiles : a.n_tiles) >= 1l << 32) return hipErrorInvalidValue;
     if (a.m_tiles == 1 && !a.shared_gpu)
         hipLaunchKernelGGL((gemm_w4_wide<EPI, MB, WN, WK, true>), grid, dim3(S::THREADS), S::LDS_BYTES, s, a);
     else
