@@ -158,7 +158,8 @@ __device__ __forceinline__ void merge_key_ranges(int tid, int* flag, const float
     }
 }
 
-template <int NQ, int LPQ = 1, int KP = 4>
+// APART: the K and the V part of a tile are fetched, waited for and freed apart, with two barriers per round (see the loader).
+template <int NQ, int LPQ = 1, int KP = 4, bool APART = true>
 __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(const u16* __restrict__ q, u16* __restrict__ o,
                                                                   int n, int d_model, int n_heads, int pos0_arg,
                                                                   KvView kv_arg, int layer, float scale_log2e,
@@ -270,32 +271,44 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
                 }
             }
         };
-        // K(it) is read between barrier A(it) and barrier B(it), V(it) between B(it) and A(it + 1), so a K slot is free from B on
-        // and a V slot from A on: K(it + 2) is fetched behind B(it), V(it + 1) behind A(it), and a part has a round and a half
-        // to arrive.  (Both parts of tile it + 1 behind one barrier, waited for at the next, a round lasted as long as
-        // 16 loads take to issue and the last of them to land.  One layer with 512 tokens behind 1536 positions, 7B shapes 272 -> 268 us,
-        // 13B 397 -> 385; 128 behind 2048 155.7 -> 153.3, 213.7 -> 209.0; whole prompts no difference.)
         const bool k_part = lpart != 1, v_part = lpart != 0;
         auto tile_of = [&](int it) { return t_lo + g + KP * it; };
-        auto landed = [&](bool more) __attribute__((always_inline)) {  // all but the parts asked for behind the wanted one
-            if (!more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            else if (LPQ == 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        auto fill = [&](int it) __attribute__((always_inline)) {
+            if (k_part) fill_part(tile_of(it), it & 1, false);
+            if (v_part) fill_part(tile_of(it), it & 1, true);
         };
-        if (cnt > 0 && k_part) fill_part(tile_of(0), 0, false);
-        if (cnt > 0 && v_part) fill_part(tile_of(0), 0, true);
-        if (cnt > 1 && k_part) fill_part(tile_of(1), 1, false);
-        for (int it = 0; it < max_cnt; ++it) {
-            const bool more = it + 1 < cnt;
-            if (k_part) {
-                if (LPQ == 1 && !more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // (V(it) may be on its way)
-                else landed(more);
+        if constexpr (APART) {
+            // K(it) is read between barrier A(it) and barrier B(it), V(it) between B(it) and A(it + 1), so a K slot is free from B
+            // on and a V slot from A on: K(it + 2) is fetched behind B(it), V(it + 1) behind A(it), and a part has a round and
+            // a half to arrive.  (Both parts of tile it + 1 behind one barrier, waited for at the next, a round lasted as long as
+            // 16 loads take to issue and the last of them to land.  One layer with 512 tokens behind 1536 positions, 7B shapes
+            // 272 -> 268 us, 13B 397 -> 385; 128 behind 2048 155.7 -> 153.3, 213.7 -> 209.0.)
+            auto landed = [&](bool more) __attribute__((always_inline)) {  // all but the parts asked for behind the wanted one
+                if (!more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                else if (LPQ == 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+            };
+            if (cnt > 0) fill(0);
+            if (cnt > 1 && k_part) fill_part(tile_of(1), 1, false);
+            for (int it = 0; it < max_cnt; ++it) {
+                const bool more = it + 1 < cnt;
+                if (k_part) {
+                    if (LPQ == 1 && !more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // (V(it) may be on its way)
+                    else landed(more);
+                }
+                __builtin_amdgcn_s_barrier();  // A
+                if (more && v_part) fill_part(tile_of(it + 1), (it + 1) & 1, true);
+                if (v_part) landed(more);
+                __builtin_amdgcn_s_barrier();  // B
+                if (it + 2 < cnt && k_part) fill_part(tile_of(it + 2), it & 1, false);
             }
-            __builtin_amdgcn_s_barrier();  // A
-            if (more && v_part) fill_part(tile_of(it + 1), (it + 1) & 1, true);
-            if (v_part) landed(more);
-            __builtin_amdgcn_s_barrier();  // B
-            if (it + 2 < cnt && k_part) fill_part(tile_of(it + 2), it & 1, false);
+        } else {
+            if (cnt > 0) fill(0);
+            for (int it = 0; it < max_cnt; ++it) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the tile of this round has landed
+                __builtin_amdgcn_s_barrier();                     // ... and the other slot is free
+                if (it + 1 < cnt) fill(it + 1);
+            }
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();  // the two barriers of the merge
@@ -335,11 +348,13 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
     const unsigned long long q_sees = tree ? tree->sees[min(q0 + qb * 32 + c, n - 1)] : 0ull;
 
     for (int it = 0; it < max_cnt; ++it) {
-        // Two barriers per round: the loader arrives at A when the K part of this round's tile has landed and at B when
-        // the V part has, the computing waves when they are done with the V part before and the K part.
+        // One barrier per round: the loader arrives when the tile of this round has landed, the computing waves
+        // when they are done with the other slot, which the loader then refills.  Two (APART): the loader arrives at A when the
+        // K part has landed and at B when the V part has, the computing waves when they are done with the V part before and
+        // the K part.
         __builtin_amdgcn_s_barrier();  // A
         if (it >= cnt) {
-            __builtin_amdgcn_s_barrier();  // B
+            if (APART) __builtin_amdgcn_s_barrier();  // B
             continue;
         }
         const int tile = t_lo + g + KP * it, slot = it & 1;
@@ -404,7 +419,7 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
                 for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
         }
 
-        __builtin_amdgcn_s_barrier();  // B
+        if (APART) __builtin_amdgcn_s_barrier();  // B
         // ---- O^T += V^T P^T ----------------------------------------------------------------------------------------
         u32x4 vf[8];
         [&]<int... F>(std::integer_sequence<int, F...>) {
@@ -839,7 +854,10 @@ hipError_t attention_configure() {
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)chunk_attention_bf16<1, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, kAttLds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)chunk_attention_bf16<4, 2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    e = hipFuncSetAttribute((const void*)chunk_attention_bf16<2, 1, 4, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kAttLds);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute((const void*)chunk_attention_bf16<4, 2, 2, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             kAttLds);
     if (e != hipSuccess) return e;
     return hipFuncSetAttribute((const void*)chunk_attention_bf16<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -851,6 +869,13 @@ namespace {
 bool split_fits(const AttScratch& sc, int wgs, int splits, int query_rows) {
     return splits == 1 || ((size_t)wgs * splits * query_rows <= sc.rows && (size_t)wgs <= sc.counters);
 }
+// 64-query workgroups: the parts of a tile apart while the launch is little more than one workgroup per CU, which then waits for
+// its tiles; with more of them the chip's matrix work bounds the launch and a second barrier per round only costs.  Whole layer,
+// one barrier -> two (us, 7B / 13B shapes): 256 workgroups, 512 tokens behind 1536 positions 269 -> 265; 288, 576 behind
+// 1536 338 -> 334, none behind 304.7 -> 304.3; 360 (576 tokens, 13B) 395 -> 399; 384, 768 tokens 336.6 -> 338.2; 512, 1024 tokens
+// 427.7 -> 431.6; 1024, 2048 tokens 808.7 -> 812.7.
+bool parts_apart(int wgs) { return wgs <= 320; }
+
 // heads x query blocks x key ranges.  A grid's y ends at 65535: the query blocks of a longer chunk (over 4 million tokens, far
 // beyond the chunks that split their keys) go on at x = n_heads, 2 n_heads, ...
 dim3 chunk_grid(int n_heads, int q_blocks, int splits) {
@@ -868,7 +893,7 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     // the CUs idle: 33.7 vs 20.1 us at 512 queries over 1536 cached keys); beside other chunks it takes a sixth less
     // CU time: 4 x 512 tokens +2.4 %, no difference at 256-token chunks.
     if (shared_gpu && n > 256) {
-        hipLaunchKernelGGL((chunk_attention_bf16<4, 2, 2>), chunk_grid(n_heads, (n + 127) / 128, 1), dim3(768), kAttLds, s, q, o,
+        hipLaunchKernelGGL((chunk_attention_bf16<4, 2, 2, false>), chunk_grid(n_heads, (n + 127) / 128, 1), dim3(768), kAttLds, s, q, o,
                            n, d_model, n_heads, pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
         return hipGetLastError();
     }
@@ -893,7 +918,7 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     } else {
         const int wgs = (n + 63) / 64 * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(chunk_attention_bf16<2>, chunk_grid(n_heads, (n + 63) / 64, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        hipLaunchKernelGGL((parts_apart(wgs * splits) ? chunk_attention_bf16<2> : chunk_attention_bf16<2, 1, 4, false>), chunk_grid(n_heads, (n + 63) / 64, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
     }
     return hipGetLastError();
@@ -913,7 +938,7 @@ hipError_t launch_branch_attention(const u16* q, u16* o, int n, int n_branches, 
     } else {
         const int wgs = n_branches * ((n + 63) / 64) * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(chunk_attention_bf16<2>, dim3(n_heads, n_branches * ((n + 63) / 64), splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        hipLaunchKernelGGL((parts_apart(wgs * splits) ? chunk_attention_bf16<2> : chunk_attention_bf16<2, 1, 4, false>), dim3(n_heads, n_branches * ((n + 63) / 64), splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            0, none, layer, scale_log2e, branches, no_tree, sc.split_buf, sc.split_count);
     }
     return hipGetLastError();

@@ -232,6 +232,17 @@ def test_w4_projections_of_long_chunks(d_model, n_heads, d_ffn, rows):
         assert np.array_equal(p.gpu_chunk(h[5:], 5), y), n
 
 
+@pytest.mark.parametrize("rows", [1280, 1281])
+def test_attention_of_long_chunks_around_one_round_of_workgroups(rows):
+    """64-query workgroups, 320 of them (K and V parts of a tile apart) and 336 (one barrier per round), with a ragged last tile,
+    behind a cached prefix."""
+    cfg = dict(si.LLAMA7B_STAGE, d_model=2048, n_heads=16, d_ffn=128, n_layers=1)
+    p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 71, max_chunk_tokens=rows)
+    hidden = p.hidden(rows + 71)
+    g, o = p.run_both(hidden, [71, rows])
+    p.check(g[71:], o[71:], f"{rows} rows")
+
+
 @pytest.mark.parametrize("d_model,n_heads,d_ffn,dtype,n_lanes,chunks,tiles", [
     # two chunks a second lane's scratch cannot hold together: side by side
     (1024, 8, 2816, "bf16", 2, [1024, 1024, 1000], {}),
