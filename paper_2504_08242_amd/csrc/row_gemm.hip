@@ -21,7 +21,8 @@
 //     split added up first.  4-bit: the eight waves of every split.
 //
 // Measured on the 7B shapes at 5 rows (us, two K-split launches and two reduce + norm passes -> two launches): bf16
-// 7.2 + 17.4 + 2 x 4.8 -> 7.7 + 17.4; 4-bit 3.7 + 9.2 + 2 x 4.3 -> 5.9 + 12.8.  A whole call: 5 rows of eight bf16 layers
+// 7.2 + 17.4 + 2 x 4.8 -> 7.7 + 17.4; 4-bit 3.7 + 9.2 + 2 x 4.3 -> 6.5 + 11.2, with four K groups in flight per wave and no division
+// in front of them 5.6 + 9.9 (six 1 % slower, eight no different).  A whole call: 5 rows of eight bf16 layers
 // 723 -> 681 us, one row of eight 4-bit layers 460 -> 416 us.  A batch of branches pays for the equal bits: 8 x 5 rows of two
 // bf16 layers 203 -> 207 us.  Narrow stages, whose d / 16 workgroups leave CUs idle (64 of them for d = 1024, each walking all
 // of K), gain more: their launches are short, and there are fewer.  Six layers, 1 / 16 rows, two launches and two passes -> two

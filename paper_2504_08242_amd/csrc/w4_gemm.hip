@@ -194,7 +194,7 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
         // Two groups in flight per wave, codes (from HBM) and rows (from L2), in two sets of registers that take turns: a
         // set is filled again as soon as its products are issued.  (As one set that is copied to the other the loads of a
         // group only started when the group before had landed, one trip to HBM per group: gate/up of one row of the 7B
-        // shapes 14.2 -> 11.9 us, QKV 9.3 -> 8.1.)
+        // shapes 14.1 -> 12.8 us, QKV 9.1 -> 8.1, with the shorter way to the first load.)
         struct Group {
             W4Codes c;
             W4Rows<RG> r;

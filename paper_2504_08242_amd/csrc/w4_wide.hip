@@ -18,9 +18,9 @@
 //     cache line (the count of loads in flight then never depends on the turn).  Codes are asked for two turns ahead:
 //     deeper (four, seven) measured 10 % slower, the unrolled loop no longer fits the instruction cache.
 //
-// Measured on the 7B shapes (us, kernel of w4_gemm.hip -> this one; QKV, gate/up, O, down): 64 rows 19 -> 19, 34 -> 23, 8.6 ->
-// 9.1, 15 -> 16; 128 rows 33 -> 23, 48 -> 37, 14 -> 12, 27 -> 22; 256 rows 50 -> 39, 87 -> 58, 25 -> 17, 48 -> 30; 512 rows
-// 94 -> 61, 155 -> 112, 48 -> 24, 89 -> 49 (the bf16 kernels there: 54, 77, 24, 46).
+// Measured on the 7B shapes (us, kernel of w4_gemm.hip at 64 rows per pass -> this one; QKV, gate/up, O, down): 64 rows gate/up
+// 34 -> 23 (the others stay there: 18, 9, 16); 128 rows 33 -> 23, 48 -> 35, 15 -> 11, 27 -> 22; 256 rows 52 -> 37, 89 -> 56, 27 ->
+// 17, 49 -> 31; 512 rows 96 -> 62, 158 -> 108, 49 -> 25, 90 -> 50 (the bf16 kernels there: 56, 81, 25, 47).
 #include <type_traits>
 #include <utility>
 
