@@ -42,6 +42,27 @@ struct WideShape {
     static constexpr int DEPTH = 2;
     static constexpr int UNITS = STAGE_BYTES / 1024;         // 1 KB loads per stage
     static constexpr int LOADS = (UNITS + WAVES - 1) / WAVES;
+    // The queue of loads, which return in order.  At the start of stage st a wave asks for the rows of stage st + STAGES - 1 and,
+    // where a turn begins, for the codes of the turn DEPTH further on; in front of the loop it asks for what the stages before 0
+    // would have, in the same order.
+    static constexpr int CODE_LOADS = 3;
+    static constexpr bool rows_asked(int st) { return st >= 1 - STAGES; }
+    static constexpr bool codes_asked(int st) { return st % PARTS == 0 && st / PARTS + DEPTH >= 0; }
+    static constexpr int FIRST = -DEPTH * PARTS < 1 - STAGES ? -DEPTH * PARTS : 1 - STAGES;  // stage that asks first
+    // Loads behind the rows of stage st when the stages before `until` have asked.
+    static constexpr int behind(int st, int until) {
+        int n = codes_asked(st + 1 - STAGES) ? CODE_LOADS : 0;
+        for (int s = st + 2 - STAGES; s < until; ++s) n += LOADS + (codes_asked(s) ? CODE_LOADS : 0);
+        return n;
+    }
+    // Stage st begins when the rows of stage st + 1 have landed: in the first stages no more loads are behind them than in any other.
+    static constexpr int behind_next(int part) { return behind(PARTS * STAGES + part + 1, PARTS * STAGES + part); }
+    static constexpr bool same_from_the_start() {
+        for (int st = 0; st < PARTS * STAGES; ++st)
+            if (behind(st + 1, st) != behind_next(st % PARTS)) return false;
+        return true;
+    }
+    static_assert(same_from_the_start(), "a wait of the loop is too weak for its first stages");
     static constexpr int RED_STRIDE = COLS + 4;
     static constexpr int RED_BYTES = WK * 32 * RED_STRIDE * 4;
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES > RED_BYTES ? STAGES * STAGE_BYTES : RED_BYTES;
@@ -68,6 +89,14 @@ struct Nibbles {
     __device__ __forceinline__ void first(u32x4& v) const { v[0] = pack_bf16x2(at(x, 0), at(x, 2)); v[2] = pack_bf16x2(at(x, 1), at(x, 3)); }
     __device__ __forceinline__ void second(u32x4& v) const { v[1] = pack_bf16x2(at(y, 0), at(y, 2)); v[3] = pack_bf16x2(at(y, 1), at(y, 3)); }
 };
+
+// fn(FROM), ..., fn(TO - 1), each number as a constant
+template <int FROM, int TO>
+__device__ __forceinline__ void static_for(auto fn) {
+    [&]<int... K>(std::integer_sequence<int, K...>) __attribute__((always_inline)) {
+        (fn(std::integral_constant<int, FROM + K>{}), ...);
+    }(std::make_integer_sequence<int, TO - FROM>{});
+}
 
 template <int EPI, int MB, int WN, int WK, bool ONCE>
 __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
@@ -153,10 +182,13 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
     constexpr int ST = S::STAGES, PARTS = S::PARTS;
     constexpr int DEPTH = S::DEPTH, BUFS = DEPTH + 1;  // groups of codes on their way
     Codes buf[BUFS];
-#pragma unroll
-    for (int i = 0; i < DEPTH; ++i) fetch_codes(buf[i], i);
-#pragma unroll
-    for (int st = 0; st < ST - 1; ++st) issue_rows(st / PARTS, st % PARTS);
+    static_for<S::FIRST, 0>([&](auto stage) __attribute__((always_inline)) {
+        constexpr int st = decltype(stage)::value, asked = st + ST - 1;
+        if constexpr (S::rows_asked(st)) issue_rows(asked / PARTS, asked % PARTS);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (S::codes_asked(st)) fetch_codes(buf[st / PARTS + DEPTH], st / PARTS + DEPTH);
+        __builtin_amdgcn_sched_barrier(0);
+    });
 
     // A chunk: two row blocks times four MFMA steps (64 features).  CHUNKS of them make a group, the first half of its features
     // for all row blocks, then the second.  Everything else is dealt out behind the eight MFMAs of a chunk: the fragments of
@@ -173,15 +205,11 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
         const unsigned char* slot = smem + st % ST * S::STAGE_BYTES + wk * S::PART_BYTES;
         f[KK] = *(const bf16x8*)(slot + (2 * pair + j) * WK * S::PART_BYTES + (((PARTS == 1 ? 4 * half : 0) + s) >> 1) * 2048 + lane_off[s & 1]);
     };
-    auto for8 = [](auto fn) __attribute__((always_inline)) {
-        [&]<int... K>(std::integer_sequence<int, K...>) __attribute__((always_inline)) {
-            (fn(std::integral_constant<int, K>{}), ...);
-        }(std::make_integer_sequence<int, 8>{});
-    };
 
-    wait_vmcnt<(ST - 2) * S::LOADS>();
+    wait_vmcnt<S::behind(0, 0)>();
     __builtin_amdgcn_s_barrier();
-    for8([&](auto k) __attribute__((always_inline)) { read_frag(0, std::integral_constant<int, 0>{}, k); });
+    asm volatile("" ::: "memory");  // (no read of the ring in front of the barrier)
+    static_for<0, 8>([&](auto k) __attribute__((always_inline)) { read_frag(0, std::integral_constant<int, 0>{}, k); });
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         const Nibbles n(buf[0].w[s & 1][s >> 1]);
@@ -205,10 +233,7 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
                 constexpr int CH = decltype(chunk)::value;
                 constexpr int pair = CH % PAIRS, half = CH / PAIRS, part = PARTS == 2 ? half : 0;
                 if constexpr (CH == 0 || (PARTS == 2 && CH == PAIRS)) {  // a stage begins
-                    // stage st + 1 has landed (its first fragments are read in this one): behind it in the queue are the
-                    // rows of ST - 3 stages and the codes of the last ST - 2 turns of the stages that ask for some
-                    constexpr int ASKED = PARTS == 1 ? ST - 2 : (ST - 2 + part) / 2;
-                    wait_vmcnt<(ST - 3) * S::LOADS + 3 * ASKED>();
+                    wait_vmcnt<S::behind_next(part)>();  // stage st + 1 has landed (its first fragments are read in this one)
                     __builtin_amdgcn_s_barrier();
                     issue_rows(it + (part + ST - 1) / PARTS, (part + ST - 1) % PARTS);
                     if (part == 0) fetch_codes(buf[(B + DEPTH) % BUFS], it + DEPTH);
@@ -216,7 +241,7 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
                 }
                 constexpr bool LAST = CH == CHUNKS - 1;
                 constexpr bool OF_THIS = CH == (MB == 2 ? 0 : 1), OF_NEXT = CH == (MB == 2 ? 1 : 2);
-                for8([&](auto k) __attribute__((always_inline)) {
+                static_for<0, 8>([&](auto k) __attribute__((always_inline)) {
                     constexpr int K = decltype(k)::value, s = K >> 1, j = K & 1;
                     if constexpr (half == 0 && s == 0) {
 #pragma unroll
