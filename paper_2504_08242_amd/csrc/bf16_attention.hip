@@ -239,6 +239,9 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
     const int max_cnt = (n_own + KP - 1) / KP;                  // of partition 0: every wave runs that many rounds
     if (loader) {
         // The whole life of a loader wave: one tile ahead of the computing waves, the same barriers as they.
+        // (nothing is in flight here, but the compiler joins the computing waves' way out with this block: where a register of
+        // the loop below is one of the merge's loads it would wait in every round, and so for the tiles)
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
         // Tile fill (loader waves).  Load j covers rows 4j..4j+3 (1 KB of LDS); lane i lands at
         // row 4j + (i >> 4), position i & 15, and fetches the chunk that belongs there.
         const int lrow = lane >> 4, lp = lane & 15;

@@ -1,5 +1,5 @@
-"""The LDS ring of the 4-bit projections of long chunks (gemm_w4_wide): what its waits leave in flight, from the compiler's own
-listing of every instantiation (no GPU needed)."""
+"""What the waits of kernels with direct global->LDS loads leave in flight, from the compiler's own listing of every instantiation
+(no GPU needed)."""
 import os
 import re
 import shutil
@@ -13,17 +13,17 @@ SLOTS = 4   # of the ring: the rows of SLOTS - 1 stages are asked for in front o
 STAGES = 24  # of the loop that are walked: at least four rounds of its body
 
 
-def listing(tmp_path):
+def listing(tmp_path, source, kernel):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc is not installed")
-    out = tmp_path / "w4_wide.s"
-    subprocess.run([hipcc, *jbuild.HIPCC_FLAGS, "-S", "--offload-device-only", os.path.join(jbuild.CSRC, "w4_wide.hip"), "-o", out],
+    out = tmp_path / "listing.s"
+    subprocess.run([hipcc, *jbuild.HIPCC_FLAGS, "-S", "--offload-device-only", os.path.join(jbuild.CSRC, source), "-o", out],
                    check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
     kernels, name = {}, None
     for line in out.read_text().splitlines():
         line = line.split(";")[0].strip()
-        if m := re.match(r"(_ZN\S*gemm_w4_wide\S*):$", line):
+        if m := re.match(rf"(_ZN\S*{kernel}\S*):$", line):
             kernels[name := m.group(1)] = []
         elif re.match(r"\.Lfunc_end\d+:$", line):
             name = None
@@ -88,7 +88,19 @@ def unlanded(path):
 
 
 def test_rows_of_a_stage_have_landed_when_its_barrier_opens(tmp_path):
-    kernels = listing(tmp_path)
+    kernels = listing(tmp_path, "w4_wide.hip", "gemm_w4_wide")
     assert kernels
     late = {name: found for name, lines in kernels.items() if (found := unlanded(loop_path(lines)))}
     assert not late, late
+
+
+def test_loader_waves_of_chunk_attention_wait_for_tiles_only(tmp_path):
+    """Between its loads a loader wave waits in front of its barriers (K and V parts apart: for all but one or both parts of the
+    next tile) and nowhere else.  The compiler, who does not know these loads, adds waits of its own where a register is still
+    the target of a load on some way to the loop; in the loop they hold up the tiles in every round."""
+    kernels = listing(tmp_path, "bf16_attention.hip", "chunk_attention_bf16")
+    assert len(kernels) == 4, sorted(kernels)
+    for name, lines in kernels.items():
+        loads = [i for i, l in enumerate(lines) if l.startswith("global_load_lds")]
+        waits = {int(m.group(1)) for l in lines[loads[0]:loads[-1]] if (m := re.match(r"s_waitcnt.*vmcnt\((\d+)\)", l))}
+        assert waits <= ({0, 8, 16} if "Lb1" in name else {0}), (name, waits)
