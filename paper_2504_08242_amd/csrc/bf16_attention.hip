@@ -872,12 +872,17 @@ namespace {
 bool split_fits(const AttScratch& sc, int wgs, int splits, int query_rows) {
     return splits == 1 || ((size_t)wgs * splits * query_rows <= sc.rows && (size_t)wgs <= sc.counters);
 }
-// 64-query workgroups: the parts of a tile apart while the launch is little more than one workgroup per CU, which then waits for
-// its tiles; with more of them the chip's matrix work bounds the launch and a second barrier per round only costs.  Whole layer,
-// one barrier -> two (us, 7B / 13B shapes): 256 workgroups, 512 tokens behind 1536 positions 269 -> 265; 288, 576 behind
-// 1536 338 -> 334, none behind 304.7 -> 304.3; 360 (576 tokens, 13B) 395 -> 399; 384, 768 tokens 336.6 -> 338.2; 512, 1024 tokens
-// 427.7 -> 431.6; 1024, 2048 tokens 808.7 -> 812.7.
-bool parts_apart(int wgs) { return wgs <= 320; }
+// 64-query workgroups: the parts of a tile apart where a workgroup waits for its tiles, one barrier per round where the matrix work
+// bounds it (the second barrier keeps the waves of a SIMD in step: no softmax beside another wave's products).  It waits
+//   - while the launch is little more than one workgroup per CU.  Whole layer, one barrier -> two (us, 7B / 13B shapes): 256
+//     workgroups, 512 tokens behind 1536 positions 269 -> 265; 288, 576 behind 1536 338 -> 334; 360 (576 tokens, 13B) 395 -> 399; 384,
+//     768 tokens 336.6 -> 338.2; 512, 1024 tokens 427.7 -> 431.6; 1024, 2048 tokens 808.7 -> 812.7;
+//   - for keys that come from memory, not from the last-level cache (from_memory).  512 tokens behind 4096 positions, us per layer:
+//     8 heads, 4 / 8 / 24 layers 86.9 -> 91.2 / 107.4 -> 97.0 / 106.6 -> 96.4; 16 heads, 1 / 2 / 8 layers 120.5 -> 124.8 / 144.5 -> 134.0 /
+//     144.0 -> 133.2 (weights and cache: 178 / 357 / 1070 and 141 / 281 / 1124 MB);
+//   - with enough of them.  Average keys of a query, from memory: 256 .. 812 (512 tokens, 1024 behind 300) 16 heads 107.0 -> 107.5 /
+//     155.9 -> 158.4, 24 heads 168.0 -> 169.0; 1089 (130 tokens behind 1024) 16 heads 91.9 -> 89.4, 1280 117.4 -> 115.9, 1792 123.4 -> 120.9.
+bool parts_apart(int wgs, int keys, bool from_memory) { return wgs <= 320 && keys >= 1024 && from_memory; }
 
 // heads x query blocks x key ranges.  A grid's y ends at 65535: the query blocks of a longer chunk (over 4 million tokens, far
 // beyond the chunks that split their keys) go on at x = n_heads, 2 n_heads, ...
@@ -888,7 +893,7 @@ dim3 chunk_grid(int n_heads, int q_blocks, int splits) {
 }  // namespace
 
 hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int n_heads, int pos0, const KvView& kv,
-                                  int layer, hipStream_t s, AttScratch sc, const TreeTable* tree, bool shared_gpu) {
+                                  int layer, hipStream_t s, AttScratch sc, bool from_memory, const TreeTable* tree, bool shared_gpu) {
     const float scale_log2e = 1.4426950408889634f / sqrtf(128.0f);
     const BranchTable* none = nullptr;
     // Beside other chunks' kernels (overlapped multi-chunk call): 128 queries per workgroup against two key halves,
@@ -921,14 +926,16 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     } else {
         const int wgs = (n + 63) / 64 * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((parts_apart(wgs * splits) ? chunk_attention_bf16<2> : chunk_attention_bf16<2, 1, 4, false>), chunk_grid(n_heads, (n + 63) / 64, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        const bool apart = parts_apart(wgs * splits, pos0 + n / 2, from_memory);
+        hipLaunchKernelGGL((apart ? chunk_attention_bf16<2> : chunk_attention_bf16<2, 1, 4, false>), chunk_grid(n_heads, (n + 63) / 64, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_branch_attention(const u16* q, u16* o, int n, int n_branches, int d_model, int n_heads,
-                                   const BranchTable* branches, int max_keys, int layer, hipStream_t s, AttScratch sc) {
+                                   const BranchTable* branches, int max_keys, int layer, hipStream_t s, AttScratch sc,
+                                   bool from_memory) {
     const float scale_log2e = 1.4426950408889634f / sqrtf(128.0f);
     const KvView none{};
     const TreeTable* no_tree = nullptr;
@@ -941,7 +948,8 @@ hipError_t launch_branch_attention(const u16* q, u16* o, int n, int n_branches, 
     } else {
         const int wgs = n_branches * ((n + 63) / 64) * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((parts_apart(wgs * splits) ? chunk_attention_bf16<2> : chunk_attention_bf16<2, 1, 4, false>), dim3(n_heads, n_branches * ((n + 63) / 64), splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        const bool apart = parts_apart(wgs * splits, max_keys - n / 2, from_memory);
+        hipLaunchKernelGGL((apart ? chunk_attention_bf16<2> : chunk_attention_bf16<2, 1, 4, false>), dim3(n_heads, n_branches * ((n + 63) / 64), splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            0, none, layer, scale_log2e, branches, no_tree, sc.split_buf, sc.split_count);
     }
     return hipGetLastError();

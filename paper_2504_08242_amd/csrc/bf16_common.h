@@ -346,14 +346,16 @@ struct AttScratch {
 };
 // o is written in the tiled layout (it is the output projection's A operand)
 hipError_t attention_configure();  // raises the dynamic-LDS limit (once per process)
+// from_memory: the call goes through more than the last-level cache holds before it comes back to these keys
 // tree (device pointer, may be null): inside the chunk a query sees the tokens of its row of the table only
 hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int n_heads, int pos0, const KvView& kv,
-                            int layer, hipStream_t s, AttScratch scratch, const TreeTable* tree = nullptr,
+                            int layer, hipStream_t s, AttScratch scratch, bool from_memory, const TreeTable* tree = nullptr,
                             bool shared_gpu = false);
 // n_branches chunks of n tokens each (rows b*n .. b*n+n-1 of q and o), every one against its own cache;
 // max_keys: the longest pos0 + n among the branches
 hipError_t launch_branch_attention(const u16* q, u16* o, int n, int n_branches, int d_model, int n_heads,
-                             const BranchTable* branches, int max_keys, int layer, hipStream_t s, AttScratch scratch);
+                             const BranchTable* branches, int max_keys, int layer, hipStream_t s, AttScratch scratch,
+                             bool from_memory);
 
 // ---- packing, first kernel of a call, reduce + norm (bf16_misc.hip) -------------------------------------------
 void launch_pack_qkv(u16* dst, const u16* wq, const u16* wk, const u16* wv, int d, hipStream_t s);

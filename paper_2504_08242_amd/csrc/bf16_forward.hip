@@ -100,6 +100,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     const AttScratch att{(float*)(ws + st.wl.att_split), (int*)(ws + st.wl.att_count), st.wl.att_split_rows,
                          st.wl.att_count_n};
     int max_keys = 0;  // batched branches: the longest key range
+    double keys = (double)pos + n;  // read per layer
     {
         TraceScope ts(st, JUP_K_RMSNORM, s);
         const BeginArgs a{x32, (const u16*)hidden_in, (const u16*)((const char*)st.packed + st.pl.g_attn), xn, n, d, c.rms_eps,
@@ -107,8 +108,12 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         if (bt) {
             bt_dev = (const BranchTable*)(ws + st.wl.branches);
             launch_begin_branches(a, *bt, (BranchTable*)(ws + st.wl.branches), s);
-            for (int b = 0; b < bt->n_branches; ++b)
-                max_keys = bt->pos0[b] + bt->n_tok > max_keys ? bt->pos0[b] + bt->n_tok : max_keys;
+            keys = 0;  // (a shared prefix once)
+            for (int b = 0; b < bt->n_branches; ++b) {
+                const int end = bt->pos0[b] + bt->n_tok;
+                max_keys = end > max_keys ? end : max_keys;
+                keys += end - (b > 0 ? bt->kv[b].n_shared : 0);
+            }
         } else if (tree) {
             tree_dev = (const TreeTable*)(ws + st.wl.tree);
             launch_begin_tree(a, pos, *tree, (TreeTable*)(ws + st.wl.tree), s);
@@ -124,6 +129,9 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     const bool w4 = c.dtype == JUP_BF16_W4 && !expanded;
     const size_t wqkv = expanded ? st.pl.xqkv : st.pl.wqkv, wo = expanded ? st.pl.xo : st.pl.wo;
     const size_t wgu = expanded ? st.pl.xgu : st.pl.wgu, wdown = expanded ? st.pl.xdown : st.pl.wdown;
+    // Weights (bf16, or codes and scales), keys and values a call goes through, against the 256 MB of the last-level cache.
+    const double layer_bytes = (w4 ? 17.0 / 32 : 2.0) * (4.0 * d * d + 3.0 * d * f) + 512.0 * H * keys;
+    const bool from_memory = c.n_layers * layer_bytes > 256e6;
     // Back to d_model.  Calls of up to 16 rows: the O / down projections finish the residual and the rows of the next
     // projection themselves (row_gemm.hip); their sums of squares take the place of the partial sums in the workspace.  All
     // other calls leave partial sums to the reduce + norm pass; batches of branches of up to 16 tokens in a form that gives
@@ -180,8 +188,8 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         {
             TraceScope ts(st, JUP_K_ATTENTION, s);
             if (e != hipSuccess) break;
-            if (bt) e = launch_branch_attention(q, o, bt->n_tok, bt->n_branches, d, H, bt_dev, max_keys, l, s, att);
-            else e = launch_chunk_attention(q, o, n, d, H, pos, kv, l, s, att, tree_dev, shared);
+            if (bt) e = launch_branch_attention(q, o, bt->n_tok, bt->n_branches, d, H, bt_dev, max_keys, l, s, att, from_memory);
+            else e = launch_chunk_attention(q, o, n, d, H, pos, kv, l, s, att, from_memory, tree_dev, shared);
         }
         {
             TraceScope ts(st, JUP_K_GEMM_O, s);

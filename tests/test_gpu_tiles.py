@@ -234,13 +234,19 @@ def test_w4_projections_of_long_chunks(d_model, n_heads, d_ffn, rows):
 
 @pytest.mark.parametrize("rows", [1280, 1281])
 def test_attention_of_long_chunks_around_one_round_of_workgroups(rows):
-    """64-query workgroups, 320 of them (K and V parts of a tile apart) and 336 (one barrier per round), with a ragged last tile,
-    behind a cached prefix."""
-    cfg = dict(si.LLAMA7B_STAGE, d_model=2048, n_heads=16, d_ffn=128, n_layers=1)
-    p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 71, max_chunk_tokens=rows)
-    hidden = p.hidden(rows + 71)
-    g, o = p.run_both(hidden, [71, rows])
-    p.check(g[71:], o[71:], f"{rows} rows")
+    """64-query workgroups, 320 and 336 of them, with a ragged last tile, behind a cached prefix: on a stage whose call stays in the
+    last-level cache (one barrier per round), and, to the bit, on one with more layers that goes through 340 MB (320 of them: K
+    and V parts of a tile apart)."""
+    cfg = dict(si.LLAMA7B_STAGE, d_model=2048, n_heads=16, d_ffn=128, n_layers=2)
+    p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 471, max_chunk_tokens=rows)
+    hidden = p.hidden(rows + 471)
+    g, o = p.run_both(hidden, [471, rows])
+    p.check(g[471:], o[471:], f"{rows} rows")
+    long = Pair(dict(cfg, n_layers=7), "bf16", seed=rows, layers_np=p.layers_np + p.layers_np[:1] * 5, max_positions=rows + 471,
+                max_chunk_tokens=rows)
+    long.gpu_chunk(hidden[:471], 0)
+    long.gpu_chunk(hidden[471:], 471)
+    assert np.array_equal(long.kv_gpu()[:2], p.kv_gpu())
 
 
 @pytest.mark.parametrize("d_model,n_heads,d_ffn,dtype,n_lanes,chunks,tiles", [
