@@ -186,12 +186,8 @@ __global__ __launch_bounds__(64 * KP * (NQ + LPQ)) void chunk_attention_bf16(con
     // grid: heads x query blocks (of all branches) x key ranges (no division in front of the first load of a single chunk);
     // see chunk_grid for x beyond the heads
     const int q_blocks = (n + NQ * 32 - 1) / (NQ * 32);
-    int head = blockIdx.x, branch = 0, bq = blockIdx.y;
-    while (head >= n_heads) {
-        head -= n_heads;
-        bq += gridDim.y;
-        if (bq >= q_blocks) return;
-    }
+    int head, branch = 0, bq = unfold_block(blockIdx.x, blockIdx.y, gridDim.y, n_heads, head);
+    if ((int)blockIdx.x >= n_heads && bq >= q_blocks * (branches ? branches->n_branches : 1)) return;
     const int block = bq * n_heads + head;
     if (branches) {
         branch = bq / q_blocks;
@@ -883,13 +879,6 @@ bool split_fits(const AttScratch& sc, int wgs, int splits, int query_rows) {
 //   - with enough of them.  Average keys of a query, from memory: 256 .. 812 (512 tokens, 1024 behind 300) 16 heads 107.0 -> 107.5 /
 //     155.9 -> 158.4, 24 heads 168.0 -> 169.0; 1089 (130 tokens behind 1024) 16 heads 91.9 -> 89.4, 1280 117.4 -> 115.9, 1792 123.4 -> 120.9.
 bool parts_apart(int wgs, int keys, bool from_memory) { return wgs <= 320 && keys >= 1024 && from_memory; }
-
-// heads x query blocks x key ranges.  A grid's y ends at 65535: the query blocks of a longer chunk (over 4 million tokens, far
-// beyond the chunks that split their keys) go on at x = n_heads, 2 n_heads, ...
-dim3 chunk_grid(int n_heads, int q_blocks, int splits) {
-    const int folds = (q_blocks + 65534) / 65535;
-    return dim3(n_heads * folds, (q_blocks + folds - 1) / folds, splits);
-}
 }  // namespace
 
 hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int n_heads, int pos0, const KvView& kv,
@@ -921,7 +910,7 @@ hipError_t launch_chunk_attention(const u16* q, u16* o, int n, int d_model, int 
     } else if (n <= 128 && !shared_gpu) {
         const int wgs = (n + 31) / 32 * n_heads;
         if (!split_fits(sc, wgs, splits, 32)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((chunk_attention_bf16<1, 2>), dim3(n_heads, (n + 31) / 32, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        hipLaunchKernelGGL((chunk_attention_bf16<1, 2>), chunk_grid(n_heads, (n + 31) / 32, splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            pos0, kv, layer, scale_log2e, none, tree, sc.split_buf, sc.split_count);
     } else {
         const int wgs = (n + 63) / 64 * n_heads;
@@ -949,7 +938,7 @@ hipError_t launch_branch_attention(const u16* q, u16* o, int n, int n_branches, 
         const int wgs = n_branches * ((n + 63) / 64) * n_heads;
         if (!split_fits(sc, wgs, splits, 64)) return hipErrorInvalidValue;
         const bool apart = parts_apart(wgs * splits, max_keys - n / 2, from_memory);
-        hipLaunchKernelGGL((apart ? chunk_attention_bf16<2> : chunk_attention_bf16<2, 1, 4, false>), dim3(n_heads, n_branches * ((n + 63) / 64), splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
+        hipLaunchKernelGGL((apart ? chunk_attention_bf16<2> : chunk_attention_bf16<2, 1, 4, false>), chunk_grid(n_heads, n_branches * ((n + 63) / 64), splits), dim3(768), kAttLds, s, q, o, n, d_model, n_heads,
                            0, none, layer, scale_log2e, branches, no_tree, sc.split_buf, sc.split_count);
     }
     return hipGetLastError();

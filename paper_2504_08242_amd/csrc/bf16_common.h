@@ -338,6 +338,17 @@ inline size_t att_split_counters(int T, int n_heads, bool branches) {
     const size_t b = T < kMaxBranches ? T : kMaxBranches;
     return ((size_t)(T + 31) / 32 + (branches ? b : 0)) * (size_t)n_heads;
 }
+// Grid of chunk attention: heads x query blocks (of all branches) x key ranges.  A grid's y ends at 65535: the query blocks of a
+// longer chunk or batch (over 4 million tokens, far beyond the chunks that split their keys) go on at x = n_heads, 2 n_heads, ...
+inline dim3 chunk_grid(int n_heads, int q_blocks, int splits) {
+    const int folds = (q_blocks + 65534) / 65535;
+    return dim3(n_heads * folds, (q_blocks + folds - 1) / folds, splits);
+}
+// The query block of a workgroup (past the last one in the last fold), and its head.
+__host__ __device__ __forceinline__ int unfold_block(int x, int y, int grid_y, int n_heads, int& head) {
+    for (head = x; head >= n_heads; head -= n_heads) y += grid_y;
+    return y;
+}
 struct AttScratch {
     float* split_buf;
     int* split_count;

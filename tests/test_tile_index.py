@@ -1,4 +1,4 @@
-"""Quotients of the tile index (a multiplication and a compare instead of a division) against integer division (no GPU needed)."""
+"""Index arithmetic of the kernels that the host compiler can run (no GPU needed)."""
 import os
 import shutil
 import subprocess
@@ -31,13 +31,53 @@ int main() {
 """
 
 
-def test_quotients_are_exact_for_every_index(tmp_path):
+BLOCKS = r"""
+#include <cstdio>
+#include <vector>
+#include "bf16_common.h"
+int main() {
+    long bad = 0, n = 0;
+    for (int heads : {1, 3, 8, 40})
+        for (int blocks : {1, 2, 65535, 65536, 64 * 1024, 64 * 1025, 131070, 131071, 200001}) {
+            const dim3 g = jup::chunk_grid(heads, blocks, 1);
+            bad += g.y > 65535 || g.z != 1;
+            std::vector<int> seen((size_t)heads * blocks);
+            for (unsigned x = 0; x < g.x; ++x)
+                for (unsigned y = 0; y < g.y; ++y) {
+                    int head;
+                    const int bq = jup::unfold_block(x, y, g.y, heads, head);
+                    if ((int)x >= heads && bq >= blocks) continue;
+                    if (head < 0 || head >= heads || bq >= blocks) ++bad;
+                    else ++seen[(size_t)bq * heads + head];
+                }
+            for (int s : seen) n += 1, bad += s != 1;
+        }
+    printf("%ld of %ld\n", bad, n);
+    return bad != 0;
+}
+"""
+
+
+def run_on_the_host(program, tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc is not installed")
-    src, exe = tmp_path / "quotient.hip", tmp_path / "quotient"
-    src.write_text(PROGRAM)
+    src, exe = tmp_path / "program.hip", tmp_path / "program"
+    src.write_text(program)
     flags = [f for f in jbuild.HIPCC_FLAGS if f not in ("-shared", "-c")]
     subprocess.run([hipcc, *flags, f"-I{jbuild.CSRC}", str(src), "-o", str(exe)], check=True)
-    out = subprocess.run([str(exe)], check=True, stdout=subprocess.PIPE, text=True).stdout
-    assert out.startswith("0 of"), out
+    return subprocess.run([str(exe)], check=True, stdout=subprocess.PIPE, text=True).stdout
+
+
+def test_quotients_are_exact_for_every_index(tmp_path):
+    """A multiplication and a compare instead of a division, against integer division."""
+    assert run_on_the_host(PROGRAM, tmp_path).startswith("0 of")
+
+
+def test_grid_of_chunk_attention_reaches_every_block_once(tmp_path):
+    """Chunks and batches of branches with more query blocks than a grid's second dimension holds, and fewer.  Every
+    launch uses this grid."""
+    assert run_on_the_host(BLOCKS, tmp_path).startswith("0 of")
+    source = open(os.path.join(jbuild.CSRC, "bf16_attention.hip")).read()
+    launches = [l for l in source.splitlines() if "hipLaunchKernelGGL" in l and "chunk_attention_bf16" in l]
+    assert len(launches) == 4 and all("chunk_grid(" in l for l in launches), launches
