@@ -286,13 +286,7 @@ __device__ __forceinline__ float w4_group(float acc, float scale, float t, float
 
 // ---- projections of a 4-bit stage (w4_gemm.hip) ----------------------------------------------------
 // epi: EPI_QKV, EPI_SWIGLU or EPI_PARTIAL; the tiling fields of `a` are filled here.  EPI_PARTIAL writes
-// w4_partial_splits(n_tok, N, K) partial buffers, w4_plan_splits(n_tok, N, K) of them up to 32 tokens.
-int w4_partial_splits(int n_tok, int N, int K);
-int w4_plan_splits(int n_tok, int N, int K);
-int w4_rows(int M, int N, int K, int splits);  // rows per workgroup of the kernel of decode-sized chunks: 16, 32 or 64
-// the kernel of longer chunks and branches (w4_wide.hip), and which projections take it
-bool w4_is_wide(int epi, int n_tok, int N, int K);
-int w4_wide_splits(int n_tok, int N, int K);
+// w4_partial_splits(n_tok, N, K) partial buffers (w4_plan.h, also which projections take the kernel of w4_wide.hip).
 hipError_t launch_gemm_w4_wide(int epi, const GemmArgs& a, hipStream_t s);
 hipError_t w4_wide_configure();  // raises the dynamic-LDS limit (once per process)
 hipError_t launch_gemm_w4(int epi, GemmArgs a, hipStream_t s);

@@ -11,7 +11,7 @@
 // The projections back to d_model are too narrow to fill 256 CUs with tall tiles, so they split K and
 // write fp32 partial tiles; the next reduce+norm pass adds them to the fp32 residual stream in a fixed
 // order (bitwise reproducible) on its way to the normalised bf16 rows it has to produce anyway.
-#include "bf16_common.h"
+#include "w4_plan.h"
 
 namespace jup {
 

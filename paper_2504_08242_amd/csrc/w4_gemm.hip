@@ -23,14 +23,10 @@
 //     Products of a bf16 value and an integer below 256 are exact in fp32, the sums round as any fp32 sum does.
 //   * A (16 rows of the tiled activation layout per row group) is read from L2 with 16-byte loads, up to 1 KB per
 //     wave and K step; lanes whose row lies past the chunk repeat its last row.
-#include "bf16_common.h"
+#include "w4_plan.h"
 
 namespace jup {
 namespace {
-
-constexpr int W4_GROUP = 128;   // input features per scale
-constexpr int W4_TILE_N = 64;   // columns per workgroup
-constexpr int W4_WAVES = 8;
 
 enum { W4_PACK_PLAIN = 0, W4_PACK_QKV = 1, W4_PACK_GATE_UP = 2 };
 
@@ -336,36 +332,6 @@ hipError_t launch_one(GemmArgs a, hipStream_t s) {
 }
 
 }  // namespace
-
-// Rows per workgroup, by rounds of workgroups: one per CU with 64 or 32 rows, two with 16.  16 where that is one workgroup per
-// CU, or where a wave has a single K group and two workgroups fit; then 32 (whose codes are expanded once for twice the
-// rows); then 16 on two workgroups per CU; then 64.  Measured on one MI355X (us): QKV of d_model 1024, 64 rows, 64 -> 16 per
-// workgroup 9.4 -> 4.7; of d_model 2048, 64 -> 32 12.7 -> 7.4; O of d_model 5120, 48 rows, 64 -> 16 12.1 -> 9.5; O of the 7B
-// shapes, 32 rows (one group per wave), 32 -> 16 5.6 -> 4.9, but QKV of those (four groups) 12.2 -> 13.3.  Whatever the rows, a
-// result's sums are the same.
-int w4_rows(int M, int N, int K, int splits) {
-    const int wgs = N / W4_TILE_N * splits, groups = (K / W4_GROUP + splits * W4_WAVES - 1) / (splits * W4_WAVES);
-    const int at_16 = wgs * ((M + 15) / 16), at_32 = wgs * ((M + 31) / 32);
-    if (M <= 16 || at_16 <= 256 || (groups == 1 && at_16 <= 512)) return 16;
-    if (M <= 32 || at_32 <= 256) return 32;
-    return at_16 <= 512 ? 16 : 64;
-}
-
-// Splits of K for the projections back to d_model (their N / 64 column tiles alone do not occupy the chip): as many
-// as keep the grid within about one workgroup per CU, at most 8 (the reduce + norm pass sums up to 8 partial
-// buffers), and no more than leave every wave a K group: with fewer groups than waves a split only adds partial sums
-// (and ranges to add up: one row of six layers of d_model 1024 157 -> 148 us).  More than
-// 16 tokens, whose rows weigh on the path from L2, spread over the CUs all the same.
-int w4_plan_splits(int n_tok, int N, int K) {
-    const int tiles = N / W4_TILE_N, G = K / W4_GROUP;
-    int splits = 1;
-    while (splits < 8 && tiles * splits * 2 <= 256 && splits * 2 * (n_tok <= kMaxProjectRows ? W4_WAVES : 1) <= G) splits *= 2;
-    return splits;
-}
-
-int w4_partial_splits(int n_tok, int N, int K) {
-    return w4_is_wide(EPI_PARTIAL, n_tok, N, K) ? w4_wide_splits(n_tok, N, K) : w4_plan_splits(n_tok, N, K);
-}
 
 hipError_t launch_gemm_w4(int epi, GemmArgs a, hipStream_t s) {
     if (a.M <= 0 || a.n_tok <= 0 || a.N % W4_TILE_N || a.K % W4_GROUP) return hipErrorInvalidValue;

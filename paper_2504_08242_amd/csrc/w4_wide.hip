@@ -24,7 +24,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "bf16_common.h"
+#include "w4_plan.h"
 
 namespace jup {
 namespace {
@@ -407,65 +407,13 @@ hipError_t launch(GemmArgs a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// (row blocks, columns blocks = waves that share a K share, K shares)
-#define JUP_WIDE_SHAPES(X) X(2, 1, 4) X(2, 2, 4) X(2, 3, 4) X(4, 4, 2) X(4, 6, 1) X(4, 8, 1)
-
-// A launch is priced as rounds of workgroups (one per CU) times what a round takes: turns of the loop and a fixed part.  The
-// constants are fitted to 900 timings of these shapes (33 .. 1024 rows, the projections of stages of d_model 1024, 2048,
-// 4096, 5120 and 8192, all numbers of splits): 5 % off on average; the pick costs 0.4 % more than the best shape measured
-// on average and 10 % at worst.
-struct WideCost {
-    int mb, wn, wk;
-    float turn, round, qkv;  // us; qkv: more per round with the QKV epilogue
-};
-constexpr WideCost kWide[] = {{2, 1, 4, 1.37f, 1.4f, 1.2f}, {2, 2, 4, 1.54f, 2.3f, 1.4f}, {2, 3, 4, 1.96f, 3.1f, 1.3f},
-                              {4, 4, 2, 1.92f, 4.3f, 1.8f}, {4, 6, 1, 1.56f, 5.9f, 2.6f}, {4, 8, 1, 1.66f, 6.1f, 2.3f}};
-constexpr int kCUs = 256;
-constexpr float kLaunchUs = 3.0f, kPartRound = 0.7f;
-constexpr float kPartialUsPerByte = 1.0f / 5.2e6f;  // what the reduce + norm pass pays to read a partial sum back
-
-int div_up(int x, int y) { return (x + y - 1) / y; }
-
-float rounds_of(int wgs) {
-    const int rest = wgs % kCUs;
-    return (float)(wgs / kCUs) + (rest ? kPartRound + (1.f - kPartRound) * rest / kCUs : 0.f);
-}
-float cost(const WideCost& c, int epi, int M, int N, int K, int splits) {
-    const int wgs = div_up(M, 32 * c.mb) * div_up(N, 32 * c.wn) * splits;
-    const int turns = div_up(div_up(K / 128, splits), c.wk);
-    return kLaunchUs + rounds_of(wgs) * (c.turn * turns + c.round + (epi == EPI_QKV ? c.qkv : 0.f)) +
-           (epi == EPI_PARTIAL ? 4.f * M * N * splits * kPartialUsPerByte : 0.f);
-}
-
-struct WidePick {
-    WideCost c;
-    int splits;
-    float us;
-};
-// The order of a sum is a matter of the K shares and splits, so these are picked for the tokens of one chunk or branch, and
-// the rest of the shape for the rows of the launch: a branch has the same bits alone and batched with others.
-WidePick pick(int epi, int n_tok, int N, int K) {
-    WidePick best{};
-    for (const WideCost& c : kWide)
-        for (int splits : {1, 2, 3, 4, 6, 8}) {
-            if (splits > 1 && (epi != EPI_PARTIAL || splits > K / 128 ||
-                               div_up(n_tok, 32 * c.mb) * div_up(N, 32 * c.wn) * splits > 2 * kCUs)) continue;
-            const float us = cost(c, epi, n_tok, N, K, splits);
-            if (best.splits == 0 || us < best.us) best = {c, splits, us};
-        }
-    return best;
-}
-
 template <int EPI>
 hipError_t dispatch(const GemmArgs& a, hipStream_t s) {
-    const WidePick p = pick(EPI, a.n_tok, a.N, a.K);
+    const WidePick p = wide_shape(EPI, a.n_tok, a.M, a.N, a.K);
     GemmArgs b = a;
     b.splits = p.splits;
-    WideCost t = p.c;
-    for (const WideCost& c : kWide)
-        if (c.wk == t.wk && cost(c, EPI, a.M, a.N, a.K, p.splits) < cost(t, EPI, a.M, a.N, a.K, p.splits)) t = c;
 #define X(MB, WN, WK) \
-    if (t.mb == MB && t.wn == WN && t.wk == WK) return launch<EPI, MB, WN, WK>(b, s);
+    if (p.c.mb == MB && p.c.wn == WN && p.c.wk == WK) return launch<EPI, MB, WN, WK>(b, s);
     JUP_WIDE_SHAPES(X)
 #undef X
     return hipErrorInvalidConfiguration;
@@ -480,27 +428,7 @@ hipError_t configure_one() {
                                S::LDS_BYTES);
 }
 
-// What a launch of w4_gemm.hip takes on 64 rows (rounds of 64-column tiles of w4_rows rows, eight waves that split a K range;
-// fitted to the same stages within 10 %).
-float cost_of_rows(int epi, int N, int K) {
-    const int splits = epi == EPI_PARTIAL ? w4_plan_splits(64, N, K) : 1;
-    const int rows = w4_rows(64, N, K, splits);
-    const float groups = (float)div_up(div_up(K / 128, splits), 8);
-    const float round = rows == 64 ? 3.3f * groups + (epi == EPI_PARTIAL ? 1.5f : 2.6f) : (rows == 32 ? 1.9f : 1.0f) * groups + 0.2f;
-    return kLaunchUs + rounds_of(N / 64 * splits * (64 / rows) / (rows == 16 ? 2 : 1)) * round + (epi == EPI_PARTIAL ? 4.f * 64 * N * splits * kPartialUsPerByte : 0.f);
-}
-
 }  // namespace
-
-// More than 64 tokens: always (1.0 - 2.5 times as fast over the stages above).  33 .. 64 tokens: where it is the faster one alone,
-// e.g. gate/up of the 7B shapes 32 -> 22 us, QKV of d_model 8192 58 -> 39 us, down of the 13B shapes 25 -> 19 us; not QKV of
-// d_model 1024, 4.0 -> 7.1 us (0.95: it is 33 rows, too, that have to gain, which w4_gemm.hip does a tenth faster than 64).
-// Up to 32 tokens the kernel of w4_gemm.hip takes half the time (QKV of the 7B shapes 14 us, here 18).
-bool w4_is_wide(int epi, int n_tok, int N, int K) {
-    if (n_tok <= 32) return false;
-    return n_tok > 64 || pick(epi, 64, N, K).us <= 0.95f * cost_of_rows(epi, N, K);
-}
-int w4_wide_splits(int n_tok, int N, int K) { return pick(EPI_PARTIAL, n_tok, N, K).splits; }
 
 hipError_t launch_gemm_w4_wide(int epi, const GemmArgs& a, hipStream_t s) {
     if (a.M <= 0 || a.n_tok <= 0 || a.N % 64 || a.K % 128) return hipErrorInvalidValue;

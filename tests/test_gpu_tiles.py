@@ -208,16 +208,21 @@ def test_batched_branches_of_more_than_64_rows_have_the_bits_they_have_alone(dty
             kv.destroy()
 
 
-@pytest.mark.parametrize("d_model,n_heads,d_ffn,rows", [
+# test_tile_index.py replays the plans: every (row blocks, column blocks, K shares) of gemm_w4_wide with every epilogue is among them
+W4_LONG_CHUNKS = [
     (256, 2, 128, [33, 65, 129]),               # fewer K groups than K shares
     (768, 6, 896, [64, 200, 513]),              # groups no multiple of the shares, column tiles past the matrix
-    (1024, 8, 2816, [33, 65, 257, 384, 1024]),  # every shape, up to six K splits
+    (1024, 8, 2816, [33, 65, 257, 384, 1024]),  # up to six K splits
     (2304, 18, 1408, [129, 513, 1024]),
+    (4096, 32, 11008, [64]),                    # gate/up alone on gemm_w4_wide
     (5120, 40, 3456, [40, 200, 1024]),
-])
+]
+
+
+@pytest.mark.parametrize("d_model,n_heads,d_ffn,rows", W4_LONG_CHUNKS)
 def test_w4_projections_of_long_chunks(d_model, n_heads, d_ffn, rows):
-    """4-bit codes, more than 32 tokens: rows on and beside the edges of the tiles of 64 and 128 rows, every (row block, column,
-    K share) shape for some projection, against the oracle, behind a cached prefix; the same bits twice."""
+    """4-bit codes, more than 32 tokens: rows on and beside the edges of the tiles of 64 and 128 rows, every tile shape with every
+    epilogue, against the oracle, behind a cached prefix; the same bits twice."""
     cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=n_heads, d_ffn=d_ffn, n_layers=1)
     p = Pair(cfg, "w4", seed=d_model + 1, max_positions=max(rows) + 5, max_chunk_tokens=max(rows))
     for n in rows:

@@ -1,4 +1,4 @@
-"""Index arithmetic of the kernels that the host compiler can run (no GPU needed)."""
+"""Index arithmetic and plans of the kernels that the host compiler can run (no GPU needed)."""
 import os
 import shutil
 import subprocess
@@ -58,6 +58,26 @@ int main() {
 """
 
 
+SHAPES = r"""
+#include <cstdio>
+#include "w4_plan.h"
+int main() {
+    struct { int d, f, n; } cases[] = {%s};
+    for (auto c : cases) {
+        struct { int epi, N, K; } projections[] = {{jup::EPI_QKV, 3 * c.d, c.d}, {jup::EPI_PARTIAL, c.d, c.d},
+                                                   {jup::EPI_SWIGLU, 2 * c.f, c.d}, {jup::EPI_PARTIAL, c.d, c.f}};
+        for (auto p : projections) {
+            if (!jup::w4_is_wide(p.epi, c.n, p.N, p.K)) continue;
+            const jup::WideCost t = jup::wide_shape(p.epi, c.n, c.n, p.N, p.K).c;
+            printf("%%d,%%d,%%d,%%d\n", t.mb, t.wn, t.wk, p.epi);
+        }
+    }
+#define X(MB, WN, WK) for (int epi = 0; epi < 3; ++epi) printf("built %%d,%%d,%%d,%%d\n", MB, WN, WK, epi);
+    JUP_WIDE_SHAPES(X)
+}
+"""
+
+
 def run_on_the_host(program, tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
@@ -81,3 +101,12 @@ def test_grid_of_chunk_attention_reaches_every_block_once(tmp_path):
     source = open(os.path.join(jbuild.CSRC, "bf16_attention.hip")).read()
     launches = [l for l in source.splitlines() if "hipLaunchKernelGGL" in l and "chunk_attention_bf16" in l]
     assert len(launches) == 4 and all("chunk_grid(" in l for l in launches), launches
+
+
+def test_gpu_test_of_long_w4_chunks_runs_every_tile_shape(tmp_path):
+    from test_gpu_tiles import W4_LONG_CHUNKS
+    cases = ", ".join(f"{{{d}, {f}, {n}}}" for d, _, f, rows in W4_LONG_CHUNKS for n in rows)
+    lines = run_on_the_host(SHAPES % cases, tmp_path).splitlines()
+    built = {l.split()[1] for l in lines if l.startswith("built ")}
+    assert len(built) == 15
+    assert built == set(lines) - {l for l in lines if l.startswith("built ")}
