@@ -48,7 +48,8 @@
  *     Hidden states, gains and the KV cache stay bfloat16 (a cache made for a JUP_BF16 configuration of the
  *     same shape serves a JUP_BF16_W4 stage and vice versa).  The kernels behind it are built for decode-sized
  *     chunks (Sec. V), which are bound by streaming the weights: up to 16 tokens stream every matrix once;
- *     longer chunks are accepted: more than 32 tokens run on kernels that expand the codes once per 64 or 128 rows.
+ *     longer chunks are accepted: chunks and branches of more than 64 tokens expand the codes once per 64 or 128 rows,
+ *     those of 17 to 64 (and batches of such branches) once per 16, 32 or 64 rows, whichever is faster.
  *   - Calls validate their arguments on the host before anything is enqueued;
  *     on error nothing is enqueued, no state changes, and jup_last_error()
  *     holds a message.  Kernel work is asynchronous on the given HIP stream.
@@ -101,8 +102,8 @@ typedef struct {
      * JUP_BF16_W4 only (must be 0 otherwise): 1 = the stage also keeps bf16(scale * (code - 8)) of its seven
      * matrices, 2 more bytes per weight in `packed`.  Chunks of more than 64 rows then run the bf16 kernels on that
      * copy (they are bound by arithmetic, where 4-bit weights save nothing) and shorter ones stream the codes (they
-     * are bound by reading the weights, Sec. V); with 0 the stage holds codes only and a longer chunk reads
-     * them once per 64 or 128 rows.  The expanded weights carry one more rounding to bf16 than the codes.
+     * are bound by reading the weights, Sec. V); with 0 the stage holds codes only, and longer chunks and
+     * branches read them once per 64 or 128 rows.  The expanded weights carry one more rounding to bf16 than the codes.
      */
     int32_t w4_expanded;
 } jup_stage_config_t;

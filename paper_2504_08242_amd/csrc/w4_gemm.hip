@@ -235,8 +235,9 @@ __global__ __launch_bounds__(64 * WAVES, RG == 1 ? 4 : 2) void gemm_w4(const Gem
             if (g + 2 < g1) compute(even.c, even.r);
         }
     } else {
-        // 64 rows: the next codes are on their way while the current ones are used; the rows are fetched when their group's
-        // turn comes.
+        // 64 rows: a group's rows are asked for when its turn comes, behind the next group's codes.  Loads return in order, so its
+        // products wait for those codes too: one trip to memory per group.  (Codes in two sets that take turns, asked for behind
+        // the rows, would stay in flight through the group: 240 registers, not measured.)
         W4Codes cur, nxt;
         W4Rows<RG> rows;
         if (g0 < g1) fetch_codes(cur, g0);

@@ -1,6 +1,6 @@
-// Projections of a 4-bit stage (JUP_BF16_W4) for chunks and branches of more than 32 tokens: C[M, N] = A[M, K] * W[N, K]^T on
-// the packed codes and scales of w4_gemm.hip, whose kernel is built for decode-sized chunks (its waves read the rows from
-// L2, 64 at a time, and expand the codes once per 64 rows).
+// Projections of a 4-bit stage (JUP_BF16_W4) for chunks and branches of more than 64 tokens, from 33 on where this is the faster
+// kernel (w4_plan.h): C[M, N] = A[M, K] * W[N, K]^T on the packed codes and scales of w4_gemm.hip, whose kernel is built for
+// decode-sized chunks (its waves read the rows from L2, 64 at a time, and expand the codes once per 64 rows).
 //
 //   * A wave owns 32 MB rows x 32 columns and every WK-th K group of its workgroup: its columns are its own, so the codes go
 //     from global memory into registers and are expanded there, once per 32 MB rows; nothing of W passes through LDS.  The
@@ -146,7 +146,9 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_w4_wide(const GemmArgs a) {
             const int j = min(q * S::WAVES + wave, S::UNITS - 1);
             const unsigned off = (row_at[q] & all) + (at + (turn == iters - 1 ? part_of_last[q] : part_of[q]));
             // (as text: beside the builtin, which the compiler takes for a flat access, it waits for every load in flight
-            // in front of each use of a code or fragment)
+            // in front of each use of a code or fragment.  Text it does not count: its wait for the next codes, all but the
+            // youngest four or five loads, half a turn later drains most of the rows asked for in the same turn, so little more
+            // than one stage of the ring is in flight)
             load_to_lds_16(rows0, off, slot + j * 1024);
         }
     };
