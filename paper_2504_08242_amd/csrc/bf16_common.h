@@ -63,6 +63,14 @@ __device__ inline void load_to_lds_16(const void* uniform_base, unsigned lane_of
                  : "v"(lane_offset), "s"(uniform_base), "s"(lds_base)
                  : "memory", "m0");
 }
+// The same for the lanes of a mask alone: the others read nothing and leave their 16 bytes of LDS as they are (with no lane
+// at all the instruction only counts).  All lanes of the wave are on.
+__device__ inline void load_to_lds_16(const void* uniform_base, unsigned lane_offset, unsigned lds_base, unsigned long long lanes) {
+    asm volatile("s_mov_b64 exec, %3\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+                 :
+                 : "v"(lane_offset), "s"(uniform_base), "s"(lds_base), "s"(lanes)
+                 : "memory", "m0");
+}
 // LDS byte address of a pointer into the workgroup's dynamic LDS.
 __device__ inline unsigned lds_byte_address(const void* p) {
     return (unsigned)(size_t)(const __attribute__((address_space(3))) void*)p;

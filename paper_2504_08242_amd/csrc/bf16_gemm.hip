@@ -185,16 +185,37 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     // 512-row chunks, whose K loop does not afford the branch below: 2 us per launch, measured)
     constexpr bool kShortChunkTile = BMB <= 2 || (BMB == 4 && WM * WN == 4);
     const bool nt_weights = a.m_tiles == 1 && !a.shared_gpu;
+    // Those tiles leave the rows past M out (LDS holds anything there, which reaches the accumulators of those rows alone): a CU
+    // takes operands at about 50 GB/s, and 40 rows in a 64-row tile spent a fifth of that on rows that do not exist.  Four
+    // rows are 256 bytes, 16 lanes.  Whole layers, before -> after (same bits): 7B 40 rows 100.8 -> 96.0 us, 100 rows 135.0 ->
+    // 128.9, 5 rows 83.5 -> 82.5, 64 rows 103.6 -> 103.4; 13B 40 rows 136.9 -> 131.4, 128 rows 182.4 -> 182.1.  (A ring of 16
+    // stages instead of 8, now that a stage of few rows is short: 5 rows 83.0 -> 85.6.)
+    const unsigned ring = __builtin_amdgcn_readfirstlane(lds_byte_address(smem));
+    unsigned long long lanes[S::LPW];
+    if constexpr (kShortChunkTile) {
+#pragma unroll
+        for (int q = 0; q < S::LPW; ++q) {
+            const int j = q * S::LOADERS + lw;
+            const int fours = j < G_BM / 16 ? max(min((a.M - (m0 + j * 16) + 3) / 4, 4), 0) : 4;
+            lanes[q] = fours == 4 ? ~0ull : (1ull << (fours * 16)) - 1;
+        }
+    }
     auto issue_one = [&](int q, int stage, int kt) {
-        const auto* src = (const __attribute__((address_space(1))) void*)(uniform_ptr(ubase[q] + (size_t)kt * 2048) + lane16);
-        auto* dst = (__attribute__((address_space(3))) void*)(smem + stage * S::STAGE_BYTES + (q * S::LOADERS + lw) * 1024);
+        const char* at = uniform_ptr(ubase[q] + (size_t)kt * 2048);
+        const int unit = q * S::LOADERS + lw;
+        const auto* src = (const __attribute__((address_space(1))) void*)(at + lane16);
+        auto* dst = (__attribute__((address_space(3))) void*)(smem + stage * S::STAGE_BYTES + unit * 1024);
         // A chunk of up to 128 tokens alone on the chip streams every weight exactly once (one M tile): its weight units
         // are fetched with the non-temporal hint, so that the stream does not push the KV cache and the activations
         // out of L2 and the last-level cache.  Measured on the 7B shapes: gate/up at 5 rows 36.1 -> 32.5 us, the
         // attention launch behind the projections 15.0 -> 12.4 us, a 5-token call 6.59 -> 5.95 ms per 8 branches, 128-token
         // chunks +6 %.  Not for the tiles of longer chunks (the branch costs their K loop 2.5 % and a second M tile re-reads
         // the weights from L2) and not inside an overlapped call (the other chunks find the weights in the caches).
-        if (kShortChunkTile && nt_weights && q * S::LOADERS + lw >= G_BM / 16) __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 2);
+        // (which of the two a unit is folds to a constant where the waves divide the units of the rows)
+        constexpr int ROW_UNITS = G_BM / 16;
+        const bool rows = (q + 1) * S::LOADERS <= ROW_UNITS || (q * S::LOADERS < ROW_UNITS && unit < ROW_UNITS);
+        if (kShortChunkTile && rows) load_to_lds_16(at, lane16, ring + stage * S::STAGE_BYTES + unit * 1024, lanes[q]);
+        else if (kShortChunkTile && nt_weights) __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 2);
         else __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
     };
     auto issue = [&](auto has_last, int stage, int kt) {

@@ -53,6 +53,21 @@ def test_bf16_tall_tiles(d_model, n_heads, d_ffn, rows, tiles):
     p.check(p.kv_gpu()[0], p.oracle.kv[0], "cache")
 
 
+@pytest.mark.parametrize("rows", [1, 4, 5, 15, 17, 29, 33, 40, 61, 64, 65, 77, 100, 127])
+def test_bf16_rows_that_do_not_exist(rows):
+    """Tiles of up to 128 rows leave out the rows past the chunk: whatever LDS holds there (here NaN, left by a chunk of
+    another cache) reaches no row of the chunk.  Groups of four rows, halves of row blocks and whole blocks."""
+    cfg = dict(si.LLAMA7B_STAGE, d_model=512, n_heads=4, d_ffn=1408, n_layers=2)
+    p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 7, max_chunk_tokens=128)
+    other = jb.KvCache(cfg, "bf16", 128)
+    hidden = p.hidden(rows + 7)
+    p.gpu_chunk(hidden[:7], 0)
+    p.oracle.prefill_chunk(hidden[:7], 0)
+    p.gpu_chunk(np.full((128 if rows > 64 else 64, cfg["d_model"]), np.nan, hidden.dtype), 0, other)
+    p.check(p.gpu_chunk(hidden[7:], 7), p.oracle.prefill_chunk(hidden[7:], 7), f"{rows} rows")
+    p.check(p.kv_gpu()[1], p.oracle.kv[1], "cache")
+
+
 @pytest.mark.parametrize("n_lanes,chunks,limit", [
     (2, [70, 3, 0, 129, 64, 300], 300),     # one group: row counts that are no multiple of a row block
     (2, [250] * 9, 250),                    # more rows than the lanes' buffer holds: several groups
