@@ -55,6 +55,7 @@ struct Shape {
                                                     // MFMAs on rows that do not exist would only slow that down)
     static constexpr int NBW = NB / WN;             // column blocks per wave
     static constexpr int MBW = BMB / WM;            // row blocks per wave
+    static constexpr int EXTRA = BMB % WM;          // a row block more, of which every wave takes one column block
     static constexpr int WAVES = WM * WN;
     static constexpr int ROWS = BM + 32 * NB;       // LDS rows per stage: A rows then W rows
     static constexpr int STAGE_BYTES = ROWS * 64;
@@ -63,7 +64,7 @@ struct Shape {
     static constexpr int NL = ROWS / 16;            // 1 KB load units (16 rows) per stage, dealt round-robin to the loading waves
     static constexpr int LPW = (NL + LOADERS - 1) / LOADERS;  // load instructions per stage of the waves that have the most
     static constexpr int REM = NL % LOADERS;        // loading waves below REM issue LPW loads, the others LPW - 1 (0: all LPW)
-    static_assert(NB % WN == 0 && BMB % WM == 0, "tile does not split evenly over the waves");
+    static_assert(NB % WN == 0 && EXTRA <= 1, "tile does not split evenly over the waves");
     // as many ring slots as LDS holds (at most 8: the in-flight count must fit the 6-bit vmcnt)
     static constexpr int STAGES = kLdsBudget / STAGE_BYTES > 8 ? 8 : kLdsBudget / STAGE_BYTES;
     // tiles that chunks of up to 16 rows take: the factors of rows with partial sums of squares, behind the ring
@@ -122,40 +123,26 @@ __device__ __forceinline__ void wait_groups(int g) {
     else wait_vmcnt<0>();
 }
 
-// Fragments of one K/16 sub-step of a wave: MB row blocks, NB column blocks.
+// Fragments of one K/16 sub-step of a wave: MB row blocks (the extra one last), NB column blocks.
 template <int MB, int NB>
 struct Frags {
     bf16x8 a[MB];
     bf16x8 b[NB];
 };
 
+// The tile of row blocks mt * BMB .. and columns [n0, n_end) (K split: split).
 // FACTOR: the results of a row may have to be multiplied by its 1 / rms.  A template parameter because on the tall tiles of
 // long chunks, which never need it, the test alone cost the 512-row launches 1 %.
-template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR = BMB <= 2 && EPI != EPI_PARTIAL>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem, int split, int mt, int n0, int n_end) {
     using S = Shape<BMB, NB, WM, WN>;
     constexpr int G_BM = S::BM;
-    constexpr int NBW = S::NBW, MBW = S::MBW;
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    constexpr int NBW = S::NBW, MBW = S::MBW, EXTRA = S::EXTRA;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;  // wave owns row blocks [wm MBW, +MBW) x column blocks [wn NBW, +NBW)
     const int lw = wave;
-
-    // ---- which tile ---------------------------------------------------------------------------------
-    // Workgroup b runs on XCD b % 8.  Tiles are numbered so that each XCD owns one contiguous range of
-    // them, M tiles fastest: the workgroups that read the same weight rows (all M tiles of an N tile) and
-    // neighbouring N tiles (same activation rows) then share one L2.
-    int mt, grp;
-    {
-        const int q = gridDim.x >> 3, r = gridDim.x & 7;
-        const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-        const int tile = xcd * q + min(xcd, r) + local;
-        grp = a.by_m.of(tile);
-        mt = tile - grp * a.m_tiles;
-    }
-    const int split = a.by_n.of(grp), nt = grp - split * a.n_tiles;
-    const int m0 = mt * G_BM, n0 = nt * a.n_stride;
+    const int m0 = mt * G_BM;
     const int KT = a.kt_per_split;
 
     // ---- global -> LDS load slots of this wave --------------------------------------------------------
@@ -249,23 +236,29 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     for (int ks = 0; ks < 2; ++ks)
         lane_off[ks] = (c >> 2) * 256 + ((((c & 3) << 2) + 2 * ks + hh) ^ ((c >> 2) & 3)) * 16;
     const int a_base = wm * MBW * 2048, b_base = G_BM * 64 + wn * NBW * 2048;
-    // Read number t of a sub-step, in the order the MFMAs need them: a[0], b[0], the other a, the other b.
-    auto load_frag_one = [&](Frags<MBW, NBW>& f, int stage, int ks, int t) {
+    // Tiles with an extra row block: the waves of a column range begin at different columns of it, and each multiplies the
+    // extra rows by the columns it begins at (b[0]; more waves than columns: some for nothing).
+    const int first_nb = EXTRA ? wm % NBW : 0;
+    auto column = [&](int nb) { return EXTRA ? (nb + first_nb >= NBW ? nb + first_nb - NBW : nb + first_nb) : nb; };
+    using F = Frags<MBW + EXTRA, NBW>;
+    // Read number t of a sub-step, in the order the MFMAs need them: a[0], b[0], the other a, the other b, the extra a.
+    constexpr int READS = MBW + NBW + EXTRA;
+    auto load_frag_one = [&](F& f, int stage, int ks, int t) {
         const unsigned char* sb = smem + stage * S::STAGE_BYTES + lane_off[ks];
         if (t == 0) f.a[0] = *(const bf16x8*)(sb + a_base);
-        else if (t == 1) f.b[0] = *(const bf16x8*)(sb + b_base);
+        else if (t == 1) f.b[0] = *(const bf16x8*)(sb + b_base + column(0) * 2048);
         else if (t < MBW + 1) f.a[t - 1] = *(const bf16x8*)(sb + a_base + (t - 1) * 2048);
-        else f.b[t - MBW] = *(const bf16x8*)(sb + b_base + (t - MBW) * 2048);
+        else if (t < MBW + NBW) f.b[t - MBW] = *(const bf16x8*)(sb + b_base + column(t - MBW) * 2048);
+        else f.a[MBW + EXTRA - 1] = *(const bf16x8*)(sb + (BMB - 1) * 2048);
     };
-    auto load_frags = [&](Frags<MBW, NBW>& f, int stage, int ks) {
-        const unsigned char* sb = smem + stage * S::STAGE_BYTES + lane_off[ks];
+    auto load_frags = [&](F& f, int stage, int ks) {
 #pragma unroll
-        for (int mb = 0; mb < MBW; ++mb) f.a[mb] = *(const bf16x8*)(sb + a_base + mb * 2048);
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) f.b[nb] = *(const bf16x8*)(sb + b_base + nb * 2048);
+        for (int t = 0; t < READS; ++t) load_frag_one(f, stage, ks, t);
     };
 
-    f32x16 acc[MBW][NBW];
+    f32x16 acc[MBW][NBW], acc_extra;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc_extra[r] = 0.f;
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
@@ -276,7 +269,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
 
     // ---- prologue: fill all but one slot of the ring, fetch the first fragments -----------------------------
     constexpr int ST = S::STAGES;
-    Frags<MBW, NBW> f0, f1;
+    F f0, f1;
     // The whole K loop exists once per load count (waves with and without the last load unit), so that no
     // load sits under a condition: a branch inside the loop would also cut it into scheduling regions.
     auto k_loop = [&](auto has_last) {
@@ -316,23 +309,24 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
         // every step: a burst of LDS reads or global->LDS loads would hold the wave's issue port while the
         // matrix pipe runs dry.  Fragment reads come first in a half, the global->LDS loads after them
         // (spreading the loads among the reads, or keeping the last MFMAs free of both, measured slower).
-        constexpr int NM = MBW * NBW;
+        constexpr int NM = MBW * NBW + EXTRA;
         constexpr int V1 = REFILL && FETCH ? (CNT + 1) / 2 : 0;
         constexpr int V2 = REFILL && FETCH ? CNT - V1 : 0;
         auto half = [&]<int... M>(std::integer_sequence<int, M...>, auto second) {
             constexpr bool SECOND = decltype(second)::value;
-            constexpr int RD = SECOND && LAST ? 0 : MBW + NBW;
+            constexpr int RD = SECOND && LAST ? 0 : READS;
             constexpr int V = SECOND ? V2 : V1;
             constexpr int TOT = RD + V;
             auto step = [&](auto mi) {
                 constexpr int m = decltype(mi)::value;
-                const Frags<MBW, NBW>& use = SECOND ? f1 : f0;
+                const F& use = SECOND ? f1 : f0;
                 // QKV and gate/up compute the TRANSPOSED block (W A^T: the weight fragment as the MFMA's first operand),
                 // so that a lane ends up with 16 output features of ONE token: see the epilogues
-                if constexpr (EPI == EPI_PARTIAL)
-                    acc[m % MBW][m / MBW] = mfma32(use.a[m % MBW], use.b[m / MBW], acc[m % MBW][m / MBW]);
-                else
-                    acc[m % MBW][m / MBW] = mfma32(use.b[m / MBW], use.a[m % MBW], acc[m % MBW][m / MBW]);
+                constexpr bool X = m == MBW * NBW;
+                constexpr int mb = X ? MBW : m % MBW, nb = X ? 0 : m / MBW;
+                f32x16& sum = X ? acc_extra : acc[X ? 0 : mb][nb];
+                if constexpr (EPI == EPI_PARTIAL) sum = mfma32(use.a[mb], use.b[nb], sum);
+                else sum = mfma32(use.b[nb], use.a[mb], sum);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (TOT > 0) {
 #pragma unroll
@@ -381,12 +375,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     }
 
     // ---- epilogues ---------------------------------------------------------------------------------------
-    // Lane (c, hh) holds, for block (mb, nb), column n0 + 32 nb + c and rows row0(mb) + 8*(i/4) + 4*hh + (i%4).
-    const int n_end = min(n0 + a.n_stride, a.N);  // columns [n0, n_end) belong to this tile
+    // Lane (c, hh) holds, for a block of rows row0 .. and columns col .., column col + c and rows row0 + 8*(i/4) + 4*hh + (i%4).
     constexpr int WROWS = 32 * MBW;  // rows of this wave
-    const int row_base = m0 + wm * WROWS + 4 * hh;
     const int nw0 = n0 + wn * NBW * 32;  // first column of this wave
-    auto row_of = [&](int mb, int i) { return row_base + mb * 32 + 8 * (i >> 2) + (i & 3); };
     if constexpr (ROW_SCALE) {
             if (scaled) {
                 sq.finish(scale_of_row, a.M, wave, lane, a.K, a.rms_eps);
@@ -396,100 +387,105 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
             }
     }
 
-    if (EPI == EPI_PARTIAL) {
-        float* pbase = a.partial + (size_t)split * a.M * a.N + nw0 + c;
+    auto store_partial = [&](const f32x16& sum, int row0, int col) __attribute__((always_inline)) {
+        float* pbase = a.partial + (size_t)split * a.M * a.N + col + c;
 #pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) {
-            if (nw0 + nb * 32 + c >= n_end) continue;
-#pragma unroll
-            for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int m = row_of(mb, i);
-                    if (m < a.M) pbase[(size_t)m * a.N + nb * 32] = acc[mb][nb][i];
-                }
+        for (int i = 0; i < 16; ++i) {
+            const int m = row0 + 8 * (i >> 2) + 4 * hh + (i & 3);
+            if (m < a.M) pbase[(size_t)m * a.N] = sum[i];
         }
-    } else if (EPI == EPI_SWIGLU) {
-        // Transposed block: lane (c, hh) holds, for block (mb, nb), token m = row block mb, row c, and the packed weight
-        // rows 8*(i/4) + 4*hh + (i%4) of the 32-row block nb.  The pack kernel orders those rows so that a lane's
-        // registers 0..7 are the gate projections of 8 consecutive features and 8..15 their up projections (block nb
-        // = features 16 nb .. 16 nb + 15, lanes of half hh the features 8 hh .. 8 hh + 7 of them).  A lane therefore
-        // finishes 8 outputs of one token by itself and stores them as one 16-byte chunk of the tiled activation
-        // layout: no exchange between lanes, no LDS, no barrier.
-        const int half_n = a.N >> 1;
+    };
+    // Transposed block: lane (c, hh) holds token m = row c of the row block and the packed weight rows 8*(i/4) + 4*hh + (i%4)
+    // of the 32-row block of W.  The pack kernel orders those rows so that a lane's registers 0..7 are the gate projections of 8
+    // consecutive features and 8..15 their up projections (block nb = features 16 nb .. 16 nb + 15, lanes of half hh the
+    // features 8 hh .. 8 hh + 7 of them).  A lane therefore finishes 8 outputs of one token by itself and stores them as
+    // one 16-byte chunk of the tiled activation layout: no exchange between lanes, no LDS, no barrier.
+    auto store_swiglu = [&](const f32x16& sum, int m, int col, float f) __attribute__((always_inline)) {
+        const int chunk = (col >> 4) + hh;  // 16-byte chunk of the output row: features 8 * chunk ..
+        u32x4 out;
 #pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) {
-            const int col = nw0 + nb * 32;  // first packed column of the block
-            if (col >= n_end) continue;
-            const int chunk = (col >> 4) + hh;  // 16-byte chunk of the output row: features 8 * chunk ..
+        for (int e = 0; e < 4; ++e) {
+            const float g0 = sum[2 * e] * f, g1 = sum[2 * e + 1] * f;
+            const float u0 = sum[8 + 2 * e] * f, u1 = sum[8 + 2 * e + 1] * f;
+            out[e] = pack_bf16x2(g0 * __builtin_amdgcn_rcpf(1.0f + __expf(-g0)) * u0,
+                                 g1 * __builtin_amdgcn_rcpf(1.0f + __expf(-g1)) * u1);
+        }
+        *(u32x4*)(a.act + tiled_offset(m, chunk, a.N >> 6)) = out;
+    };
+    // Transposed block, as above.  A 32-row block of a Q or K head holds 16 rotary indices and their partners 64 further on,
+    // ordered by the pack kernel so that a lane's registers 0..7 are the indices F .. F + 7 (F = 16 j + 8 hh for block j
+    // of the head) and registers 8..15 their partners F + 64 ..: the lane rotates its 8 pairs and stores two 16-byte pieces.
+    // A block of V holds 32 consecutive features, a lane 16 of them (16 hh ..).
+    auto store_qkv = [&](const f32x16& sum, int m, int col, float f) __attribute__((always_inline)) {
+        const int which = (col >= a.d_model) + (col >= 2 * a.d_model);  // (col: one (q|k|v, head, j) for all lanes)
+        const int in_model = col - which * a.d_model;
+        const int head = in_model >> 7, j = (in_model & 127) >> 5;
+        const int f_lo = which == 2 ? 32 * j + 16 * hh : 16 * j + 8 * hh;  // first feature of registers 0..7
+        const int f_hi = which == 2 ? f_lo + 8 : f_lo + 64;                  // ... of registers 8..15
+        u16* dst;
+        if (which == 0) {
+            dst = a.q_out + (size_t)m * a.d_model + head * 128;
+        } else if (!a.branches) {
+            dst = kv_slot_bf16(a.kv, a.layer, which - 1, head, a.n_heads, a.pos0 + m);
+        } else {  // row m is token t of branch b: that branch's cache and position
+            const int b = m / a.branches->n_tok, t = m - b * a.branches->n_tok;
+            dst = kv_slot_bf16(a.branches->kv[b], a.layer, which - 1, head, a.n_heads, a.branches->pos0[b] + t);
+        }
+        u32x4 lo, hi;
+        if (which == 2) {
 #pragma unroll
-            for (int mb = 0; mb < MBW; ++mb) {
-                const int m = m0 + wm * WROWS + mb * 32 + c;
-                if (m >= a.M) continue;
-                const float f = FACTOR ? factor[mb] : 1.0f;
-                u32x4 out;
+            for (int e = 0; e < 4; ++e) {
+                lo[e] = pack_bf16x2(sum[2 * e] * f, sum[2 * e + 1] * f);
+                hi[e] = pack_bf16x2(sum[8 + 2 * e] * f, sum[8 + 2 * e + 1] * f);
+            }
+        } else {
+            const float4* rp = (const float4*)(a.rope + (size_t)m * 64 + f_lo);  // 8 (cos, sin) pairs
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float g0 = acc[mb][nb][2 * e] * f, g1 = acc[mb][nb][2 * e + 1] * f;
-                    const float u0 = acc[mb][nb][8 + 2 * e] * f, u1 = acc[mb][nb][8 + 2 * e + 1] * f;
-                    out[e] = pack_bf16x2(g0 * __builtin_amdgcn_rcpf(1.0f + __expf(-g0)) * u0,
-                                         g1 * __builtin_amdgcn_rcpf(1.0f + __expf(-g1)) * u1);
-                }
-                *(u32x4*)(a.act + tiled_offset(m, chunk, half_n >> 5)) = out;
+            for (int e = 0; e < 4; ++e) {
+                const float4 cs = rp[e];  // (cos, sin) of indices f_lo + 2 e, f_lo + 2 e + 1
+                const float l0 = sum[2 * e] * f, l1 = sum[2 * e + 1] * f;
+                const float h0 = sum[8 + 2 * e] * f, h1 = sum[8 + 2 * e + 1] * f;
+                // lo' = lo cos - hi sin ; hi' = hi cos + lo sin
+                lo[e] = pack_bf16x2(l0 * cs.x - h0 * cs.y, l1 * cs.z - h1 * cs.w);
+                hi[e] = pack_bf16x2(h0 * cs.x + l0 * cs.y, h1 * cs.z + l1 * cs.w);
             }
         }
-    } else {  // EPI_QKV
-        // Transposed block, as above.  A 32-row block of a Q or K head holds 16 rotary indices and their partners 64
-        // further on, ordered by the pack kernel so that a lane's registers 0..7 are the indices F .. F + 7 (F = 16 j
-        // + 8 hh for block j of the head) and registers 8..15 their partners F + 64 ..: the lane rotates its 8 pairs and
-        // stores two 16-byte pieces.  A block of V holds 32 consecutive features, a lane 16 of them (16 hh ..).
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) {
-            const int col = nw0 + nb * 32;  // packed column of the block: one (q|k|v, head, j) for all lanes
-            if (col >= n_end) continue;
-            const int which = (col >= a.d_model) + (col >= 2 * a.d_model);
-            const int in_model = col - which * a.d_model;
-            const int head = in_model >> 7, j = (in_model & 127) >> 5;
-            const int f_lo = which == 2 ? 32 * j + 16 * hh : 16 * j + 8 * hh;  // first feature of registers 0..7
-            const int f_hi = which == 2 ? f_lo + 8 : f_lo + 64;                  // ... of registers 8..15
-#pragma unroll
-            for (int mb = 0; mb < MBW; ++mb) {
-                const int m = m0 + wm * WROWS + mb * 32 + c;
-                if (m >= a.M) continue;
-                u16* dst;
-                if (which == 0) {
-                    dst = a.q_out + (size_t)m * a.d_model + head * 128;
-                } else if (!a.branches) {
-                    dst = kv_slot_bf16(a.kv, a.layer, which - 1, head, a.n_heads, a.pos0 + m);
-                } else {  // row m is token t of branch b: that branch's cache and position
-                    const int b = m / a.branches->n_tok, t = m - b * a.branches->n_tok;
-                    dst = kv_slot_bf16(a.branches->kv[b], a.layer, which - 1, head, a.n_heads, a.branches->pos0[b] + t);
-                }
-                const float f = FACTOR ? factor[mb] : 1.0f;
-                u32x4 lo, hi;
-                if (which == 2) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        lo[e] = pack_bf16x2(acc[mb][nb][2 * e] * f, acc[mb][nb][2 * e + 1] * f);
-                        hi[e] = pack_bf16x2(acc[mb][nb][8 + 2 * e] * f, acc[mb][nb][8 + 2 * e + 1] * f);
-                    }
-                } else {
-                    const float4* rp = (const float4*)(a.rope + (size_t)m * 64 + f_lo);  // 8 (cos, sin) pairs
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float4 cs = rp[e];  // (cos, sin) of indices f_lo + 2 e, f_lo + 2 e + 1
-                        const float l0 = acc[mb][nb][2 * e] * f, l1 = acc[mb][nb][2 * e + 1] * f;
-                        const float h0 = acc[mb][nb][8 + 2 * e] * f, h1 = acc[mb][nb][8 + 2 * e + 1] * f;
-                        // lo' = lo cos - hi sin ; hi' = hi cos + lo sin
-                        lo[e] = pack_bf16x2(l0 * cs.x - h0 * cs.y, l1 * cs.z - h1 * cs.w);
-                        hi[e] = pack_bf16x2(h0 * cs.x + l0 * cs.y, h1 * cs.z + l1 * cs.w);
-                    }
-                }
-                *(u32x4*)(dst + f_lo) = lo;
-                *(u32x4*)(dst + f_hi) = hi;
-            }
+        *(u32x4*)(dst + f_lo) = lo;
+        *(u32x4*)(dst + f_hi) = hi;
+    };
+    auto finish = [&](const f32x16& sum, int row0, int col, float f) __attribute__((always_inline)) {
+        if constexpr (EPI == EPI_PARTIAL) {
+            store_partial(sum, row0, col);
+        } else {
+            const int m = row0 + c;
+            if (m >= a.M) return;
+            if constexpr (EPI == EPI_SWIGLU) store_swiglu(sum, m, col, f);
+            else store_qkv(sum, m, col, f);
         }
+    };
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+        const int col = nw0 + column(nb) * 32;
+        if (col >= n_end) continue;
+#pragma unroll
+        for (int mb = 0; mb < MBW; ++mb) finish(acc[mb][nb], m0 + wm * WROWS + mb * 32, col, FACTOR ? factor[mb] : 1.0f);
+        if (EXTRA && nb == 0 && wm < NBW) finish(acc_extra, m0 + (BMB - 1) * 32, col, 1.0f);
     }
+}
+
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    // Workgroup b runs on XCD b % 8.  Tiles are numbered so that each XCD owns one contiguous range of
+    // them, M tiles fastest: the workgroups that read the same weight rows (all M tiles of an N tile) and
+    // neighbouring N tiles (same activation rows) then share one L2.
+    const int q = gridDim.x >> 3, r = gridDim.x & 7;
+    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const int tile = xcd * q + min(xcd, r) + local;
+    const int grp = a.by_m.of(tile), mt = tile - grp * a.m_tiles;
+    const int split = a.by_n.of(grp), nt = grp - split * a.n_tiles;
+    const int n0 = nt * a.n_stride;
+    gemm_tile<BMB, NB, WM, WN, EPI, FACTOR>(a, smem, split, mt, n0, min(n0 + a.n_stride, a.N));
 }
 
 // ---- host side: tiling policy and launch -----------------------------------------------------------------
@@ -503,14 +499,14 @@ int pick_row_blocks(int M) { return M > 128 ? 8 : M > 64 ? 4 : 2; }
 
 template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
 hipError_t launch(GemmArgs a, hipStream_t s) {
+    using S = Shape<BMB, NB, WM, WN>;
     a.n_stride = 32 * NB;
-    a.n_tiles = div_up(a.N, a.n_stride);
     a.m_tiles = div_up(a.M, 32 * BMB);
     a.kt_per_split = a.K / G_BK / a.splits;
+    a.n_tiles = div_up(a.N, a.n_stride);
     const int grid = a.m_tiles * a.n_tiles * a.splits;
     a.by_m.set(a.m_tiles);
     a.by_n.set(a.n_tiles);
-    using S = Shape<BMB, NB, WM, WN>;
     hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR>), dim3(grid), dim3(S::THREADS), S::LDS_BYTES, s, a);
     return hipGetLastError();
 }
@@ -533,6 +529,7 @@ hipError_t configure_one() {
     JUP_GEMM_TALL(X, EPI_QKV) X(6, 6, 2, 2, EPI_QKV) X(4, 3, 4, 1, EPI_QKV)                                \
     JUP_GEMM_TALL(X, EPI_SWIGLU) X(6, 6, 2, 2, EPI_SWIGLU) X(4, 3, 4, 1, EPI_SWIGLU) X(8, 3, 4, 1, EPI_SWIGLU) \
     JUP_GEMM_TALL(X, EPI_PARTIAL)                                                                          \
+    X(9, 8, 4, 2, EPI_SWIGLU) X(9, 6, 4, 2, EPI_SWIGLU)                                                    \
     X(8, 1, 4, 1, EPI_QKV) X(8, 2, 4, 1, EPI_QKV) X(8, 3, 8, 1, EPI_QKV)                                   \
     X(4, 2, 4, 1, EPI_QKV) X(2, 2, 2, 2, EPI_QKV)                                                          \
     X(8, 2, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU) X(2, 4, 2, 2, EPI_SWIGLU)                          \
@@ -543,7 +540,6 @@ hipError_t configure_one() {
 // all take one)
 #define JUP_GEMM_FACTOR_SHAPES(X) \
     X(4, 2, 4, 1, EPI_QKV) X(4, 3, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU)
-
 hipError_t gemm_configure() {
     hipError_t e = hipSuccess;
     auto acc = [&](hipError_t r) { if (e == hipSuccess) e = r; };
@@ -584,6 +580,12 @@ constexpr TileCost kTallTiles[] = {
     {{4, 6, 4, 2}, kAnyEpi, 0.322f, 4.7f, 2.8f}, {{4, 4, 4, 2}, kAnyEpi, 0.230f, 4.1f, 2.0f},
     {{6, 6, 2, 2}, kWideEpi, 0.437f, 0.3f, 2.3f}, {{4, 3, 4, 1}, kWideEpi, 0.196f, 4.9f, 1.4f},
     {{8, 3, 4, 1}, 1 << EPI_SWIGLU, 0.343f, 1.0f, 0.0f},
+    // 288 rows: up to a row block or two more than whole 256-row tiles (the eight waves share the ninth row block's columns).
+    // Measured: gate/up of 539 rows 116.6 -> 92.7 us (two M tiles and one round of 230 workgroups instead of three M tiles
+    // and two rounds), on the 13B shapes 144 -> 133.  Not for QKV (539 rows: 79 us instead of 60; 1100 rows 110 instead of 114,
+    // the only gain) and the O / down projections, whose K splits fill the chip with any tile (down of 539 rows: 63.5 us
+    // instead of 59.2).
+    {{9, 8, 4, 2}, 1 << EPI_SWIGLU, 0.720f, 10.0f, 0.0f}, {{9, 6, 4, 2}, 1 << EPI_SWIGLU, 0.600f, 10.0f, 0.0f},
 };
 constexpr float kLaunchUs = 3.0f;
 constexpr float kPartRound = 0.84f;       // a round that fills few CUs still takes this much of a full one
@@ -594,18 +596,22 @@ struct TallPick {
     int splits;
 };
 
+float rounds(int wgs) {
+    const int rest = wgs % kCUs;
+    return (float)(wgs / kCUs) + (rest ? kPartRound + (1.f - kPartRound) * rest / kCUs : 0.f);
+}
+
 TallPick pick_tall(int epi, int M, int N, int K) {
     TallPick best{};
     float best_us = 0.f;
     const int stages = K / G_BK;
+    auto round_us = [&](const TileCost& c, int splits) { return c.stage * (stages / splits) + c.round + (epi == EPI_QKV ? c.qkv : 0.f); };
     for (const TileCost& c : kTallTiles) {
         if (!(c.epilogues >> epi & 1)) continue;
         const int tiles = div_up(M, 32 * c.t.bmb) * div_up(N, 32 * c.t.nb);
         for (int splits = 1; splits <= (epi == EPI_PARTIAL ? 8 : 1); ++splits) {
             if (stages % splits || (splits > 1 && tiles * splits > kCUs)) continue;
-            const int wgs = tiles * splits, rest = wgs % kCUs;
-            const float rounds = (float)(wgs / kCUs) + (rest ? kPartRound + (1.f - kPartRound) * rest / kCUs : 0.f);
-            float us = kLaunchUs + rounds * (c.stage * (stages / splits) + c.round + (epi == EPI_QKV ? c.qkv : 0.f));
+            float us = kLaunchUs + rounds(tiles * splits) * round_us(c, splits);
             if (epi == EPI_PARTIAL) us += 4.f * M * N * splits * kPartialUsPerByte;
             if (best.splits == 0 || us < best_us) { best = {c.t, splits}; best_us = us; }
         }
@@ -739,7 +745,8 @@ template <int EPI>
 hipError_t dispatch(TileShape t, const GemmArgs& a, hipStream_t s) {
 #define X(BMB, NB, WM, WN, E)                                                         \
     if constexpr (E == EPI)                                                           \
-        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN) return launch<BMB, NB, WM, WN, EPI, BMB <= 2 && EPI != EPI_PARTIAL>(a, s);
+        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN)                  \
+            return launch<BMB, NB, WM, WN, EPI, BMB <= 2 && EPI != EPI_PARTIAL>(a, s);
     JUP_GEMM_SHAPES(X)
 #undef X
     return hipErrorInvalidConfiguration;  // a shape the pick functions name but the list above does not hold

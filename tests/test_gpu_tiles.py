@@ -31,6 +31,8 @@ TALL_TILES = [
     (4096, 32, 11008, 639, {"gemm_qkv": "4,8,2,4", "gemm_gate_up": "4,8,2,4", "gemm_down": "6,8,2,4"}),
     (4096, 32, 11008, 893, {"gemm_qkv": "6,8,2,4", "gemm_gate_up": "8,6,4,2", "gemm_down": "8,8,4,2"}),
     (4352, 34, 128, 385, {"gemm_qkv": "8,4,4,2"}),
+    (1536, 12, 11008, 539, {"gemm_gate_up": "9,6,4,2"}),     # a row block and 27 rows more than 256-row tiles hold
+    (1024, 8, 8192, 1121, {"gemm_gate_up": "9,8,4,2"}),
 ]
 EPILOGUE = {"gemm_qkv": 0, "gemm_o": 1, "gemm_down": 1, "gemm_gate_up": 2}
 COVERED = {f"gemm_bf16<{tile},{EPILOGUE[kernel]}>" for *_, tiles in TALL_TILES for kernel, tile in tiles.items()}
