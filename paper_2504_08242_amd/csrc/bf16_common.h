@@ -164,6 +164,7 @@ struct GemmArgs {
     int m_tiles, n_tiles, splits;  // grid = m_tiles * n_tiles * splits workgroups
     Quotient by_m, by_n, by_splits;  // the three as divisors
     int n_stride;                  // columns between consecutive N tiles (tile width actually owned)
+    int wide_tiles;                // bf16 launches in tiles of two widths: workgroups that have the wider ones
     int kt_per_split;              // K tiles of 32 per split
     // EPI_QKV
     u16* q_out;          // [M, d_model] rotated queries

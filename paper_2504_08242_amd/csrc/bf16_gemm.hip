@@ -473,17 +473,29 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     }
 }
 
-template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
+// REST: launches of several rounds of workgroups whose last round would leave much of the chip idle compute its columns in
+// tiles of REST column blocks (and the same rows), those of the rounds before it in tiles of NB.
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     // Workgroup b runs on XCD b % 8.  Tiles are numbered so that each XCD owns one contiguous range of
     // them, M tiles fastest: the workgroups that read the same weight rows (all M tiles of an N tile) and
     // neighbouring N tiles (same activation rows) then share one L2.
-    const int q = gridDim.x >> 3, r = gridDim.x & 7;
-    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const bool rest = REST && (int)blockIdx.x >= a.wide_tiles;
+    const int grid = REST ? (rest ? (int)gridDim.x - a.wide_tiles : a.wide_tiles) : (int)gridDim.x;
+    const int block = REST && rest ? (int)blockIdx.x - a.wide_tiles : (int)blockIdx.x;
+    const int q = grid >> 3, r = grid & 7;
+    const int xcd = block & 7, local = block >> 3;
     const int tile = xcd * q + min(xcd, r) + local;
     const int grp = a.by_m.of(tile), mt = tile - grp * a.m_tiles;
-    const int split = a.by_n.of(grp), nt = grp - split * a.n_tiles;
+    if constexpr (REST > 0) {
+        if (rest) {
+            const int n0 = a.n_tiles * a.n_stride + grp * 32 * REST;
+            gemm_tile<BMB, REST, WM, WN, EPI, FACTOR>(a, smem, 0, mt, n0, min(n0 + 32 * REST, a.N));
+            return;
+        }
+    }
+    const int split = REST ? 0 : a.by_n.of(grp), nt = grp - split * a.n_tiles;
     const int n0 = nt * a.n_stride;
     gemm_tile<BMB, NB, WM, WN, EPI, FACTOR>(a, smem, split, mt, n0, min(n0 + a.n_stride, a.N));
 }
@@ -497,24 +509,49 @@ int div_up(int x, int y) { return (x + y - 1) / y; }
 // Row blocks of the tile for a chunk of M tokens.
 int pick_row_blocks(int M) { return M > 128 ? 8 : M > 64 ? 4 : 2; }
 
-template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
+// A launch in tiles of two widths: the N tiles of as many whole rounds of workgroups as tiles of nb column blocks fill, and the
+// tiles of rest column blocks that the other columns take.
+struct Rounds {
+    int wide_n, rest_tiles;
+};
+Rounds rounds_of(int M, int N, int bmb, int nb, int rest) {
+    const int m_tiles = div_up(M, 32 * bmb), wide_n = m_tiles * div_up(N, 32 * nb) / kCUs * kCUs / m_tiles;
+    return {wide_n, m_tiles * div_up(max(N - wide_n * 32 * nb, 0), 32 * rest)};
+}
+
+template <int BMB, int NB, int WM, int WN, int REST>
+constexpr int lds_bytes() {
+    constexpr int wide = Shape<BMB, NB, WM, WN>::LDS_BYTES, rest = Shape<BMB, REST ? REST : NB, WM, WN>::LDS_BYTES;
+    return wide > rest ? wide : rest;
+}
+
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0>
 hipError_t launch(GemmArgs a, hipStream_t s) {
     using S = Shape<BMB, NB, WM, WN>;
     a.n_stride = 32 * NB;
     a.m_tiles = div_up(a.M, 32 * BMB);
     a.kt_per_split = a.K / G_BK / a.splits;
-    a.n_tiles = div_up(a.N, a.n_stride);
-    const int grid = a.m_tiles * a.n_tiles * a.splits;
+    int grid;
+    if (REST) {
+        const Rounds r = rounds_of(a.M, a.N, BMB, NB, REST);
+        a.n_tiles = r.wide_n;
+        a.wide_tiles = r.wide_n * a.m_tiles;
+        grid = a.wide_tiles + r.rest_tiles;
+    } else {
+        a.n_tiles = div_up(a.N, a.n_stride);
+        grid = a.m_tiles * a.n_tiles * a.splits;
+    }
     a.by_m.set(a.m_tiles);
     a.by_n.set(a.n_tiles);
-    hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR>), dim3(grid), dim3(S::THREADS), S::LDS_BYTES, s, a);
+    constexpr int lds = lds_bytes<BMB, NB, WM, WN, REST>();
+    hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR, REST>), dim3(grid), dim3(S::THREADS), lds, s, a);
     return hipGetLastError();
 }
 
-template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0>
 hipError_t configure_one() {
-    return hipFuncSetAttribute((const void*)gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, Shape<BMB, NB, WM, WN>::LDS_BYTES);
+    return hipFuncSetAttribute((const void*)gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR, REST>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<BMB, NB, WM, WN, REST>());
 }
 
 }  // namespace
@@ -540,6 +577,9 @@ hipError_t configure_one() {
 // all take one)
 #define JUP_GEMM_FACTOR_SHAPES(X) \
     X(4, 2, 4, 1, EPI_QKV) X(4, 3, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU)
+// Tiles of two widths (see REST): the column blocks of the last round's behind the epilogue.
+#define JUP_GEMM_REST_SHAPES(X) X(8, 8, 4, 2, EPI_SWIGLU, 6) X(8, 8, 4, 2, EPI_SWIGLU, 4)
+
 hipError_t gemm_configure() {
     hipError_t e = hipSuccess;
     auto acc = [&](hipError_t r) { if (e == hipSuccess) e = r; };
@@ -549,12 +589,16 @@ hipError_t gemm_configure() {
 #define X(BMB, NB, WM, WN, EPI) acc(configure_one<BMB, NB, WM, WN, EPI, true>());
     JUP_GEMM_FACTOR_SHAPES(X)
 #undef X
+#define X(BMB, NB, WM, WN, EPI, REST) acc(configure_one<BMB, NB, WM, WN, EPI, false, REST>());
+    JUP_GEMM_REST_SHAPES(X)
+#undef X
     return e;
 }
 
 // ---- which instantiation serves a launch ------------------------------------------------------------------
 struct TileShape {
     int bmb, nb, wm, wn;  // row blocks, column blocks, waves along M, waves along N
+    int rest = 0;         // column blocks of the tiles of the last round, 0: as the others
 };
 
 namespace {
@@ -587,6 +631,12 @@ constexpr TileCost kTallTiles[] = {
     // instead of 59.2).
     {{9, 8, 4, 2}, 1 << EPI_SWIGLU, 0.720f, 10.0f, 0.0f}, {{9, 6, 4, 2}, 1 << EPI_SWIGLU, 0.600f, 10.0f, 0.0f},
 };
+// Gate/up in 256-row tiles of two widths: as many whole rounds of 256-column tiles as there are, and the last one of 192 or 128
+// columns where those fill it better.  Measured, all rounds alike -> two widths: 2048 rows 293.8 -> 282.6 us, 1700 rows 281 ->
+// 260, 1280 rows 193 -> 182; 13B 1024 rows 238 -> 228, 2048 rows 471 -> 443.  (QKV, whose column blocks are fewer: nothing
+// gained at 1700 and 2048 rows of either.)
+constexpr TileShape kTwoWidths[] = {{8, 8, 4, 2, 6}, {8, 8, 4, 2, 4}};
+constexpr float kTwoWidthsUs = 3.0f;      // what such a launch has to be cheaper by
 constexpr float kLaunchUs = 3.0f;
 constexpr float kPartRound = 0.84f;       // a round that fills few CUs still takes this much of a full one
 constexpr float kPartialUsPerByte = 1.0f / 5.2e6f;  // what the reduce + norm pass pays to read a partial sum back
@@ -615,6 +665,20 @@ TallPick pick_tall(int epi, int M, int N, int K) {
             if (epi == EPI_PARTIAL) us += 4.f * M * N * splits * kPartialUsPerByte;
             if (best.splits == 0 || us < best_us) { best = {c.t, splits}; best_us = us; }
         }
+    }
+    if (epi != EPI_SWIGLU) return best;
+    for (const TileShape& t : kTwoWidths) {
+        const int tiles = div_up(M, 32 * t.bmb) * div_up(N, 32 * t.nb);
+        if (tiles < kCUs || tiles % kCUs == 0) continue;
+        float wide = 0.f, rest = 0.f;
+        for (const TileCost& c : kTallTiles) {
+            if (c.t.bmb != t.bmb || c.t.wm != t.wm || c.t.wn != t.wn) continue;
+            if (c.t.nb == t.nb) wide = round_us(c, 1);
+            if (c.t.nb == t.rest) rest = round_us(c, 1);
+        }
+        const Rounds r = rounds_of(M, N, t.bmb, t.nb, t.rest);
+        const float us = kLaunchUs + kTwoWidthsUs + tiles / kCUs * wide + rounds(r.rest_tiles) * rest;
+        if (us < best_us) { best = {t, 1}; best_us = us; }
     }
     return best;
 }
@@ -745,9 +809,15 @@ template <int EPI>
 hipError_t dispatch(TileShape t, const GemmArgs& a, hipStream_t s) {
 #define X(BMB, NB, WM, WN, E)                                                         \
     if constexpr (E == EPI)                                                           \
-        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN)                  \
+        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN && !t.rest)                  \
             return launch<BMB, NB, WM, WN, EPI, BMB <= 2 && EPI != EPI_PARTIAL>(a, s);
     JUP_GEMM_SHAPES(X)
+#undef X
+#define X(BMB, NB, WM, WN, E, REST)                                                           \
+    if constexpr (E == EPI)                                                                   \
+        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN && t.rest == REST)         \
+            return launch<BMB, NB, WM, WN, EPI, false, REST>(a, s);
+    JUP_GEMM_REST_SHAPES(X)
 #undef X
     return hipErrorInvalidConfiguration;  // a shape the pick functions name but the list above does not hold
 }
@@ -784,7 +854,8 @@ hipError_t launch_gemm_partial(GemmArgs a, hipStream_t s) {
     return dispatch<EPI_PARTIAL>(pick_partial(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 
-// "gemm_bf16<row blocks,column blocks,waves along M,waves along N,epilogue>" of the launch a projection of M rows takes
+// "gemm_bf16<row blocks,column blocks,waves along M,waves along N,epilogue>" of the launch a projection of M rows takes (tiles of
+// two widths: column blocks+those of the last round)
 void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_gpu, char* buf, size_t size) {
     TileShape t{};
     int epi = EPI_PARTIAL;
@@ -795,6 +866,7 @@ void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_
         case GEMM_DOWN: t = pick_partial(M, d_model, d_ffn, shared_gpu); break;
     }
     if (epi == EPI_PARTIAL && M <= kMaxProjectRows && !shared_gpu) snprintf(buf, size, "project_rows<bf16>");
+    else if (t.rest) snprintf(buf, size, "gemm_bf16<%d,%d+%d,%d,%d,%d>", t.bmb, t.nb, t.rest, t.wm, t.wn, epi);
     else snprintf(buf, size, "gemm_bf16<%d,%d,%d,%d,%d>", t.bmb, t.nb, t.wm, t.wn, epi);
 }
 

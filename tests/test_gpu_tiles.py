@@ -33,6 +33,8 @@ TALL_TILES = [
     (4352, 34, 128, 385, {"gemm_qkv": "8,4,4,2"}),
     (1536, 12, 11008, 539, {"gemm_gate_up": "9,6,4,2"}),     # a row block and 27 rows more than 256-row tiles hold
     (1024, 8, 8192, 1121, {"gemm_gate_up": "9,8,4,2"}),
+    (1024, 8, 11008, 1239, {"gemm_gate_up": "8,8+6,4,2"}),   # tiles of two widths
+    (1536, 12, 11008, 1755, {"gemm_gate_up": "8,8+4,4,2"}),
 ]
 EPILOGUE = {"gemm_qkv": 0, "gemm_o": 1, "gemm_down": 1, "gemm_gate_up": 2}
 COVERED = {f"gemm_bf16<{tile},{EPILOGUE[kernel]}>" for *_, tiles in TALL_TILES for kernel, tile in tiles.items()}
