@@ -381,7 +381,7 @@ void launch_expand_qkv(u16* dst, const void* cq, const void* ck, const void* cv,
 void launch_expand_gate_up(u16* dst, const void* cg, const void* cu, const float* sg, const float* su, int d, int f,
                            hipStream_t s);
 void launch_expand_plain(u16* dst, const void* c, const float* sc, int n_rows, int k, hipStream_t s);
-// The first kernel of a call: norm of the first layer (x32 <- hidden_in, xn <- rmsnorm * g), the rotary table of the rows,
+// The first kernel of a call: norm of the first layer (x32 <- hidden_in, if x32; xn <- rmsnorm * g), the rotary table of the rows,
 // zero[0 .. n_zero) <- 0 (the call's arrival counters), and the call's table, if it has one, to dst.
 struct BeginArgs {
     float* x32;
@@ -398,9 +398,9 @@ struct BeginArgs {
 void launch_begin_chunk(const BeginArgs& a, int pos0, hipStream_t s);
 void launch_begin_tree(const BeginArgs& a, int pos0, const TreeTable& t, TreeTable* dst, hipStream_t s);
 void launch_begin_branches(const BeginArgs& a, const BranchTable& t, BranchTable* dst, hipStream_t s);
-// x32 <- x32 + sum_s partial[s];  if g: xn <- rmsnorm(x32) * g (tiled layout), or with factor xn <- x32 * g and factor <-
-// 1 / rms of the rows;  out <- bf16(x32) (if out), row-major
-void launch_reduce_norm(float* x32, const float* partial, int splits, size_t split_stride, const u16* g, u16* xn,
-                        float* factor, u16* out, int n, int d, float eps, hipStream_t s);
+// v = (hidden_in, or x32 if null) + sum_s partial[s];  x32 <- v, or with out: out <- bf16(v), row-major;  if g: xn <- rmsnorm(v) * g
+// (tiled layout), or with factor xn <- v * g and factor <- 1 / rms of the rows
+void launch_reduce_norm(float* x32, const u16* hidden_in, const float* partial, int splits, size_t split_stride, const u16* g,
+                        u16* xn, float* factor, u16* out, int n, int d, float eps, hipStream_t s);
 
 }  // namespace jup

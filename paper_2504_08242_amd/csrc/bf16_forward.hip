@@ -99,11 +99,16 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     const TreeTable* tree_dev = nullptr;
     const AttScratch att{(float*)(ws + st.wl.att_split), (int*)(ws + st.wl.att_count), st.wl.att_split_rows,
                          st.wl.att_count_n};
+    const bool shared = link != nullptr;                    // other chunks' kernels run beside this chunk's
+    const bool rows = n <= kMaxProjectRows && !shared;      // (see `project` below)
     int max_keys = 0;  // batched branches: the longest key range
     double keys = (double)pos + n;  // read per layer
     {
         TraceScope ts(st, JUP_K_RMSNORM, s);
-        const BeginArgs a{x32, (const u16*)hidden_in, (const u16*)((const char*)st.packed + st.pl.g_attn), xn, n, d, c.rms_eps,
+        // (more than 16 rows: the first reduce + norm pass reads hidden_in again, half the bytes of an fp32 copy that nothing else
+        // would read.  The three launches of this kind of a one-layer call, which writes no x32 behind its last projection
+        // either: 2048 rows of d_model 4096 67.5 -> 60.3 us, 512 rows 29.1 -> 27.0)
+        const BeginArgs a{rows ? x32 : nullptr, (const u16*)hidden_in, (const u16*)((const char*)st.packed + st.pl.g_attn), xn, n, d, c.rms_eps,
                           rope, c.rope_theta, att.split_count, (int)att.counters};
         if (bt) {
             bt_dev = (const BranchTable*)(ws + st.wl.branches);
@@ -122,7 +127,6 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         }
     }
 
-    const bool shared = link != nullptr;  // other chunks' kernels run beside this chunk's
     // 4-bit stage: the projections read codes, everything else is the bf16 path.  With the expanded copy at hand,
     // chunks beyond one pass of the 4-bit kernels (64 rows) take the bf16 projections on it.
     const bool expanded = c.dtype == JUP_BF16_W4 && c.w4_expanded && n > 64;
@@ -137,7 +141,6 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     // other calls leave partial sums to the reduce + norm pass; batches of branches of up to 16 tokens in a form that gives
     // every branch the bits it has alone: bf16 weights up to max_split_rows, codes whatever the rows.  (The bf16 copy of a
     // 4-bit stage is not what a branch of up to 64 rows runs on alone.)
-    const bool rows = n <= kMaxProjectRows && !shared;
     const bool small_branches = !rows && bt && bt->n_tok <= kMaxProjectRows && (w4 || (!expanded && n <= max_split_rows(d)));
     const bool as_rows = rows || small_branches;
     const int n_tok = bt ? bt->n_tok : n;
@@ -167,7 +170,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         const u16* g2 = (const u16*)(wb + st.pl.g_mlp);
         if (l > 0 && !rows) {
             TraceScope ts(st, JUP_K_RMSNORM, s);
-            launch_reduce_norm(x32, partial, splits_down, split_stride, g1, xn, late_factor, nullptr, n, d, c.rms_eps, s);
+            launch_reduce_norm(x32, nullptr, partial, splits_down, split_stride, g1, xn, late_factor, nullptr, n, d, c.rms_eps, s);
         }
         {
             TraceScope ts(st, JUP_K_GEMM_QKV, s);
@@ -197,7 +200,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
         }
         if (!rows) {
             TraceScope ts(st, JUP_K_RMSNORM, s);
-            launch_reduce_norm(x32, partial, splits_o, split_stride, g2, xn, late_factor, nullptr, n, d, c.rms_eps, s);
+            launch_reduce_norm(x32, l == 0 ? (const u16*)hidden_in : nullptr, partial, splits_o, split_stride, g2, xn, late_factor, nullptr, n, d, c.rms_eps, s);
         }
         {
             TraceScope ts(st, JUP_K_GEMM_GATE_UP, s);
@@ -216,7 +219,7 @@ hipError_t bf16_forward(const jup_stage& st, const void* hidden_in, int n, int p
     }
     if (e != hipSuccess || rows) return e;
     // last layer's down-projection partials + residual -> hidden_out
-    launch_reduce_norm(x32, partial, splits_down, split_stride, nullptr, nullptr, nullptr, (u16*)hidden_out, n, d,
+    launch_reduce_norm(x32, nullptr, partial, splits_down, split_stride, nullptr, nullptr, nullptr, (u16*)hidden_out, n, d,
                        c.rms_eps, s);
     return hipGetLastError();
 }

@@ -78,7 +78,7 @@ __global__ void pack_tiled(u16* __restrict__ dst, const void* __restrict__ s0, c
 // few bytes and there are few rows, so the block is wide (d/8 threads when that is a whole number of waves):
 // every load of a thread is independent and enough of them must be in flight per CU to cover HBM latency.
 //   v    = (hidden_in ? bf16 row of hidden_in : x32 row) + sum over splits of the partial rows
-//   x32 <- v                              (when anything was added or the row came from hidden_in)
+//   x32 <- v                              (when x32 != NULL and out == NULL: the last rows of a call go to out alone)
 //   xn  <- bf16(v * rsqrt(mean v^2 + eps) * g)   (when g != NULL)
 //   LATE: xn <- bf16(v * g), factor <- 1 / sqrt(mean v^2 + eps); the projection that reads the rows multiplies its results
 //          by the factor, as it has to behind row_gemm.hip, whose bits these are
@@ -112,7 +112,7 @@ __device__ __forceinline__ void norm_row(size_t row, float* __restrict__ x32, co
 #pragma unroll
             for (int s = 0; s < 8; ++s)
                 if (s < splits) { x.x += p[s].x; x.y += p[s].y; x.z += p[s].z; x.w += p[s].w; }
-            if (hidden_in || splits > 0) *(float4*)(x32 + row * d + idx * 4) = x;
+            if (x32 && !out) *(float4*)(x32 + row * d + idx * 4) = x;
             if (out) {
                 u32x2 o;
                 o[0] = pack_bf16x2(x.x, x.y);
@@ -163,10 +163,11 @@ __device__ __forceinline__ void norm_row(size_t row, float* __restrict__ x32, co
 }
 
 template <int IT, bool LATE>
-__global__ __launch_bounds__(1024) void reduce_norm(float* __restrict__ x32, const float* __restrict__ partial, int splits,
+__global__ __launch_bounds__(1024) void reduce_norm(float* __restrict__ x32, const u16* __restrict__ hidden_in,
+                                                    const float* __restrict__ partial, int splits,
                                                     size_t split_stride, const u16* __restrict__ g, u16* __restrict__ xn,
                                                     float* __restrict__ factor, u16* __restrict__ out, int d, float eps) {
-    norm_row<IT, LATE>(blockIdx.x, x32, nullptr, partial, splits, split_stride, g, xn, out, d, eps, factor);
+    norm_row<IT, LATE>(blockIdx.x, x32, hidden_in, partial, splits, split_stride, g, xn, out, d, eps, factor);
 }
 
 // ---- the first kernel of a call --------------------------------------------------------------------------------------
@@ -268,12 +269,12 @@ void launch_begin_tree(const BeginArgs& a, int pos0, const TreeTable& t, TreeTab
 void launch_begin_branches(const BeginArgs& a, const BranchTable& t, BranchTable* dst, hipStream_t s) {
     launch_begin(a, BranchRows{t, dst}, s);
 }
-void launch_reduce_norm(float* x32, const float* partial, int splits, size_t split_stride, const u16* g, u16* xn,
+void launch_reduce_norm(float* x32, const u16* hidden_in, const float* partial, int splits, size_t split_stride, const u16* g, u16* xn,
                         float* factor, u16* out, int n, int d, float eps, hipStream_t s) {
     const bool wide = d % 512 == 0 && d / 8 <= 1024;
     auto* kernel = wide ? (factor ? reduce_norm<2, true> : reduce_norm<2, false>)
                         : (factor ? reduce_norm<8, true> : reduce_norm<8, false>);
-    hipLaunchKernelGGL(kernel, dim3(n), dim3(wide ? d / 8 : 256), 0, s, x32, partial, splits, split_stride, g, xn, factor, out,
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(wide ? d / 8 : 256), 0, s, x32, hidden_in, partial, splits, split_stride, g, xn, factor, out,
                        d, eps);
 }
 

@@ -72,6 +72,20 @@ def test_bf16_rows_that_do_not_exist(rows):
     p.check(p.kv_gpu()[1], p.oracle.kv[1], "cache")
 
 
+@pytest.mark.parametrize("dtype,layers,rows", [("bf16", 1, 17), ("bf16", 2, 300), ("w4", 1, 70), ("w4", 2, 33), ("bf16", 1, 16)])
+def test_hidden_states_in_place(dtype, layers, rows):
+    """The residual stream begins in the input buffer: a call that overwrites it with its output, against one that does not."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=512, n_heads=4, d_ffn=1408, n_layers=layers)
+    p = Pair(cfg, dtype, seed=rows, max_positions=rows, max_chunk_tokens=rows)
+    hidden = p.hidden(rows)
+    x = torch.from_numpy(hidden).to("cuda:0", p.td)
+    apart = p.stage.prefill_chunk(x, 0, p.kv)
+    p.check(apart.float().cpu().numpy(), p.oracle.prefill_chunk(hidden, 0), "apart")
+    p.stage.prefill_chunk(x, 0, p.kv, x)
+    assert torch.equal(x, apart)
+
+
 @pytest.mark.parametrize("n_lanes,chunks,limit", [
     (2, [70, 3, 0, 129, 64, 300], 300),     # one group: row counts that are no multiple of a row block
     (2, [250] * 9, 250),                    # more rows than the lanes' buffer holds: several groups
