@@ -48,7 +48,8 @@ constexpr int G_BK = 32;
 
 constexpr int kLdsBudget = 160 * 1024;
 
-template <int BMB, int NB, int WM, int WN>
+// HALF: the last column block of the tile is half a block of W (see HalfTile)
+template <int BMB, int NB, int WM, int WN, bool HALF = false>
 struct Shape {
     static constexpr int BM = 32 * BMB;             // rows of the tile: 256 for prefill-sized chunks, 128, 64 or 32 for
                                                     // short ones (a short chunk is bound by streaming the weights:
@@ -57,7 +58,8 @@ struct Shape {
     static constexpr int MBW = BMB / WM;            // row blocks per wave
     static constexpr int EXTRA = BMB % WM;          // a row block more, of which every wave takes one column block
     static constexpr int WAVES = WM * WN;
-    static constexpr int ROWS = BM + 32 * NB;       // LDS rows per stage: A rows then W rows
+    static constexpr int COLS = 32 * NB - (HALF ? 16 : 0);
+    static constexpr int ROWS = BM + COLS;          // LDS rows per stage: A rows then W rows
     static constexpr int STAGE_BYTES = ROWS * 64;
     static constexpr int LOADERS = WAVES;           // every wave fetches its share of a stage between its MFMAs
     static constexpr int THREADS = 64 * WAVES;
@@ -130,12 +132,22 @@ struct Frags {
     bf16x8 b[NB];
 };
 
+// Tiles that end in half a column block.  Two neighbours share three blocks: the even one has the first and half of the second,
+// the odd one the other half and the third.  A half is the packed rows 8 h .. 8 h + 7 and 16 + 8 h .. of the block, half of
+// the registers of every lane of the epilogue, so that rotary partners stay together; LDS holds the 16 rows one after
+// the other, and the MFMA has every row twice (rows c and c ^ 8 of its operand).
+struct HalfTile {
+    int full, half, h;  // blocks of W, and which half of the second
+    __device__ __forceinline__ explicit HalfTile(int nt) : full(nt / 2 * 3 + nt % 2 * 2), half(nt / 2 * 3 + 1), h(nt & 1) {}
+};
+
 // The tile of row blocks mt * BMB .. and columns [n0, n_end) (K split: split).
 // FACTOR: the results of a row may have to be multiplied by its 1 / rms.  A template parameter because on the tall tiles of
 // long chunks, which never need it, the test alone cost the 512-row launches 1 %.
-template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR>
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, bool HALF = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem, int split, int mt, int n0, int n_end) {
-    using S = Shape<BMB, NB, WM, WN>;
+    using S = Shape<BMB, NB, WM, WN, HALF>;
+    static_assert(!HALF || (NB == 2 && WN == 2 && WM == 2 && BMB == 2 && EPI == EPI_QKV), "the last column block belongs to waves of its own");
     constexpr int G_BM = S::BM;
     constexpr int NBW = S::NBW, MBW = S::MBW, EXTRA = S::EXTRA;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -154,6 +166,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     const char* ubase[S::LPW];
     const int kt_total = a.K / G_BK;
     const unsigned lane16 = lane * 16;
+    const HalfTile ht(HALF ? n0 / S::COLS : 0);
+    // (of a unit of W: half a block is 512 bytes out of either KB of the block)
+    const unsigned w_lane16 = HALF && lw == S::LOADERS - 2 ? lane16 + ht.h * 512 + (lane >> 5) * 512 : lane16;
 #pragma unroll
     for (int q = 0; q < S::LPW; ++q) {
         const int j = min(q * S::LOADERS + lw, S::NL - 1);
@@ -164,6 +179,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
             base = a.A;
         } else {
             blk = min(n0 / 32 + ((j - G_BM / 16) >> 1), a.N / 32 - 1);  // blocks past N repeat the last one
+            if (HALF) blk = j - G_BM / 16 < 2 ? ht.full : ht.half;
             base = a.W;
         }
         ubase[q] = uniform_ptr((const char*)(base + ((size_t)blk * kt_total + (size_t)split * KT) * 1024 + (j & 1) * 512));
@@ -190,7 +206,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     auto issue_one = [&](int q, int stage, int kt) {
         const char* at = uniform_ptr(ubase[q] + (size_t)kt * 2048);
         const int unit = q * S::LOADERS + lw;
-        const auto* src = (const __attribute__((address_space(1))) void*)(at + lane16);
+        const auto* src = (const __attribute__((address_space(1))) void*)(at + (HALF ? w_lane16 : lane16));
         auto* dst = (__attribute__((address_space(3))) void*)(smem + stage * S::STAGE_BYTES + unit * 1024);
         // A chunk of up to 128 tokens alone on the chip streams every weight exactly once (one M tile): its weight units
         // are fetched with the non-temporal hint, so that the stream does not push the KV cache and the activations
@@ -236,6 +252,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     for (int ks = 0; ks < 2; ++ks)
         lane_off[ks] = (c >> 2) * 256 + ((((c & 3) << 2) + 2 * ks + hh) ^ ((c >> 2) & 3)) * 16;
     const int a_base = wm * MBW * 2048, b_base = G_BM * 64 + wn * NBW * 2048;
+    int b_lane_off[2] = {lane_off[0], lane_off[1]};
+    if (HALF && wn == 1)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+            b_lane_off[ks] = ((c >> 4) * 2 + ((c & 7) >> 2)) * 256 + ((((c & 3) << 2) + 2 * ks + hh) ^ (2 * ht.h + ((c & 7) >> 2))) * 16;
     // Tiles with an extra row block: the waves of a column range begin at different columns of it, and each multiplies the
     // extra rows by the columns it begins at (b[0]; more waves than columns: some for nothing).
     const int first_nb = EXTRA ? wm % NBW : 0;
@@ -246,6 +267,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     auto load_frag_one = [&](F& f, int stage, int ks, int t) {
         const unsigned char* sb = smem + stage * S::STAGE_BYTES + lane_off[ks];
         if (t == 0) f.a[0] = *(const bf16x8*)(sb + a_base);
+        else if (HALF) f.b[0] = *(const bf16x8*)(smem + stage * S::STAGE_BYTES + b_lane_off[ks] + b_base);
         else if (t == 1) f.b[0] = *(const bf16x8*)(sb + b_base + column(0) * 2048);
         else if (t < MBW + 1) f.a[t - 1] = *(const bf16x8*)(sb + a_base + (t - 1) * 2048);
         else if (t < MBW + NBW) f.b[t - MBW] = *(const bf16x8*)(sb + b_base + column(t - MBW) * 2048);
@@ -416,11 +438,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     // ordered by the pack kernel so that a lane's registers 0..7 are the indices F .. F + 7 (F = 16 j + 8 hh for block j
     // of the head) and registers 8..15 their partners F + 64 ..: the lane rotates its 8 pairs and stores two 16-byte pieces.
     // A block of V holds 32 consecutive features, a lane 16 of them (16 hh ..).
-    auto store_qkv = [&](const f32x16& sum, int m, int col, float f) __attribute__((always_inline)) {
+    // (half a block: registers 0 .. 3 and 8 .. 11 are the indices F + 4 h .. and their partners)
+    auto store_qkv = [&](const f32x16& sum, int m, int col, float f, auto half) __attribute__((always_inline)) {
+        constexpr int PAIRS = decltype(half)::value ? 2 : 4;
         const int which = (col >= a.d_model) + (col >= 2 * a.d_model);  // (col: one (q|k|v, head, j) for all lanes)
         const int in_model = col - which * a.d_model;
         const int head = in_model >> 7, j = (in_model & 127) >> 5;
-        const int f_lo = which == 2 ? 32 * j + 16 * hh : 16 * j + 8 * hh;  // first feature of registers 0..7
+        const int f_lo = (which == 2 ? 32 * j + 16 * hh : 16 * j + 8 * hh) + (PAIRS == 2 ? 4 * ht.h : 0);  // first feature of registers 0..7
         const int f_hi = which == 2 ? f_lo + 8 : f_lo + 64;                  // ... of registers 8..15
         u16* dst;
         if (which == 0) {
@@ -431,17 +455,17 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
             const int b = m / a.branches->n_tok, t = m - b * a.branches->n_tok;
             dst = kv_slot_bf16(a.branches->kv[b], a.layer, which - 1, head, a.n_heads, a.branches->pos0[b] + t);
         }
-        u32x4 lo, hi;
+        unsigned lo[PAIRS], hi[PAIRS];
         if (which == 2) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < PAIRS; ++e) {
                 lo[e] = pack_bf16x2(sum[2 * e] * f, sum[2 * e + 1] * f);
                 hi[e] = pack_bf16x2(sum[8 + 2 * e] * f, sum[8 + 2 * e + 1] * f);
             }
         } else {
-            const float4* rp = (const float4*)(a.rope + (size_t)m * 64 + f_lo);  // 8 (cos, sin) pairs
+            const float4* rp = (const float4*)(a.rope + (size_t)m * 64 + f_lo);  // (cos, sin) pairs
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < PAIRS; ++e) {
                 const float4 cs = rp[e];  // (cos, sin) of indices f_lo + 2 e, f_lo + 2 e + 1
                 const float l0 = sum[2 * e] * f, l1 = sum[2 * e + 1] * f;
                 const float h0 = sum[8 + 2 * e] * f, h1 = sum[8 + 2 * e + 1] * f;
@@ -450,8 +474,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
                 hi[e] = pack_bf16x2(h0 * cs.x + l0 * cs.y, h1 * cs.z + l1 * cs.w);
             }
         }
-        *(u32x4*)(dst + f_lo) = lo;
-        *(u32x4*)(dst + f_hi) = hi;
+        if constexpr (PAIRS == 4) {
+            *(u32x4*)(dst + f_lo) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+            *(u32x4*)(dst + f_hi) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+        } else {
+            *(u32x2*)(dst + f_lo) = u32x2{lo[0], lo[1]};
+            *(u32x2*)(dst + f_hi) = u32x2{hi[0], hi[1]};
+        }
     };
     auto finish = [&](const f32x16& sum, int row0, int col, float f) __attribute__((always_inline)) {
         if constexpr (EPI == EPI_PARTIAL) {
@@ -460,13 +489,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
             const int m = row0 + c;
             if (m >= a.M) return;
             if constexpr (EPI == EPI_SWIGLU) store_swiglu(sum, m, col, f);
-            else store_qkv(sum, m, col, f);
+            else if (HALF && wn == 1) store_qkv(sum, m, ht.half * 32, f, std::true_type{});
+            else store_qkv(sum, m, HALF ? ht.full * 32 : col, f, std::false_type{});
         }
     };
 #pragma unroll
     for (int nb = 0; nb < NBW; ++nb) {
         const int col = nw0 + column(nb) * 32;
-        if (col >= n_end) continue;
+        if (!HALF && col >= n_end) continue;
 #pragma unroll
         for (int mb = 0; mb < MBW; ++mb) finish(acc[mb][nb], m0 + wm * WROWS + mb * 32, col, FACTOR ? factor[mb] : 1.0f);
         if (EXTRA && nb == 0 && wm < NBW) finish(acc_extra, m0 + (BMB - 1) * 32, col, 1.0f);
@@ -475,7 +505,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
 
 // REST: launches of several rounds of workgroups whose last round would leave much of the chip idle compute its columns in
 // tiles of REST column blocks (and the same rows), those of the rounds before it in tiles of NB.
-template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0>
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0, bool HALF = false>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     // Workgroup b runs on XCD b % 8.  Tiles are numbered so that each XCD owns one contiguous range of
@@ -497,7 +527,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16(const GemmArgs a) {
     }
     const int split = REST ? 0 : a.by_n.of(grp), nt = grp - split * a.n_tiles;
     const int n0 = nt * a.n_stride;
-    gemm_tile<BMB, NB, WM, WN, EPI, FACTOR>(a, smem, split, mt, n0, min(n0 + a.n_stride, a.N));
+    gemm_tile<BMB, NB, WM, WN, EPI, FACTOR, HALF>(a, smem, split, mt, n0, min(n0 + a.n_stride, a.N));
 }
 
 // ---- host side: tiling policy and launch -----------------------------------------------------------------
@@ -519,16 +549,16 @@ Rounds rounds_of(int M, int N, int bmb, int nb, int rest) {
     return {wide_n, m_tiles * div_up(max(N - wide_n * 32 * nb, 0), 32 * rest)};
 }
 
-template <int BMB, int NB, int WM, int WN, int REST>
+template <int BMB, int NB, int WM, int WN, int REST, bool HALF>
 constexpr int lds_bytes() {
-    constexpr int wide = Shape<BMB, NB, WM, WN>::LDS_BYTES, rest = Shape<BMB, REST ? REST : NB, WM, WN>::LDS_BYTES;
+    constexpr int wide = Shape<BMB, NB, WM, WN, HALF>::LDS_BYTES, rest = Shape<BMB, REST ? REST : NB, WM, WN>::LDS_BYTES;
     return wide > rest ? wide : rest;
 }
 
-template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0>
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0, bool HALF = false>
 hipError_t launch(GemmArgs a, hipStream_t s) {
-    using S = Shape<BMB, NB, WM, WN>;
-    a.n_stride = 32 * NB;
+    using S = Shape<BMB, NB, WM, WN, HALF>;
+    a.n_stride = S::COLS;
     a.m_tiles = div_up(a.M, 32 * BMB);
     a.kt_per_split = a.K / G_BK / a.splits;
     int grid;
@@ -543,15 +573,15 @@ hipError_t launch(GemmArgs a, hipStream_t s) {
     }
     a.by_m.set(a.m_tiles);
     a.by_n.set(a.n_tiles);
-    constexpr int lds = lds_bytes<BMB, NB, WM, WN, REST>();
-    hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR, REST>), dim3(grid), dim3(S::THREADS), lds, s, a);
+    constexpr int lds = lds_bytes<BMB, NB, WM, WN, REST, HALF>();
+    hipLaunchKernelGGL((gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR, REST, HALF>), dim3(grid), dim3(S::THREADS), lds, s, a);
     return hipGetLastError();
 }
 
-template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0>
+template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, int REST = 0, bool HALF = false>
 hipError_t configure_one() {
-    return hipFuncSetAttribute((const void*)gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR, REST>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<BMB, NB, WM, WN, REST>());
+    return hipFuncSetAttribute((const void*)gemm_bf16<BMB, NB, WM, WN, EPI, FACTOR, REST, HALF>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<BMB, NB, WM, WN, REST, HALF>());
 }
 
 }  // namespace
@@ -592,6 +622,7 @@ hipError_t gemm_configure() {
 #define X(BMB, NB, WM, WN, EPI, REST) acc(configure_one<BMB, NB, WM, WN, EPI, false, REST>());
     JUP_GEMM_REST_SHAPES(X)
 #undef X
+    acc(configure_one<2, 2, 2, 2, EPI_QKV, true, 0, true>());
     return e;
 }
 
@@ -840,6 +871,13 @@ hipError_t dispatch_factor(const GemmArgs& a, hipStream_t s) {
 hipError_t launch_gemm_qkv(GemmArgs a, hipStream_t s) {
     a.splits = 1;
     if (a.row_factor && a.M > 64) return dispatch_factor<EPI_QKV>(a, s);
+    // 33 to 64 rows: tiles of one and a half column blocks where their grid is still one round of workgroups.  A CU takes rows and
+    // weights at about 50 GB/s, and 64-column tiles leave a quarter of the CUs out on the 7B shapes (192 of 256).  Whole layers,
+    // 64 -> 48 columns: 64 rows 7B 102.8 -> 101.8 us, d_model 2048 60.3 -> 59.8; 40 rows 95.6 -> 94.9, 56.9 -> 56.6.  Below 33 rows
+    // nothing is gained (the rows weigh little), nor with fewer workgroups (d_model 1536: 53.1 -> 52.7 and 50.5 -> 50.5; 1024: 43.4 ->
+    // 43.5 and 41.7 -> 42.4).
+    const bool halves = a.M > 32 && a.M <= 64 && !a.shared_gpu && a.N % 96 == 0 && a.N / 48 >= kCUs / 2 && a.N / 48 <= kCUs;
+    if (halves) return launch<2, 2, 2, 2, EPI_QKV, true, 0, true>(a, s);
     return dispatch<EPI_QKV>(pick_qkv(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 
@@ -855,7 +893,7 @@ hipError_t launch_gemm_partial(GemmArgs a, hipStream_t s) {
 }
 
 // "gemm_bf16<row blocks,column blocks,waves along M,waves along N,epilogue>" of the launch a projection of M rows takes (tiles of
-// two widths: column blocks+those of the last round)
+// two widths: column blocks+those of the last round; a tile that ends in half a column block is named with that block)
 void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_gpu, char* buf, size_t size) {
     TileShape t{};
     int epi = EPI_PARTIAL;

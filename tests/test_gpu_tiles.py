@@ -72,6 +72,29 @@ def test_bf16_rows_that_do_not_exist(rows):
     p.check(p.kv_gpu()[1], p.oracle.kv[1], "cache")
 
 
+@pytest.mark.parametrize("d_model,rows", [(2048, 33), (2048, 47), (2048, 64), (4096, 40)])
+def test_bf16_qkv_in_halves_of_column_blocks(d_model, rows):
+    """33 to 64 rows on 48-column tiles (128 workgroups and 256, the ends of their range): queries, keys and values against the
+    oracle, and a batch of branches against each of them alone, which runs on the 64-column tiles: the same bits."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=d_model // 128, d_ffn=256, n_layers=1)
+    p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 7, max_chunk_tokens=64)
+    hidden = p.hidden(rows + 7)
+    g, o = p.run_both(hidden, [7, rows])
+    p.check(g[7:], o[7:], "chunk")
+    p.check(p.kv_gpu()[0], p.oracle.kv[0], "cache")
+    n = 8 if rows % 8 == 0 else 1
+    if n == 1:
+        return
+    tok = rows // n
+    x = torch.from_numpy(hidden[7:]).to("cuda:0", p.td)
+    whole, alone = ([p.kv.fork(7, 7 + tok) for _ in range(n)] for _ in range(2))
+    got = p.stage.prefill_branches(x, tok, [7] * n, whole)
+    for b in range(n):
+        assert torch.equal(p.stage.prefill_chunk(x[b * tok:(b + 1) * tok].contiguous(), 7, alone[b]), got.view(n, tok, -1)[b]), b
+        assert torch.equal(alone[b].view(), whole[b].view()), b
+
+
 @pytest.mark.parametrize("dtype,layers,rows", [("bf16", 1, 17), ("bf16", 2, 300), ("w4", 1, 70), ("w4", 2, 33), ("bf16", 1, 16)])
 def test_hidden_states_in_place(dtype, layers, rows):
     """The residual stream begins in the input buffer: a call that overwrites it with its output, against one that does not."""
