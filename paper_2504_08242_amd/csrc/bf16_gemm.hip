@@ -147,7 +147,7 @@ struct HalfTile {
 template <int BMB, int NB, int WM, int WN, int EPI, bool FACTOR, bool HALF = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem, int split, int mt, int n0, int n_end) {
     using S = Shape<BMB, NB, WM, WN, HALF>;
-    static_assert(!HALF || (NB == 2 && WN == 2 && WM == 2 && BMB == 2 && EPI == EPI_QKV), "the last column block belongs to waves of its own");
+    static_assert(!HALF || (NB == 2 && WN == 2 && WM == 2 && BMB == 2 && EPI != EPI_PARTIAL), "the last column block belongs to waves of its own");
     constexpr int G_BM = S::BM;
     constexpr int NBW = S::NBW, MBW = S::MBW, EXTRA = S::EXTRA;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -179,7 +179,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
             base = a.A;
         } else {
             blk = min(n0 / 32 + ((j - G_BM / 16) >> 1), a.N / 32 - 1);  // blocks past N repeat the last one
-            if (HALF) blk = j - G_BM / 16 < 2 ? ht.full : ht.half;
+            if (HALF) blk = min(j - G_BM / 16 < 2 ? ht.full : ht.half, a.N / 32 - 1);
             base = a.W;
         }
         ubase[q] = uniform_ptr((const char*)(base + ((size_t)blk * kt_total + (size_t)split * KT) * 1024 + (j & 1) * 512));
@@ -422,17 +422,21 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     // consecutive features and 8..15 their up projections (block nb = features 16 nb .. 16 nb + 15, lanes of half hh the
     // features 8 hh .. 8 hh + 7 of them).  A lane therefore finishes 8 outputs of one token by itself and stores them as
     // one 16-byte chunk of the tiled activation layout: no exchange between lanes, no LDS, no barrier.
-    auto store_swiglu = [&](const f32x16& sum, int m, int col, float f) __attribute__((always_inline)) {
+    // (half a block: registers 0 .. 3 and 8 .. 11, features 4 h .. of those)
+    auto store_swiglu = [&](const f32x16& sum, int m, int col, float f, auto half) __attribute__((always_inline)) {
+        constexpr int PAIRS = decltype(half)::value ? 2 : 4;
         const int chunk = (col >> 4) + hh;  // 16-byte chunk of the output row: features 8 * chunk ..
-        u32x4 out;
+        unsigned out[PAIRS];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < PAIRS; ++e) {
             const float g0 = sum[2 * e] * f, g1 = sum[2 * e + 1] * f;
             const float u0 = sum[8 + 2 * e] * f, u1 = sum[8 + 2 * e + 1] * f;
             out[e] = pack_bf16x2(g0 * __builtin_amdgcn_rcpf(1.0f + __expf(-g0)) * u0,
                                  g1 * __builtin_amdgcn_rcpf(1.0f + __expf(-g1)) * u1);
         }
-        *(u32x4*)(a.act + tiled_offset(m, chunk, a.N >> 6)) = out;
+        u16* dst = a.act + tiled_offset(m, chunk, a.N >> 6);
+        if constexpr (PAIRS == 4) *(u32x4*)dst = u32x4{out[0], out[1], out[2], out[3]};
+        else *(u32x2*)(dst + 4 * ht.h) = u32x2{out[0], out[1]};
     };
     // Transposed block, as above.  A 32-row block of a Q or K head holds 16 rotary indices and their partners 64 further on,
     // ordered by the pack kernel so that a lane's registers 0..7 are the indices F .. F + 7 (F = 16 j + 8 hh for block j
@@ -488,15 +492,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
         } else {
             const int m = row0 + c;
             if (m >= a.M) return;
-            if constexpr (EPI == EPI_SWIGLU) store_swiglu(sum, m, col, f);
-            else if (HALF && wn == 1) store_qkv(sum, m, ht.half * 32, f, std::true_type{});
-            else store_qkv(sum, m, HALF ? ht.full * 32 : col, f, std::false_type{});
+            auto store = [&](int at, auto half) __attribute__((always_inline)) {
+                if constexpr (EPI == EPI_SWIGLU) store_swiglu(sum, m, at, f, half);
+                else store_qkv(sum, m, at, f, half);
+            };
+            if (HALF && wn == 1) store(col, std::true_type{});
+            else store(col, std::false_type{});
         }
     };
 #pragma unroll
     for (int nb = 0; nb < NBW; ++nb) {
-        const int col = nw0 + column(nb) * 32;
-        if (!HALF && col >= n_end) continue;
+        const int col = HALF ? (wn == 1 ? ht.half : ht.full) * 32 : nw0 + column(nb) * 32;
+        if (col >= (HALF ? a.N : n_end)) continue;
 #pragma unroll
         for (int mb = 0; mb < MBW; ++mb) finish(acc[mb][nb], m0 + wm * WROWS + mb * 32, col, FACTOR ? factor[mb] : 1.0f);
         if (EXTRA && nb == 0 && wm < NBW) finish(acc_extra, m0 + (BMB - 1) * 32, col, 1.0f);
@@ -623,6 +630,7 @@ hipError_t gemm_configure() {
     JUP_GEMM_REST_SHAPES(X)
 #undef X
     acc(configure_one<2, 2, 2, 2, EPI_QKV, true, 0, true>());
+    acc(configure_one<2, 2, 2, 2, EPI_SWIGLU, true, 0, true>());
     return e;
 }
 
@@ -799,8 +807,14 @@ TileShape pick_qkv(int M, int N, int K, bool shared_gpu) {
     return {8, 1, 4, 1};
 }
 
+bool halves_swiglu(int M, int N, bool shared_gpu) {
+    const int wgs = div_up(N, 48);
+    return M <= 64 && !shared_gpu && wgs <= kCUs && (M > 32 || (M > 8 && wgs > kCUs * 3 / 4));
+}
+
 TileShape pick_swiglu(int M, int N, int K, bool shared_gpu) {
     const int bmb = pick_row_blocks(M);
+    if (halves_swiglu(M, N, shared_gpu)) return {2, 2, 2, 2};
     // A short chunk is bound by streaming the weights, and every CU that streams adds bandwidth: the narrower
     // tile (96 columns) when its tiles still fit one round of workgroups (measured at 64 rows, N = 22016:
     // 230 workgroups 38.0 us, 172 workgroups of 128 columns 40.9 us, 344 of 64 columns 47.1 us).
@@ -884,6 +898,11 @@ hipError_t launch_gemm_qkv(GemmArgs a, hipStream_t s) {
 hipError_t launch_gemm_swiglu(GemmArgs a, hipStream_t s) {
     a.splits = 1;
     if (a.row_factor && a.M > 64) return dispatch_factor<EPI_SWIGLU>(a, s);
+    // Stages so narrow that 48-column tiles are one round of workgroups: those instead of 96 columns, for 33 to 64 rows, and for fewer
+    // where the grid then fills three quarters of the chip.  Whole layers, 96 -> 48 columns: d_model 2048 (118 -> 235 workgroups)
+    // 64 rows 59.4 -> 56.4 us, 40 rows 56.3 -> 53.3, 32 rows 54.4 -> 52.5, 16 rows 49.1 -> 48.2, 5 rows 45.1 -> 44.9; 1536 (88 -> 176) 52.6 ->
+    // 51.4, 50.0 -> 49.3, 48.1 -> 48.0; 1024 (59 -> 118) 43.6 -> 43.1, 41.9 -> 41.8, 40.5 -> 41.0.
+    if (halves_swiglu(a.M, a.N, a.shared_gpu)) return launch<2, 2, 2, 2, EPI_SWIGLU, true, 0, true>(a, s);
     return dispatch<EPI_SWIGLU>(pick_swiglu(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 

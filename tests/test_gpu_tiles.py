@@ -72,12 +72,14 @@ def test_bf16_rows_that_do_not_exist(rows):
     p.check(p.kv_gpu()[1], p.oracle.kv[1], "cache")
 
 
-@pytest.mark.parametrize("d_model,rows", [(2048, 33), (2048, 47), (2048, 64), (4096, 40)])
-def test_bf16_qkv_in_halves_of_column_blocks(d_model, rows):
-    """33 to 64 rows on 48-column tiles (128 workgroups and 256, the ends of their range): queries, keys and values against the
-    oracle, and a batch of branches against each of them alone, which runs on the 64-column tiles: the same bits."""
+@pytest.mark.parametrize("d_model,d_ffn,rows", [(2048, 2816, 33), (2048, 4224, 47), (2048, 1408, 64), (4096, 256, 40), (512, 5632, 24),
+                                                (512, 4864, 9)])
+def test_bf16_tiles_of_half_column_blocks(d_model, d_ffn, rows):
+    """48-column tiles of QKV (33 to 64 rows; 128 workgroups and 256, the ends of their range) and of gate/up (column blocks that
+    are a multiple of three, one and two more; fewer rows on 204 and 235 workgroups) against the oracle, and a batch of
+    branches against each of them alone, which runs on other tiles: the same bits."""
     import torch
-    cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=d_model // 128, d_ffn=256, n_layers=1)
+    cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=d_model // 128, d_ffn=d_ffn, n_layers=1)
     p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 7, max_chunk_tokens=64)
     hidden = p.hidden(rows + 7)
     g, o = p.run_both(hidden, [7, rows])
