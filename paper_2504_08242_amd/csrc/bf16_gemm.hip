@@ -605,7 +605,8 @@ hipError_t configure_one() {
     JUP_GEMM_TALL(X, EPI_PARTIAL)                                                                          \
     X(9, 8, 4, 2, EPI_SWIGLU) X(9, 6, 4, 2, EPI_SWIGLU)                                                    \
     X(8, 1, 4, 1, EPI_QKV) X(8, 2, 4, 1, EPI_QKV) X(8, 3, 8, 1, EPI_QKV)                                   \
-    X(4, 2, 4, 1, EPI_QKV) X(2, 2, 2, 2, EPI_QKV)                                                          \
+    X(4, 1, 4, 1, EPI_QKV) X(4, 2, 4, 1, EPI_QKV) X(2, 2, 2, 2, EPI_QKV)                                   \
+    X(4, 1, 4, 1, EPI_SWIGLU) X(4, 2, 4, 1, EPI_SWIGLU)                                                    \
     X(8, 2, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU) X(2, 4, 2, 2, EPI_SWIGLU)                          \
     X(1, 3, 1, 3, EPI_SWIGLU) X(1, 4, 1, 4, EPI_SWIGLU) X(2, 3, 2, 3, EPI_SWIGLU) X(4, 6, 4, 1, EPI_SWIGLU) \
     X(2, 6, 2, 3, EPI_SWIGLU)                                                                              \
@@ -613,7 +614,8 @@ hipError_t configure_one() {
 // Batches of more than 64 rows of branches of up to 16 tokens: rows with a factor (see FACTOR; the tiles of up to 64 rows
 // all take one)
 #define JUP_GEMM_FACTOR_SHAPES(X) \
-    X(4, 2, 4, 1, EPI_QKV) X(4, 3, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU)
+    X(4, 1, 4, 1, EPI_QKV) X(4, 2, 4, 1, EPI_QKV) X(4, 1, 4, 1, EPI_SWIGLU) X(4, 2, 4, 1, EPI_SWIGLU)     \
+    X(4, 3, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU)
 // Tiles of two widths (see REST): the column blocks of the last round's behind the epilogue.
 #define JUP_GEMM_REST_SHAPES(X) X(8, 8, 4, 2, EPI_SWIGLU, 6) X(8, 8, 4, 2, EPI_SWIGLU, 4)
 
@@ -794,6 +796,10 @@ TileShape pick_qkv(int M, int N, int K, bool shared_gpu) {
     // +2 %; 7B shapes, 16 x 128 tokens +0-1 %; 192 columns +4 % and -1 %; 64-token chunks no difference either way.
     if (shared_gpu && bmb == 4) return {4, 3, 4, 1};
     if (bmb == 2) return {2, 2, 2, 2};
+    // Narrow stages: 32 columns where that is one round of workgroups.  A CU takes rows and weights at about 50 GB/s, so as few
+    // columns each as there are CUs for.  Whole layers, 64 -> 32 columns: d_model 2048 (96 -> 192 workgroups) 128 rows 71.6 -> 69.5 us,
+    // 65 rows 60.6 -> 57.8; 1536 61.8 -> 60.0, 53.5 -> 51.8; 1024 49.1 -> 47.8, 44.1 -> 42.8.
+    if (bmb == 4 && div_up(N, 32) <= kCUs) return {4, 1, 4, 1};
     if (bmb == 4) return {4, 2, 4, 1};
     if (!shared_gpu) return pick_tall(EPI_QKV, M, N, K).t;
     static const int cands[] = {1, 2, 3};
@@ -829,6 +835,11 @@ TileShape pick_swiglu(int M, int N, int K, bool shared_gpu) {
     // waves of 32 x 32: QKV 22.8 -> 23.4 us, O / down no different: they keep the 64-row tile.)
     if (bmb == 2 && M <= 32) return narrow ? TileShape{1, 3, 1, 3} : TileShape{1, 4, 1, 4};
     if (bmb == 2) return narrow ? TileShape{2, 3, 2, 3} : TileShape{2, 4, 2, 2};
+    // 65 to 128 rows of narrow stages: the narrowest tile whose grid is one round of workgroups (see QKV).  Whole layers, 96 -> 64 ->
+    // 32 columns: d_model 2048 (118, 176 workgroups) 128 rows 75.2 -> 71.7 us, 65 rows 62.9 -> 59.9; 1536 (88, 132) 64.0 -> 62.1,
+    // 56.0 -> 53.7; 1024 (59, 88, 176) 51.9 -> 50.3 -> 49.1, 46.5 -> 45.0 -> 44.1.
+    if (bmb == 4 && div_up(N, 32) <= kCUs) return {4, 1, 4, 1};
+    if (bmb == 4 && div_up(N, 64) <= kCUs) return {4, 2, 4, 1};
     if (bmb == 4) return narrow ? TileShape{4, 3, 4, 1} : TileShape{4, 4, 4, 1};
     if (!shared_gpu) return pick_tall(EPI_SWIGLU, M, N, K).t;
     static const int cands[] = {2, 3, 4, 6};

@@ -97,6 +97,32 @@ def test_bf16_tiles_of_half_column_blocks(d_model, d_ffn, rows):
         assert torch.equal(alone[b].view(), whole[b].view()), b
 
 
+@pytest.mark.parametrize("d_model,d_ffn,rows,tiles", [(1024, 2816, 65, ("4,1,4,1", "4,1,4,1")), (1024, 4096, 127, ("4,1,4,1", "4,1,4,1")),
+                                                      (1024, 4224, 120, ("4,1,4,1", "4,2,4,1")), (2816, 8192, 72, ("4,2,4,1", "4,2,4,1")),
+                                                      (1536, 8320, 96, ("4,1,4,1", "4,3,4,1"))])
+def test_bf16_narrow_tiles_of_128_rows(d_model, d_ffn, rows, tiles):
+    """65 to 128 rows: the narrowest tile whose grid is one round of workgroups, at the ends of its range, against the oracle, and
+    a batch of branches (whose rows come with a factor) against each of them alone: the same bits."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=d_model // 128, d_ffn=d_ffn, n_layers=2)
+    p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 7, max_chunk_tokens=128)
+    for kernel, tile in zip(("gemm_qkv", "gemm_gate_up"), tiles):
+        assert p.stage.kernel_name(jb.KERNEL_IDS[kernel], rows).startswith(f"gemm_bf16<{tile},"), kernel
+    hidden = p.hidden(rows + 7)
+    g, o = p.run_both(hidden, [7, rows])
+    p.check(g[7:], o[7:], "chunk")
+    p.check(p.kv_gpu()[1], p.oracle.kv[1], "cache")
+    if rows % 8:
+        return
+    n, tok = 8, rows // 8
+    x = torch.from_numpy(hidden[7:]).to("cuda:0", p.td)
+    whole, alone = ([p.kv.fork(7, 7 + tok) for _ in range(n)] for _ in range(2))
+    got = p.stage.prefill_branches(x, tok, [7] * n, whole)
+    for b in range(n):
+        assert torch.equal(p.stage.prefill_chunk(x[b * tok:(b + 1) * tok].contiguous(), 7, alone[b]), got.view(n, tok, -1)[b]), b
+        assert torch.equal(alone[b].view(), whole[b].view()), b
+
+
 @pytest.mark.parametrize("dtype,layers,rows", [("bf16", 1, 17), ("bf16", 2, 300), ("w4", 1, 70), ("w4", 2, 33), ("bf16", 1, 16)])
 def test_hidden_states_in_place(dtype, layers, rows):
     """The residual stream begins in the input buffer: a call that overwrites it with its output, against one that does not."""
