@@ -63,13 +63,20 @@ __device__ inline void load_to_lds_16(const void* uniform_base, unsigned lane_of
                  : "v"(lane_offset), "s"(uniform_base), "s"(lds_base)
                  : "memory", "m0");
 }
-// The same for the lanes of a mask alone: the others read nothing and leave their 16 bytes of LDS as they are (with no lane
-// at all the instruction only counts).  All lanes of the wave are on.
+// The same for the lanes of a mask alone: the others read nothing and leave their 16 bytes of LDS as they are.  All lanes of the
+// wave are on.  The mask has at least one lane: callers count every load in their vmcnt waits, and nothing says that one without
+// lanes is issued and counted.
 __device__ inline void load_to_lds_16(const void* uniform_base, unsigned lane_offset, unsigned lds_base, unsigned long long lanes) {
     asm volatile("s_mov_b64 exec, %3\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
                  :
                  : "v"(lane_offset), "s"(uniform_base), "s"(lds_base), "s"(lanes)
                  : "memory", "m0");
+}
+// The lanes that such a load needs for 16 rows of 64 bytes from row `first` of a matrix of M rows: 16 lanes are four rows, and fours
+// past the last row are left out (one lane stays on where all are: its address is the caller's to clamp).
+__device__ __host__ inline unsigned long long row_lanes(int M, int first) {
+    const int fours = (M - first + 3) / 4;
+    return fours >= 4 ? ~0ull : fours > 0 ? (1ull << (fours * 16)) - 1 : 1ull;
 }
 // LDS byte address of a pointer into the workgroup's dynamic LDS.
 __device__ inline unsigned lds_byte_address(const void* p) {

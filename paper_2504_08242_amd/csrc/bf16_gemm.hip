@@ -189,18 +189,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     constexpr bool kShortChunkTile = BMB <= 2 || (BMB == 4 && WM * WN == 4);
     const bool nt_weights = a.m_tiles == 1 && !a.shared_gpu;
     // Those tiles leave the rows past M out (LDS holds anything there, which reaches the accumulators of those rows alone): a CU
-    // takes operands at about 50 GB/s, and 40 rows in a 64-row tile spent a fifth of that on rows that do not exist.  Four
-    // rows are 256 bytes, 16 lanes.  Whole layers, before -> after (same bits): 7B 40 rows 100.8 -> 96.0 us, 100 rows 135.0 ->
-    // 128.9, 5 rows 83.5 -> 82.5, 64 rows 103.6 -> 103.4; 13B 40 rows 136.9 -> 131.4, 128 rows 182.4 -> 182.1.  (A ring of 16
-    // stages instead of 8, now that a stage of few rows is short: 5 rows 83.0 -> 85.6.)
+    // takes operands at about 50 GB/s, and 40 rows in a 64-row tile spent a fifth of that on rows that do not exist.  (A unit
+    // past M keeps one lane, 16 bytes of its clamped block: every load has to count for the waits.)  Whole layers, before -> after
+    // (same bits): 7B 40 rows 100.8 -> 96.0 us, 100 rows 135.0 -> 128.9, 5 rows 83.5 -> 82.5, 64 rows 103.6 -> 103.4; 13B 40 rows
+    // 136.9 -> 131.4, 128 rows 182.4 -> 182.1.  (A ring of 16 stages instead of 8, now that a stage of few rows is short: 5 rows
+    // 83.0 -> 85.6.)
     const unsigned ring = __builtin_amdgcn_readfirstlane(lds_byte_address(smem));
     unsigned long long lanes[S::LPW];
     if constexpr (kShortChunkTile) {
 #pragma unroll
         for (int q = 0; q < S::LPW; ++q) {
             const int j = q * S::LOADERS + lw;
-            const int fours = j < G_BM / 16 ? max(min((a.M - (m0 + j * 16) + 3) / 4, 4), 0) : 4;
-            lanes[q] = fours == 4 ? ~0ull : (1ull << (fours * 16)) - 1;
+            lanes[q] = j < G_BM / 16 ? row_lanes(a.M, m0 + j * 16) : ~0ull;
         }
     }
     auto issue_one = [&](int q, int stage, int kt) {

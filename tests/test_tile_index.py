@@ -78,6 +78,27 @@ int main() {
 """
 
 
+LANES = r"""
+#include <cstdio>
+#include "bf16_common.h"
+int main() {
+    long bad = 0, n = 0;
+    for (int M = 1; M <= 300; ++M)
+        for (int first = 0; first < 320; first += 16) {
+            const unsigned long long lanes = jup::row_lanes(M, first);
+            for (int lane = 0; lane < 64; ++lane) {
+                const int row = first + lane / 4;   // 16 bytes of a row of 64
+                const bool brings_rows = row / 4 * 4 < M, keeps_count = first >= M && lane == 0;
+                ++n, bad += (lanes >> lane & 1) != (brings_rows || keeps_count);
+            }
+            bad += lanes == 0;
+        }
+    printf("%ld of %ld\n", bad, n);
+    return bad != 0;
+}
+"""
+
+
 def run_on_the_host(program, tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
@@ -101,6 +122,21 @@ def test_grid_of_chunk_attention_reaches_every_block_once(tmp_path):
     source = open(os.path.join(jbuild.CSRC, "bf16_attention.hip")).read()
     launches = [l for l in source.splitlines() if "hipLaunchKernelGGL" in l and "chunk_attention_bf16" in l]
     assert len(launches) == 4 and all("chunk_grid(" in l for l in launches), launches
+
+
+def test_masked_row_loads_bring_the_rows_of_the_chunk_and_keep_a_lane(tmp_path):
+    """Loads of short-chunk tiles: every row of the chunk, no group of four rows past it, and never an empty mask (the waits of the ring
+    count every load).  No other mask reaches such a load."""
+    assert run_on_the_host(LANES, tmp_path).startswith("0 of")
+    source = open(os.path.join(jbuild.CSRC, "bf16_gemm.hip")).read()
+    masks = [l for l in source.splitlines() if "lanes[q] =" in l]
+    assert len(masks) == 1 and masks[0].endswith("? row_lanes(a.M, m0 + j * 16) : ~0ull;"), masks
+    for name in sorted(os.listdir(jbuild.CSRC)):
+        if name.endswith((".h", ".hip")):
+            lines = open(os.path.join(jbuild.CSRC, name)).read().splitlines()
+            loads = [l for l in lines if "load_to_lds_16(" in l and "lanes" in l and "inline void" not in l]
+            assert all(l.rstrip().endswith("lanes[q]);") for l in loads), (name, loads)
+            assert sum("mov_b64 exec" in l for l in lines) == (name == "bf16_common.h"), name
 
 
 def test_gpu_test_of_long_w4_chunks_runs_every_tile_shape(tmp_path):
