@@ -412,8 +412,9 @@ JUP_API jup_status_t jup_diag_mfma_loop(const void *operands, size_t operand_byt
 /*
  * Which instantiation of the projection kernel a chunk of n_tokens runs as: "gemm_bf16<row blocks,column blocks,
  * waves along M,waves along N,epilogue>", or "project_rows<bf16>" (output and down projection of up to 16 rows),
- * written to buf (HOST, size bytes, always terminated).  overlapped != 0:
- * inside an overlapped jup_stage_prefill_chunks() call.  A benchmark uses it to tell whether a hardware-counter
+ * written to buf (HOST, size bytes, always terminated).  The column blocks (of 32 features) are a number; "8+6" for a
+ * launch in tiles of two widths, whole rounds of workgroups in tiles of 8 and the columns behind them in tiles of 6; or
+ * "1.5" for tiles that end in half a block.  A name belongs to one instantiation.  overlapped != 0: inside an overlapped jup_stage_prefill_chunks() call.  A benchmark uses it to tell whether a hardware-counter
  * reading kept on file was taken for the tiling that runs today.  kernel_id: one of the four JUP_K_GEMM_* ids.
  * Errors: JUP_EINVAL (NULL, not a projection id, not a JUP_BF16 stage).
  */

@@ -618,6 +618,8 @@ hipError_t configure_one() {
     X(4, 3, 4, 1, EPI_SWIGLU) X(4, 4, 4, 1, EPI_SWIGLU)
 // Tiles of two widths (see REST): the column blocks of the last round's behind the epilogue.
 #define JUP_GEMM_REST_SHAPES(X) X(8, 8, 4, 2, EPI_SWIGLU, 6) X(8, 8, 4, 2, EPI_SWIGLU, 4)
+// Tiles that end in half a column block (see HalfTile)
+#define JUP_GEMM_HALF_SHAPES(X) X(2, 2, 2, 2, EPI_QKV) X(2, 2, 2, 2, EPI_SWIGLU)
 
 hipError_t gemm_configure() {
     hipError_t e = hipSuccess;
@@ -631,8 +633,9 @@ hipError_t gemm_configure() {
 #define X(BMB, NB, WM, WN, EPI, REST) acc(configure_one<BMB, NB, WM, WN, EPI, false, REST>());
     JUP_GEMM_REST_SHAPES(X)
 #undef X
-    acc(configure_one<2, 2, 2, 2, EPI_QKV, true, 0, true>());
-    acc(configure_one<2, 2, 2, 2, EPI_SWIGLU, true, 0, true>());
+#define X(BMB, NB, WM, WN, EPI) acc(configure_one<BMB, NB, WM, WN, EPI, true, 0, true>());
+    JUP_GEMM_HALF_SHAPES(X)
+#undef X
     return e;
 }
 
@@ -640,6 +643,7 @@ hipError_t gemm_configure() {
 struct TileShape {
     int bmb, nb, wm, wn;  // row blocks, column blocks, waves along M, waves along N
     int rest = 0;         // column blocks of the tiles of the last round, 0: as the others
+    bool half = false;    // the last of the nb column blocks is half a block
 };
 
 namespace {
@@ -789,12 +793,20 @@ int pick_blocks(int M, int N, const int* cands, int n_cands) {
 
 namespace {
 
+constexpr TileShape kHalfTile = {2, 2, 2, 2, 0, true};
+
 TileShape pick_qkv(int M, int N, int K, bool shared_gpu) {
     const int bmb = pick_row_blocks(M);
     // 128-token chunks beside other chunks' kernels: 96-column tiles (half again as much work per workgroup; alone on
     // the chip 64 columns win, 24.0 vs 28.8 us at 64 rows).  Measured on four lanes: 13B shapes, 8 x 128 tokens
     // +2 %; 7B shapes, 16 x 128 tokens +0-1 %; 192 columns +4 % and -1 %; 64-token chunks no difference either way.
     if (shared_gpu && bmb == 4) return {4, 3, 4, 1};
+    // 33 to 64 rows: tiles of one and a half column blocks where their grid is still one round of workgroups.  A CU takes rows and
+    // weights at about 50 GB/s, and 64-column tiles leave a quarter of the CUs out on the 7B shapes (192 of 256).  Whole layers,
+    // 64 -> 48 columns: 64 rows 7B 102.8 -> 101.8 us, d_model 2048 60.3 -> 59.8; 40 rows 95.6 -> 94.9, 56.9 -> 56.6.  Below 33 rows
+    // nothing is gained (the rows weigh little), nor with fewer workgroups (d_model 1536: 53.1 -> 52.7 and 50.5 -> 50.5; 1024: 43.4 ->
+    // 43.5 and 41.7 -> 42.4).
+    if (M > 32 && M <= 64 && !shared_gpu && N % 96 == 0 && N / 48 >= kCUs / 2 && N / 48 <= kCUs) return kHalfTile;
     if (bmb == 2) return {2, 2, 2, 2};
     // Narrow stages: 32 columns where that is one round of workgroups.  A CU takes rows and weights at about 50 GB/s, so as few
     // columns each as there are CUs for.  Whole layers, 64 -> 32 columns: d_model 2048 (96 -> 192 workgroups) 128 rows 71.6 -> 69.5 us,
@@ -813,14 +825,14 @@ TileShape pick_qkv(int M, int N, int K, bool shared_gpu) {
     return {8, 1, 4, 1};
 }
 
-bool halves_swiglu(int M, int N, bool shared_gpu) {
-    const int wgs = div_up(N, 48);
-    return M <= 64 && !shared_gpu && wgs <= kCUs && (M > 32 || (M > 8 && wgs > kCUs * 3 / 4));
-}
-
 TileShape pick_swiglu(int M, int N, int K, bool shared_gpu) {
     const int bmb = pick_row_blocks(M);
-    if (halves_swiglu(M, N, shared_gpu)) return {2, 2, 2, 2};
+    // Stages so narrow that 48-column tiles are one round of workgroups: those instead of 96 columns, for 33 to 64 rows, and for fewer
+    // where the grid then fills three quarters of the chip.  Whole layers, 96 -> 48 columns: d_model 2048 (118 -> 235 workgroups)
+    // 64 rows 59.4 -> 56.4 us, 40 rows 56.3 -> 53.3, 32 rows 54.4 -> 52.5, 16 rows 49.1 -> 48.2, 5 rows 45.1 -> 44.9; 1536 (88 -> 176) 52.6 ->
+    // 51.4, 50.0 -> 49.3, 48.1 -> 48.0; 1024 (59 -> 118) 43.6 -> 43.1, 41.9 -> 41.8, 40.5 -> 41.0.
+    const int halves = div_up(N, 48);
+    if (M <= 64 && !shared_gpu && halves <= kCUs && (M > 32 || (M > 8 && halves > kCUs * 3 / 4))) return kHalfTile;
     // A short chunk is bound by streaming the weights, and every CU that streams adds bandwidth: the narrower
     // tile (96 columns) when its tiles still fit one round of workgroups (measured at 64 rows, N = 22016:
     // 230 workgroups 38.0 us, 172 workgroups of 128 columns 40.9 us, 344 of 64 columns 47.1 us).
@@ -865,7 +877,7 @@ template <int EPI>
 hipError_t dispatch(TileShape t, const GemmArgs& a, hipStream_t s) {
 #define X(BMB, NB, WM, WN, E)                                                         \
     if constexpr (E == EPI)                                                           \
-        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN && !t.rest)                  \
+        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN && !t.rest && !t.half) \
             return launch<BMB, NB, WM, WN, EPI, BMB <= 2 && EPI != EPI_PARTIAL>(a, s);
     JUP_GEMM_SHAPES(X)
 #undef X
@@ -874,6 +886,12 @@ hipError_t dispatch(TileShape t, const GemmArgs& a, hipStream_t s) {
         if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN && t.rest == REST)         \
             return launch<BMB, NB, WM, WN, EPI, false, REST>(a, s);
     JUP_GEMM_REST_SHAPES(X)
+#undef X
+#define X(BMB, NB, WM, WN, E)                                                                 \
+    if constexpr (E == EPI)                                                                   \
+        if (t.bmb == BMB && t.nb == NB && t.wm == WM && t.wn == WN && t.half)                 \
+            return launch<BMB, NB, WM, WN, EPI, true, 0, true>(a, s);
+    JUP_GEMM_HALF_SHAPES(X)
 #undef X
     return hipErrorInvalidConfiguration;  // a shape the pick functions name but the list above does not hold
 }
@@ -896,24 +914,12 @@ hipError_t dispatch_factor(const GemmArgs& a, hipStream_t s) {
 hipError_t launch_gemm_qkv(GemmArgs a, hipStream_t s) {
     a.splits = 1;
     if (a.row_factor && a.M > 64) return dispatch_factor<EPI_QKV>(a, s);
-    // 33 to 64 rows: tiles of one and a half column blocks where their grid is still one round of workgroups.  A CU takes rows and
-    // weights at about 50 GB/s, and 64-column tiles leave a quarter of the CUs out on the 7B shapes (192 of 256).  Whole layers,
-    // 64 -> 48 columns: 64 rows 7B 102.8 -> 101.8 us, d_model 2048 60.3 -> 59.8; 40 rows 95.6 -> 94.9, 56.9 -> 56.6.  Below 33 rows
-    // nothing is gained (the rows weigh little), nor with fewer workgroups (d_model 1536: 53.1 -> 52.7 and 50.5 -> 50.5; 1024: 43.4 ->
-    // 43.5 and 41.7 -> 42.4).
-    const bool halves = a.M > 32 && a.M <= 64 && !a.shared_gpu && a.N % 96 == 0 && a.N / 48 >= kCUs / 2 && a.N / 48 <= kCUs;
-    if (halves) return launch<2, 2, 2, 2, EPI_QKV, true, 0, true>(a, s);
     return dispatch<EPI_QKV>(pick_qkv(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 
 hipError_t launch_gemm_swiglu(GemmArgs a, hipStream_t s) {
     a.splits = 1;
     if (a.row_factor && a.M > 64) return dispatch_factor<EPI_SWIGLU>(a, s);
-    // Stages so narrow that 48-column tiles are one round of workgroups: those instead of 96 columns, for 33 to 64 rows, and for fewer
-    // where the grid then fills three quarters of the chip.  Whole layers, 96 -> 48 columns: d_model 2048 (118 -> 235 workgroups)
-    // 64 rows 59.4 -> 56.4 us, 40 rows 56.3 -> 53.3, 32 rows 54.4 -> 52.5, 16 rows 49.1 -> 48.2, 5 rows 45.1 -> 44.9; 1536 (88 -> 176) 52.6 ->
-    // 51.4, 50.0 -> 49.3, 48.1 -> 48.0; 1024 (59 -> 118) 43.6 -> 43.1, 41.9 -> 41.8, 40.5 -> 41.0.
-    if (halves_swiglu(a.M, a.N, a.shared_gpu)) return launch<2, 2, 2, 2, EPI_SWIGLU, true, 0, true>(a, s);
     return dispatch<EPI_SWIGLU>(pick_swiglu(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 
@@ -922,8 +928,7 @@ hipError_t launch_gemm_partial(GemmArgs a, hipStream_t s) {
     return dispatch<EPI_PARTIAL>(pick_partial(a.M, a.N, a.K, a.shared_gpu), a, s);
 }
 
-// "gemm_bf16<row blocks,column blocks,waves along M,waves along N,epilogue>" of the launch a projection of M rows takes (tiles of
-// two widths: column blocks+those of the last round; a tile that ends in half a column block is named with that block)
+// The name of the launch a projection of M rows takes; jup_diag_kernel_name (jupiter_stage.h) has the forms.
 void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_gpu, char* buf, size_t size) {
     TileShape t{};
     int epi = EPI_PARTIAL;
@@ -933,9 +938,15 @@ void gemm_kernel_name(GemmKind kind, int M, int d_model, int d_ffn, bool shared_
         case GEMM_O: t = pick_partial(M, d_model, d_model, shared_gpu); break;
         case GEMM_DOWN: t = pick_partial(M, d_model, d_ffn, shared_gpu); break;
     }
-    if (epi == EPI_PARTIAL && M <= kMaxProjectRows && !shared_gpu) snprintf(buf, size, "project_rows<bf16>");
-    else if (t.rest) snprintf(buf, size, "gemm_bf16<%d,%d+%d,%d,%d,%d>", t.bmb, t.nb, t.rest, t.wm, t.wn, epi);
-    else snprintf(buf, size, "gemm_bf16<%d,%d,%d,%d,%d>", t.bmb, t.nb, t.wm, t.wn, epi);
+    if (epi == EPI_PARTIAL && M <= kMaxProjectRows && !shared_gpu) {
+        snprintf(buf, size, "project_rows<bf16>");
+        return;
+    }
+    char cols[24];
+    if (t.rest) snprintf(cols, sizeof(cols), "%d+%d", t.nb, t.rest);
+    else if (t.half) snprintf(cols, sizeof(cols), "%d.5", t.nb - 1);
+    else snprintf(cols, sizeof(cols), "%d", t.nb);
+    snprintf(buf, size, "gemm_bf16<%d,%s,%d,%d,%d>", t.bmb, cols, t.wm, t.wn, epi);
 }
 
 }  // namespace jup

@@ -101,7 +101,7 @@ def test_kernel_name_reports_the_documented_tile_policy():
         ("gemm_qkv", 256, False): "gemm_bf16<4,3,4,1,0>", ("gemm_gate_up", 256, False): "gemm_bf16<8,3,4,1,2>",
         ("gemm_o", 256, False): "gemm_bf16<4,4,4,2,1>", ("gemm_down", 256, False): "gemm_bf16<4,4,4,2,1>",
         ("gemm_qkv", 128, False): "gemm_bf16<4,2,4,1,0>", ("gemm_gate_up", 128, False): "gemm_bf16<4,3,4,1,2>",
-        ("gemm_qkv", 64, False): "gemm_bf16<2,2,2,2,0>", ("gemm_gate_up", 64, False): "gemm_bf16<2,3,2,3,2>",
+        ("gemm_qkv", 64, False): "gemm_bf16<2,1.5,2,2,0>", ("gemm_gate_up", 64, False): "gemm_bf16<2,3,2,3,2>",
         ("gemm_gate_up", 5, False): "gemm_bf16<1,3,1,3,2>", ("gemm_qkv", 5, False): "gemm_bf16<2,2,2,2,0>",
         ("gemm_gate_up", 1024, False): "gemm_bf16<8,6,4,2,2>", ("gemm_qkv", 1024, False): "gemm_bf16<8,6,4,2,0>",
     }
