@@ -72,24 +72,31 @@ def test_bf16_rows_that_do_not_exist(rows):
     p.check(p.kv_gpu()[1], p.oracle.kv[1], "cache")
 
 
-@pytest.mark.parametrize("d_model,d_ffn,rows", [(2048, 2816, 33), (2048, 4224, 47), (2048, 1408, 64), (4096, 256, 40), (512, 5632, 24),
-                                                (512, 4864, 9)])
+HALF_TILES = {   # (d_model, d_ffn, rows): tiles of QKV and gate/up
+    (2048, 2816, 33): ("2,1.5,2,2", "2,1.5,2,2"), (2048, 4224, 47): ("2,1.5,2,2", "2,1.5,2,2"), (2048, 1408, 64): ("2,1.5,2,2", "2,1.5,2,2"),
+    (4096, 256, 40): ("2,1.5,2,2", "2,1.5,2,2"), (512, 5632, 24): ("2,2,2,2", "2,1.5,2,2"), (512, 4864, 9): ("2,2,2,2", "2,1.5,2,2"),
+}
+
+
+@pytest.mark.parametrize("d_model,d_ffn,rows", HALF_TILES)
 def test_bf16_tiles_of_half_column_blocks(d_model, d_ffn, rows):
     """48-column tiles of QKV (33 to 64 rows; 128 workgroups and 256, the ends of their range) and of gate/up (column blocks that
-    are a multiple of three, one and two more; fewer rows on 204 and 235 workgroups) against the oracle, and a batch of
+    are a multiple of three, one and two more; fewer rows on 203 and 235 workgroups) against the oracle, and a batch of
     branches against each of them alone, which runs on other tiles: the same bits."""
     import torch
     cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=d_model // 128, d_ffn=d_ffn, n_layers=1)
     p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 7, max_chunk_tokens=64)
+    n = 8 if rows % 8 == 0 else 3
+    tok = rows // n
+    names = [[p.stage.kernel_name(jb.KERNEL_IDS[k], m) for k in ("gemm_qkv", "gemm_gate_up")] for m in (rows, n * tok, tok)]
+    for m, name in zip((rows, n * tok), names):
+        assert name == [f"gemm_bf16<{tile},{e}>" for e, tile in zip((0, 2), HALF_TILES[d_model, d_ffn, rows])], m
+    assert "1.5" not in names[2][0] + names[2][1], names[2]
     hidden = p.hidden(rows + 7)
     g, o = p.run_both(hidden, [7, rows])
     p.check(g[7:], o[7:], "chunk")
     p.check(p.kv_gpu()[0], p.oracle.kv[0], "cache")
-    n = 8 if rows % 8 == 0 else 1
-    if n == 1:
-        return
-    tok = rows // n
-    x = torch.from_numpy(hidden[7:]).to("cuda:0", p.td)
+    x = torch.from_numpy(hidden[7:7 + n * tok]).to("cuda:0", p.td)
     whole, alone = ([p.kv.fork(7, 7 + tok) for _ in range(n)] for _ in range(2))
     got = p.stage.prefill_branches(x, tok, [7] * n, whole)
     for b in range(n):
