@@ -168,11 +168,11 @@ struct GemmArgs {
     const float* w_scale;  // 4-bit stages only: packed scales
     int M, N, K;
     int n_tok;             // 4-bit stages only: rows of one chunk or branch (M, or M / number of branches)
-    int m_tiles, n_tiles, splits;  // grid = m_tiles * n_tiles * splits workgroups
+    int m_tiles, n_tiles, splits;  // grid = m_tiles * n_tiles * splits workgroups (two widths: n_tiles of the wider, and the others)
     Quotient by_m, by_n, by_splits;  // the three as divisors
     int n_stride;                  // columns between consecutive N tiles (tile width actually owned)
-    int wide_tiles;                // bf16 launches in tiles of two widths: workgroups that have the wider ones
     int kt_per_split;              // K tiles of 32 per split
+    int wide_tiles;                // bf16 launches in tiles of two widths: workgroups that have the wider ones
     // EPI_QKV
     u16* q_out;          // [M, d_model] rotated queries
     const float2* rope;  // [M, 64] (cos, sin)
