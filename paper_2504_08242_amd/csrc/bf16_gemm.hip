@@ -680,31 +680,43 @@ namespace {
 // before -> after on the 7B shapes: QKV of 2048 rows 208 -> 175 us, of 539 rows (three 256-row tiles for 17 row blocks)
 // 94 -> 59 us; gate/up of 539 rows 123 -> 104 us, of 320 rows 74 -> 59 us; down of 539 rows 69 -> 58 us with its share
 // of the reduction; on the 13B shapes gate/up of 512 rows 136 -> 113 us, QKV 102 -> 76 us.
+// What gate/up launches take against the model where tiles of 288 rows or two widths are a choice: full - less * 1024 / K (the clock
+// falls under rounds of wide tiles and a long K loop).
+struct Clock {
+    float full, less;
+    float factor(int K) const { return full - less * 1024.f / K; }
+};
 struct TileCost {
     TileShape t;
     int epilogues;            // 1 << EPI_*: what it is instantiated for
     float stage, round, qkv;  // us per K stage of 32, per round of workgroups, more per round with the QKV epilogue
+    Clock clock = {1.0f, 0.0f};
 };
 constexpr int kWideEpi = 1 << EPI_QKV | 1 << EPI_SWIGLU, kAnyEpi = kWideEpi | 1 << EPI_PARTIAL;
 constexpr TileCost kTallTiles[] = {
-    {{8, 8, 4, 2}, kAnyEpi, 0.608f, 9.9f, 4.0f}, {{8, 6, 4, 2}, kAnyEpi, 0.496f, 6.3f, 5.3f},
-    {{8, 4, 4, 2}, kAnyEpi, 0.386f, 5.5f, 2.6f}, {{6, 8, 2, 4}, kAnyEpi, 0.496f, 8.1f, 2.5f},
-    {{6, 4, 2, 2}, kAnyEpi, 0.282f, 7.5f, 2.0f}, {{4, 8, 2, 4}, kAnyEpi, 0.401f, 5.4f, 2.2f},
+    {{8, 8, 4, 2}, kAnyEpi, 0.608f, 9.9f, 4.0f, {1.15f, 0.26f}}, {{8, 6, 4, 2}, kAnyEpi, 0.496f, 6.3f, 5.3f, {1.15f, 0.20f}},
+    {{8, 4, 4, 2}, kAnyEpi, 0.386f, 5.5f, 2.6f}, {{6, 8, 2, 4}, kAnyEpi, 0.496f, 8.1f, 2.5f, {1.14f, 0.0f}},
+    {{6, 4, 2, 2}, kAnyEpi, 0.282f, 7.5f, 2.0f, {0.97f, 0.0f}}, {{4, 8, 2, 4}, kAnyEpi, 0.401f, 5.4f, 2.2f, {1.02f, 0.0f}},
     {{4, 6, 4, 2}, kAnyEpi, 0.322f, 4.7f, 2.8f}, {{4, 4, 4, 2}, kAnyEpi, 0.230f, 4.1f, 2.0f},
-    {{6, 6, 2, 2}, kWideEpi, 0.437f, 0.3f, 2.3f}, {{4, 3, 4, 1}, kWideEpi, 0.196f, 4.9f, 1.4f},
+    {{6, 6, 2, 2}, kWideEpi, 0.437f, 0.3f, 2.3f, {1.01f, -0.05f}}, {{4, 3, 4, 1}, kWideEpi, 0.196f, 4.9f, 1.4f},
     {{8, 3, 4, 1}, 1 << EPI_SWIGLU, 0.343f, 1.0f, 0.0f},
-    // 288 rows: up to a row block or two more than whole 256-row tiles (the eight waves share the ninth row block's columns).
-    // Measured: gate/up of 539 rows 116.6 -> 92.7 us (two M tiles and one round of 230 workgroups instead of three M tiles
-    // and two rounds), on the 13B shapes 144 -> 133.  Not for QKV (539 rows: 79 us instead of 60; 1100 rows 110 instead of 114,
-    // the only gain) and the O / down projections, whose K splits fill the chip with any tile (down of 539 rows: 63.5 us
-    // instead of 59.2).
-    {{9, 8, 4, 2}, 1 << EPI_SWIGLU, 0.720f, 10.0f, 0.0f}, {{9, 6, 4, 2}, 1 << EPI_SWIGLU, 0.600f, 10.0f, 0.0f},
 };
-// Gate/up in 256-row tiles of two widths: as many whole rounds of 256-column tiles as there are, and the last one of 192 or 128
+// Two more ways to fit gate/up.  288 rows: up to a row block or two more than whole 256-row tiles (the eight waves share the ninth
+// row block's columns).  Measured: 539 rows 116.6 -> 92.7 us (two M tiles and one round of 230 workgroups instead of three M
+// tiles and two rounds), on the 13B shapes 144 -> 133.  Not for QKV (539 rows: 79 us instead of 60; 1100 rows 110 instead of 114, the only
+// gain) and the O / down projections, whose K splits fill the chip with any tile (down of 539 rows: 63.5 us instead of 59.2).
+constexpr TileCost kTallTiles288[] = {
+    {{9, 8, 4, 2}, 1 << EPI_SWIGLU, 0.720f, 10.0f, 0.0f, {1.13f, 0.33f}}, {{9, 6, 4, 2}, 1 << EPI_SWIGLU, 0.600f, 10.0f, 0.0f, {1.08f, 0.28f}},
+};
+// 256-row tiles of two widths: as many whole rounds of 256-column tiles as there are, and the last one of 192 or 128
 // columns where those fill it better.  Measured, all rounds alike -> two widths: 2048 rows 293.8 -> 282.6 us, 1700 rows 281 ->
 // 260, 1280 rows 193 -> 182; 13B 1024 rows 238 -> 228, 2048 rows 471 -> 443.  (QKV, whose column blocks are fewer: nothing
 // gained at 1700 and 2048 rows of either.)
-constexpr TileShape kTwoWidths[] = {{8, 8, 4, 2, 6}, {8, 8, 4, 2, 4}};
+struct TwoWidths {
+    TileShape t;
+    Clock clock;
+};
+constexpr TwoWidths kTwoWidths[] = {{{8, 8, 4, 2, 6}, {1.18f, 0.33f}}, {{8, 8, 4, 2, 4}, {1.17f, 0.33f}}};
 constexpr float kTwoWidthsUs = 3.0f;      // what such a launch has to be cheaper by
 constexpr float kLaunchUs = 3.0f;
 constexpr float kPartRound = 0.84f;       // a round that fills few CUs still takes this much of a full one
@@ -736,7 +748,20 @@ TallPick pick_tall(int epi, int M, int N, int K) {
         }
     }
     if (epi != EPI_SWIGLU) return best;
-    for (const TileShape& t : kTwoWidths) {
+    // The two other ways have to be cheaper by the model and with the clock in it.  Measured over 393 launches of 19 stages where the
+    // model alone offers one of them: by the model alone 33 got slower than with the tiles above, 1025 to 1152 rows of the 7B
+    // shapes most, 169 -> 179 us, where tiles of 192 x 192 hold the clock; with the clock none, and all of them run 1.080 times
+    // as fast (1.082 with the best choice for each).
+    const float plain_us = best_us;
+    for (const TileCost& c : kTallTiles)
+        if (c.t.bmb == best.t.bmb && c.t.nb == best.t.nb && c.t.wm == best.t.wm) best_us = plain_us * c.clock.factor(K);
+    auto offer = [&](const TileShape& t, float us, const Clock& clock) {
+        if (us < plain_us && us * clock.factor(K) < best_us) { best = {t, 1}; best_us = us * clock.factor(K); }
+    };
+    for (const TileCost& c : kTallTiles288)
+        offer(c.t, kLaunchUs + rounds(div_up(M, 32 * c.t.bmb) * div_up(N, 32 * c.t.nb)) * round_us(c, 1), c.clock);
+    for (const TwoWidths& w : kTwoWidths) {
+        const TileShape& t = w.t;
         const int tiles = div_up(M, 32 * t.bmb) * div_up(N, 32 * t.nb);
         if (tiles < kCUs || tiles % kCUs == 0) continue;
         float wide = 0.f, rest = 0.f;
@@ -746,8 +771,7 @@ TallPick pick_tall(int epi, int M, int N, int K) {
             if (c.t.nb == t.rest) rest = round_us(c, 1);
         }
         const Rounds r = rounds_of(M, N, t.bmb, t.nb, t.rest);
-        const float us = kLaunchUs + kTwoWidthsUs + tiles / kCUs * wide + rounds(r.rest_tiles) * rest;
-        if (us < best_us) { best = {t, 1}; best_us = us; }
+        offer(t, kLaunchUs + kTwoWidthsUs + tiles / kCUs * wide + rounds(r.rest_tiles) * rest, w.clock);
     }
     return best;
 }

@@ -120,3 +120,18 @@ def test_rules_of_half_tiles_at_their_ends(tmp_path):
     for d, f, rows, qkv, gate_up in HALF_TILES_END:
         assert got[d, f, rows, "gemm_qkv"] == f"gemm_bf16<{qkv},0>", (d, f, rows)
         assert got[d, f, rows, "gemm_gate_up"] == f"gemm_bf16<{gate_up},2>", (d, f, rows)
+
+
+GATE_UP_OF_LONG_CHUNKS = [   # (d_model, d_ffn, rows, tile): 288 rows and two widths where they measured faster, and only there
+    (4096, 11008, 539, "9,6,4,2"), (4096, 11008, 1280, "8,8+6,4,2"), (4096, 11008, 2048, "8,8+6,4,2"), (5120, 13824, 2048, "8,8+4,4,2"),
+    (1024, 11008, 1232, "8,8+6,4,2"), (5120, 13824, 800, "9,6,4,2"), (4096, 11008, 576, "9,6,4,2"),
+    (4096, 11008, 1025, "6,6,2,2"), (4096, 11008, 1100, "6,6,2,2"), (4096, 11008, 1152, "6,6,2,2"),     # two widths: 169 -> 179 us
+    (4096, 14336, 832, "6,6,2,2"), (5120, 13824, 912, "6,6,2,2"), (4096, 14336, 1850, "6,6,2,2"),
+]
+
+
+def test_gate_up_of_long_chunks_takes_the_measured_tile(tmp_path):
+    got = picks([(d, f) for d, f, *_ in GATE_UP_OF_LONG_CHUNKS], 129, 2100, 1, tmp_path)
+    wrong = [(d, f, rows, tile, name) for d, f, rows, tile in GATE_UP_OF_LONG_CHUNKS
+             if (name := got[d, f, rows, "gemm_gate_up"]) != f"gemm_bf16<{tile},2>"]
+    assert not wrong, wrong
