@@ -79,6 +79,15 @@ int main() {
             for (auto kind : kKinds) printf("%%d %%d %%d %%d %%s\n", st.d, st.f, M, (int)kind, name(kind, M, st.d, st.f, false).c_str());
 }
 """
+DISTINCT = RECORDER + r"""
+int main() {
+    std::set<std::string> names;
+    for (auto st : kStages)
+        for (int M = 129; M < 4097; ++M)
+            for (auto kind : kKinds) names.insert(name(kind, M, st.d, st.f, false));
+    for (const std::string& n : names) puts(n.c_str());
+}
+"""
 KINDS = ["gemm_qkv", "gemm_o", "gemm_gate_up", "gemm_down"]
 
 
@@ -135,3 +144,10 @@ def test_gate_up_of_long_chunks_takes_the_measured_tile(tmp_path):
     wrong = [(d, f, rows, tile, name) for d, f, rows, tile in GATE_UP_OF_LONG_CHUNKS
              if (name := got[d, f, rows, "gemm_gate_up"]) != f"gemm_bf16<{tile},2>"]
     assert not wrong, wrong
+
+
+def test_gpu_test_of_tall_tiles_runs_every_tile_of_its_stages(tmp_path):
+    """A plan that leads one of those stages to another tile shows here; the comparison with the oracle does not depend on it."""
+    from test_gpu_tiles import COVERED, TALL_TILES
+    names = set(run_on_the_host(DISTINCT % stages((d, f) for d, _, f, *_ in TALL_TILES), tmp_path).splitlines())
+    assert names == COVERED, names ^ COVERED

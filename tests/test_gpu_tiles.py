@@ -37,20 +37,18 @@ TALL_TILES = [
     (1536, 12, 11008, 1755, {"gemm_gate_up": "8,8+4,4,2"}),
 ]
 EPILOGUE = {"gemm_qkv": 0, "gemm_o": 1, "gemm_down": 1, "gemm_gate_up": 2}
+# test_gemm_plan.py replays the plans: whatever other chunk lengths of these stages run is among them
 COVERED = {f"gemm_bf16<{tile},{EPILOGUE[kernel]}>" for *_, tiles in TALL_TILES for kernel, tile in tiles.items()}
 
 
 @pytest.mark.parametrize("d_model,n_heads,d_ffn,rows,tiles", TALL_TILES)
 def test_bf16_tall_tiles(d_model, n_heads, d_ffn, rows, tiles):
-    """Every tile of the projections of chunks above 128 rows, with a ragged last row block and a short prefix; whatever else
-    other chunk lengths of these stages run is among them."""
+    """Every tile of the projections of chunks above 128 rows, with a ragged last row block and a short prefix."""
     cfg = dict(si.LLAMA7B_STAGE, d_model=d_model, n_heads=n_heads, d_ffn=d_ffn, n_layers=1)
     p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 7, max_chunk_tokens=rows)
     for kernel, tile in tiles.items():
         name = p.stage.kernel_name(jb.KERNEL_IDS[kernel], rows)
         assert name.startswith(f"gemm_bf16<{tile},"), (kernel, name)
-    picked = {p.stage.kernel_name(jb.KERNEL_IDS[kernel], n) for n in range(129, 4097, 16) for kernel in EPILOGUE}
-    assert picked <= COVERED, picked - COVERED
     hidden = p.hidden(rows + 7)
     g, o = p.run_both(hidden, [7, rows])
     p.check(g[7:], o[7:], f"{rows} rows of d {d_model}")
