@@ -57,8 +57,9 @@ def test_bf16_tall_tiles(d_model, n_heads, d_ffn, rows, tiles):
 
 @pytest.mark.parametrize("rows", [1, 4, 5, 15, 17, 29, 33, 40, 61, 64, 65, 77, 100, 127])
 def test_bf16_rows_that_do_not_exist(rows):
-    """Tiles of up to 128 rows leave out the rows past the chunk: whatever LDS holds there (here NaN, left by a chunk of
-    another cache) reaches no row of the chunk.  Groups of four rows, halves of row blocks and whole blocks."""
+    """Tiles of up to 128 rows leave out the rows past the chunk: what LDS holds there reaches no row of the chunk.  Groups of four
+    rows, halves of row blocks and whole blocks.  The first projection finds NaN there where a chunk of another cache left it,
+    the later ones whatever kernels of the chunk itself did; test_tile_index.py has the masks."""
     cfg = dict(si.LLAMA7B_STAGE, d_model=512, n_heads=4, d_ffn=1408, n_layers=2)
     p = Pair(cfg, "bf16", seed=rows, max_positions=rows + 7, max_chunk_tokens=128)
     other = jb.KvCache(cfg, "bf16", 128)
@@ -140,6 +141,52 @@ def test_hidden_states_in_place(dtype, layers, rows):
     p.check(apart.float().cpu().numpy(), p.oracle.prefill_chunk(hidden, 0), "apart")
     p.stage.prefill_chunk(x, 0, p.kv, x)
     assert torch.equal(x, apart)
+
+
+@pytest.mark.parametrize("dtype,n_lanes,chunks,limit", [
+    ("bf16", 2, [70, 3, 129, 64, 300], 300),     # together, as one group
+    ("bf16", 2, [250] * 9, 250),                 # several groups
+    ("bf16", 3, [1025, 30, 1100, 5], 1100),      # side by side
+    ("bf16", 0, [100, 17, 5], 100),              # one after the other
+    ("w4", 4, [1100, 65, 1026], 1100),           # the bf16 copy of a 4-bit stage, side by side
+])
+def test_chunks_in_place(dtype, n_lanes, chunks, limit):
+    """Several chunks of one call whose output overwrites its input, against a call with an output of its own."""
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=512, n_heads=4, d_ffn=1408, n_layers=2)
+    total = sum(chunks)
+    p = Pair(cfg, dtype, seed=total, max_positions=total, max_chunk_tokens=limit, w4_expanded=dtype == "w4")
+    if n_lanes:
+        p.stage.enable_overlap(n_lanes)
+    x = torch.from_numpy(p.hidden(total)).to("cuda:0", p.td)
+    apart = p.stage.prefill_chunks(x, chunks, 0, p.kv)
+    cache = p.kv.view().clone()
+    p.stage.prefill_chunks(x, chunks, 0, p.kv, x)
+    assert torch.equal(x, apart)
+    assert torch.equal(p.kv.view(), cache)
+
+
+@pytest.mark.parametrize("dtype,layers", [("bf16", 1), ("bf16", 2), ("w4", 2)])
+@pytest.mark.parametrize("branches,n", [(8, 5), (3, 5), (3, 33)])   # rows with a late factor, row projections, rows of their own norm
+def test_branches_and_trees_in_place(dtype, layers, branches, n):
+    import torch
+    cfg = dict(si.LLAMA7B_STAGE, d_model=512, n_heads=4, d_ffn=1408, n_layers=layers)
+    p = Pair(cfg, dtype, seed=branches, max_positions=128, max_chunk_tokens=128)
+    p.gpu_chunk(p.hidden(20), 0)
+    x = torch.from_numpy(p.hidden(branches * n, tag=1)).to("cuda:0", p.td)
+    parents = si.make_token_tree(min(64, branches * n), 3)
+    tree = x[:len(parents)].clone()
+    forks = [[p.kv.fork(20, 20 + n) for _ in range(branches)] for _ in range(2)]
+    apart = p.stage.prefill_branches(x, n, [20] * branches, forks[0])
+    p.stage.prefill_branches(x, n, [20] * branches, forks[1], x)
+    assert torch.equal(x, apart)
+    for a, b in zip(*forks):
+        assert torch.equal(a.view(), b.view())
+        a.destroy()
+        b.destroy()
+    apart = p.stage.prefill_tree(tree, 20, parents, p.kv)
+    p.stage.prefill_tree(tree, 20, parents, p.kv, tree)
+    assert torch.equal(tree, apart)
 
 
 @pytest.mark.parametrize("n_lanes,chunks,limit", [
