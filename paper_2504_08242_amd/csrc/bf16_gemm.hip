@@ -1,13 +1,13 @@
 // bf16 GEMM  C[M, N] = A[M, K] * W[N, K]^T  for gfx950 with fused epilogues.
 //
-// Shape of the problem.  A chunk has at most a few hundred rows (M = n_tokens) while N is the layer
+// Shape of the problem.  A chunk has at most a few thousand rows (M = n_tokens) while N is the layer
 // width, so the work per compute unit is small: about 44 K outputs for the gate/up projection of a
-// 512-token chunk on 256 CUs.  The kernel therefore gives every CU ONE tall tile, 256 rows by up to
-// 192 columns, held entirely in accumulators (the register file of a CU is 512 KB), and sizes the
-// tile width so that the number of tiles matches the number of CUs.  That is the largest tile the
-// problem allows, which is what keeps the L2 -> LDS traffic per flop low.
+// 512-token chunk on 256 CUs.  The kernel therefore gives a CU one tall tile at a time, up to 256 or 288 rows by
+// up to 256 columns, held entirely in accumulators (the register file of a CU is 512 KB), and picks the tile so that
+// its grid fills whole rounds of CUs (pick_tall).  The larger the tile, the lower the L2 -> LDS traffic per flop.  Chunks of up to
+// 128 rows take tiles of 32 to 128 rows, as narrow as one round of workgroups allows.
 //
-//   * Waves form a WM x WN grid over the tile; a wave owns 8/WM row blocks x NB/WN column blocks of
+//   * Waves form a WM x WN grid over the tile; a wave owns BMB/WM row blocks x NB/WN column blocks of
 //     32 x 32.  Measured at M = 512: eight waves (4 x 2, two per SIMD, 64 x 96 each) beat four waves of
 //     128 x 96 (2 x 2) by 20 % although the latter read a third less from LDS: with one wave per SIMD
 //     every wait of that wave idles the matrix pipe, with two the other wave's MFMAs cover it.
@@ -153,7 +153,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;  // wave owns row blocks [wm MBW, +MBW) x column blocks [wn NBW, +NBW)
-    const int lw = wave;
     const int m0 = mt * G_BM;
     const int KT = a.kt_per_split;
 
@@ -162,16 +161,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     // instruction moves four super-rows: lane i's 16 bytes land at byte 16 i of the instruction's 1 KB.
     // Unit j of a stage = rows [16j, 16j+16) of the LDS image = 1 KB that is contiguous in the tiled operand
     // too (half a 2 KB block), so one load instruction is a wave-uniform base plus 16 bytes per lane.  Unit
-    // j = q * LOADERS + lw belongs to loading wave lw; HAS_LAST says whether its unit q = LPW-1 exists.
+    // j = q * LOADERS + wave belongs to that wave; HAS_LAST says whether its unit q = LPW-1 exists.
     const char* ubase[S::LPW];
     const int kt_total = a.K / G_BK;
     const unsigned lane16 = lane * 16;
     const HalfTile ht(HALF ? n0 / S::COLS : 0);
     // (of a unit of W: half a block is 512 bytes out of either KB of the block)
-    const unsigned w_lane16 = HALF && lw == S::LOADERS - 2 ? lane16 + ht.h * 512 + (lane >> 5) * 512 : lane16;
+    const unsigned w_lane16 = HALF && wave == S::LOADERS - 2 ? lane16 + ht.h * 512 + (lane >> 5) * 512 : lane16;
 #pragma unroll
     for (int q = 0; q < S::LPW; ++q) {
-        const int j = min(q * S::LOADERS + lw, S::NL - 1);
+        const int j = min(q * S::LOADERS + wave, S::NL - 1);
         const u16* base;
         int blk;
         if (j < G_BM / 16) {
@@ -199,13 +198,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     if constexpr (kShortChunkTile) {
 #pragma unroll
         for (int q = 0; q < S::LPW; ++q) {
-            const int j = q * S::LOADERS + lw;
+            const int j = q * S::LOADERS + wave;
             lanes[q] = j < G_BM / 16 ? row_lanes(a.M, m0 + j * 16) : ~0ull;
         }
     }
     auto issue_one = [&](int q, int stage, int kt) {
         const char* at = uniform_ptr(ubase[q] + (size_t)kt * 2048);
-        const int unit = q * S::LOADERS + lw;
+        const int unit = q * S::LOADERS + wave;
         const auto* src = (const __attribute__((address_space(1))) void*)(at + (HALF ? w_lane16 : lane16));
         auto* dst = (__attribute__((address_space(3))) void*)(smem + stage * S::STAGE_BYTES + unit * 1024);
         // A chunk of up to 128 tokens alone on the chip streams every weight exactly once (one M tile): its weight units
@@ -227,7 +226,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
         for (int q = 0; q < CNT; ++q) issue_one(q, stage, kt);
     };
 
-    constexpr bool FETCH = true;
     // Up to 16 rows that come with partial sums of squares: those are loaded ahead of the ring's first stages and added up
     // behind the K loop.
     constexpr bool ROW_SCALE = S::ROW_SCALE && EPI != EPI_PARTIAL;
@@ -295,14 +293,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     // The whole K loop exists once per load count (waves with and without the last load unit), so that no
     // load sits under a condition: a branch inside the loop would also cut it into scheduling regions.
     auto k_loop = [&](auto has_last) {
-    constexpr int CNT = !FETCH ? 0 : S::REM == 0 || decltype(has_last)::value ? S::LPW : S::LPW - 1;  // loads per stage
-    if constexpr (FETCH) {
+    constexpr int CNT = S::REM == 0 || decltype(has_last)::value ? S::LPW : S::LPW - 1;  // loads per stage
 #pragma unroll
-        for (int s = 0; s < ST - 1; ++s)
-            if (s < KT) issue(has_last, s, s);
-        if (KT >= ST - 1) wait_vmcnt<(ST - 2) * CNT>();  // stage 0 landed, the others may be in flight
-        else wait_vmcnt<0>();
-    }
+    for (int s = 0; s < ST - 1; ++s)
+        if (s < KT) issue(has_last, s, s);
+    if (KT >= ST - 1) wait_vmcnt<(ST - 2) * CNT>();  // stage 0 landed, the others may be in flight
+    else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     load_frags(f0, 0, 0);
     wait_lgkmcnt0();
@@ -321,10 +317,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
     auto do_stage = [&](auto refill, auto last, int kt, int stage, int pstage, int nstage) {
         constexpr bool REFILL = decltype(refill)::value, LAST = decltype(last)::value;
         if (REFILL) {
-            if (FETCH) wait_vmcnt<(ST - 3) * CNT>();
+            wait_vmcnt<(ST - 3) * CNT>();
             __builtin_amdgcn_s_barrier();
         } else if (!LAST) {
-            if (FETCH) wait_groups<ST, CNT>(KT - 1 - (kt + 1));  // stages issued after kt+1 may stay in flight
+            wait_groups<ST, CNT>(KT - 1 - (kt + 1));  // stages issued after kt+1 may stay in flight
             __builtin_amdgcn_s_barrier();
         }
         // Memory instructions are dealt out between the MFMAs, and the compiler's scheduler is fenced at
@@ -332,8 +328,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
         // matrix pipe runs dry.  Fragment reads come first in a half, the global->LDS loads after them
         // (spreading the loads among the reads, or keeping the last MFMAs free of both, measured slower).
         constexpr int NM = MBW * NBW + EXTRA;
-        constexpr int V1 = REFILL && FETCH ? (CNT + 1) / 2 : 0;
-        constexpr int V2 = REFILL && FETCH ? CNT - V1 : 0;
+        constexpr int V1 = REFILL ? (CNT + 1) / 2 : 0;
+        constexpr int V2 = REFILL ? CNT - V1 : 0;
         auto half = [&]<int... M>(std::integer_sequence<int, M...>, auto second) {
             constexpr bool SECOND = decltype(second)::value;
             constexpr int RD = SECOND && LAST ? 0 : READS;
@@ -389,7 +385,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned char* smem
         do_stage(std::false_type{}, std::false_type{}, kt, stage, prev_slot(stage), next_slot(stage));
     if (kt < KT) do_stage(std::false_type{}, std::true_type{}, kt, stage, prev_slot(stage), next_slot(stage));
     };
-    if constexpr (S::REM == 0 || !FETCH) {
+    if constexpr (S::REM == 0) {
         k_loop(std::true_type{});
     } else {
         if (wave < S::REM) k_loop(std::true_type{});
